@@ -176,7 +176,8 @@ int wf_reverse(int dtype, int64_t m, int64_t n, const void* g_score, const void*
  *   wf_plan_destroy).  Returns WF_E_ARG for invalid sizes or overlapping offsets.
  * wf_plan_elems    number of elements the C (and D) buffer must hold, -1 for NULL.
  * wf_plan_offsets  copies the batch's element offsets into a host array of 'batch'.
- * wf_plan_config   the (tile, rows) the plan uses.
+ * wf_plan_config   the (tile, rows) the plan uses (with rows autotuned to 2, runs of a large
+ *                  batch that write tables take one row per band instead).
  * wf_batch_forward(plan, C, D, scores, stream)
  *   C       [in]  device buffer of wf_plan_elems elements holding every instance.
  *   D       [out] same layout as C, every instance's table; NULL = scores only.
@@ -232,15 +233,16 @@ int wf_batch_backward(wf_plan* plan, const void* C, const void* ckpt, int32_t ck
                       const void* g_scores, const void* g_D, void* g_C, void* stream);
 
 /*
- * Force the tile width (columns per handoff unit, 64 rows per band) used by later calls on
- * this process: 16, 32 or 64, or 0 to return to the automatic choice (wf_tile_predict).
+ * Force the tile width (columns per handoff unit) used by later calls on this process: 16,
+ * 32 or 64, or 0 to return to the automatic choice (wf_tile_predict).
  * Returns WF_E_ARG for any other value.  Used by the autotuner and the tests.
  */
 int wf_set_tile(int32_t tile);
 
 /*
- * The automatic choice: the tile G (16, 32 or 64) that wf_forward (reverse = 0) or
- * wf_reverse / wf_backward (reverse = 1) use for an m x n instance of element type dtype,
+ * The automatic choice: the tile G (16, 32 or 64) that wf_forward (reverse = 0; at most 32 or
+ * 16 where it gives each lane two or four rows) or wf_reverse / wf_backward (reverse = 1) use
+ * for an m x n instance of element type dtype,
  * by nearest-neighbour classification (k = 1, as the paper's kNN heuristic for its
  * sub-system size in the section "Building a heuristic for the optimum sub-system size"):
  * the fastest tile of the closest shape, in (log2 m, log2 n), of a table of shapes timed on

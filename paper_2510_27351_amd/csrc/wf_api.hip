@@ -173,16 +173,75 @@ int words_per_elem(int dtype) { return dtype == WF_F64 ? 2 : 1; }
 
 namespace {
 
-// Tile of the single-instance sweeps for a shape: the caller's override (wf_set_tile, then
-// WF_TILE), else the nearest-neighbour prediction from the tiles measured on MI355X.
-int choose_tile(int dtype, int64_t m, int64_t n, bool reverse) {
+// The caller's override of the tile (wf_set_tile, then WF_TILE), or 0.
+int forced_tile() {
   if (g_tile_override) return g_tile_override;
   if (const char* s = std::getenv("WF_TILE")) {
     int t = std::atoi(s);
     if (t == 16 || t == 32 || t == 64) return t;
   }
+  return 0;
+}
+
+// Tile of the single-instance sweeps for a shape: the override, else the nearest-neighbour
+// prediction from the tiles measured on MI355X.
+int choose_tile(int dtype, int64_t m, int64_t n, bool reverse) {
+  if (const int t = forced_tile()) return t;
   // the callers have validated dtype, m and n, so this is a tile, never an error code
   return wf_tile_predict(dtype, m, n, reverse ? 1 : 0);
+}
+
+// Rows per lane (1, 2 or 4; a band is 64 times as many rows) of the single-instance forward
+// sweep; ld_bytes is the larger of its leading dimensions.
+//
+// A sweep takes about (bands - 1) * lag + n * step.  More rows per lane make fewer bands, each
+// with a longer lag and step; measured on MI355X (us; the lag from 16384 x 1024 and 4096 x 256,
+// the step from 256 x 16384):
+//                     float, int32                      double
+//   rows per lane     1        2        4               1       2
+//   lag               2.9      3.9      5.1             4.5     6.3
+//   step              0.0149   0.0245   0.043           0.026   0.0455
+// so one row per lane is the fastest for m below about 0.6 n (1500 x 4001 float: 153, 162 and
+// 223 us for 1, 2 and 4), two around the square (4096^2: 282, 246, 283; 1024^2: 74, 67, 76),
+// four for m above about 2 n (16384 x 1024: 822, 552, 414).  Double, two against one: 16384 x
+// 1024 868 against 1229, 2048^2 195 against 209, 4096^2 439 against 425, hence the margin.
+// A band is addressed with 32-bit byte offsets, which bounds rows * the leading dimension.
+int forward_rows(int dtype, int64_t m, int64_t n, int64_t ld_bytes) {
+  struct Cost {
+    int rows;
+    double lag, step;
+  };
+  static const Cost f[3] = {{1, 2.9, 0.0149}, {2, 3.9, 0.0245}, {4, 5.1, 0.043}};
+  static const Cost d[2] = {{1, 4.5, 0.026}, {2, 6.6, 0.0477}};
+  const Cost* c = dtype == 1 ? d : f;
+  int best = 1;
+  double t_best = 0.0;
+  for (int i = 0; i < (dtype == 1 ? 2 : 3); ++i) {
+    const int64_t H = (int64_t)kBand * c[i].rows;
+    if (ld_bytes > ((int64_t)1 << 31) / H - 16) break;
+    const double t = (double)((m + H - 1) / H - 1) * c[i].lag + (double)n * c[i].step;
+    if (i == 0 || t < t_best) {
+      t_best = t;
+      best = c[i].rows;
+    }
+  }
+  return best;
+}
+
+// Tile of a sweep with that many rows per lane: the given one, at most 32 (two rows per lane)
+// or 16 (four, and two of double): a step does two or four rows' work, so a unit of the same
+// number of columns holds the band below back for longer (16384 x 1024 float, two rows: 552,
+// 564 and 624 us with 16, 32 and 64; 8192^2: 581, 556 and 568).
+int forward_tile(int dtype, int rows, int tile) {
+  const int cap = rows == 1 ? 64 : rows == 2 && dtype != 1 ? 32 : 16;
+  return tile < cap ? tile : cap;
+}
+
+// The same for the forward sweep with 'rows' rows per lane (the predictor's table was timed
+// with one).
+int choose_forward_tile(int dtype, int64_t m, int64_t n, int rows) {
+  if (const int t = forced_tile()) return t;
+  return forward_tile(dtype, rows, wf_tile_predict(dtype, m, n, 0));
 }
 
 int64_t nbands(int64_t m) { return (m + kBand - 1) / kBand; }
@@ -342,9 +401,10 @@ int wf_forward(int dtype, int64_t m, int64_t n, const void* C, int64_t ldc, void
   if ((m - 1) > INT64_MAX / ldc) return WF_E_ARG;
   // a band of 64 rows is addressed with 32-bit byte offsets
   if (ldc > kMaxLd / es || (D && ldd > kMaxLd / es)) return WF_E_UNSUPPORTED;
-  const int64_t band_rows = forward_band_rows(dtype);
+  if (nbands(m) > 0x7fffffff) return WF_E_ARG;
+  const int rows = forward_rows(dtype, m, n, std::max(ldc, D ? ldd : 0) * es);
+  const int64_t band_rows = (int64_t)kBand * rows;
   const int64_t nb = (m + band_rows - 1) / band_rows;
-  if (nb > 0x7fffffff) return WF_E_ARG;
 
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return WF_E_DEVICE;
@@ -364,12 +424,14 @@ int wf_forward(int dtype, int64_t m, int64_t n, const void* C, int64_t ldc, void
   a.n = n;
   a.ckpt_k = ckpt_k;
   a.nb = (int32_t)nb;
+  a.rows = rows;
+  a.pad = 0;
   a.ctl = ws->ctl;
   a.bnd = ws->bnd;
   a.trace = (g_trace && dev == g_trace_dev && nb <= g_trace_bands) ? g_trace : nullptr;
   a.kx = a.gl = 1.0;
   const int grid = (int)std::min<int64_t>(nb, ws->num_cus);
-  const int tile = choose_tile(dtype, m, n, false);
+  const int tile = choose_forward_tile(dtype, m, n, rows);
   hipError_t e = launch_forward(dtype, tile, a, grid, static_cast<hipStream_t>(stream));
   return e == hipSuccess ? WF_OK : WF_E_DEVICE;
 }
@@ -387,11 +449,9 @@ int wf_forward_noalloc(int dtype, int64_t m, int64_t n, const void* C, int64_t l
   if (ckpt_k > 0 && ckpt == nullptr && wf_ckpt_elems(m, n, ckpt_k) > 0) return WF_E_ARG;
   if ((m - 1) > INT64_MAX / ldc) return WF_E_ARG;
   if (ldc > kMaxLd / es || (D && ldd > kMaxLd / es)) return WF_E_UNSUPPORTED;
-  const int64_t band_rows = forward_band_rows(dtype);
-  const int64_t nb = (m + band_rows - 1) / band_rows;
-  if (nb > 0x7fffffff) return WF_E_ARG;
-  // the handoff words of every band boundary must fit in the scratch array
-  const int64_t words = (nb - 1) * words_per_elem(dtype);
+  if (nbands(m) > 0x7fffffff) return WF_E_ARG;
+  // the handoff words of every 64-row band boundary must fit in the scratch array
+  const int64_t words = (nbands(m) - 1) * words_per_elem(dtype);
   if (words > 0 && n > (int64_t)kScratchWords / words) return WF_E_UNSUPPORTED;
 
   int dev = 0;
@@ -399,6 +459,9 @@ int wf_forward_noalloc(int dtype, int64_t m, int64_t n, const void* C, int64_t l
   ScratchDev sd;
   int rc = scratch_of(dev, &sd);
   if (rc != WF_OK) return rc;
+  const int rows = forward_rows(dtype, m, n, std::max(ldc, D ? ldd : 0) * es);
+  const int64_t band_rows = (int64_t)kBand * rows;
+  const int64_t nb = (m + band_rows - 1) / band_rows;
   Control* ctl = reinterpret_cast<Control*>(sd.ptr);
   hipStream_t st = static_cast<hipStream_t>(stream);
   hipLaunchKernelGGL(scratch_prepare, dim3(1), dim3(64), 0, st, ctl);
@@ -415,12 +478,14 @@ int wf_forward_noalloc(int dtype, int64_t m, int64_t n, const void* C, int64_t l
   a.n = n;
   a.ckpt_k = ckpt_k;
   a.nb = (int32_t)nb;
+  a.rows = rows;
+  a.pad = 0;
   a.ctl = ctl;
   a.bnd = reinterpret_cast<uint64_t*>(sd.ptr + kScratchCtl);
   a.trace = nullptr;
   a.kx = a.gl = 1.0;
   const int grid = (int)std::min<int64_t>(nb, sd.num_cus);
-  hipError_t e = launch_forward(dtype, choose_tile(dtype, m, n, false), a, grid, st);
+  hipError_t e = launch_forward(dtype, choose_forward_tile(dtype, m, n, rows), a, grid, st);
   return e == hipSuccess ? WF_OK : WF_E_DEVICE;
 }
 
@@ -686,6 +751,7 @@ int wf_soft_forward(int dtype, int64_t m, int64_t n, double gamma, const void* C
   a.n = n;
   a.ckpt_k = 0;
   a.nb = (int32_t)nb;
+  a.rows = 1;
   a.ctl = ws->ctl;
   a.bnd = ws->bnd;
   a.trace = nullptr;

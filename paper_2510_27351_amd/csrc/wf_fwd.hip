@@ -1,42 +1,49 @@
 // Persistent band-pipelined forward sweep (gfx950).
 //
-// Work decomposition.  The m x n table is cut into bands of H = 64*R rows.  A persistent
-// workgroup claims bands in increasing order from a device counter and sweeps each band
-// from left to right as a skewed wavefront.  Lane r of the compute wave owns row r of each
-// of the band's R sub-bands of 64 rows (rows r, 64+r, ...).  Sub-band k runs 65*k steps
-// behind sub-band 0: at step t lane r produces column t - r - 65k of row 64k + r, so the
-// cells of one step lie on R anti-diagonals and all of a lane's chains are independent
-// within the step.  The three inputs of a cell come from registers:
-//   W  the lane's previous value in the same sub-band;
-//   N  the previous value of lane r-1 moved by a DPP wave_shr:1; lane 0 of sub-band 0 takes
-//      the row above the band (the "top" ring in LDS, published by the band above); lane 0
-//      of sub-band k >= 1 takes lane 63 of sub-band k-1 from two steps back, moved by a
-//      DPP wave_ror:1 one step ahead (the extra step of skew keeps that move off the chain);
+// Work decomposition.  The m x n table is cut into bands of H = 64*R rows, R = 1, 2 or 4
+// (forward_rows, wf_api.hip).  A persistent workgroup claims bands in increasing order from a device
+// counter and sweeps each band from left to right as a skewed wavefront.  Lane r of the
+// compute wave owns the R adjacent rows R*r .. R*r+R-1 of the band: at step t it produces
+// column t - r of each of them, top to bottom.  The three inputs of a cell come from registers:
+//   W  the lane's previous value in the same row;
+//   N  the cell just produced in the row above; for the lane's first row, the previous value
+//      of lane r-1's last row moved by a DPP wave_shr:1; lane 0 takes the row above the band
+//      (the "top" ring in LDS, published by the band above);
 //   NW the previous step's N.
-// A band takes n + H + R - 2 steps and the band below trails it by H + R - 1 + G steps plus
-// the handoff latency: all m+n-1 anti-diagonals in one launch, with one handoff through
-// global memory per H rows.
+// A band takes n + 63 steps and the band below trails it by 63 + G steps plus the handoff
+// latency: all m+n-1 anti-diagonals in one launch, with one handoff through global memory
+// per H rows.
 //
-// Skewed LDS ring.  Element (row i, column c) of the band lives at S[i][(i + c + i/64) mod
-// RING]: at step t every lane touches slot t in every sub-band, so a lane's four
-// consecutive steps are one aligned 16-byte LDS access per sub-band.  A 16-byte chunk of
-// slots [4j, 4j+4) of row i holds four consecutive columns, which are also consecutive in
-// global memory, so every global transfer is one (4-byte aligned) 16-byte access paired
-// with one aligned 16-byte LDS access.  The row pitch is 16 mod 256 bytes, which keeps
-// 16-byte accesses of different rows on distinct banks.  D overwrites C in place.
+// What bounds it.  A step is a serial chain in one wave (DPP move with its wait states, then a
+// v_min3 and an add per row: 5, 7 and 11 instructions of 4.1 cycles for R = 1, 2, 4) plus that
+// wave's own LDS instructions, which the chain waits out: on this chip a ds_write_b128 holds
+// the wave for 24 cycles, a ds_read_b128 for 4, and a change from VALU to LDS for 8.  Rows
+// side by side in a lane share the DPP move and halve the handoffs, so R = 2 runs 128 rows in
+// 59 cycles a step where R = 1 runs 64 in 36; against rows 64 apart in a lane (two DPP moves
+// and one more skew of 65 steps per band) 512 ragged instances take 673 us instead of 1000.
 //
-// Five waves per workgroup:
-//   wave 0  compute   per 4 steps and sub-band: one 16-byte LDS read of C, 4 x (DPP shift,
-//                     min3, add), one 16-byte LDS write of D; one broadcast read of the top;
-//   wave 1  loader    64-slot sub-chunks of C: 16R x (16-byte buffer load, 16-byte LDS write)
-//                     per lane, PF sub-chunks in flight in registers;
-//   wave 2  top       polls the band above's tagged boundary words, 64 columns per pass,
-//                     and fills the top ring with every complete unit of G columns;
-//   wave 3  storer    every 64 steps writes the sub-chunk's D back (16-byte LDS read,
-//                     16-byte global store), the checkpoint columns and the score;
-//   wave 4  publisher publishes the values of the band's last row that became final since
-//                     its previous pass (whole units of G steps, up to 64 columns) as tagged
-//                     words for the band below, and the checkpoint rows.
+// Skewed LDS ring.  LDS row l holds band row R*(l%64) + l/64, and its column c lies at slot
+// (c + l%64) mod RING: at step t every lane touches slot t of its rows, so a lane's four
+// consecutive steps are one aligned 16-byte LDS access per row.  A 16-byte chunk of slots
+// [4j, 4j+4) of a row holds four consecutive columns, which are also consecutive in global
+// memory, so every global transfer is one (4-byte aligned) 16-byte access paired with one
+// aligned 16-byte LDS access.  The row pitch is 16 mod 256 bytes, which keeps 16-byte
+// accesses of different rows on distinct banks.  D overwrites C in place.
+//
+// 3 + 2R waves per workgroup:
+//   wave 0           compute   per 4 steps and row: one 16-byte LDS read of C, 4 cells, one
+//                              16-byte LDS write of D; per G steps one read of the top row;
+//   wave 1           publisher publishes the values of the band's last row that became final
+//                              since its previous pass (whole units of G steps, up to 64
+//                              columns) as tagged words for the band below, and the
+//                              checkpoint rows;
+//   wave 2           top       polls the band above's tagged boundary words, 64 columns per
+//                              pass, and fills the top ring with every complete unit of G
+//                              columns;
+//   waves 3 .. 2+R   loaders   64 rows each: sub-chunks of SUB slots of C, 16-byte buffer loads
+//                              and 16-byte LDS writes, PF sub-chunks in flight in registers;
+//   waves 3+R ..     storers   64 rows each: every finished sub-chunk's D (16-byte LDS read,
+//                              16-byte global store), the checkpoint columns and the score.
 // The publisher has a wave of its own so that nothing delays the handoff, which sits on
 // the critical path of the whole sweep.  G (16/32/64, the "tile width") is the handoff
 // granularity.
@@ -51,8 +58,6 @@
 namespace wf {
 namespace {
 
-constexpr int kSub = 64;  // slots per loader / storer sub-chunk
-
 // Returns x unchanged, but hides its value from the optimiser at this point.
 template <typename V>
 __device__ __forceinline__ V opaque(V x) {
@@ -60,18 +65,17 @@ __device__ __forceinline__ V opaque(V x) {
   return x;
 }
 
-__device__ __forceinline__ uint32_t dpp_ror1_u32(uint32_t src) {
-  // wave_ror:1 -- lane r receives lane r-1's value, lane 0 receives lane 63's.
-  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)src, 0x13C, 0xf, 0xf, false);
+// wave_shl:1 -- lane r receives lane r+1's value; lane 63 keeps its own.
+__device__ __forceinline__ uint32_t dpp_shl1_u32(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, 0x130, 0xf, 0xf, false);
 }
-
 template <typename T>
-__device__ __forceinline__ T ror1(T x) {
+__device__ __forceinline__ T shl1(T x) {
   if constexpr (sizeof(T) == 4) {
-    return __builtin_bit_cast(T, dpp_ror1_u32(__builtin_bit_cast(uint32_t, x)));
+    return __builtin_bit_cast(T, dpp_shl1_u32(__builtin_bit_cast(uint32_t, x)));
   } else {
     const uint64_t b = __builtin_bit_cast(uint64_t, x);
-    const uint64_t lo = dpp_ror1_u32((uint32_t)b), hi = dpp_ror1_u32((uint32_t)(b >> 32));
+    const uint64_t lo = dpp_shl1_u32((uint32_t)b), hi = dpp_shl1_u32((uint32_t)(b >> 32));
     return __builtin_bit_cast(T, (hi << 32) | lo);
   }
 }
@@ -84,29 +88,48 @@ struct FwdCfg {
   static constexpr int RING = (sizeof(T) == 4 ? 512 : 256) / R;
   static constexpr int PITCH = RING + 16 / (int)sizeof(T);
   static constexpr int MASK = RING - 1;
-  // Sub-chunks the loader keeps in flight in registers (bounded by the 256 registers a wave
-  // may use when two of the five waves share a SIMD).
-  static constexpr int PF = sizeof(T) * R == 4 ? 2 : 1;
-  static constexpr int GPS = kSub / G;  // handoff units per sub-chunk
+  // Slots per loader / storer sub-chunk: four sub-chunks or more in the ring.
+  static constexpr int SUB = RING >= 256 ? 64 : 32;
+  // A sub-chunk of 64 rows is NV 4-column vectors per lane: LPR lanes side by side hold a row.
+  static constexpr int LPR = SUB / 4;
+  static constexpr int NV = 64 / (64 / LPR);
+  // Sub-chunks a loader keeps in flight in registers (bounded by the registers a wave may
+  // use when several share a SIMD).
+  static constexpr int PF = R == 4 ? 3 : SUB * sizeof(T) <= 256 ? 2 : 1;
+  static constexpr int GPS = SUB / G;   // handoff units per sub-chunk
   static constexpr int NG = G / 4;      // 4-step groups per unit
-  static_assert(RING % kSub == 0 && kSub % G == 0, "bad tiling");
-  static_assert(RING >= 4 * kSub, "ring too small");
-  // Offset between the column of row i at step t and t itself: column = t - i - i/64.
-  __device__ static __forceinline__ int skew(int i) { return i + i / kBand; }
+  // Waves: compute, top, publisher, and a loader and a storer for every 64 rows.
+  static constexpr int WAVES = 3 + 2 * R;
+  static constexpr int THREADS = 64 * WAVES;
+  static_assert(RING % SUB == 0 && SUB % G == 0, "bad tiling");
+  static_assert(RING >= 4 * SUB, "ring too small");
 };
 
-struct alignas(8) Shared {
-  uint32_t ctr[6];  // 0: C sub-chunks loaded, 1: top units loaded, 2: steps done, 3: sub-chunks stored,
-                    // 4: units published, 5: unused
+// LDS row l of a band holds the band's row R * (l % 64) + l / 64 (lane l % 64's row l / 64),
+// whose column at step t is t - l % 64.
+template <int R>
+__device__ __forceinline__ int band_row(int l) {
+  return R * (l & 63) + (l >> 6);
+}
+template <int R>
+__device__ __forceinline__ int lds_row(int i) {
+  return (i % R) * kBand + i / R;
+}
+__device__ __forceinline__ int skew(int l) { return l & 63; }
+
+struct alignas(32) Shared {
+  // 0..3: C sub-chunks loaded by loader h, 4: top units loaded, 5..7: always 0; 8: steps
+  // done, 9: units published, 10..13: sub-chunks stored by storer h
+  uint32_t ctr[16];
   uint32_t item;
   uint32_t abort;
+  uint32_t warm;  // 1 once the compute wave has run its loop once (see compute_band)
+  uint32_t spare;
 };
-
-// Both readiness counters of the compute wave in one 8-byte LDS read.
-__device__ __forceinline__ uint64_t load_ready(const Shared& sh) {
-  return __hip_atomic_load(reinterpret_cast<const uint64_t*>(&sh.ctr[0]), __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_WORKGROUP);
-}
+constexpr int kCtrTop = 4, kCtrSteps = 8, kCtrPub = 9;
+__device__ __forceinline__ constexpr int ctr_loaded(int h) { return h; }
+__device__ __forceinline__ constexpr int ctr_stored(int h) { return 10 + h; }
+constexpr uint32_t kAllReady = 0x7fffffffu;
 
 // Every role below launders the kernel-wide sizes it uses through opaque() first:
 // otherwise the compiler hoists each role's per-row address arithmetic out of the band loop
@@ -114,153 +137,249 @@ __device__ __forceinline__ uint64_t load_ready(const Shared& sh) {
 
 // ---------------------------------------------------------------------------------------
 // wave 0: the cell chains
-template <typename T, int G, int R>
+template <typename T, int R>
 struct ComputeState {
-  T X[R];   // previous value of each sub-band (W of the next cell)
-  T NW[R];  // previous N of each sub-band (NW of the next cell)
-  T Q[R];   // k >= 1: lane 63 of sub-band k-1 two steps back (rotated to lane 0)
+  T X[R];  // previous value of each of the lane's rows (W of the next cell)
+  T NW;    // previous N of the lane's first row (NW of its next cell)
+  T top;   // the row above the band, shifted down one lane per step: lane 0 holds the value
+           // at its next column
 };
 
-// Per 4-step group: C of every sub-band, and the top row's values at the group's columns
-// (read by every lane from the same LDS address; lane 0 takes them).
-template <typename T, int G, int R>
+// Four steps, X = C + min(NW, N, W) per cell, of a lane's R adjacent rows.  N of the first
+// row is lane r-1's last row's previous value, moved by a DPP wave_shr:1 whose "old" operand
+// fills lane 0 with the top row's value; NW is the previous N.  The second row's N is the
+// cell just computed and its NW the first row's previous one.
+//
+// One asm block per four steps: a DPP move may read a register two instructions after the
+// VALU wrote it at the earliest, and shifting the top row and copying it into the move's
+// "old" operand are exactly those two.  Left to the compiler, the minimum (which must be
+// v_min3 itself: fminf on DPP-shifted operands costs a canonicalising instruction each)
+// drew a further wait state per step after every asm statement, and the top row came as a
+// 16-byte LDS read per group.  The s_nop covers a copy of X or 'top' that the compiler may
+// place right before the block.
+template <typename T>
+struct Cell4;
+
+#define WF_STEP1(MIN3, ADD, CLAMP, T0, NW, X, D, C)                \
+  "v_mov_b32 " T0 ", %[top]\n\t"                                   \
+  "v_mov_b32_dpp " T0 ", " X " wave_shr:1 row_mask:0xf bank_mask:0xf\n\t" \
+  MIN3 " " D ", " NW ", " T0 ", " X "\n\t"                         \
+  ADD " " D ", " C ", " D CLAMP "\n\t"                             \
+  "v_mov_b32_dpp %[top], %[top] wave_shl:1 row_mask:0xf bank_mask:0xf\n\t"
+#define WF_STEP2(MIN3, ADD, CLAMP, T0, NW, XA, XB, DA, DB, CA, CB) \
+  "v_mov_b32 " T0 ", %[top]\n\t"                                   \
+  "v_mov_b32_dpp " T0 ", " XB " wave_shr:1 row_mask:0xf bank_mask:0xf\n\t" \
+  MIN3 " " DA ", " NW ", " T0 ", " XA "\n\t"                       \
+  ADD " " DA ", " CA ", " DA CLAMP "\n\t"                          \
+  MIN3 " " DB ", " XA ", " DA ", " XB "\n\t"                       \
+  ADD " " DB ", " CB ", " DB CLAMP "\n\t"                          \
+  "v_mov_b32_dpp %[top], %[top] wave_shl:1 row_mask:0xf bank_mask:0xf\n\t"
+#define WF_STEP4(MIN3, ADD, CLAMP, T0, NW, XA, XB, XC, XD, DA, DB, DC, DD, CA, CB, CC, CD) \
+  "v_mov_b32 " T0 ", %[top]\n\t"                                   \
+  "v_mov_b32_dpp " T0 ", " XD " wave_shr:1 row_mask:0xf bank_mask:0xf\n\t" \
+  MIN3 " " DA ", " NW ", " T0 ", " XA "\n\t"                       \
+  ADD " " DA ", " CA ", " DA CLAMP "\n\t"                          \
+  MIN3 " " DB ", " XA ", " DA ", " XB "\n\t"                       \
+  ADD " " DB ", " CB ", " DB CLAMP "\n\t"                          \
+  MIN3 " " DC ", " XB ", " DB ", " XC "\n\t"                       \
+  ADD " " DC ", " CC ", " DC CLAMP "\n\t"                          \
+  MIN3 " " DD ", " XC ", " DC ", " XD "\n\t"                       \
+  ADD " " DD ", " CD ", " DD CLAMP "\n\t"                          \
+  "v_mov_b32_dpp %[top], %[top] wave_shl:1 row_mask:0xf bank_mask:0xf\n\t"
+#define WF_CELL4(T, MIN3, ADD, CLAMP)                                                                           \
+  template <>                                                                                                   \
+  struct Cell4<T> {                                                                                             \
+    __device__ static __forceinline__ void run(ComputeState<T, 1>& st, const Vec4<T> (&c)[1], Vec4<T> (&d)[1]) { \
+      T t;                                                                                                      \
+      asm("s_nop 0\n\t" WF_STEP1(MIN3, ADD, CLAMP, "%[t]", "%[nw]", "%[x]", "%[d0]", "%[c0]")                   \
+              WF_STEP1(MIN3, ADD, CLAMP, "%[nw]", "%[t]", "%[d0]", "%[d1]", "%[c1]")                            \
+                  WF_STEP1(MIN3, ADD, CLAMP, "%[t]", "%[nw]", "%[d1]", "%[d2]", "%[c2]")                        \
+                      WF_STEP1(MIN3, ADD, CLAMP, "%[nw]", "%[t]", "%[d2]", "%[d3]", "%[c3]")                    \
+          : [top] "+v"(st.top), [nw] "+v"(st.NW), [t] "=&v"(t), [d0] "=&v"(d[0].v[0]), [d1] "=&v"(d[0].v[1]),   \
+            [d2] "=&v"(d[0].v[2]), [d3] "=&v"(d[0].v[3])                                                        \
+          : [x] "v"(st.X[0]), [c0] "v"(c[0].v[0]), [c1] "v"(c[0].v[1]), [c2] "v"(c[0].v[2]), [c3] "v"(c[0].v[3])); \
+      st.X[0] = d[0].v[3];                                                                                      \
+    }                                                                                                           \
+    __device__ static __forceinline__ void run(ComputeState<T, 2>& st, const Vec4<T> (&c)[2], Vec4<T> (&d)[2]) { \
+      T t;                                                                                                      \
+      asm("s_nop 0\n\t" WF_STEP2(MIN3, ADD, CLAMP, "%[t]", "%[nw]", "%[xa]", "%[xb]", "%[a0]", "%[b0]", "%[c0]", "%[e0]") \
+              WF_STEP2(MIN3, ADD, CLAMP, "%[nw]", "%[t]", "%[a0]", "%[b0]", "%[a1]", "%[b1]", "%[c1]", "%[e1]") \
+                  WF_STEP2(MIN3, ADD, CLAMP, "%[t]", "%[nw]", "%[a1]", "%[b1]", "%[a2]", "%[b2]", "%[c2]", "%[e2]") \
+                      WF_STEP2(MIN3, ADD, CLAMP, "%[nw]", "%[t]", "%[a2]", "%[b2]", "%[a3]", "%[b3]", "%[c3]", "%[e3]") \
+          : [top] "+v"(st.top), [nw] "+v"(st.NW), [t] "=&v"(t), [a0] "=&v"(d[0].v[0]), [a1] "=&v"(d[0].v[1]),   \
+            [a2] "=&v"(d[0].v[2]), [a3] "=&v"(d[0].v[3]), [b0] "=&v"(d[1].v[0]), [b1] "=&v"(d[1].v[1]),         \
+            [b2] "=&v"(d[1].v[2]), [b3] "=&v"(d[1].v[3])                                                        \
+          : [xa] "v"(st.X[0]), [xb] "v"(st.X[1]), [c0] "v"(c[0].v[0]), [c1] "v"(c[0].v[1]), [c2] "v"(c[0].v[2]), \
+            [c3] "v"(c[0].v[3]), [e0] "v"(c[1].v[0]), [e1] "v"(c[1].v[1]), [e2] "v"(c[1].v[2]),                 \
+            [e3] "v"(c[1].v[3]));                                                                               \
+      st.X[0] = d[0].v[3];                                                                                      \
+      st.X[1] = d[1].v[3];                                                                                      \
+    }                                                                                                           \
+    template <int q>                                                                                            \
+    __device__ static __forceinline__ void two(ComputeState<T, 4>& st, const Vec4<T> (&c)[4], Vec4<T> (&d)[4]) { \
+      T t;                                                                                                      \
+      asm("s_nop 0\n\t" WF_STEP4(MIN3, ADD, CLAMP, "%[t]", "%[nw]", "%[xa]", "%[xb]", "%[xc]", "%[xd]", "%[a0]", \
+                                 "%[b0]", "%[c0]", "%[d0]", "%[ia0]", "%[ib0]", "%[ic0]", "%[id0]")             \
+              WF_STEP4(MIN3, ADD, CLAMP, "%[nw]", "%[t]", "%[a0]", "%[b0]", "%[c0]", "%[d0]", "%[a1]", "%[b1]",  \
+                       "%[c1]", "%[d1]", "%[ia1]", "%[ib1]", "%[ic1]", "%[id1]")                                \
+          : [top] "+v"(st.top), [nw] "+v"(st.NW), [t] "=&v"(t), [a0] "=&v"(d[0].v[q]), [a1] "=&v"(d[0].v[q + 1]), \
+            [b0] "=&v"(d[1].v[q]), [b1] "=&v"(d[1].v[q + 1]), [c0] "=&v"(d[2].v[q]), [c1] "=&v"(d[2].v[q + 1]),  \
+            [d0] "=&v"(d[3].v[q]), [d1] "=&v"(d[3].v[q + 1])                                                    \
+          : [xa] "v"(st.X[0]), [xb] "v"(st.X[1]), [xc] "v"(st.X[2]), [xd] "v"(st.X[3]), [ia0] "v"(c[0].v[q]),   \
+            [ia1] "v"(c[0].v[q + 1]), [ib0] "v"(c[1].v[q]), [ib1] "v"(c[1].v[q + 1]), [ic0] "v"(c[2].v[q]),     \
+            [ic1] "v"(c[2].v[q + 1]), [id0] "v"(c[3].v[q]), [id1] "v"(c[3].v[q + 1]));                          \
+      for (int k = 0; k < 4; ++k) st.X[k] = d[k].v[q + 1];                                                      \
+    }                                                                                                           \
+    __device__ static __forceinline__ void run(ComputeState<T, 4>& st, const Vec4<T> (&c)[4], Vec4<T> (&d)[4]) { \
+      two<0>(st, c, d);                                                                                         \
+      two<2>(st, c, d);                                                                                         \
+    }                                                                                                           \
+  };
+WF_CELL4(float, "v_min3_f32", "v_add_f32", "")
+// saturating, so that +inf (INT32_MAX) stays +inf on the virtual border
+WF_CELL4(int32_t, "v_min3_i32", "v_add_i32", " clamp")
+
+__device__ __forceinline__ double min_raw(double a, double b) {
+  double r;
+  asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+template <>
+struct Cell4<double> {
+  template <int R>
+  __device__ static __forceinline__ void run(ComputeState<double, R>& st, const Vec4<double> (&c)[R],
+                                             Vec4<double> (&d)[R]) {
+    using E = Elem<double>;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      double N = E::shr1(st.X[R - 1], st.top), NW = st.NW;
+      st.NW = N;
+      st.top = shl1(st.top);
+#pragma unroll
+      for (int k = 0; k < R; ++k) {
+        const double W = st.X[k];
+        st.X[k] = c[k].v[q] + min_raw(min_raw(NW, W), N);
+        NW = W;
+        N = st.X[k];
+        d[k].v[q] = st.X[k];
+      }
+    }
+  }
+};
+
+// SOFT: the soft-min cell instead (one row per lane only), on values in the scaled domain
+// y = D log2(e) / gamma; kx scales the cell's input C the same way.
+template <typename T, int R, bool SOFT>
+__device__ __forceinline__ void cells4(ComputeState<T, R>& st, const Vec4<T> (&c)[R], Vec4<T> (&out)[R], T kx) {
+  if constexpr (SOFT) {
+    static_assert(R == 1, "the soft-min sweep uses one row per lane");
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const T N = Elem<T>::shr1(st.X[0], st.top);
+      st.top = shl1(st.top);
+      st.X[0] = soft_cell<T>(c[0].v[q] * kx, st.NW, N, st.X[0]);
+      st.NW = N;
+      out[0].v[q] = st.X[0];
+    }
+  } else {
+    Cell4<T>::run(st, c, out);
+  }
+}
+
+// C of the lane's rows at four steps.
+template <typename T, int R>
 struct GroupRegs {
   Vec4<T> c[R];
-  Vec4<T> t;
 };
-
 template <typename T, int G, int R>
-struct UnitRegs {
-  GroupRegs<T, G, R> g[2];  // the unit's first two groups
-};
-
-template <typename T, int G, int R>
-__device__ __forceinline__ void load_group(const T* __restrict__ S, const T* __restrict__ Tr, int slot, int lane,
-                                           GroupRegs<T, G, R>& r) {
+__device__ __forceinline__ void load_group(const T* __restrict__ S, int slot, int lane, GroupRegs<T, R>& r) {
   using C = FwdCfg<T, G, R>;
 #pragma unroll
   for (int k = 0; k < R; ++k) r.c[k] = *reinterpret_cast<const Vec4<T>*>(S + (k * kBand + lane) * C::PITCH + slot);
-  r.t = *reinterpret_cast<const Vec4<T>*>(Tr + slot);
 }
 
-// Four steps, X = C + min(NW, N, W) per cell.  N is lane r-1's previous value moved by a
-// DPP wave_shr:1 whose "old" operand fills lane 0: for sub-band 0 the top row's value, for
-// sub-band k >= 1 lane 63 of sub-band k-1 from two steps back; NW is the previous N.  Per
-// cell one DPP move, one v_min3, one add, all lanes' chains independent within the step.
-//
-// SOFT: the soft-min cell instead (one sub-band only), on values in the scaled domain
-// y = D log2(e) / gamma; kx scales the cell's input C the same way.
-template <typename T, int G, int R, bool SOFT>
-__device__ __forceinline__ void cells4(ComputeState<T, G, R>& st, const GroupRegs<T, G, R>& r, Vec4<T> (&out)[R],
-                                       T kx) {
-  using E = Elem<T>;
-  if constexpr (SOFT) {
-    static_assert(R == 1, "the soft-min sweep uses one sub-band per band");
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const T N = E::shr1(st.X[0], r.t.v[q]);
-      st.X[0] = soft_cell<T>(r.c[0].v[q] * kx, st.NW[0], N, st.X[0]);
-      st.NW[0] = N;
-      out[0].v[q] = st.X[0];
-    }
-    return;
-  }
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    T N[R], Qn[R];
-    N[0] = E::shr1(st.X[0], r.t.v[q]);  // lane 0 takes the top row
-#pragma unroll
-    for (int k = 1; k < R; ++k) {
-      N[k] = E::shr1(st.X[k], st.Q[k]);  // lane 0 takes lane 63 of sub-band k-1
-      Qn[k] = ror1(st.X[k - 1]);         // ... for the next step
-    }
-#pragma unroll
-    for (int k = 0; k < R; ++k) {
-      const T v = E::min3v(st.NW[k], N[k], st.X[k]);
-      st.X[k] = E::add(r.c[k].v[q], v);
-      st.NW[k] = N[k];
-      out[k].v[q] = st.X[k];
-    }
-#pragma unroll
-    for (int k = 1; k < R; ++k) st.Q[k] = Qn[k];
-  }
-}
-
-// Whether the C sub-chunk and the top unit that unit u reads are in LDS, by the counters in
-// 'ready'.
+// What the compute wave has read ahead of the unit it works on: the unit's first two groups
+// and its columns of the top row (lane l: column G u + l, l < G).
 template <typename T, int G, int R>
-__device__ __forceinline__ bool unit_in_lds(uint64_t ready, int u) {
-  const uint32_t need_c = (uint32_t)((G * u) / kSub + 1);
-  const uint32_t need_t = (uint32_t)(u + 1);
-  return (uint32_t)ready >= need_c && (uint32_t)(ready >> 32) >= need_t;
-}
+struct UnitRegs {
+  GroupRegs<T, R> g[2];
+  T top;
+};
 
-// Waits until the C sub-chunk and the top unit that unit u reads are in LDS.
 template <typename T, int G, int R>
-__device__ __forceinline__ bool unit_wait(int u, Shared& sh, Control* ctl, uint64_t& waited) {
-  return lds_wait_until([&] { return __all(unit_in_lds<T, G, R>(load_ready(sh), u)); }, &sh.abort, ctl, waited);
+__device__ __forceinline__ void load_unit(const T* __restrict__ S, const T* __restrict__ Tr, int slot, int lane,
+                                          UnitRegs<T, G, R>& r) {
+#pragma unroll
+  for (int p = 0; p < 2; ++p) load_group<T, G, R>(S, slot + 4 * p, lane, r.g[p]);
+  r.top = Tr[slot + (lane & (G - 1))];
 }
 
-// One unit of G steps.  'in' holds the first two groups of unit u (already read); the reads
-// of each later group are issued two groups ahead, and the last two groups issue the reads
-// of unit u+1's first two groups into 'out' -- always, so that both paths below leave them
-// in the same registers (conditional reads make the compiler copy every prefetched register
-// at each unit boundary).  If unit u+1's inputs were not yet in LDS two groups before the
-// end (by the counters read at the start of the unit), unit u is finished and signalled
-// first and the wave then waits for unit u+1 and reads its first groups again.  Waiting
-// earlier would hold back the last steps of unit u, and with them the band's last row,
-// until the band above has delivered unit u+1: one unit of extra lag per band.  After the
-// last unit the reads wrap around the ring and are not used.
+// The readiness of a unit's inputs: lane l's copy of counter l % 8 against what the unit
+// needs of it ('need'; the loaders' sub-chunks and the top units), so that one 4-byte LDS
+// read and one compare test all of them.
+__device__ __forceinline__ uint32_t load_ready(const Shared& sh, int lane) {
+  return __hip_atomic_load(&sh.ctr[lane & 7], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// One unit of G steps.  'P' holds the first two groups of the unit and its top row; the
+// reads of each later group are issued two groups ahead, and the last two groups issue the
+// reads of the next unit's first two groups and top row -- always, so that both paths below
+// leave them in the same registers (conditional reads make the compiler copy every
+// prefetched register at each unit boundary).  If the next unit's inputs were not yet in
+// LDS two groups before the end (by the counters read at the start of the unit), the unit is
+// finished and signalled first and the wave then waits for the next unit's inputs and reads
+// them again.  Waiting earlier would hold back the last steps of the unit, and with them the
+// band's last row, until the band above has delivered the next unit: one unit of extra lag
+// per band.  After the last unit the reads wrap around the ring and are not used.  'base' is
+// the unit's first slot, 'done' the number of steps finished after it.
 template <typename T, int G, int R, bool SOFT>
 __device__ __forceinline__ bool compute_unit(T* __restrict__ S, const T* __restrict__ Tr, Shared& sh, Control* ctl,
-                                             int u, int Us, ComputeState<T, G, R>& st, const UnitRegs<T, G, R>& in,
-                                             UnitRegs<T, G, R>& out, uint32_t& stall_c, uint32_t& stall_t,
+                                             uint32_t* steps, int base, int next_base, uint32_t done, uint32_t need,
+                                             ComputeState<T, R>& st, UnitRegs<T, G, R>& P, uint32_t (&stalls)[2],
                                              uint64_t& waited, bool trace, T kx) {
   using C = FwdCfg<T, G, R>;
   constexpr int NG = C::NG;
   const int lane = threadIdx.x & 63;
-  const int base = (G * u) & C::MASK;
-  const int next_base = (G * (u + 1)) & C::MASK;
-  const bool has_next = u + 1 < Us;
-  const uint64_t ready = load_ready(sh);  // for unit u+1, used two groups before the end
+  const uint32_t ready = load_ready(sh, lane);  // for the next unit, used two groups before the end
   __builtin_amdgcn_sched_barrier(0);
-  GroupRegs<T, G, R> gr[NG + 2];
-#pragma unroll
-  for (int p = 0; p < 2; ++p) gr[p] = in.g[p];
-  bool early = true;
+  GroupRegs<T, R> gr[NG];
+  gr[0] = P.g[0];
+  gr[1] = P.g[1];
+  st.top = P.top;
+  bool late = false;
 #pragma unroll
   for (int g = 0; g < NG; ++g) {
     if (g + 2 < NG) {
-      load_group<T, G, R>(S, Tr, base + 4 * (g + 2), lane, gr[g + 2]);
-    } else {
-      if (g + 2 == NG) {
-        __builtin_amdgcn_sched_barrier(0);
-        early = !has_next || __all(unit_in_lds<T, G, R>(ready, u + 1));
-        if (trace && !early) {
-          stall_c += (uint32_t)ready < (uint32_t)((G * (u + 1)) / kSub + 1);
-          stall_t += (uint32_t)(ready >> 32) < (uint32_t)(u + 2);
-        }
-        __builtin_amdgcn_sched_barrier(0);
+      load_group<T, G, R>(S, base + 4 * (g + 2), lane, gr[g + 2]);
+    } else if (g + 2 == NG) {
+      late = __ballot(ready < need) != 0;
+      if (trace && late) {
+        const uint64_t b = __ballot(ready < need);
+        stalls[0] += (b & 0xfu) != 0;
+        stalls[1] += (b & 0x10u) != 0;
       }
-      load_group<T, G, R>(S, Tr, next_base + 4 * (g + 2 - NG), lane, out.g[g + 2 - NG]);
+      __builtin_amdgcn_sched_barrier(0);
+      load_group<T, G, R>(S, next_base, lane, P.g[0]);
+      P.top = Tr[next_base + (lane & (G - 1))];
+    } else {
+      load_group<T, G, R>(S, next_base + 4, lane, P.g[1]);
     }
     // keeps every group's reads two groups ahead of their use (left alone, the scheduler
     // gathers the reads of several groups into one burst just before the first of them)
     __builtin_amdgcn_sched_barrier(0);
     Vec4<T> d[R];
-    cells4<T, G, R, SOFT>(st, gr[g], d, kx);
+    cells4<T, R, SOFT>(st, gr[g].c, d, kx);
 #pragma unroll
     for (int k = 0; k < R; ++k) *reinterpret_cast<Vec4<T>*>(S + (k * kBand + lane) * C::PITCH + base + 4 * g) = d[k];
   }
-  lds_signal(&sh.ctr[2], (uint32_t)(G * (u + 1)));
+  lds_signal(steps, done);
   __builtin_amdgcn_sched_barrier(0);
-  if (!early) {
-    if (!unit_wait<T, G, R>(u + 1, sh, ctl, waited)) return false;
+  if (__builtin_expect(late, 0)) {
+    if (!lds_wait_until([&] { return __ballot(load_ready(sh, lane) < need) == 0; }, &sh.abort, ctl, waited))
+      return false;
     // The slot is hidden from the optimiser: through the restrict pointers it would take
     // these reads for repeats of the early ones above and drop them.
-    const int nb = opaque(next_base);
-#pragma unroll
-    for (int p = 0; p < 2; ++p) load_group<T, G, R>(S, Tr, nb + 4 * p, lane, out.g[p]);
+    load_unit<T, G, R>(S, Tr, opaque(next_base), lane, P);
     __builtin_amdgcn_sched_barrier(0);
   }
   return true;
@@ -268,45 +387,67 @@ __device__ __forceinline__ bool compute_unit(T* __restrict__ S, const T* __restr
 
 template <typename T, int G, int R, bool SOFT>
 __device__ __forceinline__ void compute_band(T* __restrict__ S, const T* __restrict__ Tr, Shared& sh, Control* ctl,
-                                             int Us, bool first_band, uint64_t* trace, T kx) {
+                                             int Ks, bool first_band, uint64_t* trace, T kx) {
   using E = Elem<T>;
+  using C = FwdCfg<T, G, R>;
   const int lane = threadIdx.x & 63;
-  ComputeState<T, G, R> st;
-#pragma unroll
-  for (int k = 0; k < R; ++k) {
-    st.X[k] = E::inf();
-    st.NW[k] = E::inf();
-    st.Q[k] = E::inf();
-  }
-  // NW of the band's first cell: the virtual corner D[-1][-1] = 0 for the first band,
-  // D[row0-1][-1] = +inf for the others
-  if (first_band && lane == 0) st.NW[0] = E::zero();
-  uint32_t stall_c = 0, stall_t = 0;
-  uint64_t t_first = 0, waited = 0;
   const bool tr = trace != nullptr;
-  UnitRegs<T, G, R> P;
-  if (!unit_in_lds<T, G, R>(load_ready(sh), 0) && !unit_wait<T, G, R>(0, sh, ctl, waited)) {
-    sh.abort = 1u;
-    return;
-  }
-  if (tr) t_first = __builtin_amdgcn_s_memrealtime();
+  // what unit 0 needs, and what each next unit and each next sub-chunk add
+  const int which = lane & 7;
+  const bool is_c = which < R, is_top = which == kCtrTop;
+  uint32_t stalls[2] = {0, 0};
+  uint64_t t_first = 0, waited = 0;
+  // The workgroup's first band runs the loop once beforehand, on the ring's last sub-chunk
+  // (which the loaders fill last, and wait for this) with nothing to wait for and its
+  // counter stores going to a spare word: the loop's first pass on a compute unit fetches
+  // its instructions from memory, about a microsecond that would otherwise be paid after
+  // the inputs have arrived, by every band in turn.
+  for (int pass = sh.warm != 0u; pass < 2; ++pass) {
+    const bool dry = pass == 0;
+    uint32_t* steps = dry ? &sh.spare : &sh.ctr[kCtrSteps];
+    uint32_t need = !dry && (is_c || is_top) ? 1u : 0u;
+    const uint32_t per_unit = !dry && is_top ? 1u : 0u, per_sub = !dry && is_c ? 1u : 0u;
+    const int s0 = dry ? C::RING / C::SUB - 1 : 0, s1 = dry ? C::RING / C::SUB : Ks;
+    ComputeState<T, R> st;
 #pragma unroll
-  for (int p = 0; p < 2; ++p) load_group<T, G, R>(S, Tr, 4 * p, lane, P.g[p]);
-  // One unit per iteration: a unit reads its first groups from P and leaves the next
-  // unit's there (they are dead by the time those reads are issued, so both use the same
-  // registers and nothing is copied at the back edge).
-  for (int u = 0; u < Us; ++u) {
-    if (!compute_unit<T, G, R, SOFT>(S, Tr, sh, ctl, u, Us, st, P, P, stall_c, stall_t, waited, tr, kx)) {
+    for (int k = 0; k < R; ++k) st.X[k] = E::inf();
+    // NW of the band's first cell: the virtual corner D[-1][-1] = 0 for the first band,
+    // D[row0-1][-1] = +inf for the others
+    st.NW = first_band && lane == 0 ? E::zero() : E::inf();
+    UnitRegs<T, G, R> P;
+    if (!lds_wait_until([&] { return __ballot(load_ready(sh, lane) < need) == 0; }, &sh.abort, ctl, waited)) {
       sh.abort = 1u;
       return;
     }
-    if (tr && u == 62 / G + 1) trace[16] = __builtin_amdgcn_s_memrealtime();
+    if (tr) t_first = __builtin_amdgcn_s_memrealtime();
+    load_unit<T, G, R>(S, Tr, (C::SUB * s0) & C::MASK, lane, P);
+    // One sub-chunk per iteration, its units unrolled: one taken branch per SUB steps.  A unit
+    // reads its first groups from P and leaves the next unit's there (they are dead by the
+    // time those reads are issued, so both use the same registers and nothing is copied).
+    // After the band's last unit there is nothing to wait for: the loaders and the poller
+    // raise their counters to kAllReady when they are through.
+    for (int s = s0; s < s1; ++s) {
+      const int base = (C::SUB * s) & C::MASK;
+      const int next = (C::SUB * (s + 1)) & C::MASK;
+#pragma unroll
+      for (int v = 0; v < C::GPS; ++v) {
+        need += per_unit;
+        if (v + 1 == C::GPS) need += per_sub;
+        if (!compute_unit<T, G, R, SOFT>(S, Tr, sh, ctl, steps, base + G * v, v + 1 < C::GPS ? base + G * (v + 1) : next,
+                                         (uint32_t)(C::SUB * s + G * (v + 1)), need, st, P, stalls, waited, tr, kx)) {
+          sh.abort = 1u;
+          return;
+        }
+        if (tr && C::GPS * s + v == 62 / G + 1) trace[16] = __builtin_amdgcn_s_memrealtime();
+      }
+    }
+    if (dry) lds_signal(&sh.warm, 1u);
   }
   if (tr && lane == 0) {
     trace[1] = t_first;
     trace[2] = __builtin_amdgcn_s_memrealtime();
-    trace[4] = stall_c;
-    trace[5] = stall_t;
+    trace[4] = stalls[0];
+    trace[5] = stalls[1];
     trace[8] = waited;
   }
 }
@@ -314,24 +455,39 @@ __device__ __forceinline__ void compute_band(T* __restrict__ S, const T* __restr
 // ---------------------------------------------------------------------------------------
 // wave 1: global -> LDS loader.
 //
-// Vector k of a lane covers row i = 4k + lane/16 and slots [64s + 4j, 64s + 4j + 4) of
-// sub-chunk s, j = lane % 16, i.e. columns c0 .. c0+3 with c0 = 64s + 4j - skew(i).
+// One loader per 64 LDS rows (loader h: rows 64h .. 64h+63).  Vector k of a lane covers LDS
+// row l = 64h + (64/LPR) k + lane/LPR and slots [SUB s + 4j, SUB s + 4j + 4) of sub-chunk s,
+// j = lane % LPR, i.e. columns c0 .. c0+3 with c0 = SUB s + 4j - skew(l).
 template <typename T, int G, int R>
-__device__ __forceinline__ void load_sub(Vec4<T> (&buf)[16 * R], __amdgpu_buffer_rsrc_t rsrc, int64_t ldc, int s) {
+struct SubVec {
   using C = FwdCfg<T, G, R>;
-  const int lane = threadIdx.x & 63;
+  int l, t;  // LDS row, slot (not wrapped)
+  __device__ __forceinline__ SubVec(int h, int k, int s) {
+    const int lane = threadIdx.x & 63;
+    l = kBand * h + (64 / C::LPR) * k + lane / C::LPR;
+    t = C::SUB * s + 4 * (lane & (C::LPR - 1));
+  }
+  __device__ __forceinline__ int row() const { return band_row<R>(l); }
+  __device__ __forceinline__ int c0() const { return t - skew(l); }
+  __device__ __forceinline__ int lds() const { return l * C::PITCH + (t & C::MASK); }
+};
+
+template <typename T, int G, int R>
+using SubBuf = Vec4<T>[FwdCfg<T, G, R>::NV];
+
+template <typename T, int G, int R>
+__device__ __forceinline__ void load_sub(SubBuf<T, G, R>& buf, __amdgpu_buffer_rsrc_t rsrc, int64_t ldc, int h, int s) {
   // Loads of different sub-chunks stay in issue order, so the wait before a sub-chunk's
   // LDS write leaves the later sub-chunks in flight.  Columns outside [0, n) read
   // neighbouring row data; an offset below the band's start (possible only for a single
-  // column, where i*ldc + c0 can reach -1) wraps to a huge unsigned value and, like reads
-  // past the band's end, returns zeros from the range-checked buffer; store_sub_lds masks
-  // all of them.
+  // column, where row*ldc + c0 can be negative) wraps to a huge unsigned value and, like
+  // reads past the band's end, returns zeros from the range-checked buffer; store_sub_lds
+  // masks all of them.
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int k = 0; k < 16 * R; ++k) {
-    const int i = 4 * k + (lane >> 4);
-    const int c0 = kSub * s + 4 * (lane & 15) - C::skew(i);
-    const uint32_t off = (uint32_t)((int64_t)i * ldc + c0) * (uint32_t)sizeof(T);
+  for (int k = 0; k < FwdCfg<T, G, R>::NV; ++k) {
+    const SubVec<T, G, R> v(h, k, s);
+    const uint32_t off = (uint32_t)((int64_t)v.row() * ldc + v.c0()) * (uint32_t)sizeof(T);
     if constexpr (sizeof(T) == 4) {
       buf[k] = __builtin_bit_cast(Vec4<T>, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)off, 0, 0));
     } else {
@@ -344,36 +500,36 @@ __device__ __forceinline__ void load_sub(Vec4<T> (&buf)[16 * R], __amdgpu_buffer
   __builtin_amdgcn_sched_barrier(0);
 }
 
-// A sub-chunk with every row real and every column in [0, n) needs no masking.
+// A sub-chunk with every column in [0, n) needs no masking.  (Rows below the matrix read
+// zeros and their cells hold no results: no row above depends on them, and stores to them
+// fall outside the range-checked buffer.)
 template <typename T, int G, int R>
-__device__ __forceinline__ bool interior_sub(int s, int rows, int64_t n) {
-  using C = FwdCfg<T, G, R>;
-  return rows == C::H && kSub * s >= C::skew(C::H - 1) && (int64_t)kSub * s + kSub <= n;
+__device__ __forceinline__ bool interior_sub(int s, int64_t n) {
+  constexpr int SUB = FwdCfg<T, G, R>::SUB;
+  return SUB * s >= kBand - 1 && (int64_t)SUB * s + SUB <= n;
 }
 
 template <typename T, int G, int R>
-__device__ __forceinline__ void store_sub_lds(T* S, const Vec4<T> (&buf)[16 * R], int s, int rows, int64_t n) {
+__device__ __forceinline__ void store_sub_lds(T* S, const SubBuf<T, G, R>& buf, int h, int s, int64_t n) {
   using C = FwdCfg<T, G, R>;
   using E = typename C::E;
-  const int lane = threadIdx.x & 63;
-  const bool interior = interior_sub<T, G, R>(s, rows, n);
+  const bool interior = interior_sub<T, G, R>(s, n);
 #pragma unroll
-  for (int k = 0; k < 16 * R; ++k) {
-    const int i = 4 * k + (lane >> 4);
-    const int slot = (kSub * s + 4 * (lane & 15)) & C::MASK;
+  for (int k = 0; k < C::NV; ++k) {
+    const SubVec<T, G, R> q(h, k, s);
     Vec4<T> v = buf[k];
     if (!interior) {
-      const int64_t c0 = (int64_t)kSub * s + 4 * (lane & 15) - C::skew(i);
+      const int64_t c0 = q.c0();
 #pragma unroll
       for (int e = 0; e < 4; ++e)
-        if (i >= rows || c0 + e < 0 || c0 + e >= n) v.v[e] = E::inf();
+        if (c0 + e < 0 || c0 + e >= n) v.v[e] = E::inf();
     }
-    *reinterpret_cast<Vec4<T>*>(S + i * C::PITCH + slot) = v;
+    *reinterpret_cast<Vec4<T>*>(S + q.lds()) = v;
   }
 }
 
 template <typename T, int G, int R>
-__device__ __forceinline__ void loader_band(T* S, Shared& sh, const FwdArgs& a, int band, int Ks, uint64_t* tr) {
+__device__ __forceinline__ void loader_band(T* S, Shared& sh, const FwdArgs& a, int band, int h, int Ks, uint64_t* tr) {
   using C = FwdCfg<T, G, R>;
   const int64_t ldc = opaque(a.ldc), n = opaque(a.n);
   const int64_t row0 = (int64_t)band * C::H;
@@ -381,26 +537,30 @@ __device__ __forceinline__ void loader_band(T* S, Shared& sh, const FwdArgs& a, 
   const __amdgpu_buffer_rsrc_t rsrc = make_rsrc(static_cast<const T*>(a.C) + row0 * ldc,
                                                 (uint32_t)(((rows - 1) * ldc + n) * (int64_t)sizeof(T)));
   uint64_t waited = 0;
-  Vec4<T> buf[C::PF][16 * R];
+  SubBuf<T, G, R> buf[C::PF];
 #pragma unroll
-  for (int p = 0; p < C::PF; ++p) load_sub<T, G, R>(buf[p], rsrc, ldc, p);
+  for (int p = 0; p < C::PF; ++p) load_sub<T, G, R>(buf[p], rsrc, ldc, h, p);
   for (int s0 = 0; s0 < Ks; s0 += C::PF) {
 #pragma unroll
     for (int p = 0; p < C::PF; ++p) {
       const int s = s0 + p;
       if (s < Ks) {
-        // sub-chunk s reuses the slots of sub-chunk s - RING/64, which must be stored (by
-        // the storer) and whose last rows must be read (by the publisher)
-        const int older = s - C::RING / kSub;
-        if (older >= 0 && (!lds_wait_ge<false>(&sh.ctr[3], (uint32_t)(older + 1), &sh.abort, a.ctl, waited) ||
-                           !lds_wait_ge<false>(&sh.ctr[4], (uint32_t)(C::GPS * (older + 1)), &sh.abort, a.ctl,
-                                               waited))) {
+        // sub-chunk s reuses the slots of sub-chunk s - RING/SUB, which must be stored (by
+        // the storer of these rows) and whose last rows must be read (by the publisher)
+        const int older = s - C::RING / C::SUB;
+        if (older == -1 && !lds_wait_ge<false>(&sh.warm, 1u, &sh.abort, a.ctl, waited)) {
           sh.abort = 1u;
           return;
         }
-        store_sub_lds<T, G, R>(S, buf[p], s, rows, n);
-        lds_signal(&sh.ctr[0], (uint32_t)(s + 1));
-        if (s + C::PF < Ks) load_sub<T, G, R>(buf[p], rsrc, ldc, s + C::PF);
+        if (older >= 0 &&
+            (!lds_wait_ge<false>(&sh.ctr[ctr_stored(h)], (uint32_t)(older + 1), &sh.abort, a.ctl, waited) ||
+             !lds_wait_ge<false>(&sh.ctr[kCtrPub], (uint32_t)(C::GPS * (older + 1)), &sh.abort, a.ctl, waited))) {
+          sh.abort = 1u;
+          return;
+        }
+        store_sub_lds<T, G, R>(S, buf[p], h, s, n);
+        lds_signal(&sh.ctr[ctr_loaded(h)], s + 1 < Ks ? (uint32_t)(s + 1) : kAllReady);
+        if (s + C::PF < Ks) load_sub<T, G, R>(buf[p], rsrc, ldc, h, s + C::PF);
       }
     }
   }
@@ -411,12 +571,15 @@ __device__ __forceinline__ void loader_band(T* S, Shared& sh, const FwdArgs& a, 
 }
 
 // ---------------------------------------------------------------------------------------
-// wave 2: top boundary poller.  Each pass fetches the band above's boundary words for the
-// 64 columns from the first unit not yet handed over and hands over every unit of G columns
-// that is complete, so one global round trip advances it by up to 64 columns whatever G is.
+// The top boundary poller.  A poll fetches the band above's boundary words for the 64 columns
+// from the first one not yet handed over, and every unit of G columns it completes is handed
+// over at once, so one round trip (about 0.55 us) advances it by up to 64 columns whatever G
+// is.  One poll at a time: with two, four or six in flight the words were seen later, not
+// sooner (0.60 us from the store to the hand-over with one, 0.95 with two; 4096 x 256: 209,
+// 224, 242 and 267 us).
 template <typename T, int G, int R>
-__device__ __forceinline__ void top_band(const T* S, T* Tr, Shared& sh, const FwdArgs& a, int band, int Ut,
-                                         uint32_t epoch, uint64_t* tr) {
+__device__ __forceinline__ void top_band(T* Tr, Shared& sh, const FwdArgs& a, int band, int Ut, uint32_t epoch,
+                                         uint64_t* tr) {
   using C = FwdCfg<T, G, R>;
   using E = typename C::E;
   constexpr int W = E::W;
@@ -426,102 +589,64 @@ __device__ __forceinline__ void top_band(const T* S, T* Tr, Shared& sh, const Fw
   uint32_t polls = 0;
   int u = 0;  // units handed over
   while (u < Ut) {
-    const int64_t j0 = (int64_t)G * u;
-    // the top ring slot of column j is read at step j and reused RING steps later
-    const int64_t need_steps = j0 + 64 - C::RING;
-    if (need_steps > 0 && !lds_wait_ge(&sh.ctr[2], (uint32_t)need_steps, &sh.abort, a.ctl, waited)) {
-      sh.abort = 1u;
-      return;
-    }
-    const int64_t j = j0 + lane;
-    const bool real = j < n;
-    // Every lane loads on every pass (a lane with no word to read loads spare words of the
-    // control block and ignores them): loads under a lane mask would make each wait drain
-    // all of the wave's loads.
-    const bool live = band > 0 && real;
-    const uint64_t* src = live ? a.bnd + ((int64_t)(band - 1) * n + j) * W : reinterpret_cast<const uint64_t*>(a.ctl) + 4;
-    // Two polls in flight: while one pass's words are checked, the next pass's are on their
-    // way, so readiness is seen about half a round trip sooner than with one.
-    uint64_t xa[W], xb[W];
-    auto issue = [&](uint64_t (&x)[W]) {
-#pragma unroll
-      for (int q = 0; q < W; ++q) x[q] = load_word(src + q);
-    };
-    // units complete in x: the leading run of ready columns (columns past the matrix count
-    // as ready), in whole units
-    auto complete = [&](const uint64_t (&x)[W]) -> int {
+    const int64_t j = (int64_t)G * u + lane;
+    T val = E::inf();
+    int k = 64 / G;  // units to hand over
+    if (band > 0) {
+      // every lane loads (a lane with no column to read loads spare words of the control
+      // block and ignores them)
+      const uint64_t* src = j < n ? a.bnd + ((int64_t)(band - 1) * n + j) * W : reinterpret_cast<const uint64_t*>(a.ctl) + 4;
+      uint32_t x[W];
       bool ok = true;
 #pragma unroll
-      for (int q = 0; q < W; ++q) ok = ok && (uint32_t)(x[q] >> 32) == epoch;
-      ok = ok || !live;
-      const uint64_t okm = __ballot(ok);
-      const int run = ~okm == 0 ? 64 : __builtin_ctzll(~okm);
-      const int k = run / G;
-      return k < Ut - u ? k : Ut - u;
-    };
-    auto value = [&](const uint64_t (&x)[W]) -> T {
-      if (!live) return E::inf();
-      uint32_t w[W];
-#pragma unroll
-      for (int q = 0; q < W; ++q) w[q] = (uint32_t)x[q];
-      return E::from_words(w);
-    };
-    // false when the wait has to give up
-    auto pause = [&]() -> bool {
+      for (int w = 0; w < W; ++w) {
+        const uint64_t word = load_word(src + w);
+        ok = ok && (uint32_t)(word >> 32) == epoch;
+        x[w] = (uint32_t)word;
+      }
+      if (j < n) val = E::from_words(x);
+      // the leading run of ready columns (columns past the matrix count as ready), in whole
+      // units
+      const uint64_t missing = ~__ballot(ok || j >= n);
+      k = (missing == 0 ? 64 : __builtin_ctzll(missing)) / G;
+    }
+    // else the first band: its top row is virtual, +inf without a round trip through memory,
+    // so that the band whose pace every later one follows never waits for its poller
+    if (k > Ut - u) k = Ut - u;
+    if (k == 0) {
       if (polls == 0 && tr) t0 = __builtin_amdgcn_s_memrealtime();
       __builtin_amdgcn_s_sleep(1);
       if ((++polls & 63u) == 0u) {
-        if (lds_load(&sh.abort) != 0u || global_aborted(a.ctl)) return false;
+        bool give_up = lds_load(&sh.abort) != 0u || global_aborted(a.ctl);
         const uint64_t now = __builtin_amdgcn_s_memrealtime();
         if (polls == 64u) {
           if (!tr) t0 = now;
         } else if (now - t0 > kSpinTicks) {
           raise_timeout(a.ctl);
-          return false;
+          give_up = true;
         }
-      }
-      return true;
-    };
-    T val;
-    int k;
-    if (band == 0 || j0 >= n) {
-      // nothing to fetch (the first band's top row is virtual, and so are the columns past
-      // the matrix): +inf without a round trip through memory, so that the first band --
-      // whose pace every later band follows -- never waits for its poller
-      k = (int)(kSub / G) < Ut - u ? (int)(kSub / G) : Ut - u;
-      val = E::inf();
-    } else {
-      issue(xa);
-      for (;;) {
-        issue(xb);
-        if ((k = complete(xa)) > 0) {
-          val = value(xa);
-          break;
-        }
-        if (!pause()) {
-          sh.abort = 1u;
-          return;
-        }
-        issue(xa);
-        if ((k = complete(xb)) > 0) {
-          val = value(xb);
-          break;
-        }
-        if (!pause()) {
+        if (give_up) {
           sh.abort = 1u;
           return;
         }
       }
+      continue;
     }
     if (polls != 0u) {
       if (tr) waited += __builtin_amdgcn_s_memrealtime() - t0;
       polls = 0;
     }
-    const int cols = k * G;
-    if (lane < cols) Tr[(int)(j & C::MASK)] = real ? val : E::inf();
+    // the top ring slot of column j is read before step j and reused RING steps later
+    const int64_t need_steps = (int64_t)G * (u + k) - C::RING;
+    if (need_steps > 0 && !lds_wait_ge(&sh.ctr[kCtrSteps], (uint32_t)need_steps, &sh.abort, a.ctl, waited)) {
+      sh.abort = 1u;
+      return;
+    }
+    if (lane < k * G) Tr[(int)(j & C::MASK)] = val;
+    const bool first = u == 0;
     u += k;
-    lds_signal(&sh.ctr[1], (uint32_t)u);
-    if (tr && u == k && lane == 0) tr[15] = __builtin_amdgcn_s_memrealtime();
+    lds_signal(&sh.ctr[kCtrTop], (uint32_t)u);
+    if (tr && first && lane == 0) tr[15] = __builtin_amdgcn_s_memrealtime();
   }
   if (tr && lane == 0) {
     tr[10] = waited;
@@ -531,89 +656,65 @@ __device__ __forceinline__ void top_band(const T* S, T* Tr, Shared& sh, const Fw
 
 // ---------------------------------------------------------------------------------------
 // wave 3: storer.  SOFT: the ring holds scaled values; D = y * gl (gl = gamma ln 2).
-template <typename T, int R, bool SOFT>
-__device__ __forceinline__ void unscale(Vec4<T> (&v)[16], T gl) {
+template <typename T, int NV, bool SOFT>
+__device__ __forceinline__ void unscale(Vec4<T> (&v)[NV], T gl) {
   if constexpr (SOFT) {
 #pragma unroll
-    for (int k = 0; k < 16; ++k)
+    for (int k = 0; k < NV; ++k)
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[k].v[e] *= gl;
   }
 }
 
+// One storer per 64 LDS rows, like the loaders.
 template <typename T, int G, int R, bool SOFT>
-__device__ __forceinline__ void store_sub(const T* S, __amdgpu_buffer_rsrc_t drs, int64_t ldd, int64_t n, int rows,
+__device__ __forceinline__ void store_sub(const T* S, __amdgpu_buffer_rsrc_t drs, int64_t ldd, int64_t n, int h,
                                           int s, T gl) {
   using C = FwdCfg<T, G, R>;
   typedef int v4i __attribute__((ext_vector_type(4)));
-  const int lane = threadIdx.x & 63;
-  const int j4 = 4 * (lane & 15);
-  const int slot = (kSub * s + j4) & C::MASK;
-  if (interior_sub<T, G, R>(s, rows, n)) {
-    // Interior sub-chunk: 16 LDS reads first, then one 16-byte store per 16 bytes.
+  auto put = [&](int off, const Vec4<T>& x) {
+    if constexpr (sizeof(T) == 4) {
+      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4i, x), drs, off, 0, 0);
+    } else {
+      struct Hf { v4i lo, hi; };
+      const Hf hh = __builtin_bit_cast(Hf, x);
+      __builtin_amdgcn_raw_buffer_store_b128(hh.lo, drs, off, 0, 0);
+      __builtin_amdgcn_raw_buffer_store_b128(hh.hi, drs, off + 16, 0, 0);
+    }
+  };
+  // The LDS reads first.
+  Vec4<T> v[C::NV];
 #pragma unroll
-    for (int h = 0; h < R; ++h) {
-      Vec4<T> v[16];
+  for (int k = 0; k < C::NV; ++k) v[k] = *reinterpret_cast<const Vec4<T>*>(S + SubVec<T, G, R>(h, k, s).lds());
+  unscale<T, C::NV, SOFT>(v, gl);
+  if (interior_sub<T, G, R>(s, n)) {
+    // Interior sub-chunk: one 16-byte store per 16 bytes.
 #pragma unroll
-      for (int k = 0; k < 16; ++k) {
-        const int i = 64 * h + 4 * k + (lane >> 4);
-        v[k] = *reinterpret_cast<const Vec4<T>*>(S + i * C::PITCH + slot);
-      }
-      unscale<T, R, SOFT>(v, gl);
-#pragma unroll
-      for (int k = 0; k < 16; ++k) {
-        const int i = 64 * h + 4 * k + (lane >> 4);
-        const int off = (int)(((int64_t)i * ldd + kSub * s + j4 - C::skew(i)) * (int64_t)sizeof(T));
-        if constexpr (sizeof(T) == 4) {
-          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4i, v[k]), drs, off, 0, 0);
-        } else {
-          struct Hf { v4i lo, hi; };
-          const Hf hh = __builtin_bit_cast(Hf, v[k]);
-          __builtin_amdgcn_raw_buffer_store_b128(hh.lo, drs, off, 0, 0);
-          __builtin_amdgcn_raw_buffer_store_b128(hh.hi, drs, off + 16, 0, 0);
-        }
-      }
+    for (int k = 0; k < C::NV; ++k) {
+      const SubVec<T, G, R> q(h, k, s);
+      put((int)(((int64_t)q.row() * ldd + q.c0()) * (int64_t)sizeof(T)), v[k]);
     }
     return;
   }
-  // Edge sub-chunk (first, last, or a partial band): the same 16 LDS reads first, then per
-  // vector one 16-byte store if its four cells lie inside the matrix, else a store per cell
-  // that does (one sub-band at a time: both at once would not fit the registers).
-#pragma unroll 1
-  for (int h = 0; h < R; ++h) {
-    Vec4<T> v[16];
+  // Edge sub-chunk (first, last, or a partial band): per vector one 16-byte store if its four
+  // cells lie inside the matrix, else a store per cell that does.
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      const int i = 64 * h + 4 * k + (lane >> 4);
-      v[k] = *reinterpret_cast<const Vec4<T>*>(S + i * C::PITCH + slot);
+  for (int k = 0; k < C::NV; ++k) {
+    const SubVec<T, G, R> q(h, k, s);
+    const int64_t c0 = q.c0();
+    const int off = (int)(((int64_t)q.row() * ldd + c0) * (int64_t)sizeof(T));
+    if (c0 >= 0 && c0 + 4 <= n) {
+      put(off, v[k]);
+      continue;
     }
-    unscale<T, R, SOFT>(v, gl);
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      const int i = 64 * h + 4 * k + (lane >> 4);
-      const int64_t c0 = (int64_t)kSub * s + j4 - C::skew(i);
-      if (i >= rows) continue;
-      const int off = (int)(((int64_t)i * ldd + c0) * (int64_t)sizeof(T));
-      if (c0 >= 0 && c0 + 4 <= n) {
+    for (int e = 0; e < 4; ++e) {
+      if (c0 + e >= 0 && c0 + e < n) {
         if constexpr (sizeof(T) == 4) {
-          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4i, v[k]), drs, off, 0, 0);
+          __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, v[k].v[e]), drs, off + 4 * e, 0, 0);
         } else {
-          struct Hf { v4i lo, hi; };
-          const Hf hh = __builtin_bit_cast(Hf, v[k]);
-          __builtin_amdgcn_raw_buffer_store_b128(hh.lo, drs, off, 0, 0);
-          __builtin_amdgcn_raw_buffer_store_b128(hh.hi, drs, off + 16, 0, 0);
-        }
-        continue;
-      }
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        if (c0 + e >= 0 && c0 + e < n) {
-          if constexpr (sizeof(T) == 4) {
-            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, v[k].v[e]), drs, off + 4 * e, 0, 0);
-          } else {
-            typedef int v2i __attribute__((ext_vector_type(2)));
-            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(v2i, v[k].v[e]), drs, off + 8 * e, 0, 0);
-          }
+          typedef int v2i __attribute__((ext_vector_type(2)));
+          __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(v2i, v[k].v[e]), drs, off + 8 * e, 0, 0);
         }
       }
     }
@@ -621,7 +722,7 @@ __device__ __forceinline__ void store_sub(const T* S, __amdgpu_buffer_rsrc_t drs
 }
 
 template <typename T, int G, int R, bool SOFT>
-__device__ __forceinline__ void store_band(const T* S, Shared& sh, const FwdArgs& a, int band, int Ks,
+__device__ __forceinline__ void store_band(const T* S, Shared& sh, const FwdArgs& a, int band, int h, int Ks,
                                            uint64_t* tr) {
   using C = FwdCfg<T, G, R>;
   const int lane = threadIdx.x & 63;
@@ -630,42 +731,42 @@ __device__ __forceinline__ void store_band(const T* S, Shared& sh, const FwdArgs
   const int rows = (int)(m - row0 < C::H ? m - row0 : C::H);
   T* ck_cols = a.ckpt ? static_cast<T*>(a.ckpt) + ((m + kBand - 1) / kBand - 1) * n : nullptr;
   const int K = a.ckpt_k;
-  const int64_t sc_row = m - 1 - row0;  // band row of the score, if it lies in this band
+  // LDS row of the score, if it is one of this storer's rows
+  const int64_t sc = m - 1 - row0;
+  const int sc_l = sc >= 0 && sc < C::H && lds_row<R>((int)sc) / kBand == h ? lds_row<R>((int)sc) : -1;
   const T gl = SOFT ? (T)a.gl : T(1);
   const __amdgpu_buffer_rsrc_t drs =
       make_rsrc(a.D ? static_cast<T*>(a.D) + row0 * ldd : nullptr,
                 a.D ? (uint32_t)(((rows - 1) * ldd + n) * (int64_t)sizeof(T)) : 0u);
   uint64_t waited = 0;
   for (int s = 0; s < Ks; ++s) {
-    // sub-chunk s (slots [64s, 64s+64) of every row) is final after step 64s + 63; its D
+    // sub-chunk s (slots [SUB s, SUB (s+1)) of every row) is final after its last step; its D
     // goes out after the publisher has issued the boundary words of those steps, which
     // the band below waits for
-    if (!lds_wait_ge(&sh.ctr[4], (uint32_t)(C::GPS * (s + 1)), &sh.abort, a.ctl, waited)) {
+    if (!lds_wait_ge(&sh.ctr[kCtrPub], (uint32_t)(C::GPS * (s + 1)), &sh.abort, a.ctl, waited)) {
       sh.abort = 1u;
       return;
     }
-    if (a.D) store_sub<T, G, R, SOFT>(S, drs, ldd, n, rows, s, gl);
+    if (a.D) store_sub<T, G, R, SOFT>(S, drs, ldd, n, h, s, gl);
     if (ck_cols) {
-#pragma unroll
-      for (int h = 0; h < R; ++h) {
-        const int i = 64 * h + lane;
-        if (i >= rows) continue;
+      const int l = kBand * h + lane, i = band_row<R>(l);
+      if (i < rows) {
         // checkpoint columns D[.][Kq-1] of row i held by sub-chunk s
-        const int64_t lo = (int64_t)kSub * s - C::skew(i), hi = lo + kSub;
+        const int64_t lo = (int64_t)C::SUB * s - skew(l), hi = lo + C::SUB;
         for (int64_t j = ((lo > 0 ? lo : 0) + K) / K * K - 1; j < hi; j += K) {
           if (j >= lo && j + 1 < n)
-            ck_cols[((j + 1) / K - 1) * m + row0 + i] = S[i * C::PITCH + ((int)(j + C::skew(i)) & C::MASK)];
+            ck_cols[((j + 1) / K - 1) * m + row0 + i] = S[l * C::PITCH + ((int)(j + skew(l)) & C::MASK)];
         }
       }
     }
-    if (sc_row >= 0 && sc_row < C::H && lane == (int)(sc_row % kBand)) {
-      const int64_t slot = n - 1 + C::skew((int)sc_row);
-      if (slot / kSub == s) {
-        const T y = S[sc_row * C::PITCH + ((int)slot & C::MASK)];
+    if (sc_l >= 0 && lane == sc_l % kBand) {
+      const int64_t slot = n - 1 + skew(sc_l);
+      if (slot / C::SUB == s) {
+        const T y = S[sc_l * C::PITCH + ((int)slot & C::MASK)];
         *static_cast<T*>(a.score) = SOFT ? y * gl : y;
       }
     }
-    lds_publish(&sh.ctr[3], (uint32_t)(s + 1));
+    lds_publish(&sh.ctr[ctr_stored(h)], (uint32_t)(s + 1));
   }
   if (tr && lane == 0) tr[11] = waited;
 }
@@ -689,40 +790,41 @@ __device__ __forceinline__ void publish_band(const T* S, Shared& sh, const FwdAr
   uint64_t waited = 0;
   for (int u = 0; u < Us;) {
     uint32_t done;
-    if (!lds_wait_value<true, false>(&sh.ctr[2], (uint32_t)(G * (u + 1)), &sh.abort, a.ctl, waited, done)) {
+    if (!lds_wait_value<true, false>(&sh.ctr[kCtrSteps], (uint32_t)(G * (u + 1)), &sh.abort, a.ctl, waited, done)) {
       sh.abort = 1u;
       return;
     }
     // every unit finished by now goes out in this pass, up to 64 columns
     int k = (int)(done / G) - u;
-    if (k > kSub / G) k = kSub / G;
+    if (k > 64 / G) k = 64 / G;
     if (k > Us - u) k = Us - u;
     const int cols = k * G;
     const bool mark = tr && u <= 62 / G + 1 && 62 / G + 1 < u + k && lane == 0;
     if (mark) tr[17] = __builtin_amdgcn_s_memrealtime();
     if (lane < cols) {
       const int slot = (G * u + lane) & C::MASK;
-      // the band's last row, row H-1, finished column Gu + lane - skew(H-1) at this step
-      const int64_t j = (int64_t)G * u + lane - C::skew(C::H - 1);
+      // the band's last row, row H-1 (the last LDS row, lane 63's), finished this column at
+      // this step
+      const int64_t j = (int64_t)G * u + lane - skew(C::H - 1);
       if (!last_band && !withhold && j >= 0 && j < n) {
         const T x = S[(C::H - 1) * C::PITCH + slot];
 #pragma unroll
         for (int q = 0; q < W; ++q) store_word(a.bnd + ((int64_t)band * n + j) * W + q, tagged(E::word(x, q), epoch));
       }
-      // checkpoint rows: the last row of every 64-row sub-band except the matrix's last one
+      // checkpoint rows: rows 63, 127, ... of the matrix except its last one
       if (ck_rows) {
 #pragma unroll
         for (int h = 0; h < R; ++h) {
-          const int i = 64 * h + 63;
+          const int l = lds_row<R>(kBand * h + kBand - 1);
           const int b64 = band * R + h;
-          const int64_t jc = (int64_t)G * u + lane - C::skew(i);
-          if (b64 < nb64 - 1 && jc >= 0 && jc < n) ck_rows[(int64_t)b64 * n + jc] = S[i * C::PITCH + slot];
+          const int64_t jc = (int64_t)G * u + lane - skew(l);
+          if (b64 < nb64 - 1 && jc >= 0 && jc < n) ck_rows[(int64_t)b64 * n + jc] = S[l * C::PITCH + slot];
         }
       }
     }
     if (mark) tr[14] = __builtin_amdgcn_s_memrealtime();
     u += k;
-    lds_publish(&sh.ctr[4], (uint32_t)u);
+    lds_publish(&sh.ctr[kCtrPub], (uint32_t)u);
   }
   if (tr && lane == 0) tr[18] = waited;
 }
@@ -733,31 +835,31 @@ template <typename T, int G, int R, bool SOFT = false>
 __device__ __forceinline__ void run_band(T* S, T* Tr, Shared& sh, const FwdArgs& a, int band, uint32_t epoch,
                                          uint64_t* tr) {
   using C = FwdCfg<T, G, R>;
-  const int wave = threadIdx.x >> 6;
-  // steps of a band: n + skew(H-1), rounded up to whole 64-slot sub-chunks
-  const int Ks = (int)((a.n + C::skew(C::H - 1) + kSub - 1) / kSub);  // C sub-chunks
-  const int Us = Ks * C::GPS;                                          // compute / publish units
-  const int Ut = (int)((a.n + G - 1) / G);                             // top units holding real columns
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  // steps of a band: n + 63, rounded up to whole sub-chunks
+  const int Ks = (int)((a.n + kBand - 1 + C::SUB - 1) / C::SUB);  // C sub-chunks
+  const int Us = Ks * C::GPS;                                  // compute / publish units
+  const int Ut = (int)((a.n + G - 1) / G);                     // top units holding real columns
   if (wave == 0) {
-    compute_band<T, G, R, SOFT>(S, Tr, sh, a.ctl, Us, band == 0, tr, SOFT ? (T)a.kx : T(1));
+    compute_band<T, G, R, SOFT>(S, Tr, sh, a.ctl, Ks, band == 0, tr, SOFT ? (T)a.kx : T(1));
   } else if (wave == 1) {
-    loader_band<T, G, R>(S, sh, a, band, Ks, tr);
+    publish_band<T, G, R>(S, sh, a, band, Us, epoch, tr);
   } else if (wave == 2) {
-    top_band<T, G, R>(S, Tr, sh, a, band, Ut, epoch, tr);
+    top_band<T, G, R>(Tr, sh, a, band, Ut, epoch, tr);
     // Top units beyond the last real column hold no values any real cell reads; mark
     // them loaded so that the compute wave's readiness test stays one comparison.
-    if ((threadIdx.x & 63) == 0 && sh.abort == 0u) lds_signal(&sh.ctr[1], 0x7fffffffu);
-  } else if (wave == 3) {
-    store_band<T, G, R, SOFT>(S, sh, a, band, Ks, tr);
+    if ((threadIdx.x & 63) == 0 && sh.abort == 0u) lds_signal(&sh.ctr[kCtrTop], kAllReady);
+  } else if (wave < 3 + R) {
+    loader_band<T, G, R>(S, sh, a, band, wave - 3, Ks, tr);
   } else {
-    publish_band<T, G, R>(S, sh, a, band, Us, epoch, tr);
+    store_band<T, G, R, SOFT>(S, sh, a, band, wave - 3 - R, Ks, tr);
   }
 }
 
 // TRACE = false compiles every trace statement out (the production instance); the traced
 // instance is launched only while tracing is enabled.
 template <typename T, int G, int R, bool TRACE, bool SOFT = false>
-__global__ __launch_bounds__(kThreads, 1) void fwd_kernel(FwdArgs a) {
+__global__ __launch_bounds__((64 * (3 + 2 * R)), 1) void fwd_kernel(FwdArgs a) {
   using C = FwdCfg<T, G, R>;
   if constexpr (!TRACE) a.trace = nullptr;
   __shared__ Vec4<T> S4[C::H * C::PITCH / 4];
@@ -767,9 +869,12 @@ __global__ __launch_bounds__(kThreads, 1) void fwd_kernel(FwdArgs a) {
   T* Tr = reinterpret_cast<T*>(Tr4);
   Control* ctl = a.ctl;
   const uint32_t epoch = __hip_atomic_load(&ctl->epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if (threadIdx.x == 0) sh.abort = 0u;
+  if (threadIdx.x == 0) {
+    sh.abort = 0u;
+    sh.warm = 0u;
+  }
   for (;;) {
-    if (threadIdx.x < 6) sh.ctr[threadIdx.x] = 0u;
+    if (threadIdx.x < 16) sh.ctr[threadIdx.x] = 0u;
     claim_next(ctl, &sh.item, &sh.abort);
     const int band = (int)sh.item;
     if (band >= a.nb || sh.abort != 0u) break;
@@ -782,7 +887,7 @@ __global__ __launch_bounds__(kThreads, 1) void fwd_kernel(FwdArgs a) {
       tr[7] = blockIdx.x;
     }
     run_band<T, G, R, SOFT>(S, Tr, sh, a, band, epoch, tr);
-    if (tr && threadIdx.x == 3 * 64) tr[3] = __builtin_amdgcn_s_memrealtime();
+    if (tr && threadIdx.x == (3 + R) * 64) tr[3] = __builtin_amdgcn_s_memrealtime();
     __syncthreads();
   }
   finish_launch(ctl, epoch);
@@ -793,7 +898,7 @@ __global__ __launch_bounds__(kThreads, 1) void fwd_kernel(FwdArgs a) {
 // instances by decreasing critical path), so a claimed band only ever waits for bands
 // that were claimed before it and are running or done.
 template <typename T, int G, int R>
-__global__ __launch_bounds__(kThreads, 1) void fwd_batch_kernel(BatchArgs b) {
+__global__ __launch_bounds__((64 * (3 + 2 * R)), 1) void fwd_batch_kernel(BatchArgs b) {
   using C = FwdCfg<T, G, R>;
   __shared__ Vec4<T> S4[C::H * C::PITCH / 4];
   __shared__ Vec4<T> Tr4[C::RING / 4];
@@ -802,9 +907,12 @@ __global__ __launch_bounds__(kThreads, 1) void fwd_batch_kernel(BatchArgs b) {
   T* Tr = reinterpret_cast<T*>(Tr4);
   Control* ctl = b.ctl;
   const uint32_t epoch = __hip_atomic_load(&ctl->epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if (threadIdx.x == 0) sh.abort = 0u;
+  if (threadIdx.x == 0) {
+    sh.abort = 0u;
+    sh.warm = 0u;
+  }
   for (;;) {
-    if (threadIdx.x < 6) sh.ctr[threadIdx.x] = 0u;
+    if (threadIdx.x < 16) sh.ctr[threadIdx.x] = 0u;
     claim_next(ctl, &sh.item, &sh.abort);
     const uint32_t item = sh.item;
     if (item >= (uint32_t)b.n_items || sh.abort != 0u) break;
@@ -821,6 +929,8 @@ __global__ __launch_bounds__(kThreads, 1) void fwd_batch_kernel(BatchArgs b) {
     a.n = in.n;
     a.ckpt_k = b.ckpt ? b.ckpt_k : 0;
     a.nb = in.nb;
+    a.rows = R;
+    a.pad = 0;
     a.ctl = ctl;
     a.bnd = b.bnd + in.bnd_off;
     a.trace = nullptr;
@@ -834,9 +944,11 @@ __global__ __launch_bounds__(kThreads, 1) void fwd_batch_kernel(BatchArgs b) {
 template <typename T, int R, bool TRACE>
 hipError_t launch_tt(int tile, const FwdArgs& a, int grid, hipStream_t s) {
   switch (tile) {
-    case 16: hipLaunchKernelGGL((fwd_kernel<T, 16, R, TRACE>), dim3(grid), dim3(kThreads), 0, s, a); break;
-    case 32: hipLaunchKernelGGL((fwd_kernel<T, 32, R, TRACE>), dim3(grid), dim3(kThreads), 0, s, a); break;
-    case 64: hipLaunchKernelGGL((fwd_kernel<T, 64, R, TRACE>), dim3(grid), dim3(kThreads), 0, s, a); break;
+    case 16: hipLaunchKernelGGL((fwd_kernel<T, 16, R, TRACE>), dim3(grid), dim3(64 * (3 + 2 * R)), 0, s, a); break;
+    case 32: hipLaunchKernelGGL((fwd_kernel<T, 32, R, TRACE>), dim3(grid), dim3(64 * (3 + 2 * R)), 0, s, a); break;
+    case 64:  // 32 where the ring holds sub-chunks of 32
+      hipLaunchKernelGGL((fwd_kernel<T, FwdCfg<T, 16, R>::SUB, R, TRACE>), dim3(grid), dim3(64 * (3 + 2 * R)), 0, s, a);
+      break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -849,30 +961,28 @@ hipError_t launch_t(int tile, const FwdArgs& a, int grid, hipStream_t s) {
 
 template <typename T, int R>
 hipError_t launch_batch_t(int tile, const BatchArgs& b, int grid, hipStream_t s) {
+  const dim3 g(grid), t(64 * (3 + 2 * R));
   switch (tile) {
-    case 16: hipLaunchKernelGGL((fwd_batch_kernel<T, 16, R>), dim3(grid), dim3(kThreads), 0, s, b); break;
-    case 32: hipLaunchKernelGGL((fwd_batch_kernel<T, 32, R>), dim3(grid), dim3(kThreads), 0, s, b); break;
-    case 64: hipLaunchKernelGGL((fwd_batch_kernel<T, 64, R>), dim3(grid), dim3(kThreads), 0, s, b); break;
+    case 16: hipLaunchKernelGGL((fwd_batch_kernel<T, 16, R>), g, t, 0, s, b); break;
+    case 32: hipLaunchKernelGGL((fwd_batch_kernel<T, 32, R>), g, t, 0, s, b); break;
+    case 64: hipLaunchKernelGGL((fwd_batch_kernel<T, 64, R>), g, t, 0, s, b); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
-// 64-row sub-bands per band of the single-instance sweep for the 4-byte types.  One is the
-// fastest at 16384 x 16384 on MI355X (two halve the handoffs but double the compute wave's
-// work per step and leave half of the compute units idle at 256 bands); double always
-// uses one.  The batch sweep lets its autotuner choose one or two.
-constexpr int kRowsF = 1;
-
 }  // namespace
 
-int forward_band_rows(int dtype) { return dtype == 1 ? kBand : kBand * kRowsF; }
-
 hipError_t launch_forward(int dtype, int tile, const FwdArgs& a, int grid, hipStream_t s) {
-  switch (dtype) {
-    case 0: return launch_t<float, kRowsF>(tile, a, grid, s);
-    case 1: return launch_t<double, 1>(tile, a, grid, s);
-    case 2: return launch_t<int32_t, kRowsF>(tile, a, grid, s);
+  switch (dtype * 8 + a.rows) {
+    case 1: return launch_t<float, 1>(tile, a, grid, s);
+    case 2: return launch_t<float, 2>(tile, a, grid, s);
+    case 4: return launch_t<float, 4>(tile, a, grid, s);
+    case 8 + 1: return launch_t<double, 1>(tile, a, grid, s);
+    case 8 + 2: return launch_t<double, 2>(tile, a, grid, s);
+    case 16 + 1: return launch_t<int32_t, 1>(tile, a, grid, s);
+    case 16 + 2: return launch_t<int32_t, 2>(tile, a, grid, s);
+    case 16 + 4: return launch_t<int32_t, 4>(tile, a, grid, s);
     default: return hipErrorInvalidValue;
   }
 }
@@ -881,8 +991,8 @@ hipError_t launch_forward(int dtype, int tile, const FwdArgs& a, int grid, hipSt
 // logarithm per cell), so the finest handoff unit, 16 columns, serves it best.
 hipError_t launch_forward_soft(int dtype, const FwdArgs& a, int grid, hipStream_t s) {
   switch (dtype) {
-    case 0: hipLaunchKernelGGL((fwd_kernel<float, 16, 1, false, true>), dim3(grid), dim3(kThreads), 0, s, a); break;
-    case 1: hipLaunchKernelGGL((fwd_kernel<double, 16, 1, false, true>), dim3(grid), dim3(kThreads), 0, s, a); break;
+    case 0: hipLaunchKernelGGL((fwd_kernel<float, 16, 1, false, true>), dim3(grid), dim3(5 * 64), 0, s, a); break;
+    case 1: hipLaunchKernelGGL((fwd_kernel<double, 16, 1, false, true>), dim3(grid), dim3(5 * 64), 0, s, a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

@@ -9,11 +9,6 @@ namespace wf {
 
 // Rows per band: one band is swept by one 64-lane wavefront, lane r owning band row r.
 constexpr int kBand = 64;
-// Waves of a sweep workgroup: 0 = compute, 1 = input loader, 2 = top-boundary poller,
-// 3 = output storer, 4 = boundary publisher.
-constexpr int kWaves = 5;
-constexpr int kThreads = kWaves * 64;
-
 // Device-resident control block of a workspace.  It resets itself: the last workgroup of a
 // launch clears 'claim' and 'done' and advances 'epoch', so a launch needs no host-side
 // memset and may be captured in a graph and replayed.
@@ -41,7 +36,9 @@ struct FwdArgs {
   int64_t ldc, ldd;
   int64_t m, n;
   int32_t ckpt_k;   // 0 = no checkpoints
-  int32_t nb;       // bands of the sweep = ceil(m / forward_band_rows(dtype))
+  int32_t nb;       // bands of the sweep = ceil(m / (64 * rows))
+  int32_t rows;     // rows per lane of a band: 1, 2 or 4 (double: 1 or 2)
+  int32_t pad;
   Control* ctl;
   uint64_t* bnd;    // (nb-1) * n * words-per-element handoff words (last row of each band)
   uint64_t* trace;  // null, or kTraceWords words per band (see wf_trace_enable)
@@ -169,8 +166,6 @@ struct BwdBatchArgs {
 
 // Host-side launchers (defined in wf_fwd.hip).  'tile' is 16, 32 or 64.
 hipError_t launch_forward(int dtype, int tile, const FwdArgs& a, int grid, hipStream_t s);
-// Rows per band of the single-instance forward sweep for a dtype.
-int forward_band_rows(int dtype);
 // Batch sweep; 'rows' = 64-row sub-bands per band: 1, or 2 for the 4-byte types.
 hipError_t launch_forward_batch(int dtype, int tile, int rows, const BatchArgs& b, int grid, hipStream_t s);
 // Adjoint launchers (defined in wf_bwd.hip), float (dtype 0) and double (dtype 1) only.

@@ -20,6 +20,14 @@
 
 using namespace wf;
 
+// A forward work list on the device, for bands of 64 * rows rows.
+struct WorkList {
+  int rows = 0;
+  BatchInst* inst = nullptr;      // instance table
+  BatchItem* items = nullptr;     // (instance, band) items
+  int32_t n_items = 0;
+};
+
 struct wf_plan {
   int dtype = 0;
   int dev = 0;
@@ -27,12 +35,11 @@ struct wf_plan {
   std::vector<int64_t> m, n, off;
   int64_t elems = 0;
   int tile = 0, rows = 0;         // the configuration in use
+  int table_rows = 0;             // rows per lane of the runs that write tables
   int num_cus = 0;
   Control* ctl = nullptr;         // the plan's own control block
-  BatchInst* inst = nullptr;      // device copy of the instance table for 'rows'
-  BatchItem* items = nullptr;     // device work list for 'rows'
-  int32_t n_items = 0;
-  int32_t ck_k = 0;               // checkpoint spacing K the instance table's ck_off is for
+  WorkList work[2];               // for 'rows', and for 'table_rows' where that differs
+  int32_t ck_k = 0;               // checkpoint spacing K the instance tables' ck_off is for
   uint64_t* bnd = nullptr;        // handoff words (sized for one row per band, the larger)
   hipStream_t cap = nullptr;      // private stream used only to capture the graph
   hipGraphExec_t exec = nullptr;  // captured launch, valid for the pointers below
@@ -110,24 +117,32 @@ void build_work(const wf_plan& p, int rows, int32_t K, std::vector<BatchInst>& i
   if (bnd_words == 0) bnd_words = 1;
 }
 
-int upload_work(wf_plan& p, int rows, int32_t K) {
+int upload_list(const wf_plan& p, WorkList& w, int rows, int32_t K) {
   std::vector<BatchInst> inst;
   std::vector<BatchItem> items;
   size_t words = 0;
   build_work(p, rows, K, inst, items, words);
-  if (p.inst) (void)hipFree(p.inst);
-  if (p.items) (void)hipFree(p.items);
-  p.inst = nullptr;
-  p.items = nullptr;
-  if (hipMalloc(&p.inst, inst.size() * sizeof(BatchInst)) != hipSuccess) { p.inst = nullptr; return WF_E_NOMEM; }
-  if (hipMalloc(&p.items, items.size() * sizeof(BatchItem)) != hipSuccess) { p.items = nullptr; return WF_E_NOMEM; }
-  if (hipMemcpy(p.inst, inst.data(), inst.size() * sizeof(BatchInst), hipMemcpyHostToDevice) != hipSuccess ||
-      hipMemcpy(p.items, items.data(), items.size() * sizeof(BatchItem), hipMemcpyHostToDevice) != hipSuccess)
+  if (w.inst) (void)hipFree(w.inst);
+  if (w.items) (void)hipFree(w.items);
+  w.inst = nullptr;
+  w.items = nullptr;
+  if (hipMalloc(&w.inst, inst.size() * sizeof(BatchInst)) != hipSuccess) { w.inst = nullptr; return WF_E_NOMEM; }
+  if (hipMalloc(&w.items, items.size() * sizeof(BatchItem)) != hipSuccess) { w.items = nullptr; return WF_E_NOMEM; }
+  if (hipMemcpy(w.inst, inst.data(), inst.size() * sizeof(BatchInst), hipMemcpyHostToDevice) != hipSuccess ||
+      hipMemcpy(w.items, items.data(), items.size() * sizeof(BatchItem), hipMemcpyHostToDevice) != hipSuccess)
     return WF_E_DEVICE;
-  p.n_items = (int32_t)items.size();
-  p.rows = rows;
-  p.ck_k = K;
+  w.n_items = (int32_t)items.size();
+  w.rows = rows;
   return WF_OK;
+}
+
+// The work lists of 'rows' and, where it differs, of 'table_rows'.
+int upload_work(wf_plan& p, int rows, int table_rows, int32_t K) {
+  p.rows = rows;
+  p.table_rows = table_rows;
+  p.ck_k = K;
+  const int rc = upload_list(p, p.work[0], rows, K);
+  return rc != WF_OK || table_rows == rows ? rc : upload_list(p, p.work[1], table_rows, K);
 }
 
 hipError_t launch_plan(const wf_plan& p, const void* C, void* D, void* scores, void* ckpt, hipStream_t s) {
@@ -138,14 +153,15 @@ hipError_t launch_plan(const wf_plan& p, const void* C, void* D, void* scores, v
   b.ckpt = ckpt;
   b.ckpt_k = ckpt ? p.ck_k : 0;
   b.pad2 = 0;
-  b.inst = p.inst;
-  b.items = p.items;
-  b.n_items = p.n_items;
+  const WorkList& w = p.work[D && p.table_rows != p.rows ? 1 : 0];
+  b.inst = w.inst;
+  b.items = w.items;
+  b.n_items = w.n_items;
   b.pad = 0;
   b.ctl = p.ctl;
   b.bnd = p.bnd;
-  const int grid = std::min(p.n_items, p.num_cus);
-  return launch_forward_batch(p.dtype, p.tile, p.rows, b, grid, s);
+  const int grid = std::min(w.n_items, p.num_cus);
+  return launch_forward_batch(p.dtype, p.tile, w.rows, b, grid, s);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -206,18 +222,18 @@ void tune_store(const std::string& key, int tile, int rows) {
 }
 
 // Times every allowed (tile, rows) on scratch buffers of the plan's size (the sweep's time
-// does not depend on the values) and keeps the fastest.  Synchronizes the stream.
+// does not depend on the values), scores only, and keeps the fastest.  Synchronizes the
+// stream.
 int autotune(wf_plan& p, int want_tile, int want_rows, hipStream_t s) {
   const int es = elem_size(p.dtype);
   const size_t bytes = (size_t)std::max<int64_t>(p.elems, 1) * es;
   void* C = nullptr;
-  void* D = nullptr;
   void* sc = nullptr;
   int rc = WF_OK;
   hipEvent_t e0 = nullptr, e1 = nullptr;
   float best = 1e30f;
   int best_tile = 0, best_rows = 0;
-  if (hipMalloc(&C, bytes) != hipSuccess || hipMalloc(&D, bytes) != hipSuccess ||
+  if (hipMalloc(&C, bytes) != hipSuccess ||
       hipMalloc(&sc, (size_t)p.batch * es) != hipSuccess) {
     rc = WF_E_NOMEM;
     goto done;
@@ -230,13 +246,13 @@ int autotune(wf_plan& p, int want_tile, int want_rows, hipStream_t s) {
   for (int rows : {1, 2}) {
     if (want_rows && rows != want_rows) continue;
     if (rows == 2 && p.dtype == WF_F64) continue;
-    if ((rc = upload_work(p, rows, 0)) != WF_OK) goto done;
+    if ((rc = upload_work(p, rows, rows, 0)) != WF_OK) goto done;
     for (int tile : {16, 32, 64}) {
       if (want_tile && tile != want_tile) continue;
       p.tile = tile;
       float t_min = 1e30f;
       for (int rep = 0; rep < 3; ++rep) {
-        if (hipEventRecord(e0, s) != hipSuccess || launch_plan(p, C, D, sc, nullptr, s) != hipSuccess ||
+        if (hipEventRecord(e0, s) != hipSuccess || launch_plan(p, C, nullptr, sc, nullptr, s) != hipSuccess ||
             hipEventRecord(e1, s) != hipSuccess || hipEventSynchronize(e1) != hipSuccess) {
           rc = WF_E_DEVICE;
           goto done;
@@ -262,7 +278,6 @@ done:
   if (e1) (void)hipEventDestroy(e1);
   (void)hipStreamSynchronize(s);
   if (C) (void)hipFree(C);
-  if (D) (void)hipFree(D);
   if (sc) (void)hipFree(sc);
   return rc;
 }
@@ -272,8 +287,10 @@ void free_plan(wf_plan* p) {
   (void)hipDeviceSynchronize();
   if (p->exec) (void)hipGraphExecDestroy(p->exec);
   if (p->cap) (void)hipStreamDestroy(p->cap);
-  if (p->inst) (void)hipFree(p->inst);
-  if (p->items) (void)hipFree(p->items);
+  for (WorkList& w : p->work) {
+    if (w.inst) (void)hipFree(w.inst);
+    if (w.items) (void)hipFree(w.items);
+  }
   if (p->bnd) (void)hipFree(p->bnd);
   if (p->b_inst) (void)hipFree(p->b_inst);
   if (p->b_items) (void)hipFree(p->b_items);
@@ -373,7 +390,7 @@ int ensure_fwd_ckpt(wf_plan& p, int32_t K) {
     (void)hipGraphExecDestroy(p.exec);
     p.exec = nullptr;
   }
-  return upload_work(p, p.rows, K);
+  return upload_work(p, p.rows, p.table_rows, K);
 }
 
 }  // namespace
@@ -487,7 +504,19 @@ int wf_plan_create(wf_plan** out, int dtype, int32_t batch, const int64_t* m, co
     }
   }
   p->tile = want_tile;
-  rc = upload_work(*p, want_rows, 0);
+  // Two rows per lane are the faster shape for scores alone (512 instances of 64 to 2048:
+  // 673 us against 1070; one loader's loads in flight per compute unit are too few).  With
+  // tables to write a large batch is bound by its memory traffic, which the one-row bands
+  // spread more evenly (1333 us against 1427; 64 x 2048^2: 592 against 682), a small one by
+  // its bands' starts and ends (300 instances of 64 to 300: 98 against 75).  The line lies
+  // at six 64-row bands per compute unit.
+  int table_rows = want_rows;
+  if (rows == 0 && want_rows == 2) {
+    int64_t bands = 0;
+    for (int32_t i = 0; i < batch; ++i) bands += (m[i] + kBand - 1) / kBand;
+    if (bands >= 6 * (int64_t)p->num_cus) table_rows = 1;
+  }
+  rc = upload_work(*p, want_rows, table_rows, 0);
   if (rc == WF_OK && hipStreamCreateWithFlags(&p->cap, hipStreamNonBlocking) != hipSuccess) {
     p->cap = nullptr;
     rc = WF_E_DEVICE;

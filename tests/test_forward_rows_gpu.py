@@ -1,0 +1,78 @@
+"""The forward sweep with one, two and four rows per lane, on the GPU.
+
+Which of them a shape takes depends on m / n; the shapes here lie on both sides of the rule's
+lines and of the band edges (64, 128 and 256 rows), with matrices narrower than one handoff
+unit, one column wide and with padded rows.  Tables, scores and checkpoint grids are bitwise
+equal to the float32 / float64 / int64 oracle's (one add per cell in every schedule).
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2510_27351_amd as wf
+from paper_2510_27351_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+SHAPES = [(65, 600), (64, 64), (65, 64), (127, 63), (128, 128), (129, 130), (300, 300), (255, 33), (256, 40),
+          (257, 60), (512, 100), (513, 7), (700, 1), (1025, 200), (1300, 31), (2049, 257)]
+
+
+def matrix(dtype, m, n, seed):
+    if dtype == torch.int32:
+        return inputs.integers(m, n, seed, lo=-100, hi=1000), "i64"
+    return inputs.normal_clipped(m, n, seed, dtype), "f32" if dtype == torch.float32 else "f64"
+
+
+def grid_of(D, k):
+    m, n = D.shape
+    parts = [D[r] for r in range(63, m - 1, 64)] + [D[:, q * k - 1] for q in range(1, (n + k - 1) // k)]
+    return torch.cat(parts) if parts else D.new_empty(0)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.int32, torch.float64])
+@pytest.mark.parametrize("m,n", SHAPES)
+def test_rows_per_lane_bitwise(dtype, m, n):
+    C, prec = matrix(dtype, m, n, 7 * m + n)
+    ref, _ = oracle.forward(C.numpy(), prec, want_sel=False)
+    pad = torch.full((m, n + 5), 3, dtype=dtype, device=DEV)
+    pad[:, :n] = C.to(DEV)
+    out = torch.full((m, n + 3), -7, dtype=dtype, device=DEV)
+    for tile in (0, 16, 64):
+        wf.set_tile(tile)
+        try:
+            D, score, ck = wf.forward(pad[:, :n], D=out[:, :n], ckpt_k=5)
+            _, alone, _ = wf.forward(C.to(DEV), table=False)
+            wf.last_async_error()
+        finally:
+            wf.set_tile(0)
+        got = D.cpu().numpy().astype(ref.dtype)
+        assert np.array_equal(got, ref), f"{m}x{n} tile {tile}: {(got != ref).sum()} cells differ"
+        assert score.item() == ref[-1, -1] and alone.item() == ref[-1, -1]
+        assert torch.equal(ck.cpu(), grid_of(D, 5).cpu())
+        assert bool((out[:, n:] == -7).all())
+
+
+@pytest.mark.parametrize("table", [False, True])
+@pytest.mark.parametrize("count", [3, 40, 1600])
+def test_autotuned_batch_bitwise(count, table):
+    """Small and large batches with the library's own configurations (runs with and without
+    tables may take different ones), one plan used for both in turn."""
+    g = torch.Generator().manual_seed(count)
+    ms = torch.randint(1, 140, (count,), generator=g).tolist()
+    ns = torch.randint(1, 90, (count,), generator=g).tolist()
+    mats = [torch.randn(m, n, generator=g) for m, n in zip(ms, ns)]
+    plan = wf.Plan(ms, ns)
+    C = plan.pack([x.to(DEV) for x in mats])
+    for t in (table, not table, table):
+        scores, D = plan.forward(C, table=t)
+        wf.last_async_error()
+        got = scores.cpu().numpy()
+        tabs = [d.cpu().numpy() for d in plan.unpack(D)] if t else None
+        for i, x in enumerate(mats):
+            ref, _ = oracle.forward(x.numpy(), "f32", want_sel=False)
+            assert got[i] == ref[-1, -1], f"instance {i} {ms[i]}x{ns[i]}"
+            if t:
+                assert np.array_equal(tabs[i], ref), f"instance {i} {ms[i]}x{ns[i]}"
