@@ -268,19 +268,62 @@ struct Cell4<double> {
 };
 
 // SOFT: the soft-min cell instead (one row per lane only), on values in the scaled domain
-// y = D log2(e) / gamma; kx scales the cell's input C the same way.
+// y = D log2(e) / gamma, the loader having scaled C the same way.  float: the operations of
+// soft_cell, one instruction each, as one block per four steps like the min-plus cell's.  A
+// step is issue-bound (13 instructions of 4.1 cycles and 3 transcendental ones of 8.6); left
+// to the compiler it took 62 ns: it canonicalised the shifted operands, tested for +inf by a
+// compare and a select, and waited a state after most inline or transcendental results.  A
+// transcendental result may be read two instructions later at the earliest: the second
+// exponential, an add and the top row's shift stand between.  Three inputs of +inf give
+// inf - inf = NaN, which the final minimum with +inf turns into +inf, and leaves every other
+// value as it is.
+template <typename T>
+__device__ __forceinline__ void soft_cells4(ComputeState<T, 1>& st, const Vec4<T> (&c)[1], Vec4<T> (&d)[1]) {
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const T N = Elem<T>::shr1(st.X[0], st.top);
+    st.top = shl1(st.top);
+    st.X[0] = soft_cell<T>(c[0].v[q], st.NW, N, st.X[0]);
+    st.NW = N;
+    d[0].v[q] = st.X[0];
+  }
+}
+#define WF_SOFT1(T0, NW, X, D, C)                                         \
+  "v_mov_b32 " T0 ", %[top]\n\t"                                          \
+  "v_mov_b32_dpp " T0 ", " X " wave_shr:1 row_mask:0xf bank_mask:0xf\n\t" \
+  "v_min3_f32 %[mn], " NW ", " T0 ", " X "\n\t"                           \
+  "v_med3_f32 %[md], " NW ", " T0 ", " X "\n\t"                           \
+  "v_max3_f32 %[mx], " NW ", " T0 ", " X "\n\t"                           \
+  "v_sub_f32 %[md], %[mn], %[md]\n\t"                                     \
+  "v_sub_f32 %[mx], %[mn], %[mx]\n\t"                                     \
+  "v_exp_f32 %[md], %[md]\n\t"                                            \
+  "v_exp_f32 %[mx], %[mx]\n\t"                                            \
+  "v_add_f32 %[md], 1.0, %[md]\n\t"                                       \
+  "v_add_f32 %[md], %[md], %[mx]\n\t"                                     \
+  "v_log_f32 %[md], %[md]\n\t"                                            \
+  "v_mov_b32_dpp %[top], %[top] wave_shl:1 row_mask:0xf bank_mask:0xf\n\t" \
+  "v_sub_f32 %[md], %[mn], %[md]\n\t"                                     \
+  "v_add_f32 " D ", " C ", %[md]\n\t"                                     \
+  "v_min_f32 " D ", %[inf], " D "\n\t"
+__device__ __forceinline__ void soft_cells4(ComputeState<float, 1>& st, const Vec4<float> (&c)[1], Vec4<float> (&d)[1]) {
+  float t, mn, md, mx;
+  const float inf = Elem<float>::inf();
+  asm("s_nop 0\n\t" WF_SOFT1("%[t]", "%[nw]", "%[x]", "%[d0]", "%[c0]") "s_nop 0\n\t"
+          WF_SOFT1("%[nw]", "%[t]", "%[d0]", "%[d1]", "%[c1]") "s_nop 0\n\t"
+              WF_SOFT1("%[t]", "%[nw]", "%[d1]", "%[d2]", "%[c2]") "s_nop 0\n\t"
+                  WF_SOFT1("%[nw]", "%[t]", "%[d2]", "%[d3]", "%[c3]")
+      : [top] "+v"(st.top), [nw] "+v"(st.NW), [t] "=&v"(t), [mn] "=&v"(mn), [md] "=&v"(md), [mx] "=&v"(mx),
+        [d0] "=&v"(d[0].v[0]), [d1] "=&v"(d[0].v[1]), [d2] "=&v"(d[0].v[2]), [d3] "=&v"(d[0].v[3])
+      : [x] "v"(st.X[0]), [c0] "v"(c[0].v[0]), [c1] "v"(c[0].v[1]), [c2] "v"(c[0].v[2]), [c3] "v"(c[0].v[3]),
+        [inf] "v"(inf));
+  st.X[0] = d[0].v[3];
+}
+
 template <typename T, int R, bool SOFT>
-__device__ __forceinline__ void cells4(ComputeState<T, R>& st, const Vec4<T> (&c)[R], Vec4<T> (&out)[R], T kx) {
+__device__ __forceinline__ void cells4(ComputeState<T, R>& st, const Vec4<T> (&c)[R], Vec4<T> (&out)[R]) {
   if constexpr (SOFT) {
     static_assert(R == 1, "the soft-min sweep uses one row per lane");
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const T N = Elem<T>::shr1(st.X[0], st.top);
-      st.top = shl1(st.top);
-      st.X[0] = soft_cell<T>(c[0].v[q] * kx, st.NW, N, st.X[0]);
-      st.NW = N;
-      out[0].v[q] = st.X[0];
-    }
+    soft_cells4(st, c, out);
   } else {
     Cell4<T>::run(st, c, out);
   }
@@ -336,7 +379,7 @@ template <typename T, int G, int R, bool SOFT>
 __device__ __forceinline__ bool compute_unit(T* __restrict__ S, const T* __restrict__ Tr, Shared& sh, Control* ctl,
                                              uint32_t* steps, int base, int next_base, uint32_t done, uint32_t need,
                                              ComputeState<T, R>& st, UnitRegs<T, G, R>& P, uint32_t (&stalls)[2],
-                                             uint64_t& waited, bool trace, T kx) {
+                                             uint64_t& waited, bool trace) {
   using C = FwdCfg<T, G, R>;
   constexpr int NG = C::NG;
   const int lane = threadIdx.x & 63;
@@ -368,7 +411,7 @@ __device__ __forceinline__ bool compute_unit(T* __restrict__ S, const T* __restr
     // gathers the reads of several groups into one burst just before the first of them)
     __builtin_amdgcn_sched_barrier(0);
     Vec4<T> d[R];
-    cells4<T, R, SOFT>(st, gr[g].c, d, kx);
+    cells4<T, R, SOFT>(st, gr[g].c, d);
 #pragma unroll
     for (int k = 0; k < R; ++k) *reinterpret_cast<Vec4<T>*>(S + (k * kBand + lane) * C::PITCH + base + 4 * g) = d[k];
   }
@@ -387,9 +430,12 @@ __device__ __forceinline__ bool compute_unit(T* __restrict__ S, const T* __restr
 
 template <typename T, int G, int R, bool SOFT>
 __device__ __forceinline__ void compute_band(T* __restrict__ S, const T* __restrict__ Tr, Shared& sh, Control* ctl,
-                                             int Ks, bool first_band, uint64_t* trace, T kx) {
+                                             int Ks, bool first_band, uint64_t* trace) {
   using E = Elem<T>;
   using C = FwdCfg<T, G, R>;
+  // The double soft-min cell is some 170 instructions: a sub-chunk's 64 unrolled would not
+  // fit the instruction cache (500 x 700: 535 us against 496).
+  constexpr int UNROLL = SOFT && sizeof(T) == 8 ? 1 : C::GPS;
   const int lane = threadIdx.x & 63;
   const bool tr = trace != nullptr;
   // what unit 0 needs, and what each next unit and each next sub-chunk add
@@ -429,12 +475,12 @@ __device__ __forceinline__ void compute_band(T* __restrict__ S, const T* __restr
     for (int s = s0; s < s1; ++s) {
       const int base = (C::SUB * s) & C::MASK;
       const int next = (C::SUB * (s + 1)) & C::MASK;
-#pragma unroll
+#pragma unroll UNROLL
       for (int v = 0; v < C::GPS; ++v) {
         need += per_unit;
         if (v + 1 == C::GPS) need += per_sub;
         if (!compute_unit<T, G, R, SOFT>(S, Tr, sh, ctl, steps, base + G * v, v + 1 < C::GPS ? base + G * (v + 1) : next,
-                                         (uint32_t)(C::SUB * s + G * (v + 1)), need, st, P, stalls, waited, tr, kx)) {
+                                         (uint32_t)(C::SUB * s + G * (v + 1)), need, st, P, stalls, waited, tr)) {
           sh.abort = 1u;
           return;
         }
@@ -509,8 +555,9 @@ __device__ __forceinline__ bool interior_sub(int s, int64_t n) {
   return SUB * s >= kBand - 1 && (int64_t)SUB * s + SUB <= n;
 }
 
-template <typename T, int G, int R>
-__device__ __forceinline__ void store_sub_lds(T* S, const SubBuf<T, G, R>& buf, int h, int s, int64_t n) {
+// SOFT: scaled by kx = log2(e) / gamma on the way.
+template <typename T, int G, int R, bool SOFT>
+__device__ __forceinline__ void store_sub_lds(T* S, const SubBuf<T, G, R>& buf, int h, int s, int64_t n, T kx) {
   using C = FwdCfg<T, G, R>;
   using E = typename C::E;
   const bool interior = interior_sub<T, G, R>(s, n);
@@ -518,6 +565,10 @@ __device__ __forceinline__ void store_sub_lds(T* S, const SubBuf<T, G, R>& buf, 
   for (int k = 0; k < C::NV; ++k) {
     const SubVec<T, G, R> q(h, k, s);
     Vec4<T> v = buf[k];
+    if constexpr (SOFT) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v.v[e] *= kx;
+    }
     if (!interior) {
       const int64_t c0 = q.c0();
 #pragma unroll
@@ -528,10 +579,11 @@ __device__ __forceinline__ void store_sub_lds(T* S, const SubBuf<T, G, R>& buf, 
   }
 }
 
-template <typename T, int G, int R>
+template <typename T, int G, int R, bool SOFT>
 __device__ __forceinline__ void loader_band(T* S, Shared& sh, const FwdArgs& a, int band, int h, int Ks, uint64_t* tr) {
   using C = FwdCfg<T, G, R>;
   const int64_t ldc = opaque(a.ldc), n = opaque(a.n);
+  const T kx = SOFT ? (T)a.kx : T(1);
   const int64_t row0 = (int64_t)band * C::H;
   const int rows = (int)(a.m - row0 < C::H ? a.m - row0 : C::H);
   const __amdgpu_buffer_rsrc_t rsrc = make_rsrc(static_cast<const T*>(a.C) + row0 * ldc,
@@ -558,7 +610,7 @@ __device__ __forceinline__ void loader_band(T* S, Shared& sh, const FwdArgs& a, 
           sh.abort = 1u;
           return;
         }
-        store_sub_lds<T, G, R>(S, buf[p], h, s, n);
+        store_sub_lds<T, G, R, SOFT>(S, buf[p], h, s, n, kx);
         lds_signal(&sh.ctr[ctr_loaded(h)], s + 1 < Ks ? (uint32_t)(s + 1) : kAllReady);
         if (s + C::PF < Ks) load_sub<T, G, R>(buf[p], rsrc, ldc, h, s + C::PF);
       }
@@ -841,7 +893,7 @@ __device__ __forceinline__ void run_band(T* S, T* Tr, Shared& sh, const FwdArgs&
   const int Us = Ks * C::GPS;                                  // compute / publish units
   const int Ut = (int)((a.n + G - 1) / G);                     // top units holding real columns
   if (wave == 0) {
-    compute_band<T, G, R, SOFT>(S, Tr, sh, a.ctl, Ks, band == 0, tr, SOFT ? (T)a.kx : T(1));
+    compute_band<T, G, R, SOFT>(S, Tr, sh, a.ctl, Ks, band == 0, tr);
   } else if (wave == 1) {
     publish_band<T, G, R>(S, sh, a, band, Us, epoch, tr);
   } else if (wave == 2) {
@@ -850,7 +902,7 @@ __device__ __forceinline__ void run_band(T* S, T* Tr, Shared& sh, const FwdArgs&
     // them loaded so that the compute wave's readiness test stays one comparison.
     if ((threadIdx.x & 63) == 0 && sh.abort == 0u) lds_signal(&sh.ctr[kCtrTop], kAllReady);
   } else if (wave < 3 + R) {
-    loader_band<T, G, R>(S, sh, a, band, wave - 3, Ks, tr);
+    loader_band<T, G, R, SOFT>(S, sh, a, band, wave - 3, Ks, tr);
   } else {
     store_band<T, G, R, SOFT>(S, sh, a, band, wave - 3 - R, Ks, tr);
   }
@@ -871,7 +923,8 @@ __global__ __launch_bounds__((64 * (3 + 2 * R)), 1) void fwd_kernel(FwdArgs a) {
   const uint32_t epoch = __hip_atomic_load(&ctl->epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if (threadIdx.x == 0) {
     sh.abort = 0u;
-    sh.warm = 0u;
+    // (the double soft-min loop is so slow that a pass over it costs more than its fetch)
+    sh.warm = SOFT && sizeof(T) == 8 ? 1u : 0u;
   }
   for (;;) {
     if (threadIdx.x < 16) sh.ctr[threadIdx.x] = 0u;
