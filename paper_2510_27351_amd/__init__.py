@@ -261,6 +261,8 @@ class SoftWfFunction(torch.autograd.Function):
     @staticmethod
     def forward(ctx, C: torch.Tensor, gamma: float):
         C = C.contiguous()
+        # an output the loss does not use arrives as None, not as zeros to be filled and read
+        ctx.set_materialize_grads(False)
         D, score = soft_forward(C, gamma)
         ctx.save_for_backward(C, D)
         ctx.gamma = gamma

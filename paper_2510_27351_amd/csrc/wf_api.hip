@@ -147,6 +147,21 @@ int ensure_path(int dev, hipStream_t s, size_t exits, size_t caps, size_t F, Pat
   return rc;
 }
 
+// Copies of inputs that a caller's output overlaps (the soft-min adjoint), per (device, stream).
+struct CopyWs {
+  int32_t* buf[2] = {nullptr, nullptr};
+  size_t words[2] = {0, 0};
+};
+std::map<std::pair<int, hipStream_t>, CopyWs> g_copy;
+
+int ensure_copy(int dev, hipStream_t s, int which, size_t bytes, void** out) {
+  std::lock_guard<std::mutex> lk(g_mu);
+  CopyWs& w = g_copy[{dev, s}];
+  const int rc = grow_words(&w.buf[which], &w.words[which], (bytes + 3) / 4);
+  *out = w.buf[which];
+  return rc;
+}
+
 // Grows the adjoint's selection buffer of a workspace that ensure_ws has set up.
 int ensure_sel(DeviceWs* w, size_t words) {
   std::lock_guard<std::mutex> lk(g_mu);
@@ -776,8 +791,29 @@ int wf_soft_backward(int dtype, int64_t m, int64_t n, double gamma, const void* 
   if (hipGetDevice(&dev) != hipSuccess) return WF_E_DEVICE;
   DeviceWs* ws = nullptr;
   rc = ensure_ws_on(dev, static_cast<hipStream_t>(stream),
-                    (size_t)(nb > 1 ? nb - 1 : 1) * (size_t)n * 3 * words_per_elem(dtype), &ws);
+                    (size_t)(nb > 1 ? nb - 1 : 1) * (size_t)n * words_per_elem(dtype), &ws);
   if (rc != WF_OK) return rc;
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  // The loaders read a row again after the band below it may have written its gradient: an
+  // output that overlaps C or D (a gradient written in place) gets a copy of that input.
+  auto bytes_of = [&](int64_t ld) { return (size_t)((m - 1) * ld + n) * es; };
+  auto overlaps = [&](const void* p, int64_t ld) {
+    const uintptr_t a0 = reinterpret_cast<uintptr_t>(p), b0 = reinterpret_cast<uintptr_t>(g_C);
+    return a0 < b0 + bytes_of(ldgc) && b0 < a0 + bytes_of(ld);
+  };
+  const void** in[2] = {&C, &D};
+  int64_t* ld[2] = {&ldc, &ldd};
+  for (int k = 0; k < 2; ++k) {
+    if (!overlaps(*in[k], *ld[k])) continue;
+    void* copy = nullptr;
+    rc = ensure_copy(dev, st, k, (size_t)m * n * es, &copy);
+    if (rc != WF_OK) return rc;
+    if (hipMemcpy2DAsync(copy, (size_t)n * es, *in[k], (size_t)*ld[k] * es, (size_t)n * es, (size_t)m,
+                         hipMemcpyDeviceToDevice, st) != hipSuccess)
+      return WF_E_DEVICE;
+    *in[k] = copy;
+    *ld[k] = n;
+  }
   SoftArgs a;
   std::memset(&a, 0, sizeof(a));
   a.C = C;
@@ -795,8 +831,8 @@ int wf_soft_backward(int dtype, int64_t m, int64_t n, double gamma, const void* 
   a.kx = 1.0 / (gamma * std::log(2.0));
   a.ctl = ws->ctl;
   a.bnd = ws->bnd;
-  const int grid = (int)std::min<int64_t>(nb, 4 * (int64_t)ws->num_cus);
-  return launch_soft_backward(dtype, a, grid, static_cast<hipStream_t>(stream)) == hipSuccess ? WF_OK : WF_E_DEVICE;
+  const int grid = (int)std::min<int64_t>(nb, ws->num_cus);
+  return launch_soft_backward(dtype, a, grid, st) == hipSuccess ? WF_OK : WF_E_DEVICE;
 }
 
 int wf_trace_enable(int64_t max_bands) {

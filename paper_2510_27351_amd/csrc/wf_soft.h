@@ -21,7 +21,7 @@ struct SoftArgs {
   int32_t pad;
   double kx;
   Control* ctl;
-  uint64_t* bnd;        // adjoint: (nb-1) * n * 3 * W words, (A, D, C) per column
+  uint64_t* bnd;        // adjoint: (nb-1) * n * W words, the last row of each band
 };
 hipError_t launch_soft_backward(int dtype, const SoftArgs& a, int grid, hipStream_t s);
 // The soft-min forward runs in the min-plus forward's band pipeline (wf_fwd.hip) with the

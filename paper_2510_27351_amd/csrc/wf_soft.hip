@@ -1,10 +1,10 @@
-// Smooth (soft-min) variant of the wavefront recurrence on gfx950 (wf_soft_forward,
-// wf_soft_backward in include/wf.h).
+// Smooth (soft-min) variant of the wavefront recurrence on gfx950: the adjoint
+// (wf_soft_backward in include/wf.h).  The forward runs in the min-plus forward's band
+// pipeline (wf_fwd.hip) with the soft-min cell in place of the minimum.
 //
 // The minimum of the north-west, north and west neighbours is replaced by the soft minimum
-// of temperature gamma,  softmin(x) = -gamma log sum_k exp(-x_k / gamma),  evaluated about
-// the smallest argument mn:  softmin = mn - gamma ln2 log2( sum_k 2^((mn - x_k) log2e / gamma) ).
-// The adjoint of  L = sum(gD * D) + gscore * score  is
+// of temperature gamma,  softmin(x) = -gamma log sum_k exp(-x_k / gamma).  The adjoint of
+// L = sum(gD * D) + gscore * score  is
 //     A[i][j] = gD[i][j] + [last] gscore + w(i+1,j+1) A[i+1][j+1] + w(i+1,j) A[i+1][j]
 //             + w(i,j+1) A[i][j+1],       w(succ) = 2^((V(succ) - D[i][j]) log2e / gamma),
 // with V(succ) = D(succ) - C(succ) the successor's soft minimum, so the weight is the
@@ -12,23 +12,37 @@
 // exponent is evaluated as (D(succ) - D[i][j]) log2e/gamma - C(succ) log2e/gamma, one fused
 // multiply-add after the difference of two neighbouring table values, which is exact in
 // floating point, so the weight's error is that of numbers of the size of C, not of the
-// table.  (Forming V first would round it at the
-// table's magnitude, and along a path of L cells those roundings add up: at 16384 x 16384
-// in float32 that made the first cell's gradient 8% off.)
+// table.  (Forming V first would round it at the table's magnitude, and along a path of L
+// cells those roundings add up: at 16384 x 16384 in float32 that made the first cell's
+// gradient 8% off.)
 //
-// The forward runs in the min-plus forward's band pipeline (wf_fwd.hip) with the soft-min
-// cell in place of the minimum; this file holds the adjoint, a band pipeline of six waves
-// per 64-row band (described with its kernel below).  Every wait is bounded.
+// Structure.  The weights depend on C and D alone, so only three fused multiply-adds per cell
+// are serial; the three exponentials are taken by the waves that load the inputs.  Seen from
+// the far corner the sweep is a forward sweep: with row i' = m-1-i and column c' = n-1-c a
+// cell reads its west, north and north-west neighbours, and this is the forward's band
+// pipeline (wf_fwd.hip) over 64-row bands of i', lane r owning row i' = 64b + r and handling
+// column t - r at step t.  Three LDS rings hold the weights of the three neighbours (and a
+// fourth gD, when given) at slot (c' + r) mod RING, so that at step t every lane touches slot
+// t and four steps are one aligned 16-byte read per ring; A overwrites the west weight, from
+// where it is stored as gC.  The waves:
+//   wave 0        compute    per 4 steps: the vectors of every ring, 4 x (DPP shift of A from
+//                            the lane above, 3 fused multiply-adds), the A vector back to LDS;
+//   wave 1        publisher  the band's last row of A as epoch-tagged words for the next band;
+//   wave 2        top        polls those of the band before into the top ring, 64 columns per
+//                            pass;
+//   waves 3 .. 6  loaders    16 rows each: D and C of the row and of the row below it, the
+//                            weights into the rings;
+//   wave 7        storer     each finished sub-chunk of A back to gC;
+//   wave 8        gD loader  (only with gD).
+// Every wait is bounded.  What bounds it: the compute wave's issue (six VALU instructions per
+// step and its LDS accesses) and 63 + 16 steps of skew plus the handoff (about 1.1 us) from
+// band to band; in float64 the loaders' exponentials.  With the exponentials in the compute
+// wave and (A, D, C) handed on, 4096 x 4096 float32 took 1181 us and one band 64 ns per step.
 #include "wf_common.h"
 #include "wf_soft.h"
 
-#include <type_traits>
-
 namespace wf {
 namespace {
-
-constexpr int kRing = 512;   // handoff ring: columns
-constexpr int kFill = 128;   // fill columns after the last one (at least the groups' overhang)
 
 // Four consecutive columns of one row, as one (float) or two (double) 16-byte transfers.
 template <typename T>
@@ -50,18 +64,12 @@ __device__ __forceinline__ Vec4<T> load4(__amdgpu_buffer_rsrc_t r, uint32_t off)
   return v;
 }
 
-// wave_shl:1 -- lane r receives lane r+1's value; lane 63 keeps 'old'.
 template <typename T>
-__device__ __forceinline__ T shl1_(T src, T old) {
-  auto mv = [](uint32_t s, uint32_t o) {
-    return (uint32_t)__builtin_amdgcn_update_dpp((int)o, (int)s, 0x130, 0xf, 0xf, false);
-  };
+__device__ __forceinline__ T load1(__amdgpu_buffer_rsrc_t r, uint32_t off) {
   if constexpr (sizeof(T) == 4) {
-    return __builtin_bit_cast(T, mv(__builtin_bit_cast(uint32_t, src), __builtin_bit_cast(uint32_t, old)));
+    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
   } else {
-    const uint64_t s = __builtin_bit_cast(uint64_t, src), o = __builtin_bit_cast(uint64_t, old);
-    const uint64_t lo = mv((uint32_t)s, (uint32_t)o), hi = mv((uint32_t)(s >> 32), (uint32_t)(o >> 32));
-    return __builtin_bit_cast(T, (hi << 32) | lo);
+    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
   }
 }
 
@@ -73,216 +81,6 @@ __device__ __forceinline__ void store1(__amdgpu_buffer_rsrc_t r, uint32_t off, T
     using V2 = __attribute__((ext_vector_type(2))) uint32_t;
     __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(V2, x), r, off, 0, 0);
   }
-}
-
-// Range-checked resource over rows [row0, row0 + rows) of a matrix with leading dimension
-// ld: the last row ends at its n-th element, so nothing past the caller's data is touched.
-template <typename T>
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t band_rsrc(const void* base, int64_t row0, int rows, int64_t ld,
-                                                            int64_t n) {
-  const T* p = static_cast<const T*>(base) + row0 * ld;
-  const int64_t bytes = rows > 0 ? ((int64_t)(rows - 1) * ld + n) * (int64_t)sizeof(T) : 0;
-  return make_rsrc(p, (uint32_t)bytes);
-}
-
-struct alignas(8) SoftShared {
-  uint32_t avail;     // handoff columns in the ring, in the consumer's order
-  uint32_t used;      // columns the compute wave has finished with
-  uint32_t item;
-  uint32_t abort;
-  uint32_t produced;  // steps whose edge-row values the compute wave has put in the out ring
-  uint32_t pubd;      // steps whose values the publisher has stored
-  uint32_t ld[2];     // adjoint: sub-chunks of D and of C staged in LDS
-  uint32_t done;      // adjoint: sub-chunks the compute wave has finished
-  uint32_t stored;    // adjoint: sub-chunks of gC the storer has written back
-};
-
-// Out ring: the compute wave's edge-row values (NV per step) for the publisher wave, which
-// turns them into coalesced tagged words; kPub steps.
-constexpr int kPub = 256;
-
-// The publisher wave: stores the values of steps [0, total) of the out ring as tagged words,
-// 64 steps per pass, as the compute wave produces them.  Step s holds the values of column
-// col(s) (or none, outside [0, n)); 'dst(c, v)' is the first word of value v of column c.
-template <typename T, int NV, typename Col, typename Dst>
-__device__ __forceinline__ bool publish_ring(const T* pub, SoftShared& sh, Control* ctl, int64_t n, uint32_t total,
-                                             uint32_t epoch, Col col, Dst dst) {
-  using E = Elem<T>;
-  constexpr int W = E::W;
-  const int lane = threadIdx.x & 63;
-  uint64_t waited = 0;
-  uint32_t ps = 0;
-  while (ps < total) {
-    uint32_t have;
-    if (!lds_wait_value<true, false>(&sh.produced, ps + 1, &sh.abort, ctl, waited, have)) return false;
-    const uint32_t pe = have < ps + 64 ? have : ps + 64;
-    const uint32_t st = ps + (uint32_t)lane;
-    if (st < pe) {
-      const int64_t c = col((int64_t)st);
-      if (c >= 0 && c < n) {
-#pragma unroll
-        for (int v = 0; v < NV; ++v) {
-          const T x = pub[v * kPub + (int)(st & (kPub - 1))];
-          uint64_t* d = dst(c, v);
-#pragma unroll
-          for (int w = 0; w < W; ++w) store_word(d + w, tagged(E::word(x, w), epoch));
-        }
-      }
-    }
-    ps = pe;
-    lds_signal(&sh.pubd, ps);
-  }
-  return true;
-}
-
-// ---------------------------------------------------------------------------------------
-// The poller: fetches the producer band's tagged words, 64 columns per pass from the first
-// one not yet handed over, and hands over the leading run of complete columns.  NV values
-// per column (the adjoint's A, D and scaled C), each of W payload words; 'word_at(k)' is the
-// address of the first word of consumer column k.  After the last column it writes 'fill'
-// into the next kFill columns of the ring and counts them as delivered.
-template <typename T, int NV, typename WordAt>
-__device__ __forceinline__ bool poll_ring(T* ring, SoftShared& sh, Control* ctl, int64_t n, uint32_t epoch,
-                                          const T (&fill)[NV], WordAt word_at) {
-  using E = Elem<T>;
-  constexpr int W = E::W;
-  const int lane = threadIdx.x & 63;
-  uint64_t waited = 0, t0 = 0;
-  uint32_t polls = 0;
-  int64_t u = 0;
-  while (u < n) {
-    // ring slots of columns u .. u+63 are free once the compute wave is past column u+63-kRing
-    const int64_t need = u + 64 - kRing;
-    if (need > 0 && !lds_wait_ge(&sh.used, (uint32_t)need, &sh.abort, ctl, waited)) return false;
-    const int64_t k = u + lane;
-    const bool real = k < n;
-    const uint64_t* src = real ? word_at(k) : reinterpret_cast<const uint64_t*>(ctl) + 4;
-    // Two polls in flight: while one pass's words are checked, the next pass's are on their
-    // way, so readiness is seen about half a round trip sooner than with one.
-    uint64_t xa[NV * W], xb[NV * W];
-    auto issue = [&](uint64_t (&x)[NV * W]) {
-#pragma unroll
-      for (int q = 0; q < NV * W; ++q) x[q] = load_word(src + q);
-    };
-    // the leading run of complete columns in x (columns past the matrix count as complete)
-    auto complete = [&](const uint64_t (&x)[NV * W]) -> int {
-      bool ok = true;
-#pragma unroll
-      for (int q = 0; q < NV * W; ++q) ok = ok && (uint32_t)(x[q] >> 32) == epoch;
-      ok = ok || !real;
-      const uint64_t okm = __ballot(ok);
-      const int run = ~okm == 0 ? 64 : __builtin_ctzll(~okm);
-      return (int)(run < n - u ? run : n - u);
-    };
-    // false when the wait has to give up
-    auto pause = [&]() -> bool {
-      if (polls == 0) t0 = __builtin_amdgcn_s_memrealtime();
-      __builtin_amdgcn_s_sleep(1);
-      if ((++polls & 63u) == 0u) {
-        if (lds_load(&sh.abort) != 0u || global_aborted(ctl)) return false;
-        if (__builtin_amdgcn_s_memrealtime() - t0 > kSpinTicks) {
-          raise_timeout(ctl);
-          return false;
-        }
-      }
-      return true;
-    };
-    auto deliver = [&](const uint64_t (&x)[NV * W], int take) {
-      if (lane < take) {
-#pragma unroll
-        for (int v = 0; v < NV; ++v) {
-          uint32_t w[W];
-#pragma unroll
-          for (int q = 0; q < W; ++q) w[q] = (uint32_t)x[v * W + q];
-          ring[v * kRing + (int)((u + lane) & (kRing - 1))] = E::from_words(w);
-        }
-      }
-      u += take;
-      lds_publish(&sh.avail, (uint32_t)u);
-    };
-    issue(xa);
-    for (;;) {
-      issue(xb);
-      int take = complete(xa);
-      if (take > 0) {
-        deliver(xa, take);
-        break;
-      }
-      if (!pause()) return false;
-      issue(xa);
-      take = complete(xb);
-      if (take > 0) {
-        deliver(xb, take);
-        break;
-      }
-      if (!pause()) return false;
-    }
-    polls = 0;
-  }
-  // the kFill columns after the last one hold 'fill', so that the consumer's vector reads of
-  // them need no selects; they count as delivered once written
-  if (n + kFill - kRing > 0 && !lds_wait_ge(&sh.used, (uint32_t)(n + kFill - kRing), &sh.abort, ctl, waited))
-    return false;
-  for (int c = lane; c < kFill; c += 64) {
-#pragma unroll
-    for (int v = 0; v < NV; ++v) ring[v * kRing + (int)((n + c) & (kRing - 1))] = fill[v];
-  }
-  lds_publish(&sh.avail, (uint32_t)(n + kFill));
-  return true;
-}
-
-// ---------------------------------------------------------------------------------------
-// Adjoint: a band pipeline of six waves per 64-row band, bands claimed bottom-up.
-//
-// Lane r owns band row r and at step t handles column n + 62 - r - t (the bottom row leads,
-// right to left).  D and C are staged in two skewed LDS rings: element (row r, column c) sits
-// at slot (n + 62 - r - c) mod RING, the step that uses it, so at step t every lane touches
-// slot t and four steps are one aligned 16-byte LDS read per ring.  Slots [4j, 4j+4) of a row
-// hold four consecutive columns in descending order, one (4-byte aligned) 16-byte global
-// transfer with its elements reversed.  The compute wave writes A over C in place; a storer
-// wave writes it back as gC.
-//   wave 0  compute   per 4 steps: the D and C vectors (read one group ahead), the band
-//                     below's (A, D, C log2e/gamma) from the handoff ring, 3 x 4 weights,
-//                     the A vector back to LDS, and row 0's (A, D, C log2e/gamma) into the
-//                     out ring;
-//   wave 1  loader    sub-chunks of D (SUB slots of every row), one in flight in registers;
-//   wave 2  loader    the same for C;
-//   wave 3  poller    the band below's row-0 (A, D, C log2e/gamma) words into the handoff ring;
-//   wave 4  storer    each finished sub-chunk's A back to gC;
-//   wave 5  publisher this band's row-0 (A, D, C log2e/gamma) words for the band above.
-// With an upstream gD the compute wave reads it straight from global memory along its own
-// row, issued PD groups ahead (a third ring does not fit in LDS).
-template <typename T>
-struct SbCfg {
-  static constexpr int RING = sizeof(T) == 4 ? 256 : 128;   // slots per row (about 64 KiB a ring)
-  static constexpr int SUB = sizeof(T) == 4 ? 64 : 32;      // slots per sub-chunk
-  static constexpr int PITCH = RING + 16 / (int)sizeof(T);  // row pitch 16 mod 256 bytes
-  static constexpr int MASK = RING - 1;
-  static constexpr int CPR = SUB / 4;                       // 4-slot chunks per row of a sub-chunk
-  static constexpr int RPV = 64 / CPR;                      // rows one vector index spans across the wave
-  static constexpr int NV = CPR;                            // vectors per lane per sub-chunk
-  static constexpr int GPS = SUB / 4;                       // 4-step groups per sub-chunk
-  static constexpr int NSUB = RING / SUB;                   // sub-chunks the ring holds
-  static constexpr int PF = 1;                              // sub-chunks a loader keeps in flight
-  static constexpr int PD = sizeof(T) == 4 ? 8 : 2;         // gD groups in flight (divides GPS)
-  static_assert(NSUB >= 4 && GPS % PD == 0, "bad tiling");
-};
-
-constexpr int kSbThreads = 6 * 64;
-
-// Returns x unchanged, but hides its value from the optimiser at this point: each role
-// launders the kernel-wide sizes it uses, or the compiler hoists every role's address
-// arithmetic out of the band loop and keeps all of it live across all roles.
-template <typename V>
-__device__ __forceinline__ V opaque(V x) {
-  asm volatile("" : "+s"(x));
-  return x;
-}
-// The same for a per-lane value.
-__device__ __forceinline__ int opaque_lane() {
-  int x = (int)(threadIdx.x & 63);
-  asm volatile("" : "+v"(x));
-  return x;
 }
 
 template <typename T>
@@ -306,449 +104,616 @@ __device__ __forceinline__ Vec4<T> reversed(const Vec4<T>& v) {
   return o;
 }
 
-// Vector k of a lane in sub-chunk s: row i, slots t0 .. t0+3, which hold columns c_lo+3 down
-// to c_lo.  32-bit arithmetic: a band spans less than 2^30 bytes (the leading-dimension
-// limit of the entry points), so every element offset within it fits.
+// wave_shl:1 -- lane r receives lane r+1's value; lane 63 keeps its own.
 template <typename T>
-struct SbVec {
-  int i;
-  int t0;
-  int c_lo;
-  __device__ __forceinline__ SbVec(int lane, int k, int s, int n) {
-    using K = SbCfg<T>;
-    i = K::RPV * k + lane / K::CPR;
-    t0 = K::SUB * s + 4 * (lane % K::CPR);
-    c_lo = n + 59 - i - t0;
-  }
-  __device__ __forceinline__ int lds(int pitch) const { return i * pitch + (t0 & SbCfg<T>::MASK); }
-};
-
-template <typename T>
-__device__ __forceinline__ T load1(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+__device__ __forceinline__ T shl1(T x) {
+  auto mv = [](uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x130, 0xf, 0xf, false); };
   if constexpr (sizeof(T) == 4) {
-    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
+    return __builtin_bit_cast(T, mv(__builtin_bit_cast(uint32_t, x)));
   } else {
-    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
+    const uint64_t b = __builtin_bit_cast(uint64_t, x);
+    const uint64_t lo = mv((uint32_t)b), hi = mv((uint32_t)(b >> 32));
+    return __builtin_bit_cast(T, (hi << 32) | lo);
   }
 }
 
-// Four consecutive elements from element offset e of a resource.  Offsets below 0 (columns
-// below 0, near the left edge only) read element 0 instead: those positions hold no data
-// that a real cell uses.
+// Returns x unchanged, but hides its value from the optimiser at this point: each role
+// launders the kernel-wide sizes it uses, or the compiler hoists every role's address
+// arithmetic out of the band loop and keeps all of it live across all roles.
+template <typename V>
+__device__ __forceinline__ V opaque(V x) {
+  asm volatile("" : "+s"(x));
+  return x;
+}
+
 template <typename T>
-__device__ __forceinline__ Vec4<T> sb_load4(__amdgpu_buffer_rsrc_t r, int e) {
-  if (__all(e >= 0)) return load4<T>(r, (uint32_t)e * (uint32_t)sizeof(T));
+struct SbCfg {
+  static constexpr int RING = sizeof(T) == 4 ? 128 : 64;    // slots per row (about 34 KiB a ring)
+  static constexpr int PITCH = RING + 16 / (int)sizeof(T);  // row pitch 16 mod 256 bytes
+  static constexpr int MASK = RING - 1;
+  static constexpr int SUB = RING / 4;       // slots per loader / storer sub-chunk
+  static constexpr int LPR = SUB / 4;        // lanes side by side that hold a row of a sub-chunk
+  static constexpr int RPV = 64 / LPR;       // rows one vector index spans across the wave
+  static constexpr int G = 16;               // columns per handoff unit
+  static constexpr int GPS = SUB / G;        // units per sub-chunk
+  static constexpr int NG = G / 4;           // 4-step groups per unit
+  static constexpr int NL = 4;               // weight loaders
+  static constexpr int LROWS = kBand / NL;   // rows of each
+  static constexpr int NV = LROWS / RPV;     // a weight loader's vectors per lane and sub-chunk
+  static constexpr int NVS = kBand / RPV;    // the storer's (and the gD loader's)
+  static constexpr int PF = sizeof(T) == 4 ? 2 : 1;  // sub-chunks a weight loader keeps in flight
+  static_assert(NV >= 1 && GPS >= 1 && SUB % G == 0, "bad tiling");
+};
+
+template <bool HAS_GD>
+constexpr int kSbThreads = 64 * (HAS_GD ? 9 : 8);
+
+struct alignas(32) SoftShared {
+  // 0..3: sub-chunks of weights loaded by loader h, 4: top units loaded, 5: sub-chunks of gD
+  // loaded, 6, 7: always 0; 8: steps done, 9: units published, 10: sub-chunks stored
+  uint32_t ctr[16];
+  uint32_t item;
+  uint32_t abort;
+};
+constexpr int kCtrTop = 4, kCtrGd = 5, kCtrSteps = 8, kCtrPub = 9, kCtrStored = 10;
+constexpr uint32_t kAllReady = 0x7fffffffu;
+
+// The matrix as a band sees it.  Band b holds rows i' = 64b .. 64b+63, i.e. matrix rows
+// row_hi = m-1-64b down; rows below 0 (the last band's) do not exist.  'base' is the band's
+// lowest existing matrix row.
+struct BandRows {
+  int64_t base;
+  int hi;     // row_hi - base: the band's first row, relative to base
+  int below;  // 1 if the matrix has a row row_hi + 1
+};
+__device__ __forceinline__ BandRows band_rows(int64_t m, int band) {
+  BandRows r;
+  const int64_t row_hi = m - 1 - (int64_t)band * kBand;
+  r.base = row_hi >= kBand - 1 ? row_hi - (kBand - 1) : 0;
+  r.hi = (int)(row_hi - r.base);
+  r.below = band > 0 ? 1 : 0;
+  return r;
+}
+// Range-checked resource over 'rows' rows from 'base' of a matrix with leading dimension ld:
+// the last row ends at its n-th element.  A negative element offset wraps to a huge one, so
+// rows below 0 read as zero and are not stored.
+template <typename T>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_rsrc(const void* p, int64_t base, int rows, int64_t ld, int64_t n) {
+  return make_rsrc(static_cast<const T*>(p) + base * ld, (uint32_t)(((int64_t)(rows - 1) * ld + n) * (int64_t)sizeof(T)));
+}
+
+// Vector k of a lane in sub-chunk s, of the rows from r0 on: band row l, slots t .. t+3, columns
+// c' = t - l .. t - l + 3, i.e. matrix columns c_lo + 3 down to c_lo.
+template <typename T>
+struct SbVec {
+  int l, t;
+  __device__ __forceinline__ SbVec(int r0, int k, int s) {
+    using K = SbCfg<T>;
+    const int lane = threadIdx.x & 63;
+    l = r0 + K::RPV * k + lane / K::LPR;
+    t = K::SUB * s + 4 * (lane & (K::LPR - 1));
+  }
+  __device__ __forceinline__ int c_lo(int n) const { return n - 4 - t + l; }
+  __device__ __forceinline__ int lds() const { return l * SbCfg<T>::PITCH + (t & SbCfg<T>::MASK); }
+};
+
+// Four elements from element offset e of a resource.  EDGE: offsets below 0 read element 0
+// instead (a vector that straddles column 0 of the lowest row would otherwise lose its valid
+// elements with the others).  32-bit arithmetic: a band spans less than 2^30 bytes.
+template <typename T, bool EDGE>
+__device__ __forceinline__ Vec4<T> at4(__amdgpu_buffer_rsrc_t r, int e) {
+  if constexpr (!EDGE) return load4<T>(r, (uint32_t)e * (uint32_t)sizeof(T));
   Vec4<T> v;
 #pragma unroll
   for (int q = 0; q < 4; ++q) v.v[q] = load1<T>(r, (uint32_t)(e + q > 0 ? e + q : 0) * (uint32_t)sizeof(T));
   return v;
 }
-
-// Loads sub-chunk s of one input.  Columns past the row's end read the next row (or zeros
-// past the band's end), columns below 0 the row before (or nothing, before the band's
-// start); none of them reaches a real cell.
 template <typename T>
-__device__ __forceinline__ void sb_load_sub(Vec4<T> (&buf)[SbCfg<T>::NV], __amdgpu_buffer_rsrc_t rsrc, int ld, int n,
-                                            int s, int lane) {
-  using K = SbCfg<T>;
-  __builtin_amdgcn_sched_barrier(0);
-  // an element offset is at least n + 63 - SUB (s+1): below 0 in the last sub-chunks only
-  if (n + 63 >= K::SUB * (s + 1)) {
-#pragma unroll
-    for (int k = 0; k < K::NV; ++k) {
-      const SbVec<T> v(lane, k, s, n);
-      buf[k] = load4<T>(rsrc, (uint32_t)(v.i * ld + v.c_lo) * (uint32_t)sizeof(T));
-    }
-  } else {
-#pragma unroll
-    for (int k = 0; k < K::NV; ++k) {
-      const SbVec<T> v(lane, k, s, n);
-      buf[k] = sb_load4<T>(rsrc, v.i * ld + v.c_lo);
-    }
-  }
-  __builtin_amdgcn_sched_barrier(0);
+__device__ __forceinline__ T at1(__amdgpu_buffer_rsrc_t r, int e) {
+  return load1<T>(r, (uint32_t)(e > 0 ? e : 0) * (uint32_t)sizeof(T));
 }
 
-// waves 1 and 2: one input into its ring.  Sub-chunk s reuses the slots of sub-chunk
-// s - NSUB, which 'freed' must have released.
+// Sub-chunks from here on hold columns below 0 (or element offsets below 0).
 template <typename T>
-__device__ __forceinline__ bool sb_loader(T* P, SoftShared& sh, const SoftArgs& a, const void* src, int64_t ld64,
-                                          int band, int Ks, uint32_t* cnt, const uint32_t* freed) {
-  using K = SbCfg<T>;
-  const int n = (int)opaque(a.n);
-  const int ld = (int)opaque(ld64);
-  const int lane = opaque_lane();
-  const int64_t row0 = (int64_t)band * kBand;
-  const int rows = (int)(a.m - row0 < kBand ? a.m - row0 : kBand);
-  const __amdgpu_buffer_rsrc_t rsrc = band_rsrc<T>(src, row0, rows, ld, n);
-  uint64_t waited = 0;
-  Vec4<T> buf[K::PF][K::NV];
+__device__ __forceinline__ bool left_edge(int s, int n) {
+  return SbCfg<T>::SUB * (s + 1) > n;
+}
+
+// ---------------------------------------------------------------------------------------
+// waves 3 .. 6: the weights.  A lane's vector needs D of its row at columns c_lo .. c_lo+4,
+// D of the row below at the same columns, C of its row at c_lo+1 .. c_lo+4 and C of the row
+// below at c_lo .. c_lo+4.
+template <typename T>
+struct WeightIn {
+  Vec4<T> d, db, c, cb;  // c_lo .. c_lo+3 (c: c_lo+1 .. c_lo+4)
+  T d4, db4, cb4;        // c_lo+4
+};
+
+template <typename T, bool EDGE>
+__device__ __forceinline__ void load_weights(WeightIn<T> (&in)[SbCfg<T>::NV], __amdgpu_buffer_rsrc_t rd,
+                                             __amdgpu_buffer_rsrc_t rc, int ldd, int ldc, int n, int hi, int r0, int s) {
 #pragma unroll
-  for (int p = 0; p < K::PF; ++p) sb_load_sub<T>(buf[p], rsrc, ld, n, p, lane);
+  for (int k = 0; k < SbCfg<T>::NV; ++k) {
+    const SbVec<T> v(r0, k, s);
+    const int c = v.c_lo(n), i = hi - v.l;
+    const int ed = i * ldd + c, ec = i * ldc + c;
+    in[k].d = at4<T, EDGE>(rd, ed);
+    in[k].d4 = at1<T>(rd, ed + 4);
+    in[k].db = at4<T, EDGE>(rd, ed + ldd);
+    in[k].db4 = at1<T>(rd, ed + ldd + 4);
+    in[k].c = at4<T, EDGE>(rc, ec + 1);
+    in[k].cb = at4<T, EDGE>(rc, ec + ldc);
+    in[k].cb4 = at1<T>(rc, ec + ldc + 4);
+  }
+}
+
+// The weights of the lane's cells into the rings.  A weight between cells one of which lies
+// outside the matrix is 0; that of the corner's virtual north-west neighbour, which carries
+// gscore, is 1.
+template <typename T>
+__device__ __forceinline__ void store_weights(T* Ww, T* Wn, T* Wx, const WeightIn<T> (&in)[SbCfg<T>::NV], T kx, int n,
+                                              int hi, int below, int r0, int s) {
+  using M = SoftMath<T>;
+  using K = SbCfg<T>;
+  // every column c' of the sub-chunk in [1, n), every row and the row below it in the matrix
+  const bool interior = K::SUB * s >= kBand && K::SUB * (s + 1) <= n && hi >= kBand - 1 && below != 0;
+#pragma unroll
+  for (int k = 0; k < K::NV; ++k) {
+    const SbVec<T> v(r0, k, s);
+    const WeightIn<T>& x = in[k];
+    const T d5[5] = {x.d.v[0], x.d.v[1], x.d.v[2], x.d.v[3], x.d4};
+    const T b5[5] = {x.db.v[0], x.db.v[1], x.db.v[2], x.db.v[3], x.db4};
+    T cb[5] = {x.cb.v[0], x.cb.v[1], x.cb.v[2], x.cb.v[3], x.cb4};
+#pragma unroll
+    for (int q = 0; q < 5; ++q) cb[q] *= kx;
+    Vec4<T> w, nn, xx;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int q = 3 - e;  // matrix column c_lo + q
+      w.v[e] = M::exp2_(M::fma_(d5[q + 1] - d5[q], kx, -(x.c.v[q] * kx)));
+      nn.v[e] = M::exp2_(M::fma_(b5[q] - d5[q], kx, -cb[q]));
+      xx.v[e] = M::exp2_(M::fma_(b5[q + 1] - d5[q], kx, -cb[q + 1]));
+    }
+    if (!interior) {
+      const bool row = hi - v.l >= 0, rowb = row && (v.l > 0 || below != 0);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int c1 = v.t - v.l + e;  // c'
+        const bool in_w = c1 >= 1 && c1 < n, in_n = c1 >= 0 && c1 < n;
+        if (!(row && in_w)) w.v[e] = T(0);
+        if (!(rowb && in_n)) nn.v[e] = T(0);
+        if (!(rowb && in_w)) xx.v[e] = v.l == 0 && below == 0 && c1 == 0 ? T(1) : T(0);
+      }
+    }
+    *reinterpret_cast<Vec4<T>*>(Ww + v.lds()) = w;
+    *reinterpret_cast<Vec4<T>*>(Wn + v.lds()) = nn;
+    *reinterpret_cast<Vec4<T>*>(Wx + v.lds()) = xx;
+  }
+}
+
+template <typename T>
+__device__ __forceinline__ bool weight_loader(T* Ww, T* Wn, T* Wx, SoftShared& sh, const SoftArgs& a, int band, int h,
+                                              int Ks) {
+  using K = SbCfg<T>;
+  const int n = (int)opaque(a.n), ldd = (int)opaque(a.ldd), ldc = (int)opaque(a.ldc);
+  const BandRows br = band_rows(opaque(a.m), band);
+  const __amdgpu_buffer_rsrc_t rd = rows_rsrc<T>(a.Din, br.base, br.hi + 1 + br.below, ldd, n);
+  const __amdgpu_buffer_rsrc_t rc = rows_rsrc<T>(a.C, br.base, br.hi + 1 + br.below, ldc, n);
+  const T kx = (T)a.kx;
+  const int r0 = K::LROWS * h;
+  uint64_t waited = 0;
+  WeightIn<T> in[K::PF][K::NV];
+  auto load = [&](WeightIn<T> (&x)[K::NV], int s) {
+    __builtin_amdgcn_sched_barrier(0);
+    if (left_edge<T>(s, n)) {
+      load_weights<T, true>(x, rd, rc, ldd, ldc, n, br.hi, r0, s);
+    } else {
+      load_weights<T, false>(x, rd, rc, ldd, ldc, n, br.hi, r0, s);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+#pragma unroll
+  for (int p = 0; p < K::PF; ++p) load(in[p], p);
   for (int s0 = 0; s0 < Ks; s0 += K::PF) {
 #pragma unroll
     for (int p = 0; p < K::PF; ++p) {
       const int s = s0 + p;
       if (s < Ks) {
-        const int older = s - K::NSUB;
-        if (older >= 0 && !lds_wait_ge<false>(freed, (uint32_t)(older + 1), &sh.abort, a.ctl, waited)) return false;
-#pragma unroll
-        for (int k = 0; k < K::NV; ++k) {
-          const SbVec<T> v(lane, k, s, n);
-          *reinterpret_cast<Vec4<T>*>(P + v.lds(K::PITCH)) = reversed(buf[p][k]);
-        }
-        lds_signal(cnt, (uint32_t)(s + 1));
-        if (s + K::PF < Ks) sb_load_sub<T>(buf[p], rsrc, ld, n, s + K::PF, lane);
+        // sub-chunk s reuses the slots of sub-chunk s - 4, which must be stored and whose last
+        // row must be published
+        const int older = s - K::RING / K::SUB;
+        if (older >= 0 &&
+            (!lds_wait_ge<false>(&sh.ctr[kCtrStored], (uint32_t)(older + 1), &sh.abort, a.ctl, waited) ||
+             !lds_wait_ge<false>(&sh.ctr[kCtrPub], (uint32_t)(K::GPS * (older + 1)), &sh.abort, a.ctl, waited)))
+          return false;
+        store_weights<T>(Ww, Wn, Wx, in[p], kx, n, br.hi, br.below, r0, s);
+        lds_signal(&sh.ctr[h], s + 1 < Ks ? (uint32_t)(s + 1) : kAllReady);
+        if (s + K::PF < Ks) load(in[p], s + K::PF);
       }
     }
   }
   return true;
 }
 
-// wave 4: gC from the C ring (which the compute wave overwrote with A).
+// wave 8: gD into its ring, 0 outside the matrix.
 template <typename T>
-__device__ __forceinline__ bool sb_store(const T* P, SoftShared& sh, const SoftArgs& a, int band, int Ks) {
+__device__ __forceinline__ bool gd_loader(T* Gd, SoftShared& sh, const SoftArgs& a, int band, int Ks) {
   using K = SbCfg<T>;
-  const int n = (int)opaque(a.n);
-  const int lane = opaque_lane();
-  const int64_t row0 = (int64_t)band * kBand;
-  const int rows = (int)(a.m - row0 < kBand ? a.m - row0 : kBand);
-  const int ldgc = (int)opaque(a.ldgc);
-  const __amdgpu_buffer_rsrc_t ro = band_rsrc<T>(a.gC, row0, rows, ldgc, n);
+  const int n = (int)opaque(a.n), ld = (int)opaque(a.ldgd);
+  const BandRows br = band_rows(opaque(a.m), band);
+  const __amdgpu_buffer_rsrc_t rg = rows_rsrc<T>(a.gD, br.base, br.hi + 1, ld, n);
+  uint64_t waited = 0;
+  Vec4<T> x[K::NVS];
+  auto load = [&](int s) {
+    __builtin_amdgcn_sched_barrier(0);
+    const bool edge = left_edge<T>(s, n);
+#pragma unroll
+    for (int k = 0; k < K::NVS; ++k) {
+      const SbVec<T> v(0, k, s);
+      const int e = (br.hi - v.l) * ld + v.c_lo(n);
+      x[k] = edge ? at4<T, true>(rg, e) : at4<T, false>(rg, e);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  load(0);
+  for (int s = 0; s < Ks; ++s) {
+    // its slots are read by the compute wave alone
+    const int older = s - K::RING / K::SUB;
+    if (older >= 0 && !lds_wait_ge<false>(&sh.ctr[kCtrSteps], (uint32_t)(K::SUB * (older + 1)), &sh.abort, a.ctl, waited))
+      return false;
+#pragma unroll
+    for (int k = 0; k < K::NVS; ++k) {
+      const SbVec<T> v(0, k, s);
+      Vec4<T> g = reversed(x[k]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int c1 = v.t - v.l + e;
+        if (c1 < 0 || c1 >= n || v.l > br.hi) g.v[e] = T(0);
+      }
+      *reinterpret_cast<Vec4<T>*>(Gd + v.lds()) = g;
+    }
+    lds_signal(&sh.ctr[kCtrGd], s + 1 < Ks ? (uint32_t)(s + 1) : kAllReady);
+    if (s + 1 < Ks) load(s + 1);
+  }
+  return true;
+}
+
+// wave 7: gC from the west weights' ring, which the compute wave overwrote with A.
+template <typename T>
+__device__ __forceinline__ bool sb_store(const T* S, SoftShared& sh, const SoftArgs& a, int band, int Ks) {
+  using K = SbCfg<T>;
+  const int n = (int)opaque(a.n), ld = (int)opaque(a.ldgc);
+  const BandRows br = band_rows(opaque(a.m), band);
+  const __amdgpu_buffer_rsrc_t ro = rows_rsrc<T>(a.gC, br.base, br.hi + 1, ld, n);
   constexpr uint32_t es = sizeof(T);
   uint64_t waited = 0;
   for (int s = 0; s < Ks; ++s) {
-    if (!lds_wait_ge(&sh.done, (uint32_t)(s + 1), &sh.abort, a.ctl, waited)) return false;
-    // every row real and every column in [0, n): columns n - SUB(s+1) .. n + 62 - SUB s
-    if (rows == kBand && K::SUB * s >= 63 && K::SUB * (s + 1) <= n) {
-      Vec4<T> v[K::NV];
+    // after the publisher has issued the boundary words of these steps, which the next band
+    // waits for
+    if (!lds_wait_ge(&sh.ctr[kCtrPub], (uint32_t)(K::GPS * (s + 1)), &sh.abort, a.ctl, waited)) return false;
+    Vec4<T> x[K::NVS];
 #pragma unroll
-      for (int k = 0; k < K::NV; ++k) {
-        const SbVec<T> q(lane, k, s, n);
-        v[k] = reversed(*reinterpret_cast<const Vec4<T>*>(P + q.lds(K::PITCH)));
-      }
+    for (int k = 0; k < K::NVS; ++k) x[k] = reversed(*reinterpret_cast<const Vec4<T>*>(S + SbVec<T>(0, k, s).lds()));
+    if (K::SUB * s >= kBand - 1 && K::SUB * (s + 1) <= n) {  // every column in [0, n)
 #pragma unroll
-      for (int k = 0; k < K::NV; ++k) {
-        const SbVec<T> q(lane, k, s, n);
-        store4<T>(ro, (uint32_t)(q.i * ldgc + q.c_lo) * es, v[k]);
+      for (int k = 0; k < K::NVS; ++k) {
+        const SbVec<T> v(0, k, s);
+        if (v.l <= br.hi) store4<T>(ro, (uint32_t)((br.hi - v.l) * ld + v.c_lo(n)) * es, x[k]);
       }
     } else {
-      // the edge sub-chunks at a band's two ends: one vector at a time, in a loop (one copy
-      // of this code instead of sixteen)
-#pragma unroll 1
-      for (int k = 0; k < K::NV; ++k) {
-        const SbVec<T> q(lane, k, s, n);
-        if (q.i >= rows) continue;
-        const Vec4<T> x = reversed(*reinterpret_cast<const Vec4<T>*>(P + q.lds(K::PITCH)));
-        if (q.c_lo >= 0 && q.c_lo + 4 <= n) {
-          store4<T>(ro, (uint32_t)(q.i * ldgc + q.c_lo) * es, x);
+#pragma unroll
+      for (int k = 0; k < K::NVS; ++k) {
+        const SbVec<T> v(0, k, s);
+        if (v.l > br.hi) continue;
+        const int c = v.c_lo(n), e0 = (br.hi - v.l) * ld + c;
+        if (c >= 0 && c + 4 <= n) {
+          store4<T>(ro, (uint32_t)e0 * es, x[k]);
           continue;
         }
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int c = q.c_lo + e;
-          if (c >= 0 && c < n) store1<T>(ro, (uint32_t)(q.i * ldgc + c) * es, x.v[e]);
-        }
+        for (int q = 0; q < 4; ++q)
+          if (c + q >= 0 && c + q < n) store1<T>(ro, (uint32_t)(e0 + q) * es, x[k].v[q]);
       }
     }
-    lds_publish(&sh.stored, (uint32_t)(s + 1));
+    lds_publish(&sh.ctr[kCtrStored], (uint32_t)(s + 1));
   }
   return true;
 }
 
-// Both loader counters in one 8-byte LDS read: sub-chunk s of D and of C is in LDS.
-__device__ __forceinline__ bool sb_loaded(const SoftShared& sh, int s) {
-  const uint64_t w =
-      __hip_atomic_load(reinterpret_cast<const uint64_t*>(&sh.ld[0]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)w);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(w >> 32));
-  return lo >= (uint32_t)(s + 1) && hi >= (uint32_t)(s + 1);  // wave-uniform
+// wave 1: the band's last row (lane 63's) for the next band.
+template <typename T>
+__device__ __forceinline__ bool sb_publish(const T* S, SoftShared& sh, const SoftArgs& a, int band, int Us,
+                                           uint32_t epoch) {
+  using K = SbCfg<T>;
+  using E = Elem<T>;
+  constexpr int G = K::G, W = E::W;
+  const int lane = threadIdx.x & 63;
+  const int64_t n = opaque(a.n);
+  const bool last_band = band == a.nb - 1;
+  uint64_t waited = 0;
+  for (int u = 0; u < Us;) {
+    uint32_t done;
+    if (!lds_wait_value<true, false>(&sh.ctr[kCtrSteps], (uint32_t)(G * (u + 1)), &sh.abort, a.ctl, waited, done))
+      return false;
+    int k = (int)(done / G) - u;
+    if (k > 64 / G) k = 64 / G;
+    if (k > Us - u) k = Us - u;
+    if (lane < k * G && !last_band) {
+      const int64_t j = (int64_t)G * u + lane - (kBand - 1);
+      if (j >= 0 && j < n) {
+        const T x = S[(kBand - 1) * K::PITCH + ((G * u + lane) & K::MASK)];
+#pragma unroll
+        for (int q = 0; q < W; ++q) store_word(a.bnd + ((int64_t)band * n + j) * W + q, tagged(E::word(x, q), epoch));
+      }
+    }
+    u += k;
+    lds_publish(&sh.ctr[kCtrPub], (uint32_t)u);
+  }
+  return true;
 }
 
-// wave 0: the adjoint chain.  BOTTOM: the matrix's last band, whose successors below lie
-// outside (A = 0, V = -inf) and which reads no handoff.
-template <typename T, bool HAS_GD, bool BOTTOM>
-__device__ __forceinline__ bool sb_compute(const T* __restrict__ Dp, T* __restrict__ Cp, const T* ring, T* pub,
-                                           SoftShared& sh, const SoftArgs& a, int band, int Ks) {
-  using E = Elem<T>;
-  using M = SoftMath<T>;
+// wave 2: the top row of the band, i.e. the last row of the band before it (zeros for the first
+// band and past the last column), one poll of 64 columns at a time.
+template <typename T>
+__device__ __forceinline__ bool sb_top(T* Tr, SoftShared& sh, const SoftArgs& a, int band, uint32_t epoch) {
   using K = SbCfg<T>;
-  constexpr int PD = K::PD;
-  const int lane = opaque_lane();
-  const int64_t m = opaque(a.m), n = opaque(a.n);
-  const int64_t row0 = (int64_t)band * kBand;
-  const int rows = (int)(m - row0 < kBand ? m - row0 : kBand);
-  const bool live = lane < rows;
-  const int n32 = (int)n;
-  const bool score_lane = lane == rows - 1;  // in the last band: the matrix's last row
-  const T kx = (T)a.kx;
-  const bool pubband = band > 0;  // a band above reads this band's first row
-  const bool publish = lane == 0 && pubband;
-  const T gs = a.gscore ? *static_cast<const T*>(a.gscore) : E::zero();
-  const T NEG = -E::inf();
-  const int64_t groups = (int64_t)Ks * K::GPS;
-  // groups [g_lo, g_hi) have every lane's four columns inside the matrix (a full band only):
-  // lane 0's highest column n+62-4g <= n-1 needs g >= 16, lane 63's lowest n-4-4g >= 0 needs
-  // g <= (n-4)/4
-  const int64_t g_lo = rows == kBand ? 16 : groups, g_hi = rows == kBand && n >= 4 ? (n - 4) / 4 + 1 : 0;
-  __amdgpu_buffer_rsrc_t rg;
-  Vec4<T> gb[PD];
-  int gbase = 0;  // element offset of this lane's column n + 59 - lane (32-bit: see SbVec)
-  if constexpr (HAS_GD) {
-    const int ldgd = (int)opaque(a.ldgd);
-    rg = band_rsrc<T>(a.gD, row0, rows, ldgd, n);
-    gbase = lane * ldgd + (int)n + 59 - lane;
+  using E = Elem<T>;
+  constexpr int G = K::G, W = E::W;
+  // columns one poll covers: the ring must hold them beside a unit in use
+  constexpr int COLS = K::RING >= 128 ? 64 : 32;
+  const int lane = threadIdx.x & 63;
+  const int64_t n = opaque(a.n);
+  const int Ut = (int)((n + G - 1) / G);
+  uint64_t waited = 0, t0 = 0;
+  uint32_t polls = 0;
+  int u = 0;
+  while (u < Ut) {
+    const int64_t j = (int64_t)G * u + lane;
+    T val = E::zero();
+    int k = COLS / G;
+    if (band > 0) {
+      // every lane loads (a lane with no column to read loads spare words of the control block
+      // and ignores them)
+      const uint64_t* src = j < n ? a.bnd + ((int64_t)(band - 1) * n + j) * W : reinterpret_cast<const uint64_t*>(a.ctl) + 4;
+      uint32_t x[W];
+      bool ok = true;
 #pragma unroll
-    for (int k = 0; k < PD; ++k) gb[k] = sb_load4<T>(rg, gbase - 4 * k);
-  }
-  // A, D and C log2(e)/gamma of the east successor (this lane's previous cell) and of the
-  // south successor of the previous step (the south-east one now); a weight's exponent is
-  // (D(succ) - D) log2(e)/gamma - C(succ) log2(e)/gamma, one fused multiply-add after an
-  // exact difference.  A successor outside the matrix has A = 0, D = -inf, C = 0: its weight
-  // is exactly 0.
-  T Ae = E::zero(), De = NEG, Ce = E::zero();
-  T Aso = E::zero(), Dso = NEG, Cso = E::zero();
-  uint64_t waited = 0;
-  // Consumer columns of the band below's first row known to be in the handoff ring
-  // (wave-uniform); 'pend' is the counter read issued one group earlier, so that no group
-  // waits for it.  Group g reads the ring's columns 4g .. 4g+3, which past the last column
-  // hold the fill values the poller writes after it (counted as kFill more columns).
-  uint32_t have = 0u, pend = 0u;
-  auto need_of = [&](int64_t g) -> int64_t { return 4 * g + 4 <= n ? 4 * g + 4 : n + kFill; };
-  auto avail_for = [&](int64_t g) -> bool {
-    const int64_t need = need_of(g);
-    if (need <= (int64_t)have) return true;
-    uint32_t seen;
-    if (!lds_wait_value<true, false>(&sh.avail, (uint32_t)need, &sh.abort, a.ctl, waited, seen)) return false;
-    have = (uint32_t)__builtin_amdgcn_readfirstlane((int)seen);
-    return true;
-  };
-  // the band below's row-0 (A, D, C) at lane 63's columns n-1-4g-q, consumer order 4g+q: one
-  // aligned vector per plane, read unconditionally (a read under a condition would make the
-  // wave wait for it where the paths join)
-  auto read_bottom = [&](int64_t g, Vec4<T>& va, Vec4<T>& vd, Vec4<T>& vc) {
-    const int sl = (int)((4 * g) & (kRing - 1));
-    va = *reinterpret_cast<const Vec4<T>*>(ring + sl);
-    vd = *reinterpret_cast<const Vec4<T>*>(ring + kRing + sl);
-    vc = *reinterpret_cast<const Vec4<T>*>(ring + 2 * kRing + sl);
-  };
-  Vec4<T> ba, bd, bc;
-  if constexpr (BOTTOM) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      ba.v[q] = E::zero();
-      bd.v[q] = NEG;
-      bc.v[q] = E::zero();
-    }
-  } else {
-    if (!avail_for(0)) return false;
-    read_bottom(0, ba, bd, bc);
-  }
-  const T* Drow = Dp + lane * K::PITCH;
-  T* Crow = Cp + lane * K::PITCH;
-  auto wait_loaded = [&](int s) -> bool {
-    return lds_wait_until([&] { return sb_loaded(sh, s); }, &sh.abort, a.ctl, waited);
-  };
-  if (!wait_loaded(0)) return false;
-  Vec4<T> dn = *reinterpret_cast<const Vec4<T>*>(Drow), cn = *reinterpret_cast<const Vec4<T>*>(Crow);
-  for (int s = 0; s < Ks; ++s) {
-    for (int64_t g0 = (int64_t)s * K::GPS; g0 < (int64_t)(s + 1) * K::GPS; g0 += PD) {
-      // the batch's out-ring slots must have been published
-      if (pubband && 4 * (g0 + PD) > kPub &&
-          !lds_wait_ge(&sh.pubd, (uint32_t)(4 * (g0 + PD) - kPub), &sh.abort, a.ctl, waited))
-        return false;
-      // One 4-step group; false when a wait has to give up.  PATH: 0 picks the interior or
-      // the edge path per group, 1 takes the interior path, 2 the edge path (which is right
-      // for every group, only slower).
-      auto group = [&](int k, auto path) -> bool {
-        constexpr int PATH = decltype(path)::value;
-        const int64_t g = g0 + k;
-        if constexpr (!BOTTOM) {
-          // The counter read issued a group ago, into a scalar before any of this group's
-          // reads are issued: waiting for it then waits for nothing recent.
-          const uint32_t p = (uint32_t)__builtin_amdgcn_readfirstlane((int)pend);
-          have = p > have ? p : have;
-          __builtin_amdgcn_sched_barrier(0);
-        }
-        const Vec4<T> dg = dn;
-        Vec4<T> cg;  // C log2(e)/gamma
-#pragma unroll
-        for (int q = 0; q < 4; ++q) cg.v[q] = cn.v[q] * kx;
-        // the next group's D and C: in this sub-chunk, or in the next one if already loaded
-        const bool next_sub = (g + 1) % K::GPS == 0;
-        const bool pre = g + 1 < groups && (!next_sub || sb_loaded(sh, s + 1));
-        if (pre) {
-          const int sl = (int)((4 * (g + 1)) & K::MASK);
-          dn = *reinterpret_cast<const Vec4<T>*>(Drow + sl);
-          cn = *reinterpret_cast<const Vec4<T>*>(Crow + sl);
-        }
-        Vec4<T> gg;
-        if constexpr (HAS_GD) {
-          gg = gb[k];
-          gb[k] = sb_load4<T>(rg, gbase - 4 * (int)(g + PD));
-        }
-        // the next group's handoff values, valid if the counter read before them covers them
-        Vec4<T> na = ba, nd = bd, nc = bc;
-        bool n_ready = true;
-        if constexpr (!BOTTOM) {
-          n_ready = need_of(g + 1) <= (int64_t)have;
-          read_bottom(g + 1, na, nd, nc);
-          pend = lds_load(&sh.avail);
-          // keeps later ring reads after this counter read (the LDS performs one wave's
-          // accesses in order)
-          __atomic_signal_fence(__ATOMIC_SEQ_CST);
-        }
-        // this lane's column at step 4g (32-bit: n < 2^31, and the edge path below runs in
-        // every band's first and last groups, on the critical path of the band below's start)
-        const int j0 = n32 + 62 - lane - 4 * (int)g;
-        const bool interior = PATH == 1 || (PATH == 0 && g >= g_lo && g < g_hi);
-        Vec4<T> out;
-        if (interior) {
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const T As = shl1_(Ae, ba.v[q]), Ds = shl1_(De, bd.v[q]), Cs = shl1_(Ce, bc.v[q]);
-            const T dd = dg.v[q], cc = cg.v[q];
-            T acc = HAS_GD ? gg.v[3 - q] : E::zero();
-            acc = M::fma_(M::exp2_(M::fma_(Dso - dd, kx, -Cso)), Aso, acc);
-            acc = M::fma_(M::exp2_(M::fma_(Ds - dd, kx, -Cs)), As, acc);
-            acc = M::fma_(M::exp2_(M::fma_(De - dd, kx, -Ce)), Ae, acc);
-            Aso = As;
-            Dso = Ds;
-            Cso = Cs;
-            Ae = acc;
-            De = dd;
-            Ce = cc;
-            out.v[q] = acc;
-          }
-        } else {
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int j = j0 - q;
-            const bool valid = live && (uint32_t)j < (uint32_t)n32;
-            const T As = shl1_(Ae, ba.v[q]), Ds = shl1_(De, bd.v[q]), Cs = shl1_(Ce, bc.v[q]);
-            const T dd = dg.v[q], cc = cg.v[q];
-            T acc = HAS_GD ? gg.v[3 - q] : E::zero();
-            if constexpr (BOTTOM) {
-              // the score's cell: the matrix's last row, last column
-              if (score_lane && j == n32 - 1) acc = acc + gs;
-            }
-            acc = M::fma_(M::exp2_(M::fma_(Dso - dd, kx, -Cso)), Aso, acc);
-            acc = M::fma_(M::exp2_(M::fma_(Ds - dd, kx, -Cs)), As, acc);
-            acc = M::fma_(M::exp2_(M::fma_(De - dd, kx, -Ce)), Ae, acc);
-            Aso = As;
-            Dso = Ds;
-            Cso = Cs;
-            Ae = valid ? acc : E::zero();
-            De = valid ? dd : NEG;
-            Ce = valid ? cc : E::zero();
-            out.v[q] = Ae;
-          }
-        }
-        *reinterpret_cast<Vec4<T>*>(Crow + ((4 * g) & K::MASK)) = out;
-        if (publish) {
-          // lane 0's (A, D, C) of steps 4g .. 4g+3 (columns j0 .. j0-3) to the out ring
-          const int ps = (int)((4 * g) & (kPub - 1));
-          *reinterpret_cast<Vec4<T>*>(pub + ps) = out;
-          *reinterpret_cast<Vec4<T>*>(pub + kPub + ps) = dg;
-          *reinterpret_cast<Vec4<T>*>(pub + 2 * kPub + ps) = cg;
-          lds_signal(&sh.produced, (uint32_t)(4 * g + 4));
-        }
-        if constexpr (!BOTTOM) {
-          if (!n_ready && g + 1 < groups) {
-            if (!avail_for(g + 1)) return false;
-            read_bottom(g + 1, na, nd, nc);
-          }
-        }
-        ba = na;
-        bd = nd;
-        bc = nc;
-        if (!pre && g + 1 < groups) {
-          if (!wait_loaded(s + 1)) return false;
-          const int sl = (int)((4 * (g + 1)) & K::MASK);
-          dn = *reinterpret_cast<const Vec4<T>*>(Drow + sl);
-          cn = *reinterpret_cast<const Vec4<T>*>(Crow + sl);
-        }
-        return true;
-      };
-      if constexpr (HAS_GD) {
-        // the g_D registers need constant indices: every group of the block unrolled
-#pragma unroll
-        for (int k = 0; k < PD; ++k)
-          if (!group(k, std::integral_constant<int, 0>())) return false;
-      } else if (g0 >= g_lo && g0 + PD <= g_hi) {
-        // Interior blocks, nearly all of them, unrolled with the interior path only; the few
-        // edge blocks at a band's two ends loop over one copy of the edge path.  Half the
-        // code of unrolling both paths: a band starts on a compute unit whose instruction
-        // cache has never held the loop, and the fetch of each new line is on the critical
-        // path of the band above.
-#pragma unroll
-        for (int k = 0; k < PD; ++k)
-          if (!group(k, std::integral_constant<int, 1>())) return false;
-      } else {
-#pragma unroll 1
-        for (int k = 0; k < PD; ++k)
-          if (!group(k, std::integral_constant<int, 2>())) return false;
+      for (int w = 0; w < W; ++w) {
+        const uint64_t word = load_word(src + w);
+        ok = ok && (uint32_t)(word >> 32) == epoch;
+        x[w] = (uint32_t)word;
       }
-      if (!BOTTOM && lane == 0) lds_signal(&sh.used, (uint32_t)(4 * (g0 + PD) < n ? 4 * (g0 + PD) : n));
+      if (j < n) val = E::from_words(x);
+      const uint64_t missing = ~__ballot(ok || j >= n);
+      const int run = missing == 0 ? 64 : __builtin_ctzll(missing);
+      k = (run < COLS ? run : COLS) / G;
     }
-    lds_signal(&sh.done, (uint32_t)(s + 1));
+    if (k > Ut - u) k = Ut - u;
+    if (k == 0) {
+      __builtin_amdgcn_s_sleep(1);
+      if ((++polls & 63u) == 0u) {
+        if (lds_load(&sh.abort) != 0u || global_aborted(a.ctl)) return false;
+        const uint64_t now = __builtin_amdgcn_s_memrealtime();
+        if (polls == 64u) {
+          t0 = now;
+        } else if (now - t0 > kSpinTicks) {
+          raise_timeout(a.ctl);
+          return false;
+        }
+      }
+      continue;
+    }
+    polls = 0;
+    // the top ring slot of column j is read before step j and reused RING steps later
+    const int64_t need_steps = (int64_t)G * (u + k) - K::RING;
+    if (need_steps > 0 && !lds_wait_ge(&sh.ctr[kCtrSteps], (uint32_t)need_steps, &sh.abort, a.ctl, waited)) return false;
+    if (lane < k * G) Tr[(int)(j & K::MASK)] = val;
+    u += k;
+    lds_signal(&sh.ctr[kCtrTop], (uint32_t)u);
+  }
+  // units past the last real column hold no values any real cell reads
+  if (lane == 0) lds_signal(&sh.ctr[kCtrTop], kAllReady);
+  return true;
+}
+
+// ---------------------------------------------------------------------------------------
+// wave 0: the chain.
+template <typename T>
+struct SbState {
+  T X;    // previous A (the west neighbour)
+  T NW;   // previous step's north neighbour
+  T top;  // the row above the band, shifted down one lane per step: lane 0 holds its next column
+};
+
+template <typename T, bool HAS_GD>
+struct SbGroup {
+  Vec4<T> w, n, x;  // weights of the west, north and north-west neighbours
+  Vec4<T> g[1];     // gD (read only with HAS_GD)
+};
+
+template <typename T, bool HAS_GD>
+__device__ __forceinline__ void sb_load_group(const T* Ww, const T* Wn, const T* Wx, const T* Gd, int at,
+                                              SbGroup<T, HAS_GD>& r) {
+  r.w = *reinterpret_cast<const Vec4<T>*>(Ww + at);
+  r.n = *reinterpret_cast<const Vec4<T>*>(Wn + at);
+  r.x = *reinterpret_cast<const Vec4<T>*>(Wx + at);
+  if constexpr (HAS_GD) r.g[0] = *reinterpret_cast<const Vec4<T>*>(Gd + at);
+}
+
+// Four steps: A = ((gD + w_nw A_nw) + w_n A_n) + w_w A_w, one fused multiply-add per term, in
+// this order.
+template <typename T, bool HAS_GD>
+__device__ __forceinline__ void sb_cells4(SbState<T>& st, const SbGroup<T, HAS_GD>& r, Vec4<T>& d) {
+  using M = SoftMath<T>;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const T N = Elem<T>::shr1(st.X, st.top);
+    st.top = shl1(st.top);
+    T acc = M::fma_(r.x.v[q], st.NW, HAS_GD ? r.g[0].v[q] : T(0));
+    acc = M::fma_(r.n.v[q], N, acc);
+    st.X = M::fma_(r.w.v[q], st.X, acc);
+    st.NW = N;
+    d.v[q] = st.X;
+  }
+}
+
+// float: one instruction block per four steps, as the forward's cells (wf_fwd.hip): shifting
+// the top row and copying it into the DPP move's "old" operand fill the two states between
+// the write of A and the move that reads it; the s_nop covers a copy of A or 'top' placed
+// right before the block.
+#define WF_SB1(T0, NW, X, D, WX, WN, WW, GD)                              \
+  "v_mov_b32 " T0 ", %[top]\n\t"                                          \
+  "v_mov_b32_dpp " T0 ", " X " wave_shr:1 row_mask:0xf bank_mask:0xf\n\t" \
+  "v_fma_f32 " D ", " WX ", " NW ", " GD "\n\t"                           \
+  "v_fma_f32 " D ", " WN ", " T0 ", " D "\n\t"                            \
+  "v_fma_f32 " D ", " WW ", " X ", " D "\n\t"                             \
+  "v_mov_b32_dpp %[top], %[top] wave_shl:1 row_mask:0xf bank_mask:0xf\n\t"
+#define WF_SB_REGS                                                                                                  \
+  [top] "+v"(st.top), [nw] "+v"(st.NW), [t] "=&v"(t), [d0] "=&v"(d.v[0]), [d1] "=&v"(d.v[1]), [d2] "=&v"(d.v[2]), \
+      [d3] "=&v"(d.v[3])
+#define WF_SB_IN                                                                                                   \
+  [x] "v"(st.X), [x0] "v"(r.x.v[0]), [x1] "v"(r.x.v[1]), [x2] "v"(r.x.v[2]), [x3] "v"(r.x.v[3]),                   \
+      [n0] "v"(r.n.v[0]), [n1] "v"(r.n.v[1]), [n2] "v"(r.n.v[2]), [n3] "v"(r.n.v[3]), [w0] "v"(r.w.v[0]),          \
+      [w1] "v"(r.w.v[1]), [w2] "v"(r.w.v[2]), [w3] "v"(r.w.v[3])
+template <>
+__device__ __forceinline__ void sb_cells4<float, false>(SbState<float>& st, const SbGroup<float, false>& r,
+                                                        Vec4<float>& d) {
+  float t;
+  asm("s_nop 0\n\t" WF_SB1("%[t]", "%[nw]", "%[x]", "%[d0]", "%[x0]", "%[n0]", "%[w0]", "0")
+          WF_SB1("%[nw]", "%[t]", "%[d0]", "%[d1]", "%[x1]", "%[n1]", "%[w1]", "0")
+              WF_SB1("%[t]", "%[nw]", "%[d1]", "%[d2]", "%[x2]", "%[n2]", "%[w2]", "0")
+                  WF_SB1("%[nw]", "%[t]", "%[d2]", "%[d3]", "%[x3]", "%[n3]", "%[w3]", "0")
+      : WF_SB_REGS
+      : WF_SB_IN);
+  st.X = d.v[3];
+}
+template <>
+__device__ __forceinline__ void sb_cells4<float, true>(SbState<float>& st, const SbGroup<float, true>& r,
+                                                       Vec4<float>& d) {
+  float t;
+  asm("s_nop 0\n\t" WF_SB1("%[t]", "%[nw]", "%[x]", "%[d0]", "%[x0]", "%[n0]", "%[w0]", "%[g0]")
+          WF_SB1("%[nw]", "%[t]", "%[d0]", "%[d1]", "%[x1]", "%[n1]", "%[w1]", "%[g1]")
+              WF_SB1("%[t]", "%[nw]", "%[d1]", "%[d2]", "%[x2]", "%[n2]", "%[w2]", "%[g2]")
+                  WF_SB1("%[nw]", "%[t]", "%[d2]", "%[d3]", "%[x3]", "%[n3]", "%[w3]", "%[g3]")
+      : WF_SB_REGS
+      : WF_SB_IN, [g0] "v"(r.g[0].v[0]), [g1] "v"(r.g[0].v[1]), [g2] "v"(r.g[0].v[2]), [g3] "v"(r.g[0].v[3]));
+  st.X = d.v[3];
+}
+
+template <typename T, bool HAS_GD>
+__device__ __forceinline__ bool sb_compute(T* __restrict__ Ww, const T* __restrict__ Wn, const T* __restrict__ Wx,
+                                           const T* __restrict__ Gd, const T* __restrict__ Tr, SoftShared& sh,
+                                           const SoftArgs& a, int band, int Ks) {
+  using K = SbCfg<T>;
+  using E = Elem<T>;
+  const int lane = threadIdx.x & 63;
+  SbState<T> st{E::zero(), E::zero(), E::zero()};
+  // the score's upstream value enters through the corner's virtual north-west neighbour
+  if (band == 0 && lane == 0 && a.gscore) st.NW = *static_cast<const T*>(a.gscore);
+  uint64_t waited = 0;
+  // lane l's copy of counter l % 8 against what the next unit needs of it: one LDS read and
+  // one compare test all of them
+  const int which = lane & 7;
+  const bool is_sub = which < K::NL || (HAS_GD && which == kCtrGd), is_top = which == kCtrTop;
+  uint32_t need = is_sub || is_top ? 1u : 0u;
+  const uint32_t per_unit = is_top ? 1u : 0u, per_sub = is_sub ? 1u : 0u;
+  auto load_ready = [&]() -> uint32_t {
+    return __hip_atomic_load(&sh.ctr[which], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  };
+  auto wait = [&]() -> bool {
+    return lds_wait_until([&] { return __ballot(load_ready() < need) == 0; }, &sh.abort, a.ctl, waited);
+  };
+  const int row = lane * K::PITCH;
+  SbGroup<T, HAS_GD> P[2];
+  T top;
+  auto load_unit = [&](int slot) {
+    sb_load_group<T, HAS_GD>(Ww, Wn, Wx, Gd, row + slot, P[0]);
+    sb_load_group<T, HAS_GD>(Ww, Wn, Wx, Gd, row + slot + 4, P[1]);
+    top = Tr[slot + (lane & (K::G - 1))];
+  };
+  if (!wait()) return false;
+  load_unit(0);
+  for (int s = 0; s < Ks; ++s) {
+#pragma unroll
+    for (int v = 0; v < K::GPS; ++v) {
+      const int base = (K::SUB * s + K::G * v) & K::MASK, next = (K::SUB * s + K::G * (v + 1)) & K::MASK;
+      need += per_unit;
+      if (v + 1 == K::GPS) need += per_sub;
+      // one unit, as in the forward: reads two groups ahead, the next unit's first groups read
+      // early and, if its inputs were not there yet, again after this unit is signalled
+      const uint32_t ready = load_ready();
+      __builtin_amdgcn_sched_barrier(0);
+      SbGroup<T, HAS_GD> gr[K::NG];
+      gr[0] = P[0];
+      gr[1] = P[1];
+      st.top = top;
+      bool late = false;
+#pragma unroll
+      for (int g = 0; g < K::NG; ++g) {
+        if (g + 2 < K::NG) {
+          sb_load_group<T, HAS_GD>(Ww, Wn, Wx, Gd, row + base + 4 * (g + 2), gr[g + 2]);
+        } else if (g + 2 == K::NG) {
+          late = __ballot(ready < need) != 0;
+          __builtin_amdgcn_sched_barrier(0);
+          sb_load_group<T, HAS_GD>(Ww, Wn, Wx, Gd, row + next, P[0]);
+          top = Tr[next + (lane & (K::G - 1))];
+        } else {
+          sb_load_group<T, HAS_GD>(Ww, Wn, Wx, Gd, row + next + 4, P[1]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        Vec4<T> d;
+        sb_cells4<T, HAS_GD>(st, gr[g], d);
+        *reinterpret_cast<Vec4<T>*>(Ww + row + base + 4 * g) = d;
+      }
+      lds_signal(&sh.ctr[kCtrSteps], (uint32_t)(K::SUB * s + K::G * (v + 1)));
+      __builtin_amdgcn_sched_barrier(0);
+      if (__builtin_expect(late, 0)) {
+        if (!wait()) return false;
+        // hidden from the optimiser, which would take these reads for repeats of the early ones
+        load_unit(opaque(next));
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
   }
   return true;
 }
 
 template <typename T, bool HAS_GD>
-__global__ __launch_bounds__(kSbThreads, 1) void soft_bwd_kernel(SoftArgs a) {
-  using E = Elem<T>;
+__global__ __launch_bounds__(kSbThreads<HAS_GD>, 1) void soft_bwd_kernel(SoftArgs a) {
   using K = SbCfg<T>;
-  __shared__ Vec4<T> D4[kBand * K::PITCH / 4];
-  __shared__ Vec4<T> C4[kBand * K::PITCH / 4];
-  __shared__ alignas(16) T ring[3 * kRing];
-  __shared__ alignas(16) T pub[3 * kPub];
+  constexpr int NV4 = kBand * K::PITCH / 4;
+  __shared__ Vec4<T> W4[3][NV4];
+  __shared__ Vec4<T> G4[HAS_GD ? NV4 : 1];
+  __shared__ Vec4<T> Tr4[K::RING / 4];
   __shared__ SoftShared sh;
-  T* Dp = reinterpret_cast<T*>(D4);
-  T* Cp = reinterpret_cast<T*>(C4);
+  T* Ww = reinterpret_cast<T*>(W4[0]);
+  T* Wn = reinterpret_cast<T*>(W4[1]);
+  T* Wx = reinterpret_cast<T*>(W4[2]);
+  T* Gd = reinterpret_cast<T*>(G4);
+  T* Tr = reinterpret_cast<T*>(Tr4);
   Control* ctl = a.ctl;
   const uint32_t epoch = __hip_atomic_load(&ctl->epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if (threadIdx.x == 0) sh.abort = 0u;
   for (;;) {
-    if (threadIdx.x == 0) {
-      sh.avail = 0u;
-      sh.used = 0u;
-      sh.produced = 0u;
-      sh.pubd = 0u;
-      sh.ld[0] = 0u;
-      sh.ld[1] = 0u;
-      sh.done = 0u;
-      sh.stored = 0u;
-    }
+    if (threadIdx.x < 16) sh.ctr[threadIdx.x] = 0u;
     claim_next(ctl, &sh.item, &sh.abort);
-    // bands from the bottom up
-    const int band = a.nb - 1 - (int)sh.item;
-    if ((int)sh.item >= a.nb || sh.abort != 0u) break;
+    const int band = (int)sh.item;
+    if (band >= a.nb || sh.abort != 0u) break;
     bool ok = true;
-    const int64_t n = a.n;
-    const int Ks = (int)((n + 63 + K::SUB - 1) / K::SUB);
+    const int Ks = (int)((a.n + kBand - 1 + K::SUB - 1) / K::SUB);
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));  // uniform branches below
     if (wave == 0) {
-      ok = band == a.nb - 1 ? sb_compute<T, HAS_GD, true>(Dp, Cp, ring, pub, sh, a, band, Ks)
-                            : sb_compute<T, HAS_GD, false>(Dp, Cp, ring, pub, sh, a, band, Ks);
+      ok = sb_compute<T, HAS_GD>(Ww, Wn, Wx, Gd, Tr, sh, a, band, Ks);
     } else if (wave == 1) {
-      ok = sb_loader<T>(Dp, sh, a, a.Din, a.ldd, band, Ks, &sh.ld[0], &sh.done);
+      ok = sb_publish<T>(Ww, sh, a, band, Ks * K::GPS, epoch);
     } else if (wave == 2) {
-      ok = sb_loader<T>(Cp, sh, a, a.C, a.ldc, band, Ks, &sh.ld[1], &sh.stored);
-    } else if (wave == 3) {
-      // consumer column k is matrix column n-1-k of the band below's first row
-      if (band < a.nb - 1)
-        ok = poll_ring<T, 3>(ring, sh, ctl, n, epoch, {E::zero(), -E::inf(), E::zero()}, [&](int64_t k) {
-          return a.bnd + ((int64_t)band * n + (n - 1 - k)) * 3 * E::W;
-        });
-    } else if (wave == 4) {
-      ok = sb_store<T>(Cp, sh, a, band, Ks);
-    } else if (band > 0) {
-      // the first row (lane 0 handles column n + 62 - s at step s) for the band above
-      const uint32_t total = (uint32_t)(4 * (int64_t)Ks * K::GPS);
-      ok = publish_ring<T, 3>(pub, sh, ctl, n, total, epoch, [n](int64_t st) { return n + 62 - st; },
-                              [&](int64_t c, int v) { return a.bnd + ((int64_t)(band - 1) * n + c) * 3 * E::W + v * E::W; });
+      ok = sb_top<T>(Tr, sh, a, band, epoch);
+    } else if (wave < 3 + K::NL) {
+      ok = weight_loader<T>(Ww, Wn, Wx, sh, a, band, wave - 3, Ks);
+    } else if (wave == 3 + K::NL) {
+      ok = sb_store<T>(Ww, sh, a, band, Ks);
+    } else {
+      if constexpr (HAS_GD) ok = gd_loader<T>(Gd, sh, a, band, Ks);
     }
     if (!ok) sh.abort = 1u;
     __syncthreads();
@@ -756,16 +721,22 @@ __global__ __launch_bounds__(kSbThreads, 1) void soft_bwd_kernel(SoftArgs a) {
   finish_launch(ctl, epoch);
 }
 
+template <typename T>
+void launch_t(const SoftArgs& a, int grid, hipStream_t s) {
+  if (a.gD) {
+    hipLaunchKernelGGL((soft_bwd_kernel<T, true>), dim3(grid), dim3(kSbThreads<true>), 0, s, a);
+  } else {
+    hipLaunchKernelGGL((soft_bwd_kernel<T, false>), dim3(grid), dim3(kSbThreads<false>), 0, s, a);
+  }
+}
+
 }  // namespace
 
 hipError_t launch_soft_backward(int dtype, const SoftArgs& a, int grid, hipStream_t s) {
-  const bool gd = a.gD != nullptr;
   if (dtype == 0) {
-    if (gd) hipLaunchKernelGGL((soft_bwd_kernel<float, true>), dim3(grid), dim3(kSbThreads), 0, s, a);
-    else hipLaunchKernelGGL((soft_bwd_kernel<float, false>), dim3(grid), dim3(kSbThreads), 0, s, a);
+    launch_t<float>(a, grid, s);
   } else if (dtype == 1) {
-    if (gd) hipLaunchKernelGGL((soft_bwd_kernel<double, true>), dim3(grid), dim3(kSbThreads), 0, s, a);
-    else hipLaunchKernelGGL((soft_bwd_kernel<double, false>), dim3(grid), dim3(kSbThreads), 0, s, a);
+    launch_t<double>(a, grid, s);
   } else {
     return hipErrorInvalidValue;
   }

@@ -1,4 +1,5 @@
-"""The forward sweep with one, two and four rows per lane, on the GPU.
+"""Edges of the band pipelines on the GPU: the forward sweep with one, two and four rows per
+lane, autotuned batches, the soft-min adjoint.
 
 Which of them a shape takes depends on m / n; the shapes here lie on both sides of the rule's
 lines and of the band edges (64, 128 and 256 rows), with matrices narrower than one handoff
@@ -76,3 +77,38 @@ def test_autotuned_batch_bitwise(count, table):
             assert got[i] == ref[-1, -1], f"instance {i} {ms[i]}x{ns[i]}"
             if t:
                 assert np.array_equal(tabs[i], ref), f"instance {i} {ms[i]}x{ns[i]}"
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("m,n", [(1, 1), (1, 40), (40, 1), (63, 64), (64, 65), (65, 31), (129, 33), (200, 47), (321, 200)])
+def test_soft_adjoint_edges(dtype, m, n):
+    """The soft-min adjoint at its tile edges (units of 16 columns, sub-chunks of 16 and 32,
+    bands of 64 rows), with padded rows, with and without gD, and with the gradient written
+    over D, over C and over gD.  Bounds: the float64 result against the oracle on the same
+    table, 1e-10; float32 against it by the path-length law 12 sqrt(m+n-1) u max|D| / gamma
+    (at least 1e-4), as in the soft-min tests."""
+    gamma = 0.5
+    C = inputs.uniform(m, n, 31 * m + n).to(dtype)
+    gD = inputs.normal_clipped(m, n, 17 * m + n).to(dtype)
+    D, _ = wf.soft_forward(C.to(DEV), gamma)
+    gs = torch.tensor(0.75, dtype=dtype, device=DEV)
+    u = np.finfo(np.float32 if dtype == torch.float32 else np.float64).eps / 2
+    law = 12 * (m + n - 1) ** 0.5 * u * max(1.0, float(D.abs().max())) / gamma
+    tol = max(1e-4 if dtype == torch.float32 else 1e-10, law)
+    for g in (None, gD):
+        ref = oracle.soft_backward(C.double().numpy(), D.double().cpu().numpy(), gamma,
+                                   None if g is None else g.double().numpy(), 0.75)
+        gdev = None if g is None else g.to(DEV)
+        pad = torch.full((m, n + 3), -9, dtype=dtype, device=DEV)
+        out = wf.soft_backward(C.to(DEV), D, gamma, g_score=gs, g_D=gdev, g_C=pad[:, :n])
+        wf.last_async_error()
+        got = out.double().cpu().numpy()
+        assert np.max(np.abs(got - ref)) <= tol * max(1.0, np.max(np.abs(ref)))
+        assert bool((pad[:, n:] == -9).all())
+        over_D, over_C = D.clone(), C.to(DEV)
+        wf.soft_backward(C.to(DEV), over_D, gamma, g_score=gs, g_D=gdev, g_C=over_D)
+        wf.soft_backward(over_C, D, gamma, g_score=gs, g_D=gdev, g_C=over_C)
+        assert torch.equal(over_D, out) and torch.equal(over_C, out)
+        if g is not None:
+            wf.soft_backward(C.to(DEV), D, gamma, g_score=gs, g_D=gdev, g_C=gdev)
+            assert torch.equal(gdev, out)
