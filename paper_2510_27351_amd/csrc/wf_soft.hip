@@ -30,10 +30,10 @@
 //   wave 1        publisher  the band's last row of A as epoch-tagged words for the next band;
 //   wave 2        top        polls those of the band before into the top ring, 64 columns per
 //                            pass;
-//   waves 3 .. 6  loaders    16 rows each: D and C of the row and of the row below it, the
+//   NL waves      loaders    64 / NL rows each: D and C of the row and of the row below it, the
 //                            weights into the rings;
-//   wave 7        storer     each finished sub-chunk of A back to gC;
-//   wave 8        gD loader  (only with gD).
+//   one wave      storer     each finished sub-chunk of A back to gC;
+//   one wave      gD loader  (only with gD).
 // Every wait is bounded.  What bounds it: the compute wave's issue (six VALU instructions per
 // step and its LDS accesses) and 63 + 16 steps of skew plus the handoff (about 1.1 us) from
 // band to band; in float64 the loaders' exponentials.  With the exponentials in the compute
@@ -137,25 +137,36 @@ struct SbCfg {
   static constexpr int G = 16;               // columns per handoff unit
   static constexpr int GPS = SUB / G;        // units per sub-chunk
   static constexpr int NG = G / 4;           // 4-step groups per unit
-  static constexpr int NL = 4;               // weight loaders
-  static constexpr int LROWS = kBand / NL;   // rows of each
-  static constexpr int NV = LROWS / RPV;     // a weight loader's vectors per lane and sub-chunk
   static constexpr int NVS = kBand / RPV;    // the storer's (and the gD loader's)
-  static constexpr int PF = sizeof(T) == 4 ? 2 : 1;  // sub-chunks a weight loader keeps in flight
-  static_assert(NV >= 1 && GPS >= 1 && SUB % G == 0, "bad tiling");
+  static_assert(GPS >= 1 && SUB % G == 0, "bad tiling");
 };
 
-template <bool HAS_GD>
-constexpr int kSbThreads = 64 * (HAS_GD ? 9 : 8);
+// The weight loaders.  Their loads' latency bounds a band (a sub-chunk of 32 columns is read in
+// 0.6 us): many loaders of few rows keep more sub-chunks in flight in the registers a wave may
+// use.  float: 8 of 8 rows with 4 sub-chunks each against 4 of 16 rows with 2: one band 124 us
+// against 154 per 4096 columns, 4096 x 4096 401 against 434; with gD the ninth and tenth waves'
+// share of the registers makes four loaders the faster (531 against 552).
+template <typename T, bool HAS_GD>
+struct SbLoad {
+  using K = SbCfg<T>;
+  static constexpr int NL = sizeof(T) == 4 && !HAS_GD ? 8 : 4;
+  static constexpr int ROWS = kBand / NL;    // rows of each
+  static constexpr int NV = ROWS / K::RPV;   // vectors per lane and sub-chunk
+  static constexpr int PF = sizeof(T) == 4 ? (HAS_GD ? 3 : 4) : 2;  // sub-chunks in flight
+  static_assert(NV >= 1, "bad tiling");
+};
 
-struct alignas(32) SoftShared {
-  // 0..3: sub-chunks of weights loaded by loader h, 4: top units loaded, 5: sub-chunks of gD
-  // loaded, 6, 7: always 0; 8: steps done, 9: units published, 10: sub-chunks stored
-  uint32_t ctr[16];
+template <typename T, bool HAS_GD>
+constexpr int kSbThreads = 64 * (4 + SbLoad<T, HAS_GD>::NL + (HAS_GD ? 1 : 0));
+
+struct alignas(64) SoftShared {
+  // 0..7: sub-chunks of weights loaded by loader h, 8: top units loaded, 9: sub-chunks of gD
+  // loaded, 10..15: always 0; 16: steps done, 17: units published, 18: sub-chunks stored
+  uint32_t ctr[24];
   uint32_t item;
   uint32_t abort;
 };
-constexpr int kCtrTop = 4, kCtrGd = 5, kCtrSteps = 8, kCtrPub = 9, kCtrStored = 10;
+constexpr int kCtrTop = 8, kCtrGd = 9, kCtrSteps = 16, kCtrPub = 17, kCtrStored = 18;
 constexpr uint32_t kAllReady = 0x7fffffffu;
 
 // The matrix as a band sees it.  Band b holds rows i' = 64b .. 64b+63, i.e. matrix rows
@@ -220,7 +231,7 @@ __device__ __forceinline__ bool left_edge(int s, int n) {
 }
 
 // ---------------------------------------------------------------------------------------
-// waves 3 .. 6: the weights.  A lane's vector needs D of its row at columns c_lo .. c_lo+4,
+// The weight loaders.  A lane's vector needs D of its row at columns c_lo .. c_lo+4,
 // D of the row below at the same columns, C of its row at c_lo+1 .. c_lo+4 and C of the row
 // below at c_lo .. c_lo+4.
 template <typename T>
@@ -229,11 +240,11 @@ struct WeightIn {
   T d4, db4, cb4;        // c_lo+4
 };
 
-template <typename T, bool EDGE>
-__device__ __forceinline__ void load_weights(WeightIn<T> (&in)[SbCfg<T>::NV], __amdgpu_buffer_rsrc_t rd,
+template <typename T, bool EDGE, int NV>
+__device__ __forceinline__ void load_weights(WeightIn<T> (&in)[NV], __amdgpu_buffer_rsrc_t rd,
                                              __amdgpu_buffer_rsrc_t rc, int ldd, int ldc, int n, int hi, int r0, int s) {
 #pragma unroll
-  for (int k = 0; k < SbCfg<T>::NV; ++k) {
+  for (int k = 0; k < NV; ++k) {
     const SbVec<T> v(r0, k, s);
     const int c = v.c_lo(n), i = hi - v.l;
     const int ed = i * ldd + c, ec = i * ldc + c;
@@ -250,15 +261,14 @@ __device__ __forceinline__ void load_weights(WeightIn<T> (&in)[SbCfg<T>::NV], __
 // The weights of the lane's cells into the rings.  A weight between cells one of which lies
 // outside the matrix is 0; that of the corner's virtual north-west neighbour, which carries
 // gscore, is 1.
-template <typename T>
-__device__ __forceinline__ void store_weights(T* Ww, T* Wn, T* Wx, const WeightIn<T> (&in)[SbCfg<T>::NV], T kx, int n,
-                                              int hi, int below, int r0, int s) {
+template <typename T, int NV>
+__device__ __forceinline__ void store_weights(T* Ww, T* Wn, T* Wx, const WeightIn<T> (&in)[NV], T kx, int n, int hi, int below, int r0, int s) {
   using M = SoftMath<T>;
   using K = SbCfg<T>;
   // every column c' of the sub-chunk in [1, n), every row and the row below it in the matrix
   const bool interior = K::SUB * s >= kBand && K::SUB * (s + 1) <= n && hi >= kBand - 1 && below != 0;
 #pragma unroll
-  for (int k = 0; k < K::NV; ++k) {
+  for (int k = 0; k < NV; ++k) {
     const SbVec<T> v(r0, k, s);
     const WeightIn<T>& x = in[k];
     const T d5[5] = {x.d.v[0], x.d.v[1], x.d.v[2], x.d.v[3], x.d4};
@@ -291,32 +301,33 @@ __device__ __forceinline__ void store_weights(T* Ww, T* Wn, T* Wx, const WeightI
   }
 }
 
-template <typename T>
+template <typename T, bool HAS_GD>
 __device__ __forceinline__ bool weight_loader(T* Ww, T* Wn, T* Wx, SoftShared& sh, const SoftArgs& a, int band, int h,
                                               int Ks) {
   using K = SbCfg<T>;
+  constexpr int NV = SbLoad<T, HAS_GD>::NV, PF = SbLoad<T, HAS_GD>::PF;
   const int n = (int)opaque(a.n), ldd = (int)opaque(a.ldd), ldc = (int)opaque(a.ldc);
   const BandRows br = band_rows(opaque(a.m), band);
   const __amdgpu_buffer_rsrc_t rd = rows_rsrc<T>(a.Din, br.base, br.hi + 1 + br.below, ldd, n);
   const __amdgpu_buffer_rsrc_t rc = rows_rsrc<T>(a.C, br.base, br.hi + 1 + br.below, ldc, n);
   const T kx = (T)a.kx;
-  const int r0 = K::LROWS * h;
+  const int r0 = SbLoad<T, HAS_GD>::ROWS * h;
   uint64_t waited = 0;
-  WeightIn<T> in[K::PF][K::NV];
-  auto load = [&](WeightIn<T> (&x)[K::NV], int s) {
+  WeightIn<T> in[PF][NV];
+  auto load = [&](WeightIn<T> (&x)[NV], int s) {
     __builtin_amdgcn_sched_barrier(0);
     if (left_edge<T>(s, n)) {
-      load_weights<T, true>(x, rd, rc, ldd, ldc, n, br.hi, r0, s);
+      load_weights<T, true, NV>(x, rd, rc, ldd, ldc, n, br.hi, r0, s);
     } else {
-      load_weights<T, false>(x, rd, rc, ldd, ldc, n, br.hi, r0, s);
+      load_weights<T, false, NV>(x, rd, rc, ldd, ldc, n, br.hi, r0, s);
     }
     __builtin_amdgcn_sched_barrier(0);
   };
 #pragma unroll
-  for (int p = 0; p < K::PF; ++p) load(in[p], p);
-  for (int s0 = 0; s0 < Ks; s0 += K::PF) {
+  for (int p = 0; p < PF; ++p) load(in[p], p);
+  for (int s0 = 0; s0 < Ks; s0 += PF) {
 #pragma unroll
-    for (int p = 0; p < K::PF; ++p) {
+    for (int p = 0; p < PF; ++p) {
       const int s = s0 + p;
       if (s < Ks) {
         // sub-chunk s reuses the slots of sub-chunk s - 4, which must be stored and whose last
@@ -326,16 +337,16 @@ __device__ __forceinline__ bool weight_loader(T* Ww, T* Wn, T* Wx, SoftShared& s
             (!lds_wait_ge<false>(&sh.ctr[kCtrStored], (uint32_t)(older + 1), &sh.abort, a.ctl, waited) ||
              !lds_wait_ge<false>(&sh.ctr[kCtrPub], (uint32_t)(K::GPS * (older + 1)), &sh.abort, a.ctl, waited)))
           return false;
-        store_weights<T>(Ww, Wn, Wx, in[p], kx, n, br.hi, br.below, r0, s);
+        store_weights<T, NV>(Ww, Wn, Wx, in[p], kx, n, br.hi, br.below, r0, s);
         lds_signal(&sh.ctr[h], s + 1 < Ks ? (uint32_t)(s + 1) : kAllReady);
-        if (s + K::PF < Ks) load(in[p], s + K::PF);
+        if (s + PF < Ks) load(in[p], s + PF);
       }
     }
   }
   return true;
 }
 
-// wave 8: gD into its ring, 0 outside the matrix.
+// The gD loader: gD into its ring, 0 outside the matrix.
 template <typename T>
 __device__ __forceinline__ bool gd_loader(T* Gd, SoftShared& sh, const SoftArgs& a, int band, int Ks) {
   using K = SbCfg<T>;
@@ -378,7 +389,7 @@ __device__ __forceinline__ bool gd_loader(T* Gd, SoftShared& sh, const SoftArgs&
   return true;
 }
 
-// wave 7: gC from the west weights' ring, which the compute wave overwrote with A.
+// The storer: gC from the west weights' ring, which the compute wave overwrote with A.
 template <typename T>
 __device__ __forceinline__ bool sb_store(const T* S, SoftShared& sh, const SoftArgs& a, int band, int Ks) {
   using K = SbCfg<T>;
@@ -611,10 +622,10 @@ __device__ __forceinline__ bool sb_compute(T* __restrict__ Ww, const T* __restri
   // the score's upstream value enters through the corner's virtual north-west neighbour
   if (band == 0 && lane == 0 && a.gscore) st.NW = *static_cast<const T*>(a.gscore);
   uint64_t waited = 0;
-  // lane l's copy of counter l % 8 against what the next unit needs of it: one LDS read and
+  // lane l's copy of counter l % 16 against what the next unit needs of it: one LDS read and
   // one compare test all of them
-  const int which = lane & 7;
-  const bool is_sub = which < K::NL || (HAS_GD && which == kCtrGd), is_top = which == kCtrTop;
+  const int which = lane & 15;
+  const bool is_sub = which < SbLoad<T, HAS_GD>::NL || (HAS_GD && which == kCtrGd), is_top = which == kCtrTop;
   uint32_t need = is_sub || is_top ? 1u : 0u;
   const uint32_t per_unit = is_top ? 1u : 0u, per_sub = is_sub ? 1u : 0u;
   auto load_ready = [&]() -> uint32_t {
@@ -679,8 +690,9 @@ __device__ __forceinline__ bool sb_compute(T* __restrict__ Ww, const T* __restri
 }
 
 template <typename T, bool HAS_GD>
-__global__ __launch_bounds__(kSbThreads<HAS_GD>, 1) void soft_bwd_kernel(SoftArgs a) {
+__global__ __launch_bounds__((kSbThreads<T, HAS_GD>), 1) void soft_bwd_kernel(SoftArgs a) {
   using K = SbCfg<T>;
+  constexpr int NL = SbLoad<T, HAS_GD>::NL;
   constexpr int NV4 = kBand * K::PITCH / 4;
   __shared__ Vec4<T> W4[3][NV4];
   __shared__ Vec4<T> G4[HAS_GD ? NV4 : 1];
@@ -695,7 +707,7 @@ __global__ __launch_bounds__(kSbThreads<HAS_GD>, 1) void soft_bwd_kernel(SoftArg
   const uint32_t epoch = __hip_atomic_load(&ctl->epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if (threadIdx.x == 0) sh.abort = 0u;
   for (;;) {
-    if (threadIdx.x < 16) sh.ctr[threadIdx.x] = 0u;
+    if (threadIdx.x < 24) sh.ctr[threadIdx.x] = 0u;
     claim_next(ctl, &sh.item, &sh.abort);
     const int band = (int)sh.item;
     if (band >= a.nb || sh.abort != 0u) break;
@@ -708,9 +720,9 @@ __global__ __launch_bounds__(kSbThreads<HAS_GD>, 1) void soft_bwd_kernel(SoftArg
       ok = sb_publish<T>(Ww, sh, a, band, Ks * K::GPS, epoch);
     } else if (wave == 2) {
       ok = sb_top<T>(Tr, sh, a, band, epoch);
-    } else if (wave < 3 + K::NL) {
-      ok = weight_loader<T>(Ww, Wn, Wx, sh, a, band, wave - 3, Ks);
-    } else if (wave == 3 + K::NL) {
+    } else if (wave < 3 + NL) {
+      ok = weight_loader<T, HAS_GD>(Ww, Wn, Wx, sh, a, band, wave - 3, Ks);
+    } else if (wave == 3 + NL) {
       ok = sb_store<T>(Ww, sh, a, band, Ks);
     } else {
       if constexpr (HAS_GD) ok = gd_loader<T>(Gd, sh, a, band, Ks);
@@ -724,9 +736,9 @@ __global__ __launch_bounds__(kSbThreads<HAS_GD>, 1) void soft_bwd_kernel(SoftArg
 template <typename T>
 void launch_t(const SoftArgs& a, int grid, hipStream_t s) {
   if (a.gD) {
-    hipLaunchKernelGGL((soft_bwd_kernel<T, true>), dim3(grid), dim3(kSbThreads<true>), 0, s, a);
+    hipLaunchKernelGGL((soft_bwd_kernel<T, true>), dim3(grid), dim3(kSbThreads<T, true>), 0, s, a);
   } else {
-    hipLaunchKernelGGL((soft_bwd_kernel<T, false>), dim3(grid), dim3(kSbThreads<false>), 0, s, a);
+    hipLaunchKernelGGL((soft_bwd_kernel<T, false>), dim3(grid), dim3(kSbThreads<T, false>), 0, s, a);
   }
 }
 
