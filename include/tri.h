@@ -16,7 +16,7 @@
  *
  * The paper runs Stage 2 on the host.  Here every stage runs on the device: the deepest
  * interface system is solved by the Thomas algorithm (Gaussian elimination restricted to
- * the three diagonals, no pivoting) by one lane per system, staged through LDS.  Nothing
+ * the three diagonals, no pivoting) by two lanes per system, staged through LDS.  Nothing
  * crosses PCIe.
  *
  * Storage (the paper states none).  A system is four arrays of N elements: a (sub-diagonal,
@@ -114,7 +114,8 @@ int tri_plan_create(tri_plan** plan, int dtype, int32_t batch, int64_t N, int32_
 int tri_plan_config(const tri_plan* plan, int32_t* m, int32_t* R, int32_t* ms, int64_t* sizes);
 /* Solves the plan's batch: x = A^-1 d.  All four inputs are read only; x may not alias
  * them.  Stage 1 on every level from the top, the Thomas solve of the deepest interface
- * system, Stage 3 on every level from the bottom: 2R + 3 kernel launches on 'stream'.
+ * system, Stage 3 on every level from the bottom: at most 2R + 3 kernel launches on 'stream'
+ * (the deepest levels, as many as fit in one workgroup's LDS, share one).
  * Calls with one plan on overlapping streams race on its interface buffers. */
 int tri_solve(const tri_plan* plan, const void* a, const void* b, const void* c, const void* d,
               void* x, void* stream);

@@ -279,12 +279,139 @@ __global__ __launch_bounds__(64) void stage3_kernel(StageArgs g) {
 }
 
 // ---------------------------------------------------------------------------------------
-// The Thomas algorithm for one system per workgroup: forward elimination
+// The Thomas algorithm: forward elimination
 //   piv_i = b_i - a_i cp_{i-1},  cp_i = c_i / piv_i,  dp_i = (d_i - a_i dp_{i-1}) / piv_i
 // (row 0: piv = b_0, dp_0 = d_0 / b_0; cp of the last row is 0), then back substitution
-// x_{n-1} = dp_{n-1}, x_i = dp_i - cp_i x_{i+1}.  The recurrences are serial, so one lane
-// runs them; the workgroup stages the rows through LDS in chunks with coalesced loads and
-// writes cp, dp to the scratch arrays and the solution back with coalesced stores.
+// x_{n-1} = dp_{n-1}, x_i = dp_i - cp_i x_{i+1}.  The recurrences are serial: what bounds them
+// is the latency of a product, a difference and an IEEE division per row.  Two lanes run
+// them, lane 0 the cp and lane 1 the dp, so that one instruction stream does both products
+// and both divisions.  1564 float64 rows, both passes: 310 us with one lane doing both in turn
+// and clamped read-ahead, 145 us so.
+
+// Lane 0's value in lanes 0 and 1.
+template <typename T>
+__device__ __forceinline__ T lane0_of_pair(T x) {
+  auto mv = [](uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xA0, 0xf, 0xf, false); };
+  if constexpr (sizeof(T) == 4) {
+    return __builtin_bit_cast(T, mv(__builtin_bit_cast(uint32_t, x)));
+  } else {
+    const uint64_t b = __builtin_bit_cast(uint64_t, x);
+    const uint64_t lo = mv((uint32_t)b), hi = mv((uint32_t)(b >> 32));
+    return __builtin_bit_cast(T, (hi << 32) | lo);
+  }
+}
+
+// Rows a group of the two routines below reads ahead: arrays must be readable this far beyond
+// both of their ends.
+constexpr int kThomasAhead = 8;
+
+// Lanes 0 and 1 of a wave eliminate rows [i0, i0 + len) of a system of n rows, in LDS: cp goes
+// to sc (lane 0), dp to sd (lane 1).  'prev' carries cp (lane 0) and dp (lane 1) from chunk to
+// chunk.  Groups of 8 rows read the next group's operands, at fixed offsets from one address
+// per array, before their own chain: reads clamped to the chunk's end cost five instructions
+// each and a change between the vector and the LDS unit, more than the division.
+template <typename T>
+__device__ __forceinline__ void thomas_eliminate(const T* sa, const T* sb, T* sc, T* sd, int64_t i0, int len, int64_t n,
+                                                 int lane, T& prev) {
+  constexpr int U = kThomasAhead;
+  T* sn = lane == 0 ? sc : sd;
+  auto row = [&](int64_t i, T a, T b, T x) -> T {
+    T piv = b, num = x;
+    if (i != 0) {
+      const T t = a * prev;
+      piv = b - lane0_of_pair(t);
+      num = lane == 0 ? x : x - t;
+    }
+    prev = num / piv;
+    return prev;
+  };
+  T ra[U], rb[U], rn[U];
+  auto fetch = [&](int q0) {
+    const T *pa = sa + q0, *pb = sb + q0, *pn = sn + q0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      ra[u] = pa[u];
+      rb[u] = pb[u];
+      rn[u] = pn[u];
+    }
+  };
+  fetch(0);
+  int q0 = 0;
+  for (; q0 + U <= len; q0 += U) {
+    T xa[U], xb[U], xn[U], out[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      xa[u] = ra[u];
+      xb[u] = rb[u];
+      xn[u] = rn[u];
+    }
+    fetch(q0 + U);
+    __builtin_amdgcn_sched_barrier(0);
+    if (i0 + q0 == 0) {
+      out[0] = row(0, xa[0], xb[0], xn[0]);
+    } else {
+      out[0] = row(1, xa[0], xb[0], xn[0]);
+    }
+#pragma unroll
+    for (int u = 1; u < U; ++u) out[u] = row(1, xa[u], xb[u], xn[u]);
+    __builtin_amdgcn_sched_barrier(0);
+    T* po = sn + q0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) po[u] = out[u];
+  }
+  for (; q0 < len; ++q0) sn[q0] = row(i0 + q0, sa[q0], sb[q0], sn[q0]);
+  // cp of the last row is 0 (nothing reads it before the substitution, which does not either)
+  if (i0 + len == n && lane == 0) sc[len - 1] = T(0);
+}
+
+// One lane back-substitutes rows i0 + len - 1 .. i0 of a system of n rows, in LDS, x into sx.
+template <typename T>
+__device__ __forceinline__ void thomas_substitute(const T* sc, const T* sd, T* sx, int64_t i0, int len, int64_t n,
+                                                  T& xnext) {
+  constexpr int U = kThomasAhead;
+  int q1 = len;  // rows left
+  if (i0 + len == n) {
+    xnext = sd[len - 1];
+    sx[len - 1] = xnext;
+    --q1;
+  }
+  T rc[U], rd[U];
+  auto fetch = [&](int q) {  // rows q-1 .. q-U
+    const T *pc = sc + q - U, *pd = sd + q - U;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      rc[u] = pc[u];
+      rd[u] = pd[u];
+    }
+  };
+  fetch(q1);
+  for (; q1 >= U; q1 -= U) {
+    T xc[U], xd[U], out[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      xc[u] = rc[u];
+      xd[u] = rd[u];
+    }
+    fetch(q1 - U);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = U - 1; u >= 0; --u) {
+      xnext = xd[u] - xc[u] * xnext;
+      out[u] = xnext;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    T* po = sx + q1 - U;
+#pragma unroll
+    for (int u = 0; u < U; ++u) po[u] = out[u];
+  }
+  for (--q1; q1 >= 0; --q1) {
+    xnext = sd[q1] - sc[q1] * xnext;
+    sx[q1] = xnext;
+  }
+}
+
+// A whole system per workgroup: the rows pass through LDS in chunks with coalesced loads, cp
+// and dp to the scratch arrays and the solution back with coalesced stores.
 template <typename T>
 struct ThomasCfg {
   static constexpr int CH = 8192 / sizeof(T);  // rows per chunk: 8 KiB per array
@@ -296,7 +423,8 @@ __global__ __launch_bounds__(kThomasThreads) void thomas_kernel(const T* __restr
                                                                 T* __restrict__ x, T* __restrict__ cp,
                                                                 T* __restrict__ dp, int64_t n) {
   constexpr int CH = ThomasCfg<T>::CH;
-  __shared__ T sa[CH], sb[CH], sc[CH], sd[CH];
+  __shared__ T lds[4 * CH + 2 * kThomasAhead];
+  T *sa = lds + kThomasAhead, *sb = sa + CH, *sc = sb + CH, *sd = sc + CH;
   const int64_t off = (int64_t)blockIdx.x * n;
   a += off;
   b += off;
@@ -308,7 +436,7 @@ __global__ __launch_bounds__(kThomasThreads) void thomas_kernel(const T* __restr
   const int t = threadIdx.x;
   const int64_t nch = (n + CH - 1) / CH;
 
-  T cprev = T(0), dprev = T(0);
+  T prev = T(0);
   for (int64_t ch = 0; ch < nch; ++ch) {
     const int64_t i0 = ch * CH;
     const int len = (int)std::min<int64_t>(CH, n - i0);
@@ -319,60 +447,7 @@ __global__ __launch_bounds__(kThomasThreads) void thomas_kernel(const T* __restr
       sd[q] = d[i0 + q];
     }
     __syncthreads();
-    if (t == 0) {
-      // the chain runs through piv and the two divisions; the next rows' LDS reads are
-      // issued a group ahead so that their latency stays off it
-      constexpr int U = 8;
-      T ra[U], rb[U], rc[U], rd[U];
-      auto fetch = [&](int q0) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const int q = q0 + u < len ? q0 + u : len - 1;
-          ra[u] = sa[q];
-          rb[u] = sb[q];
-          rc[u] = sc[q];
-          rd[u] = sd[q];
-        }
-      };
-      fetch(0);
-      for (int q0 = 0; q0 < len; q0 += U) {
-        T xa[U], xb[U], xc[U], xd[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          xa[u] = ra[u];
-          xb[u] = rb[u];
-          xc[u] = rc[u];
-          xd[u] = rd[u];
-        }
-        fetch(q0 + U < len ? q0 + U : q0);
-        T cpo[U], dpo[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const int64_t i = i0 + q0 + u;
-          T piv, dpi;
-          if (i == 0) {
-            piv = xb[u];
-            dpi = xd[u] / piv;
-          } else {
-            piv = xb[u] - xa[u] * cprev;
-            dpi = (xd[u] - xa[u] * dprev) / piv;
-          }
-          const T cpi = i < n - 1 ? xc[u] / piv : T(0);
-          cpo[u] = cpi;
-          dpo[u] = dpi;
-          cprev = cpi;
-          dprev = dpi;
-        }
-        // the stored values go to the scratch arrays through LDS (the chunk's c and d slots,
-        // already read)
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-          if (q0 + u < len) {
-            sc[q0 + u] = cpo[u];
-            sd[q0 + u] = dpo[u];
-          }
-      }
-    }
+    if (t < 2) thomas_eliminate<T>(sa, sb, sc, sd, i0, len, n, t, prev);
     __syncthreads();
     for (int q = t; q < len; q += kThomasThreads) {
       cp[i0 + q] = sc[q];
@@ -390,32 +465,147 @@ __global__ __launch_bounds__(kThomasThreads) void thomas_kernel(const T* __restr
       sd[q] = dp[i0 + q];
     }
     __syncthreads();
-    if (t == 0) {
-      constexpr int U = 8;
-      for (int q1 = len; q1 > 0; q1 -= U) {
-        T xc[U], xd[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const int q = q1 - 1 - u >= 0 ? q1 - 1 - u : 0;
-          xc[u] = sc[q];
-          xd[u] = sd[q];
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const int q = q1 - 1 - u;
-          if (q >= 0) {
-            const int64_t i = i0 + q;
-            const T xi = i == n - 1 ? xd[u] : xd[u] - xc[u] * xnext;
-            sa[q] = xi;
-            xnext = xi;
-          }
-        }
-      }
-    }
+    if (t == 0) thomas_substitute<T>(sc, sd, sa, i0, len, n, xnext);
     __syncthreads();
     for (int q = t; q < len; q += kThomasThreads) x[i0 + q] = sa[q];
     __syncthreads();
   }
+}
+
+// ---------------------------------------------------------------------------------------
+// The deep levels of a plan in one workgroup per system: from the first level whose rows and
+// those of every deeper level fit in LDS, Stage 1 down the levels, the Thomas solve and Stage 3
+// back up, without a launch between them.  A level's launch costs 5 to 8 us and the gap
+// before it 4, whatever little it has to do: 10^5 float64 unknowns (levels of 12500, 2500, 314
+// and 32 rows) took 9 launches and 55 us and take 5 and 45 us so; 1000 unknowns 27 and 16 us.
+// Reading each row's operands a row ahead in Stage 1 and Stage 3 here lost 1 to 3 us.  The operations are those of the kernels above, so
+// the results are the same bit for bit; the interface systems also go to the plan's buffers.
+struct TailArgs {
+  const void* in[4];                 // the first level's system
+  void* x;                           // its solution
+  void* out[TRI_MAX_R + 1][4];       // levels 1 ..: the interface systems
+  int32_t n[TRI_MAX_R + 2];          // rows per level
+  int32_t m[TRI_MAX_R + 1];          // sub-system sizes (levels 0 .. L-1)
+  int32_t P[TRI_MAX_R + 1];          // sub-systems
+  int32_t pitch[TRI_MAX_R + 1];      // LDS row pitch of a sub-system (as the stage kernels')
+  float rm[TRI_MAX_R + 1];           // 1 / m
+  int32_t at[TRI_MAX_R + 2];         // first LDS element of the level
+  int32_t size[TRI_MAX_R + 2];       // LDS elements of one of its four arrays
+  int32_t L;                         // levels with a Stage 1; level L is solved directly
+};
+
+// LDS element of row q of a level.
+__device__ __forceinline__ int tail_at(const TailArgs& g, int l, int q) {
+  if (l == g.L) return q;
+  const int k = block_sub(q, g.m[l], g.rm[l], g.P[l] - 1);
+  return k * g.pitch[l] + (q - k * g.m[l]);
+}
+
+template <typename T, int BYTES, int THREADS>
+__global__ __launch_bounds__(THREADS) void tail_kernel(TailArgs g) {
+  __shared__ T lds0[BYTES / sizeof(T)];
+  T* lds = lds0 + kThomasAhead;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  constexpr int WAVES = THREADS / 64;
+  const int64_t sys = blockIdx.x;
+  auto arr = [&](int l, int v) -> T* { return lds + g.at[l] + v * g.size[l]; };
+  {
+    const int n0 = g.n[0];
+    T *A = arr(0, 0), *B = arr(0, 1), *C = arr(0, 2), *D = arr(0, 3);
+    const T* ga = static_cast<const T*>(g.in[0]) + sys * n0;
+    const T* gb = static_cast<const T*>(g.in[1]) + sys * n0;
+    const T* gc = static_cast<const T*>(g.in[2]) + sys * n0;
+    const T* gd = static_cast<const T*>(g.in[3]) + sys * n0;
+    for (int q = t; q < n0; q += THREADS) {
+      const int s = tail_at(g, 0, q);
+      A[s] = ga[q];
+      B[s] = gb[q];
+      C[s] = gc[q];
+      D[s] = gd[q];
+    }
+  }
+  __syncthreads();
+  for (int l = 0; l < g.L; ++l) {
+    const T *la = arr(l, 0), *lb = arr(l, 1), *lc = arr(l, 2), *ld = arr(l, 3);
+    T *A = arr(l + 1, 0), *B = arr(l + 1, 1), *C = arr(l + 1, 2), *D = arr(l + 1, 3);
+    const int P = g.P[l], blocks = (P + 63) / 64;
+    // items: a direction of 64 sub-systems each, one per wave
+    for (int item = wave; item < 2 * blocks; item += WAVES) {
+      const bool down = (item & 1) == 0;
+      const int k = (item >> 1) * 64 + lane;
+      if (k >= P) continue;
+      const int rows = k == P - 1 ? g.n[l] - (P - 1) * g.m[l] : g.m[l];
+      const T* Ur = down ? la : lc;
+      const T* Yr = down ? lc : la;
+      const int base = k * g.pitch[l], dir = down ? 1 : -1;
+      int i = down ? 1 : rows - 2;
+      T x1 = Ur[base + i], x2 = lb[base + i], x3 = ld[base + i];
+      for (int j = 0; j < rows - 2; ++j) {
+        i += dir;
+        const T w = Ur[base + i] / x2;
+        x1 = -w * x1;
+        x2 = lb[base + i] - w * Yr[base + i - dir];
+        x3 = ld[base + i] - w * x3;
+      }
+      const int row = 2 * k + (down ? 1 : 0);
+      const T ra = down ? x1 : (k > 0 ? la[base] : T(0));
+      const T rc = down ? (k < P - 1 ? lc[base + rows - 1] : T(0)) : x1;
+      const int s = tail_at(g, l + 1, row);
+      A[s] = ra;
+      B[s] = x2;
+      C[s] = rc;
+      D[s] = x3;
+      const int64_t o = sys * g.n[l + 1] + row;
+      static_cast<T*>(g.out[l][0])[o] = ra;
+      static_cast<T*>(g.out[l][1])[o] = x2;
+      static_cast<T*>(g.out[l][2])[o] = rc;
+      static_cast<T*>(g.out[l][3])[o] = x3;
+    }
+    __syncthreads();
+  }
+  // the deepest system; its solution replaces its right-hand side
+  if (t < 2) {
+    const int n = g.n[g.L];
+    T *A = arr(g.L, 0), *B = arr(g.L, 1), *C = arr(g.L, 2), *D = arr(g.L, 3);
+    T prev = T(0), xnext = T(0);
+    thomas_eliminate<T>(A, B, C, D, 0, n, n, t, prev);
+    if (t == 0) thomas_substitute<T>(C, D, A, 0, n, n, xnext);
+  }
+  __syncthreads();
+  for (int l = g.L - 1; l >= 0; --l) {
+    T *la = arr(l, 0), *lb = arr(l, 1), *ld = arr(l, 3);
+    const T* lc = arr(l, 2);
+    const T* z = l + 1 == g.L ? arr(g.L, 0) : arr(l + 1, 3);
+    for (int k = t; k < g.P[l]; k += THREADS) {
+      const int rows = k == g.P[l] - 1 ? g.n[l] - (g.P[l] - 1) * g.m[l] : g.m[l];
+      const int base = k * g.pitch[l];
+      const T xs = z[tail_at(g, l + 1, 2 * k)], xe = z[tail_at(g, l + 1, 2 * k + 1)];
+      if (rows >= 3) {
+        T f = la[base + 1], p = lb[base + 1], q = ld[base + 1];
+        la[base + 1] = p;
+        lb[base + 1] = q - f * xs;
+        for (int i = 2; i <= rows - 2; ++i) {
+          const T w = la[base + i] / p;
+          f = -w * f;
+          p = lb[base + i] - w * lc[base + i - 1];
+          q = ld[base + i] - w * q;
+          la[base + i] = p;
+          lb[base + i] = q - f * xs;
+        }
+        T xn = xe;
+        for (int i = rows - 2; i >= 1; --i) {
+          xn = (lb[base + i] - lc[base + i] * xn) / la[base + i];
+          ld[base + i] = xn;
+        }
+      }
+      ld[base] = xs;
+      ld[base + rows - 1] = xe;
+    }
+    __syncthreads();
+  }
+  const T* X = g.L == 0 ? arr(0, 0) : arr(0, 3);
+  T* gx = static_cast<T*>(g.x) + sys * g.n[0];
+  for (int q = t; q < g.n[0]; q += THREADS) gx[q] = X[tail_at(g, 0, q)];
 }
 
 // ---------------------------------------------------------------------------------------
@@ -475,6 +665,38 @@ hipError_t launch_thomas(int dtype, int32_t batch, int64_t n, const void* a, con
   return hipGetLastError();
 }
 
+// LDS of the deep levels' workgroup: 144 KiB, one workgroup per compute unit, or 36 KiB and
+// four where there are more systems than compute units.
+constexpr int kTailBig = 144 * 1024, kTailSmall = 36 * 1024;
+constexpr int kTailBatch = 256;  // systems beyond which the small one is used
+
+int tail_bytes(int32_t batch) { return batch > kTailBatch ? kTailSmall : kTailBig; }
+
+// LDS bytes of levels l0 .. R+1 (n, m as in a plan).
+int64_t tail_need(int es, const int64_t* n, const int32_t* m, int32_t R, int l0) {
+  int64_t e = n[R + 1];
+  for (int l = l0; l <= R; ++l) e += partition_count(n[l], m[l]) * pitch_of(m[l]);
+  return (4 * e + 2 * kThomasAhead) * es;
+}
+
+template <typename T>
+void launch_tail_t(int32_t batch, const TailArgs& g, hipStream_t s) {
+  if (batch > kTailBatch) {
+    hipLaunchKernelGGL((tail_kernel<T, kTailSmall, 256>), dim3((unsigned)batch), dim3(256), 0, s, g);
+  } else {
+    hipLaunchKernelGGL((tail_kernel<T, kTailBig, 512>), dim3((unsigned)batch), dim3(512), 0, s, g);
+  }
+}
+
+hipError_t launch_tail(int dtype, int32_t batch, const TailArgs& g, hipStream_t s) {
+  if (dtype == WF_F64) {
+    launch_tail_t<double>(batch, g, s);
+  } else {
+    launch_tail_t<float>(batch, g, s);
+  }
+  return hipGetLastError();
+}
+
 // Shared checks of the stage entry points.  Grid sizes: batch * groups workgroups must fit a
 // 32-bit grid dimension.
 int check_stage(int dtype, int32_t batch, int64_t N, int32_t m) {
@@ -502,6 +724,7 @@ struct tri_plan {
   int64_t n[TRI_MAX_R + 2] = {};             // n[0] = N, n[l+1] = 2 P(n[l], m[l])
   void* lv[TRI_MAX_R + 2][5] = {};           // level l >= 1: A, B, C, D, X (batch * n[l] each)
   void* scratch = nullptr;                   // Thomas cp, dp of the deepest system
+  int32_t tail = 0;                          // levels tail .. R+1 run in one launch; R+2 = none do
 };
 
 namespace tri {
@@ -723,6 +946,8 @@ int tri_plan_create(tri_plan** out, int dtype, int32_t batch, int64_t N, int32_t
         }
   }
   const int64_t deep = p->R >= 0 ? p->n[p->R + 1] : 1;
+  p->tail = p->R + 2;
+  while (p->R >= 0 && p->tail > 0 && tail_need(es, p->n, p->m, p->R, p->tail - 1) <= tail_bytes(batch)) --p->tail;
   if (hipMalloc(&p->scratch, (size_t)2 * batch * deep * es) != hipSuccess) {
     p->scratch = nullptr;
     free_plan(p);
@@ -750,8 +975,9 @@ int tri_solve(const tri_plan* p, const void* a, const void* b, const void* c, co
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int dt = p->dtype;
   if (p->R < 0) return launch_thomas(dt, p->batch, 1, a, b, c, d, x, p->scratch, s) == hipSuccess ? WF_OK : WF_E_DEVICE;
-  // Stage 1 on every level from the top
-  for (int l = 0; l <= p->R; ++l) {
+  const int top = std::min(p->tail, p->R + 1);  // levels above it take launches of their own
+  // Stage 1 on those levels from the top
+  for (int l = 0; l < top; ++l) {
     StageArgs g = stage_args(dt, p->n[l], p->m[l], 32);
     g.a = l == 0 ? a : p->lv[l][0];
     g.b = l == 0 ? b : p->lv[l][1];
@@ -763,13 +989,39 @@ int tri_solve(const tri_plan* p, const void* a, const void* b, const void* c, co
     g.D = p->lv[l + 1][3];
     if (launch_stage1(dt, p->batch, g, s) != hipSuccess) return WF_E_DEVICE;
   }
-  // Stage 2: the deepest interface system, directly
-  const int deep = p->R + 1;
-  void* const* L = p->lv[deep];
-  if (launch_thomas(dt, p->batch, p->n[deep], L[0], L[1], L[2], L[3], L[4], p->scratch, s) != hipSuccess)
-    return WF_E_DEVICE;
-  // Stage 3 on every level from the bottom
-  for (int l = p->R; l >= 0; --l) {
+  if (p->tail <= p->R + 1) {
+    // Stage 1 on the deeper levels, Stage 2 and Stage 3 on them
+    TailArgs g;
+    std::memset(&g, 0, sizeof(g));
+    const void* in[4] = {a, b, c, d};
+    for (int q = 0; q < 4; ++q) g.in[q] = top == 0 ? in[q] : p->lv[top][q];
+    g.x = top == 0 ? x : p->lv[top][4];
+    g.L = p->R + 1 - top;
+    int32_t at = 0;
+    for (int j = 0; j <= g.L; ++j) {
+      const int l = top + j;
+      g.n[j] = (int32_t)p->n[l];
+      g.size[j] = g.n[j];
+      if (j < g.L) {
+        g.m[j] = p->m[l];
+        g.P[j] = (int32_t)partition_count(p->n[l], p->m[l]);
+        g.pitch[j] = pitch_of(p->m[l]);
+        g.rm[j] = 1.0f / (float)p->m[l];
+        g.size[j] = g.P[j] * g.pitch[j];
+        for (int q = 0; q < 4; ++q) g.out[j][q] = p->lv[l + 1][q];
+      }
+      g.at[j] = at;
+      at += 4 * g.size[j];
+    }
+    if (launch_tail(dt, p->batch, g, s) != hipSuccess) return WF_E_DEVICE;
+  } else {
+    // Stage 2: the deepest interface system, directly
+    void* const* L = p->lv[p->R + 1];
+    if (launch_thomas(dt, p->batch, p->n[p->R + 1], L[0], L[1], L[2], L[3], L[4], p->scratch, s) != hipSuccess)
+      return WF_E_DEVICE;
+  }
+  // Stage 3 on the levels above from the bottom
+  for (int l = top - 1; l >= 0; --l) {
     StageArgs g = stage_args(dt, p->n[l], p->m[l], 64);
     g.a = l == 0 ? a : p->lv[l][0];
     g.b = l == 0 ? b : p->lv[l][1];
