@@ -25,9 +25,14 @@
 //     the receiving cell, as bytes in LDS.  Lane 63's inputs come from the band below, which
 //     publishes them (tagged 64-bit words, as in the forward sweep); the poller adds them to
 //     lane 63's upstream value before the compute wave reads it.
-// Waves of the reverse sweep: compute; value loader (gD); factor loader (bit-planes ->
-// factors); poller (values from the band below); storer (gC); publisher (values for the
-// band above).
+// Waves of the reverse sweep: compute; two value loaders (gD, 32 rows each); factor loader
+// (bit-planes -> factors); poller (values from the band below); storer (gC); publisher (values
+// for the band above).
+// What bounds it: the compute wave's issue (47 cycles a step) and, per band, 63 + G steps of
+// skew plus the handoff (about 1.1 us).  3000 x 2500 float32 with gD: 396 us with one value
+// loader one sub-chunk ahead, address arithmetic and three counter tests per unit in the
+// compute wave and a per-element path for a last band of fewer rows (which alone took 162 us
+// against 75), 236 us so; float64 549 and 420.
 #include <algorithm>
 
 #include "wf_common.h"
@@ -598,41 +603,23 @@ __global__ __launch_bounds__(128, 1) void sel_batch_kernel(BwdBatchArgs b) {
 }
 
 // =======================================================================================
-// 2. Reverse sweep: six waves, one 64-row band per workgroup, bands from the bottom up.
+// 2. Reverse sweep: seven waves, one 64-row band per workgroup, bands from the bottom up.
 // =======================================================================================
-struct alignas(8) AdjShared {
-  uint32_t ctr[7];  // 0: sub-chunks of upstream values loaded, 1: units whose lane-63 inputs
-                    // from the band below are added in, 2: reverse steps done, 3: sub-chunks
-                    // stored, 4: units published, 5: unused, 6: sub-chunks of factors loaded
+struct alignas(64) AdjShared {
+  uint32_t ctr[8];  // kAdj..: progress of the roles (the others stay 0)
   uint32_t item;
   uint32_t abort;
 };
-constexpr int kAdjCounters = 7;
-constexpr int kAdjThreads = 6 * 64;
-
-// Both readiness counters of the compute wave in one 8-byte LDS read.  'zero' is 0, but
-// the compiler cannot tell: the value counts as per-lane data and is compared where it is
-// used, so the wave waits for it there rather than right after the read (where it would
-// also wait for every earlier LDS read, the prefetches).
-__device__ __forceinline__ uint64_t adj_ready(const AdjShared& sh, int zero) {
-  return __hip_atomic_load(reinterpret_cast<const uint64_t*>(&sh.ctr[0]) + zero, __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-__device__ __forceinline__ uint32_t adj_ready_f(const AdjShared& sh, int zero) {
-  return __hip_atomic_load(&sh.ctr[6] + zero, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-// Whether the compute wave's inputs are in LDS: need_l sub-chunks of values and of factors,
-// need_b units of the band below's inputs (all three counters read before any compare).
-__device__ __forceinline__ bool adj_inputs_ready(const AdjShared& sh, int zero, uint32_t need_l, uint32_t need_b) {
-  const uint64_t r = adj_ready(sh, zero);
-  const uint32_t f = adj_ready_f(sh, zero);
-  return __all((uint32_t)r >= need_l && (uint32_t)(r >> 32) >= need_b && f >= need_l);
-}
-__device__ __forceinline__ int adj_opaque_zero() {
-  int z = 0;
-  asm volatile("" : "+v"(z));
-  return z;
-}
+constexpr int kAdjCounters = 8;
+constexpr int kAdjVal = 0;     // and 5: sub-chunks of upstream values loaded, by either half's loader
+constexpr int kAdjPolled = 1;  // units whose lane-63 inputs from the band below are added in
+constexpr int kAdjSteps = 2;   // reverse steps done
+constexpr int kAdjStored = 3;  // sub-chunks stored
+constexpr int kAdjPub = 4;     // units published
+constexpr int kAdjVal1 = 5;
+constexpr int kAdjFac = 6;     // sub-chunks of factors loaded
+constexpr uint32_t kAdjAll = 0x7fffffffu;
+constexpr int kAdjThreads = 7 * 64;
 
 // wave_shl:1 with bound_ctrl: lane r receives lane r+1's value, lane 63 reads zero.  Feeding
 // a multiply or a fused multiply-add, the move folds into a DPP form of that instruction.
@@ -658,7 +645,7 @@ __device__ __forceinline__ T factor(uint32_t w) {
 }
 
 // wave 0: the reverse chain.  Slot group [b4, b4+4) is processed from b4+3 down to b4.
-// The LDS reads of a group (upstream values and factor words) are issued PD groups ahead of
+// The LDS reads of a group (upstream values and factor words) are issued two groups ahead of
 // their use: LDS latency under the other waves' traffic is longer than one group's compute.
 template <typename T>
 struct AdjGroup {
@@ -666,26 +653,13 @@ struct AdjGroup {
   uint32_t f[3];   // factor words: [0] W (east), [1] N (south), [2] NW (south-east)
 };
 
-template <typename T, int G>
-struct AdjCfg {
-  static constexpr int NG = G / 4;
-  static constexpr int PD = sizeof(T) == 4 ? 2 : 1;
-};
-
-template <typename T, int G>
-struct AdjUnitRegs {
-  AdjGroup<T> g[AdjCfg<T, G>::PD];
-};
-
 template <typename T>
-__device__ __forceinline__ void adj_load_group(const T* __restrict__ S, const uint32_t* __restrict__ F, int b4,
-                                               int lane, AdjGroup<T>& r) {
-  using C = BCfg<T>;
-  r.gv = *reinterpret_cast<const Vec4<T>*>(S + lane * C::PITCH + b4);
+__device__ __forceinline__ void adj_load_group(const T* __restrict__ S, const uint32_t* __restrict__ F, AdjGroup<T>& r) {
+  r.gv = *reinterpret_cast<const Vec4<T>*>(S);
   // three words: a read of the unused fourth would leave a register that the compiler
   // reuses as a temporary while the read is still in flight
   typedef uint32_t v3u __attribute__((ext_vector_type(3)));
-  const v3u f = *reinterpret_cast<const v3u*>(F + lane * C::FPITCH + b4);
+  const v3u f = *reinterpret_cast<const v3u*>(F);
   r.f[0] = f.x;
   r.f[1] = f.y;
   r.f[2] = f.z;
@@ -697,7 +671,6 @@ struct AdjState {
   T A2;  // A two steps back (slot + 2)
 };
 
-__device__ __forceinline__ float fma_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
 template <typename T, int q>
@@ -720,102 +693,122 @@ __device__ __forceinline__ void adj_cells4(AdjState<T>& st, const AdjGroup<T>& r
   out.v[0] = adj_cell<T, 0>(st, r);
 }
 
-// Unit u covers slots [S0 - G(u+1), S0 - Gu), groups in descending slot order.  The last
-// PD groups always read unit u+1's first groups into 'out' (so that both paths below leave
-// them in the same registers; conditional reads make the compiler copy every prefetched
-// register at each unit boundary).  If unit u+1's inputs were not yet in LDS PD groups
-// before the end (by the counters read at the start of the unit), unit u is finished and
-// signalled first and the wave then waits for unit u+1 and reads its first groups again.
-// Waiting earlier would hold back the last steps of unit u, and with them row 0's values
-// for the band above, until the band below has delivered unit u+1: one unit of extra lag
-// per band.  After the last unit the reads wrap around the ring and are not used.
-template <typename T, int G>
-__device__ __forceinline__ bool adj_unit(T* __restrict__ S, const uint32_t* __restrict__ F, AdjShared& sh,
-                                         Control* ctl, int zero, int u, int Us, int S0, AdjState<T>& st,
-                                         const AdjUnitRegs<T, G>& in, AdjUnitRegs<T, G>& out, uint32_t& stall,
-                                         uint64_t& waited) {
-  using C = BCfg<T>;
-  constexpr int NG = AdjCfg<T, G>::NG, PD = AdjCfg<T, G>::PD;
-  const int lane = threadIdx.x & 63;
-  const int top = S0 - G * u, next_top = top - G;
-  const bool has_next = u + 1 < Us;
-  const uint32_t need_l = (uint32_t)((G * (u + 1)) / kSub + 1), need_b = (uint32_t)(u + 2);
-  const uint64_t ready = adj_ready(sh, zero);
-  const uint32_t ready_f = adj_ready_f(sh, zero);
-  AdjGroup<T> gr[NG + PD];
-#pragma unroll
-  for (int p = 0; p < PD; ++p) gr[p] = in.g[p];
-  bool early = true;
-#pragma unroll
-  for (int g = 0; g < NG; ++g) {
-    if (g + PD < NG) {
-      adj_load_group<T>(S, F, (top - 4 * (g + PD + 1)) & C::MASK, lane, gr[g + PD]);
-    } else {
-      if (g + PD == NG) {
-        __builtin_amdgcn_sched_barrier(0);
-        early = !has_next || __all((uint32_t)ready >= need_l && (uint32_t)(ready >> 32) >= need_b && ready_f >= need_l);
-        stall += !early;
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      adj_load_group<T>(S, F, (next_top - 4 * (g + PD - NG + 1)) & C::MASK, lane, out.g[g + PD - NG]);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    const int b4 = (top - 4 * (g + 1)) & C::MASK;
-    Vec4<T> o;
-    adj_cells4<T>(st, gr[g], o);
-    *reinterpret_cast<Vec4<T>*>(S + lane * C::PITCH + b4) = o;
-  }
-  lds_signal(&sh.ctr[2], (uint32_t)(G * (u + 1)));
-  __builtin_amdgcn_sched_barrier(0);
-  if (!early) {
-    if (!lds_wait_until([&] { return adj_inputs_ready(sh, zero, need_l, need_b); }, &sh.abort, ctl, waited))
-      return false;
-    // The slot is hidden from the optimiser: through the restrict pointers it would take
-    // these reads for repeats of the early ones above and drop them.
-    const int nt = opaque(next_top);
-#pragma unroll
-    for (int p = 0; p < PD; ++p) adj_load_group<T>(S, F, (nt - 4 * (p + 1)) & C::MASK, lane, out.g[p]);
-    __builtin_amdgcn_sched_barrier(0);
-  }
-  return true;
+// float: one instruction block per four steps, six instructions a step.  The compiler moves
+// the shifted A to a register of its own once per step (seven); here the shift is part of the
+// two multiply-adds that take it.  A DPP operand needs two wait states after the vector write of
+// its register: the conversions and the multiply-add between give three, and the s_nop covers a
+// copy of A placed right before the block.
+#define WF_ADJ1(D, A1, A2, Q)                                                                     \
+  "v_cvt_f32_ubyte" Q " %[t], %[f2]\n\t"                                                          \
+  "v_fmac_f32_dpp " D ", " A2 ", %[t] wave_shl:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"     \
+  "v_cvt_f32_ubyte" Q " %[t], %[f1]\n\t"                                                          \
+  "v_fmac_f32_dpp " D ", " A1 ", %[t] wave_shl:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"     \
+  "v_cvt_f32_ubyte" Q " %[t], %[f0]\n\t"                                                          \
+  "v_fmac_f32 " D ", " A1 ", %[t]\n\t"
+template <>
+__device__ __forceinline__ void adj_cells4<float>(AdjState<float>& st, const AdjGroup<float>& r, Vec4<float>& out) {
+  float t;
+  out = r.gv;
+  asm("s_nop 0\n\t" WF_ADJ1("%[d3]", "%[a1]", "%[a2]", "3") WF_ADJ1("%[d2]", "%[d3]", "%[a1]", "2")
+          WF_ADJ1("%[d1]", "%[d2]", "%[d3]", "1") WF_ADJ1("%[d0]", "%[d1]", "%[d2]", "0")
+      : [d0] "+v"(out.v[0]), [d1] "+v"(out.v[1]), [d2] "+v"(out.v[2]), [d3] "+v"(out.v[3]), [t] "=&v"(t)
+      : [a1] "v"(st.A1), [a2] "v"(st.A2), [f0] "v"(r.f[0]), [f1] "v"(r.f[1]), [f2] "v"(r.f[2]));
+  st.A1 = out.v[0];
+  st.A2 = out.v[1];
 }
 
+// Units of G slots from the top slot down; a sub-chunk's units are unrolled, so that every
+// slot is a constant offset from the sub-chunk's two row addresses.  One LDS read (lane l's
+// copy of counter l % 8) and one compare test all the inputs of the next unit.  The last two
+// groups of a unit always read the next unit's first groups.  If unit u+1's inputs were not
+// yet in LDS by the counters read at the start of unit u, unit u is finished and signalled
+// first and the wave then waits for unit u+1 and reads its first groups again.  Waiting
+// earlier would hold back the last steps of unit u, and with them row 0's values for the band
+// above, until the band below has delivered unit u+1: one unit of extra lag per band.  After
+// the last unit the reads wrap around the ring and are not used.
 template <typename T, int G>
-__device__ __forceinline__ void adj_compute(T* __restrict__ S, const uint32_t* __restrict__ F, AdjShared& sh,
+__device__ __forceinline__ bool adj_compute(T* __restrict__ S, const uint32_t* __restrict__ F, AdjShared& sh,
                                             Control* ctl, int Ks, uint64_t* trace) {
   using C = BCfg<T>;
   using E = typename C::E;
-  constexpr int PD = AdjCfg<T, G>::PD;
+  constexpr int NG = G / 4, GPS = kSub / G;
   const int lane = threadIdx.x & 63;
-  const int S0 = kSub * Ks;  // slots [0, S0), processed from the top down
-  const int Us = S0 / G;
   AdjState<T> st{E::zero(), E::zero()};
   uint64_t waited = 0, t_first = 0;
   uint32_t stall = 0;
-  const int zero = adj_opaque_zero();
-  {
-    if (!adj_inputs_ready(sh, zero, 1u, 1u)) {
-      ++stall;
-      if (!lds_wait_until([&] { return adj_inputs_ready(sh, zero, 1u, 1u); }, &sh.abort, ctl, waited)) {
-        sh.abort = 1u;
-        return;
+  const int which = lane & (kAdjCounters - 1);
+  const bool is_sub = which == kAdjVal || which == kAdjVal1 || which == kAdjFac, is_unit = which == kAdjPolled;
+  uint32_t need = is_sub || is_unit ? 1u : 0u;
+  const uint32_t per_unit = is_unit ? 1u : 0u, per_sub = is_sub ? 1u : 0u;
+  auto load_ready = [&]() -> uint32_t {
+    return __hip_atomic_load(&sh.ctr[which], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  };
+  auto wait = [&]() -> bool {
+    return lds_wait_until([&] { return __ballot(load_ready() < need) == 0; }, &sh.abort, ctl, waited);
+  };
+  T* const rowS = S + lane * C::PITCH;
+  const uint32_t* const rowF = F + lane * C::FPITCH;
+  int at = (kSub * (Ks - 1)) & C::MASK;  // the sub-chunk's first slot in the rings
+  AdjGroup<T> P[2];
+  auto load_first = [&](int slot) {  // the two groups below 'slot'
+    adj_load_group<T>(rowS + slot - 4, rowF + slot - 4, P[0]);
+    adj_load_group<T>(rowS + slot - 8, rowF + slot - 8, P[1]);
+  };
+  stall += __ballot(load_ready() < need) != 0;
+  if (!wait()) return false;
+  if (trace) t_first = __builtin_amdgcn_s_memrealtime();
+  load_first(at + kSub);
+  for (int k = 0; k < Ks; ++k) {
+    const int below = (at - kSub) & C::MASK;
+    T* const pS = rowS + at;
+    const uint32_t* const pF = rowF + at;
+    const T* const nS = rowS + below;
+    const uint32_t* const nF = rowF + below;
+#pragma unroll
+    for (int v = 0; v < GPS; ++v) {
+      constexpr int last = GPS - 1;
+      need += per_unit;
+      if (v == last) need += per_sub;
+      const uint32_t ready = load_ready();
+      __builtin_amdgcn_sched_barrier(0);
+      AdjGroup<T> gr[NG + 2];
+      gr[0] = P[0];
+      gr[1] = P[1];
+      bool late = false;
+#pragma unroll
+      for (int g = 0; g < NG; ++g) {
+        // two groups ahead: of this unit, or the next one's first two
+        const int off = kSub - G * v - 4 * (g + 3);
+        if (g + 2 < NG) {
+          adj_load_group<T>(pS + off, pF + off, gr[g + 2]);
+        } else {
+          if (g + 2 == NG) late = __ballot(ready < need) != 0;
+          __builtin_amdgcn_sched_barrier(0);
+          if (v < last) {
+            adj_load_group<T>(pS + off, pF + off, P[g + 2 - NG]);
+          } else {
+            adj_load_group<T>(nS + off + kSub, nF + off + kSub, P[g + 2 - NG]);
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        Vec4<T> o;
+        adj_cells4<T>(st, gr[g], o);
+        *reinterpret_cast<Vec4<T>*>(pS + kSub - G * v - 4 * (g + 1)) = o;
+      }
+      lds_signal(&sh.ctr[kAdjSteps], (uint32_t)(kSub * k + G * (v + 1)));
+      __builtin_amdgcn_sched_barrier(0);
+      // the first unit whose row 0 the band above's first unit needs is done
+      if (trace && GPS * k + v == (G + kBand - 1) / G) trace[16] = __builtin_amdgcn_s_memrealtime();
+      if (__builtin_expect(late, 0)) {
+        ++stall;
+        if (!wait()) return false;
+        // The slot is hidden from the optimiser: through the restrict pointers it would take
+        // these reads for repeats of the early ones above and drop them.
+        load_first(opaque(v < last ? at + kSub - G * (v + 1) : below + kSub));
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
-  }
-  if (trace) t_first = __builtin_amdgcn_s_memrealtime();
-  AdjUnitRegs<T, G> P;
-#pragma unroll
-  for (int p = 0; p < PD; ++p) adj_load_group<T>(S, F, (S0 - 4 * (p + 1)) & C::MASK, lane, P.g[p]);
-  // One unit per iteration: a unit reads its first groups from P and leaves the next
-  // unit's there (they are dead by the time those reads are issued, so both use the same
-  // registers and nothing is copied at the back edge).
-  for (int u = 0; u < Us; ++u) {
-    if (!adj_unit<T, G>(S, F, sh, ctl, zero, u, Us, S0, st, P, P, stall, waited)) {
-      sh.abort = 1u;
-      return;
-    }
-    // the first unit whose row 0 the band above's first unit needs is done
-    if (trace && u == (G + kBand - 1) / G) trace[16] = __builtin_amdgcn_s_memrealtime();
+    at = below;
   }
   if (trace && lane == 0) {
     trace[1] = t_first;
@@ -823,35 +816,30 @@ __device__ __forceinline__ void adj_compute(T* __restrict__ S, const uint32_t* _
     trace[4] = stall;
     trace[8] = waited;
   }
+  return true;
 }
 
-// waves 1 and 5: loaders, one 64-slot sub-chunk at a time from the top slot down.  Wave 1:
-//  - upstream values gD (plus gscore on the last cell; zeros when gD is absent) into the
-//    value ring.
-// Wave 5:
-//  - the factor words: for the cell of lane r at slot s, byte 0 of the W word says whether
-//    cell (r, slot s+1) selected W, byte 0 of the N word whether (r+1, s+1) selected N, byte
-//    0 of the NW word whether (r+1, s+2) selected NW -- i.e. whether that successor routes
-//    its value here -- and bytes 1..3 the same for slots s+1..s+3 (the group of 4 slots);
-//  - row 0's own N and NW planes, which the publisher needs.
-// The loads of the next PF (gD) and PFS (planes) sub-chunks are in flight in registers.
+// waves 1 and 6: loaders of the upstream values gD (plus gscore on the last cell; zeros when gD
+// is absent), 32 rows each, one 64-slot sub-chunk at a time from the top slot down.  The loads
+// of the next PF sub-chunks are in flight in registers.
 template <typename T>
-struct AdjPF {
-  static constexpr int PF = 1;                         // gD sub-chunks
-  static constexpr int PFS = 4;                        // bit-plane sub-chunks
-};
+constexpr int kAdjPF = sizeof(T) == 4 ? 3 : 2;
+constexpr int kAdjHalf = kBand / 2;
+constexpr int kAdjNV = kAdjHalf / 4;  // vectors of a lane per sub-chunk
+
+// Row and first slot of a lane's vector v in sub-chunk k.
+__device__ __forceinline__ int adj_row(int h, int v) { return kAdjHalf * h + 4 * v + (int)(threadIdx.x & 63) / 16; }
+__device__ __forceinline__ int adj_slot(int k) { return kSub * k + 4 * (int)(threadIdx.x & 15); }
 
 template <typename T>
-__device__ __forceinline__ void adj_load_g(Vec4<T> (&x)[16], __amdgpu_buffer_rsrc_t rsrc, int64_t ldg_, int k) {
-  const int lane = threadIdx.x & 63;
-  // recomputed per call: hoisted out of the loop, the 16 row offsets would stay live
-  const int64_t ldg = opaque(ldg_);
+__device__ __forceinline__ void adj_load_g(Vec4<T> (&x)[kAdjNV], __amdgpu_buffer_rsrc_t rsrc, int ldg_, int h, int k) {
+  // recomputed per call: hoisted out of the loop, the row offsets would stay live
+  const int ldg = opaque(ldg_);
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    const int i = 4 * v + (lane >> 4);
-    const int64_t c0 = (int64_t)kSub * k + 4 * (lane & 15) - i;
-    const uint32_t off = (uint32_t)(i * ldg + c0) * (uint32_t)sizeof(T);
+  for (int v = 0; v < kAdjNV; ++v) {
+    const int i = adj_row(h, v);
+    const uint32_t off = (uint32_t)(i * ldg + adj_slot(k) - i) * (uint32_t)sizeof(T);
     if constexpr (sizeof(T) == 4) {
       x[v] = __builtin_bit_cast(Vec4<T>, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)off, 0, 0));
     } else {
@@ -864,6 +852,90 @@ __device__ __forceinline__ void adj_load_g(Vec4<T> (&x)[16], __amdgpu_buffer_rsr
   __builtin_amdgcn_sched_barrier(0);
 }
 
+// Whether a slot of a sub-chunk may be reused by the kr-th one: the sub-chunk that held it is
+// stored and its row 0 published.
+template <typename T, int G>
+__device__ __forceinline__ bool adj_wait_free(AdjShared& sh, Control* ctl, int kr, uint64_t& waited) {
+  const int older = kr - BCfg<T>::NSUB;
+  return older < 0 || (lds_wait_ge<false>(&sh.ctr[kAdjStored], (uint32_t)(older + 1), &sh.abort, ctl, waited) &&
+                       lds_wait_ge<false>(&sh.ctr[kAdjPub], (uint32_t)((kSub / G) * (older + 1)), &sh.abort, ctl, waited));
+}
+
+template <typename T, int G, bool HAS_G>
+__device__ __forceinline__ bool adj_load_values(T* S, AdjShared& sh, const AdjArgs& a, int band, int Ks, int h,
+                                                uint64_t* tr) {
+  using C = BCfg<T>;
+  using E = typename C::E;
+  constexpr int PF = HAS_G ? kAdjPF<T> : 1;
+  const int lane = threadIdx.x & 63;
+  const int ldg = (int)opaque(a.ldgd), n = (int)opaque(a.n);
+  const int64_t m = opaque(a.m), row0 = (int64_t)band * kBand;
+  const int rows = (int)(m - row0 < kBand ? m - row0 : kBand);
+  // rows past the matrix lie past the end of the resource and read as zero
+  const __amdgpu_buffer_rsrc_t rsrc =
+      make_rsrc(HAS_G ? static_cast<const T*>(a.gD) + row0 * a.ldgd : a.gC,
+                HAS_G ? (uint32_t)(((rows - 1) * (int64_t)ldg + n) * (int64_t)sizeof(T)) : 0u);
+  // gscore lands on cell (m-1, n-1): band row m-1-row0, slot n-1 + that row
+  const int last_row = band == a.nb - 1 && a.gscore ? rows - 1 : -1;
+  const T gs = last_row >= 0 ? *static_cast<const T*>(a.gscore) : E::zero();
+  const int last_slot = n - 1 + last_row;
+  uint64_t waited = 0;
+  Vec4<T> buf[PF][kAdjNV];
+  // Loads are issued unconditionally (indices clamped to sub-chunk 0), so that the number in
+  // flight is the same at every wait.
+  if constexpr (HAS_G) {
+#pragma unroll
+    for (int p = 0; p < PF; ++p) adj_load_g<T>(buf[p], rsrc, ldg, h, Ks - 1 - p >= 0 ? Ks - 1 - p : 0);
+  }
+  for (int kr0 = 0; kr0 < Ks; kr0 += PF) {
+#pragma unroll
+    for (int p = 0; p < PF; ++p) {
+      const int kr = kr0 + p, k = Ks - 1 - kr;  // the kr-th sub-chunk processed: slots [64k, 64k+64)
+      if (kr < Ks) {
+        if (!adj_wait_free<T, G>(sh, a.ctl, kr, waited)) return false;
+        // every column of the sub-chunk lies in the matrix (rows past it: see the resource)
+        const bool interior = k > 0 && kSub * (k + 1) <= n;
+        const bool has_last = last_row >= 0 && last_slot / kSub == k;
+#pragma unroll
+        for (int v = 0; v < kAdjNV; ++v) {
+          const int i = adj_row(h, v), slot = adj_slot(k);
+          Vec4<T> x;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) x.v[e] = E::zero();
+          if constexpr (HAS_G) {
+            x = buf[p][v];
+            if (!interior) {
+#pragma unroll
+              for (int e = 0; e < 4; ++e)
+                if (i >= rows || slot - i + e < 0 || slot - i + e >= n) x.v[e] = E::zero();
+            }
+          }
+          if (has_last && i == last_row) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              if (last_slot == slot + e) x.v[e] = E::add(x.v[e], gs);
+          }
+          *reinterpret_cast<Vec4<T>*>(S + i * C::PITCH + (slot & C::MASK)) = x;
+        }
+        lds_publish(&sh.ctr[h == 0 ? kAdjVal : kAdjVal1], kr + 1 < Ks ? (uint32_t)(kr + 1) : kAdjAll);
+        if constexpr (HAS_G) adj_load_g<T>(buf[p], rsrc, ldg, h, k - PF >= 0 ? k - PF : 0);
+      }
+    }
+  }
+  if (h == 0 && tr && lane == 0) {
+    tr[9] = waited;
+    tr[12] = __builtin_amdgcn_s_memrealtime();
+  }
+  return true;
+}
+
+// wave 5: the factor words: for the cell of lane r at slot s, byte 0 of the W word says whether
+// cell (r, slot s+1) selected W, byte 0 of the N word whether (r+1, s+1) selected N, byte 0 of
+// the NW word whether (r+1, s+2) selected NW -- i.e. whether that successor routes its value
+// here -- and bytes 1..3 the same for slots s+1..s+3 (the group of 4 slots); and row 0's own N
+// and NW planes, which the publisher needs.
+constexpr int kAdjPFS = 4;  // sub-chunks of bit-planes in flight
+
 typedef int v4i_t __attribute__((ext_vector_type(4)));
 
 // The four 0/1 bits of a 64-bit plane at slots [4g, 4g+4), spread to the four bytes of a word.
@@ -872,134 +944,60 @@ __device__ __forceinline__ uint32_t spread4(uint64_t bits, int g) {
   return (nib * 0x00204081u) & 0x01010101u;
 }
 
-// Two waves share the loading: PART 0 writes the upstream values (HAS_G: whether gD is
-// given; without it no loads are issued at all) and counts them in ctr[0], PART 1 the factor
-// words and row 0's planes, counted in ctr[6].  One wave doing both falls behind the reverse
-// chain: it spends longer per sub-chunk than the chain takes to consume it.
-template <typename T, int G, bool HAS_G, int PART>
-__device__ __forceinline__ void adj_loader(T* S, uint32_t* F, uint32_t* PubR, AdjShared& sh, const AdjArgs& a,
-                                           int band, int Ks, uint64_t* tr) {
+template <typename T, int G>
+__device__ __forceinline__ bool adj_load_factors(uint32_t* F, uint32_t* PubR, AdjShared& sh, const AdjArgs& a, int band,
+                                                 int Ks) {
   using C = BCfg<T>;
-  using E = typename C::E;
-  constexpr int PF = AdjPF<T>::PF, PFS = AdjPF<T>::PFS;
-  static_assert(PFS % PF == 0, "prefetch depths must nest");
+  typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+  constexpr int PF = kAdjPFS;
   const int lane = threadIdx.x & 63;
-  const int64_t ldg = opaque(a.ldgd), n = opaque(a.n), m = opaque(a.m);
-  const int64_t row0 = (int64_t)band * kBand;
-  const int rows = (int)(m - row0 < kBand ? m - row0 : kBand);
-  const __amdgpu_buffer_rsrc_t rsrc =
-      make_rsrc(HAS_G ? static_cast<const T*>(a.gD) + row0 * ldg : a.gC,
-                HAS_G ? (uint32_t)(((rows - 1) * ldg + n) * (int64_t)sizeof(T)) : 0u);
-  // gscore lands on cell (m-1, n-1): band row m-1-row0, slot n-1 + that row
-  const int64_t last_row = m - 1 - row0;
-  const bool has_last = last_row >= 0 && last_row < kBand && a.gscore != nullptr;
-  const T gs = has_last ? *static_cast<const T*>(a.gscore) : E::zero();
-  const int64_t last_slot = n - 1 + last_row;
   const uint32_t* selp = a.sel + sel_index(band, Ks, 0, lane);  // + 512 words per sub-chunk
   uint64_t waited = 0;
-  constexpr bool LOAD_G = PART == 0 && HAS_G;
-  Vec4<T> gbuf[LOAD_G ? PF : 1][16];
-  v4i_t sbuf[PART == 1 ? PFS : 1][2];
+  v4i_t buf[PF][2];
+  auto load = [&](v4i_t (&x)[2], int k) {
+    const v4i_t* src = reinterpret_cast<const v4i_t*>(selp + (int64_t)(k >= 0 ? k : 0) * 512);
+    x[0] = __builtin_nontemporal_load(src);
+    x[1] = __builtin_nontemporal_load(src + 1);
+  };
   // bits of the slots just above the current sub-chunk (the one processed before it)
   uint64_t carry_w = 0, carry_n = 0, carry_nw = 0;
-  // reverse order: the kr-th sub-chunk processed is k = Ks-1-kr
-  // Loads are issued unconditionally (indices clamped to sub-chunk 0), PFS / PF sub-chunks
-  // ahead, so that the number in flight is the same at every wait.
-  if constexpr (PART == 1) {
 #pragma unroll
-    for (int p = 0; p < PFS; ++p) {
-      const v4i_t* src = reinterpret_cast<const v4i_t*>(selp + (int64_t)(Ks - 1 - p >= 0 ? Ks - 1 - p : 0) * 512);
-      sbuf[p][0] = __builtin_nontemporal_load(src);
-      sbuf[p][1] = __builtin_nontemporal_load(src + 1);
-    }
-  }
-  if constexpr (LOAD_G) {
+  for (int p = 0; p < PF; ++p) load(buf[p], Ks - 1 - p);
+  for (int kr0 = 0; kr0 < Ks; kr0 += PF) {
 #pragma unroll
-    for (int p = 0; p < PF; ++p) adj_load_g<T>(gbuf[p], rsrc, ldg, Ks - 1 - p >= 0 ? Ks - 1 - p : 0);
-  }
-  for (int kr0 = 0; kr0 < Ks; kr0 += PFS) {
-#pragma unroll
-    for (int p = 0; p < PFS; ++p) {
-      const int kr = kr0 + p;
-      const int k = Ks - 1 - kr;  // sub-chunk (slots [64k, 64k+64))
-      Vec4<T>(&gx)[16] = gbuf[LOAD_G ? p % PF : 0];
+    for (int p = 0; p < PF; ++p) {
+      const int kr = kr0 + p, k = Ks - 1 - kr;
       if (kr < Ks) {
-      const int older = kr - C::NSUB;
-      if (older >= 0 && (!lds_wait_ge<false>(&sh.ctr[3], (uint32_t)(older + 1), &sh.abort, a.ctl, waited) ||
-                         !lds_wait_ge<false>(&sh.ctr[4], (uint32_t)((kSub / G) * (older + 1)), &sh.abort, a.ctl,
-                                             waited))) {
-        sh.abort = 1u;
-        return;
-      }
-      if constexpr (PART == 0) {
-      // upstream values
-      const bool interior = rows == kBand && k > 0 && (int64_t)kSub * k + kSub <= n;
+        if (!adj_wait_free<T, G>(sh, a.ctl, kr, waited)) return false;
+        // factors, aligned to the receiving cell
+        const v4i_t w0 = buf[p][0], w1 = buf[p][1];
+        const uint64_t pw = (uint32_t)w0.x | ((uint64_t)(uint32_t)w0.y << 32);
+        const uint64_t pn_own = (uint32_t)w0.z | ((uint64_t)(uint32_t)w0.w << 32);
+        const uint64_t pnw_own = (uint32_t)w1.x | ((uint64_t)(uint32_t)w1.y << 32);
+        const uint64_t pn = shl1z_u32((uint32_t)pn_own) | ((uint64_t)shl1z_u32((uint32_t)(pn_own >> 32)) << 32);
+        const uint64_t pnw = shl1z_u32((uint32_t)pnw_own) | ((uint64_t)shl1z_u32((uint32_t)(pnw_own >> 32)) << 32);
+        const uint64_t fw = (pw >> 1) | (carry_w << 63);     // W selected at slot s+1, own row
+        const uint64_t fn = (pn >> 1) | (carry_n << 63);     // N selected at slot s+1, row r+1
+        const uint64_t fnw = (pnw >> 2) | (carry_nw << 62);  // NW selected at slot s+2, row r+1
+        carry_w = pw & 1u;
+        carry_n = pn & 1u;
+        carry_nw = pnw & 3u;
+        uint32_t* frow = F + lane * C::FPITCH + ((kSub * k) & C::MASK);
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int i = 4 * v + (lane >> 4);
-        const int slot = kSub * k + 4 * (lane & 15);
-        const int64_t c0 = (int64_t)slot - i;
-        Vec4<T> x;
-        if constexpr (HAS_G) {
-          x = gx[v];
-          if (!interior) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-              if (i >= rows || c0 + e < 0 || c0 + e >= n) x.v[e] = E::zero();
-          }
-        } else {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) x.v[e] = E::zero();
+        for (int g = 0; g < 16; ++g) {
+          const v4u f = {spread4(fw, g), spread4(fn, g), spread4(fnw, g), 0u};
+          *reinterpret_cast<v4u*>(frow + 4 * g) = f;
         }
-        if (has_last && i == (int)last_row) {
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if (last_slot == slot + e) x.v[e] = E::add(x.v[e], gs);
+        if (lane == 0) {
+          const v4u r0 = {(uint32_t)pn_own, (uint32_t)(pn_own >> 32), (uint32_t)pnw_own, (uint32_t)(pnw_own >> 32)};
+          *reinterpret_cast<v4u*>(PubR + 4 * (k & (C::NSUB - 1))) = r0;
         }
-        *reinterpret_cast<Vec4<T>*>(S + i * C::PITCH + (slot & C::MASK)) = x;
+        lds_publish(&sh.ctr[kAdjFac], kr + 1 < Ks ? (uint32_t)(kr + 1) : kAdjAll);
+        load(buf[p], k - PF);
       }
-      lds_publish(&sh.ctr[0], (uint32_t)(kr + 1));
-      } else {
-      // factors, aligned to the receiving cell
-      const v4i_t w0 = sbuf[p % PFS][0], w1 = sbuf[p % PFS][1];
-      const uint64_t pw = (uint32_t)w0.x | ((uint64_t)(uint32_t)w0.y << 32);
-      const uint64_t pn_own = (uint32_t)w0.z | ((uint64_t)(uint32_t)w0.w << 32);
-      const uint64_t pnw_own = (uint32_t)w1.x | ((uint64_t)(uint32_t)w1.y << 32);
-      const uint64_t pn = shl1z_u32((uint32_t)pn_own) | ((uint64_t)shl1z_u32((uint32_t)(pn_own >> 32)) << 32);
-      const uint64_t pnw = shl1z_u32((uint32_t)pnw_own) | ((uint64_t)shl1z_u32((uint32_t)(pnw_own >> 32)) << 32);
-      const uint64_t fw = (pw >> 1) | (carry_w << 63);       // W selected at slot s+1, own row
-      const uint64_t fn = (pn >> 1) | (carry_n << 63);       // N selected at slot s+1, row r+1
-      const uint64_t fnw = (pnw >> 2) | (carry_nw << 62);    // NW selected at slot s+2, row r+1
-      carry_w = pw & 1u;
-      carry_n = pn & 1u;
-      carry_nw = pnw & 3u;
-      uint32_t* frow = F + lane * C::FPITCH + ((kSub * k) & C::MASK);
-#pragma unroll
-      for (int g = 0; g < 16; ++g) {
-        typedef uint32_t v4u __attribute__((ext_vector_type(4)));
-        const v4u f = {spread4(fw, g), spread4(fn, g), spread4(fnw, g), 0u};
-        *reinterpret_cast<v4u*>(frow + 4 * g) = f;
-      }
-      if (lane == 0) {
-        typedef uint32_t v4u __attribute__((ext_vector_type(4)));
-        const v4u r0 = {(uint32_t)pn_own, (uint32_t)(pn_own >> 32), (uint32_t)pnw_own, (uint32_t)(pnw_own >> 32)};
-        *reinterpret_cast<v4u*>(PubR + 4 * (k & (C::NSUB - 1))) = r0;
-      }
-      lds_publish(&sh.ctr[6], (uint32_t)(kr + 1));
-      }
-      }
-      if constexpr (PART == 1) {
-        const v4i_t* src = reinterpret_cast<const v4i_t*>(selp + (int64_t)(k - PFS >= 0 ? k - PFS : 0) * 512);
-        sbuf[p][0] = __builtin_nontemporal_load(src);
-        sbuf[p][1] = __builtin_nontemporal_load(src + 1);
-      }
-      if constexpr (LOAD_G) adj_load_g<T>(gx, rsrc, ldg, k - PF >= 0 ? k - PF : 0);
     }
   }
-  if (PART == 0 && tr && lane == 0) {
-    tr[9] = waited;
-    tr[12] = __builtin_amdgcn_s_memrealtime();
-  }
+  return true;
 }
 
 // wave 2: inputs from the band below.  For lane 63 (band row 63) at slot s, column c = s-63,
@@ -1009,7 +1007,7 @@ __device__ __forceinline__ void adj_loader(T* S, uint32_t* F, uint32_t* PubR, Ad
 // the 64 slots below the last unit handed over and hands over every complete unit of G
 // slots, so one global round trip advances it by up to 64 slots whatever G is.
 template <typename T, int G>
-__device__ __forceinline__ void adj_poll(T* S, AdjShared& sh, const AdjArgs& a, int band, int Ks, uint32_t epoch,
+__device__ __forceinline__ bool adj_poll(T* S, AdjShared& sh, const AdjArgs& a, int band, int Ks, uint32_t epoch,
                                          uint64_t* tr) {
   using C = BCfg<T>;
   using E = typename C::E;
@@ -1018,8 +1016,8 @@ __device__ __forceinline__ void adj_poll(T* S, AdjShared& sh, const AdjArgs& a, 
   const int64_t n = opaque(a.n);
   const int S0 = kSub * Ks, Us = S0 / G;
   if (band == a.nb - 1) {  // the bottom band has nothing below it
-    if (lane == 0) lds_signal(&sh.ctr[1], 0x7fffffffu);
-    return;
+    if (lane == 0) lds_signal(&sh.ctr[kAdjPolled], kAdjAll);
+    return true;
   }
   uint64_t waited = 0, t0 = 0;
   uint32_t polls = 0;
@@ -1031,28 +1029,23 @@ __device__ __forceinline__ void adj_poll(T* S, AdjShared& sh, const AdjArgs& a, 
     const bool real = c >= 0 && c < n;
     // Every lane loads on every pass (a lane with no word to read loads spare words of the
     // control block and ignores them): loads under a lane mask would make each wait drain
-    // all of the wave's loads.  Two polls are in flight: while one pass's words are checked
-    // the next pass's are on their way.
+    // all of the wave's loads.
     const uint64_t* src = real ? a.bnd + ((int64_t)band * n + c) * 2 * W : reinterpret_cast<const uint64_t*>(a.ctl) + 4;
-    uint64_t xa[2 * W], xb[2 * W];
-    auto issue = [&](uint64_t (&x)[2 * W]) {
+    uint32_t w[2 * W];
+    bool ok = true;
 #pragma unroll
-      for (int q = 0; q < 2 * W; ++q) x[q] = load_word(src + q);
-    };
-    // units complete in x: the run of ready slots from the top of the window down (slots
-    // outside the matrix count as ready), in whole units
-    auto complete = [&](const uint64_t (&x)[2 * W]) -> int {
-      bool ok = true;
-#pragma unroll
-      for (int q = 0; q < 2 * W; ++q) ok = ok && (uint32_t)(x[q] >> 32) == epoch;
-      ok = ok || !real;
-      const uint64_t okm = __ballot(ok);
-      const int run = ~okm == 0 ? 64 : __builtin_clzll(~okm);
-      const int k = run / G;
-      return k < Us - u ? k : Us - u;
-    };
-    // false when the wait has to give up
-    auto pause = [&]() -> bool {
+    for (int q = 0; q < 2 * W; ++q) {
+      const uint64_t x = load_word(src + q);
+      ok = ok && (uint32_t)(x >> 32) == epoch;
+      w[q] = (uint32_t)x;
+    }
+    // units complete: the run of ready slots from the top of the window down (slots outside the
+    // matrix count as ready), in whole units
+    const uint64_t okm = __ballot(ok || !real);
+    const int run = ~okm == 0 ? 64 : __builtin_clzll(~okm);
+    int k = run / G;
+    if (k > Us - u) k = Us - u;
+    if (k == 0) {
       if (polls == 0 && a.trace) t0 = __builtin_amdgcn_s_memrealtime();
       __builtin_amdgcn_s_sleep(1);
       if ((++polls & 63u) == 0u) {
@@ -1065,34 +1058,7 @@ __device__ __forceinline__ void adj_poll(T* S, AdjShared& sh, const AdjArgs& a, 
           return false;
         }
       }
-      return true;
-    };
-    uint32_t w[2 * W];
-    auto take = [&](const uint64_t (&x)[2 * W]) {
-#pragma unroll
-      for (int q = 0; q < 2 * W; ++q) w[q] = (uint32_t)x[q];
-    };
-    int k;
-    issue(xa);
-    for (;;) {
-      issue(xb);
-      if ((k = complete(xa)) > 0) {
-        take(xa);
-        break;
-      }
-      if (!pause()) {
-        sh.abort = 1u;
-        return;
-      }
-      issue(xa);
-      if ((k = complete(xb)) > 0) {
-        take(xb);
-        break;
-      }
-      if (!pause()) {
-        sh.abort = 1u;
-        return;
-      }
+      continue;
     }
     if (polls != 0u) {
       if (a.trace) waited += __builtin_amdgcn_s_memrealtime() - t0;
@@ -1110,103 +1076,92 @@ __device__ __forceinline__ void adj_poll(T* S, AdjShared& sh, const AdjArgs& a, 
     carry_pnw = lane_value(vnw, kSub - cols);
     // the value ring must hold the upstream values of the units handed over
     const uint32_t need_l = (uint32_t)((G * (u + k - 1)) / kSub + 1);
-    if (!lds_wait_ge(&sh.ctr[0], need_l, &sh.abort, a.ctl, waited)) {
-      sh.abort = 1u;
-      return;
-    }
+    if (!lds_wait_ge(&sh.ctr[kAdjVal1], need_l, &sh.abort, a.ctl, waited)) return false;
     if (real && lane >= kSub - cols) {
       T* cell = S + (kBand - 1) * C::PITCH + (s & C::MASK);
       *cell = E::add(E::add(*cell, nw_next), vn);
     }
     u += k;
-    lds_signal(&sh.ctr[1], (uint32_t)u);
+    lds_signal(&sh.ctr[kAdjPolled], u < Us ? (uint32_t)u : kAdjAll);
     if (tr && lane == 0 && u == k) tr[15] = __builtin_amdgcn_s_memrealtime();
   }
   if (tr && lane == 0) tr[10] = waited;
+  return true;
 }
 
 // wave 3: storer of gC (= A), one sub-chunk at a time from the top slot down
-template <typename T, int G>
-__device__ __forceinline__ void adj_store(const T* S, AdjShared& sh, const AdjArgs& a, int band, int Ks, uint64_t* tr) {
-  using C = BCfg<T>;
+template <typename T>
+__device__ __forceinline__ void adj_put(__amdgpu_buffer_rsrc_t r, int off, const Vec4<T>& x) {
   typedef int v4i __attribute__((ext_vector_type(4)));
+  if constexpr (sizeof(T) == 4) {
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4i, x), r, off, 0, 0);
+  } else {
+    struct Hf { v4i lo, hi; };
+    const Hf hh = __builtin_bit_cast(Hf, x);
+    __builtin_amdgcn_raw_buffer_store_b128(hh.lo, r, off, 0, 0);
+    __builtin_amdgcn_raw_buffer_store_b128(hh.hi, r, off + 16, 0, 0);
+  }
+}
+
+template <typename T, int G>
+__device__ __forceinline__ bool adj_store(const T* S, AdjShared& sh, const AdjArgs& a, int band, int Ks, uint64_t* tr) {
+  using C = BCfg<T>;
+  constexpr int es = sizeof(T);
   const int lane = threadIdx.x & 63;
-  const int64_t ldo = opaque(a.ldgc), n = opaque(a.n), m = opaque(a.m);
-  const int64_t row0 = (int64_t)band * kBand;
+  const int ldo = (int)opaque(a.ldgc), n = (int)opaque(a.n);
+  const int64_t m = opaque(a.m), row0 = (int64_t)band * kBand;
   const int rows = (int)(m - row0 < kBand ? m - row0 : kBand);
+  // rows past the matrix lie past the end of the resource: their stores are dropped
   const __amdgpu_buffer_rsrc_t drs =
-      make_rsrc(static_cast<T*>(a.gC) + row0 * ldo, (uint32_t)(((rows - 1) * ldo + n) * (int64_t)sizeof(T)));
+      make_rsrc(static_cast<T*>(a.gC) + row0 * a.ldgc, (uint32_t)(((rows - 1) * (int64_t)ldo + n) * (int64_t)es));
   uint64_t waited = 0;
   for (int kr = 0; kr < Ks; ++kr) {
     const int k = Ks - 1 - kr;
-    if (!lds_wait_ge(&sh.ctr[4], (uint32_t)((kSub / G) * (kr + 1)), &sh.abort, a.ctl, waited)) {
-      sh.abort = 1u;
-      return;
-    }
-    const int j4 = 4 * (lane & 15);
-    const int slot = (kSub * k + j4) & C::MASK;
-    if (rows == kBand && k > 0 && (int64_t)kSub * k + kSub <= n) {
-      Vec4<T> v[16];
+    if (!lds_wait_ge(&sh.ctr[kAdjPub], (uint32_t)((kSub / G) * (kr + 1)), &sh.abort, a.ctl, waited)) return false;
+    const int slot = adj_slot(k);
+    const bool interior = k > 0 && kSub * (k + 1) <= n;  // every column lies in the matrix
 #pragma unroll
-      for (int q = 0; q < 16; ++q) v[q] = *reinterpret_cast<const Vec4<T>*>(S + (4 * q + (lane >> 4)) * C::PITCH + slot);
+    for (int h = 0; h < 2; ++h) {
+      Vec4<T> x[kAdjNV];
 #pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const int i = 4 * q + (lane >> 4);
-        const int off = (int)(((int64_t)i * ldo + kSub * k + j4 - i) * (int64_t)sizeof(T));
-        if constexpr (sizeof(T) == 4) {
-          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4i, v[q]), drs, off, 0, 0);
-        } else {
-          struct Hf { v4i lo, hi; };
-          const Hf hh = __builtin_bit_cast(Hf, v[q]);
-          __builtin_amdgcn_raw_buffer_store_b128(hh.lo, drs, off, 0, 0);
-          __builtin_amdgcn_raw_buffer_store_b128(hh.hi, drs, off + 16, 0, 0);
+      for (int v = 0; v < kAdjNV; ++v)
+        x[v] = *reinterpret_cast<const Vec4<T>*>(S + adj_row(h, v) * C::PITCH + (slot & C::MASK));
+#pragma unroll
+      for (int v = 0; v < kAdjNV; ++v) {
+        const int i = adj_row(h, v), c0 = slot - i, off = (int)((uint32_t)(i * ldo + c0) * (uint32_t)es);
+        if (interior) {
+          adj_put<T>(drs, off, x[v]);
+          continue;
         }
-      }
-    } else {
-      // edge sub-chunk: the same 16 LDS reads first, then per vector one 16-byte store if its
-      // four cells lie inside the matrix, else a store per cell that does
-      Vec4<T> v[16];
-#pragma unroll
-      for (int q = 0; q < 16; ++q) v[q] = *reinterpret_cast<const Vec4<T>*>(S + (4 * q + (lane >> 4)) * C::PITCH + slot);
-#pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const int i = 4 * q + (lane >> 4);
+        // edge: one 16-byte store if the four cells lie inside, else a store per cell that does
         if (i >= rows) continue;
-        const int64_t c0 = (int64_t)kSub * k + j4 - i;
-        const int off = (int)(((int64_t)i * ldo + c0) * (int64_t)sizeof(T));
         if (c0 >= 0 && c0 + 4 <= n) {
-          if constexpr (sizeof(T) == 4) {
-            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4i, v[q]), drs, off, 0, 0);
-          } else {
-            struct Hf { v4i lo, hi; };
-            const Hf hh = __builtin_bit_cast(Hf, v[q]);
-            __builtin_amdgcn_raw_buffer_store_b128(hh.lo, drs, off, 0, 0);
-            __builtin_amdgcn_raw_buffer_store_b128(hh.hi, drs, off + 16, 0, 0);
-          }
+          adj_put<T>(drs, off, x[v]);
           continue;
         }
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           if (c0 + e >= 0 && c0 + e < n) {
-            if constexpr (sizeof(T) == 4) {
-              __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, v[q].v[e]), drs, off + 4 * e, 0, 0);
+            if constexpr (es == 4) {
+              __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, x[v].v[e]), drs, off + 4 * e, 0, 0);
             } else {
               typedef int v2i __attribute__((ext_vector_type(2)));
-              __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(v2i, v[q].v[e]), drs, off + 8 * e, 0, 0);
+              __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(v2i, x[v].v[e]), drs, off + 8 * e, 0, 0);
             }
           }
         }
       }
     }
-    lds_publish(&sh.ctr[3], (uint32_t)(kr + 1));
+    lds_publish(&sh.ctr[kAdjStored], (uint32_t)(kr + 1));
   }
   if (tr && lane == 0) tr[11] = waited;
+  return true;
 }
 
 // wave 4: publisher of row 0's routed values for the band above: at column c (slot c of
 // row 0), A times "selected N" and A times "selected NW".
 template <typename T, int G>
-__device__ __forceinline__ void adj_publish(const T* S, const uint32_t* PubR, AdjShared& sh, const AdjArgs& a,
+__device__ __forceinline__ bool adj_publish(const T* S, const uint32_t* PubR, AdjShared& sh, const AdjArgs& a,
                                             int band, int Ks, uint32_t epoch, uint64_t* tr) {
   using C = BCfg<T>;
   using E = typename C::E;
@@ -1220,10 +1175,8 @@ __device__ __forceinline__ void adj_publish(const T* S, const uint32_t* PubR, Ad
   uint64_t waited = 0;
   for (int u = 0; u < Us;) {
     uint32_t done;
-    if (!lds_wait_value<true, false>(&sh.ctr[2], (uint32_t)(G * (u + 1)), &sh.abort, a.ctl, waited, done)) {
-      sh.abort = 1u;
-      return;
-    }
+    if (!lds_wait_value<true, false>(&sh.ctr[kAdjSteps], (uint32_t)(G * (u + 1)), &sh.abort, a.ctl, waited, done))
+      return false;
     // every unit finished by now goes out in this pass, up to 64 slots
     int k = (int)(done / G) - u;
     if (k > kSub / G) k = kSub / G;
@@ -1248,9 +1201,10 @@ __device__ __forceinline__ void adj_publish(const T* S, const uint32_t* PubR, Ad
     }
     if (mark) tr[14] = __builtin_amdgcn_s_memrealtime();
     u += k;
-    lds_publish(&sh.ctr[4], (uint32_t)u);
+    lds_publish(&sh.ctr[kAdjPub], (uint32_t)u);
   }
   if (tr && lane == 0) tr[18] = waited;
+  return true;
 }
 
 template <typename T>
@@ -1260,27 +1214,30 @@ struct AdjLds {
   uint32_t PubR[4 * BCfg<T>::NSUB];
 };
 
-// One band of the instance 'a' describes, all six roles.  The LDS counters must be zero on
+// One band of the instance 'a' describes, all seven roles.  The LDS counters must be zero on
 // entry.
 template <typename T, int G>
 __device__ __forceinline__ void adj_band(AdjLds<T>& L, AdjShared& sh, const AdjArgs& a, int band, uint32_t epoch,
                                          uint64_t* tr) {
   T* S = reinterpret_cast<T*>(L.S4);
-  const int wave = threadIdx.x >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));  // uniform branches below
   const int Ks = (int)((a.n + kBand - 1 + kSub - 1) / kSub);
-  if (wave == 0)
-    adj_compute<T, G>(S, L.F, sh, a.ctl, Ks, tr);
-  else if (wave == 1)
-    a.gD ? adj_loader<T, G, true, 0>(S, L.F, L.PubR, sh, a, band, Ks, tr)
-         : adj_loader<T, G, false, 0>(S, L.F, L.PubR, sh, a, band, Ks, tr);
-  else if (wave == 2)
-    adj_poll<T, G>(S, sh, a, band, Ks, epoch, tr);
-  else if (wave == 3)
-    adj_store<T, G>(S, sh, a, band, Ks, tr);
-  else if (wave == 4)
-    adj_publish<T, G>(S, L.PubR, sh, a, band, Ks, epoch, tr);
-  else
-    adj_loader<T, G, false, 1>(S, L.F, L.PubR, sh, a, band, Ks, tr);
+  bool ok;
+  if (wave == 0) {
+    ok = adj_compute<T, G>(S, L.F, sh, a.ctl, Ks, tr);
+  } else if (wave == 2) {
+    ok = adj_poll<T, G>(S, sh, a, band, Ks, epoch, tr);
+  } else if (wave == 3) {
+    ok = adj_store<T, G>(S, sh, a, band, Ks, tr);
+  } else if (wave == 4) {
+    ok = adj_publish<T, G>(S, L.PubR, sh, a, band, Ks, epoch, tr);
+  } else if (wave == 5) {
+    ok = adj_load_factors<T, G>(L.F, L.PubR, sh, a, band, Ks);
+  } else {
+    ok = a.gD ? adj_load_values<T, G, true>(S, sh, a, band, Ks, wave == 1 ? 0 : 1, tr)
+              : adj_load_values<T, G, false>(S, sh, a, band, Ks, wave == 1 ? 0 : 1, tr);
+  }
+  if (!ok) sh.abort = 1u;
 }
 
 // TRACE = false compiles every trace statement out (the production instance); the traced

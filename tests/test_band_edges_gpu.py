@@ -1,5 +1,5 @@
 """Edges of the band pipelines on the GPU: the forward sweep with one, two and four rows per
-lane, autotuned batches, the soft-min adjoint.
+lane, autotuned batches, the soft-min adjoint, the reverse sweep.
 
 Which of them a shape takes depends on m / n; the shapes here lie on both sides of the rule's
 lines and of the band edges (64, 128 and 256 rows), with matrices narrower than one handoff
@@ -112,3 +112,28 @@ def test_soft_adjoint_edges(dtype, m, n):
         if g is not None:
             wf.soft_backward(C.to(DEV), D, gamma, g_score=gs, g_D=gdev, g_C=gdev)
             assert torch.equal(gdev, out)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("m,n", [(1, 65), (2, 63), (31, 130), (33, 64), (65, 257), (95, 128), (97, 1), (120, 700), (191, 62)])
+def test_adjoint_ragged_rows_padded(dtype, m, n):
+    """The reverse sweep where the last band holds a part of its rows (either half of them, with
+    whole and partial column edges), gD and gC with a leading dimension beyond n, gC also written
+    over gD: bitwise equal to the oracle, nothing written beside the matrix."""
+    prec = "f32" if dtype == torch.float32 else "f64"
+    C = inputs.normal_clipped(m, n, 5 * m + n, dtype)
+    gD = inputs.normal_clipped(m, n, 3 * m + n, dtype)
+    D, sel = oracle.forward(C.numpy(), prec, want_sel=True)
+    ref = torch.from_numpy(oracle.backward(sel, gD.numpy(), 0.75, prec))
+    gs = torch.tensor(0.75, dtype=dtype, device=DEV)
+    Dd = torch.from_numpy(D).to(DEV)
+    for pad in (0, 3):
+        g_in = torch.full((m, n + pad), 1e30, dtype=dtype, device=DEV)
+        g_in[:, :n] = gD.to(DEV)
+        out = torch.full((m + 2, n + pad), -9, dtype=dtype, device=DEV)
+        wf.backward(C.to(DEV), g_score=gs, g_D=g_in[:, :n], D=Dd, g_C=out[1:m + 1, :n])
+        wf.backward(C.to(DEV), g_score=gs, g_D=g_in[:, :n], D=Dd, g_C=g_in[:, :n])
+        wf.last_async_error()
+        assert torch.equal(out[1:m + 1, :n].cpu(), ref) and torch.equal(g_in[:, :n].cpu(), ref)
+        assert bool((out[0] == -9).all()) and bool((out[m + 1] == -9).all()) and bool((out[:, n:] == -9).all())
+        assert bool((g_in[:, n:] == g_in.new_tensor(1e30)).all())
