@@ -137,3 +137,21 @@ def test_adjoint_ragged_rows_padded(dtype, m, n):
         assert torch.equal(out[1:m + 1, :n].cpu(), ref) and torch.equal(g_in[:, :n].cpu(), ref)
         assert bool((out[0] == -9).all()) and bool((out[m + 1] == -9).all()) and bool((out[:, n:] == -9).all())
         assert bool((g_in[:, n:] == g_in.new_tensor(1e30)).all())
+
+
+@pytest.mark.parametrize("gamma", [1e-3, 0.02, 1.0, 50.0])
+@pytest.mark.parametrize("m,n", [(1, 1), (3, 70), (70, 3), (130, 77), (64, 129)])
+def test_soft_forward_f64_weights(m, n, gamma):
+    """The float64 soft minimum from terms that vanish (small gamma: exponents far below -64) to
+    three nearly equal ones (large gamma, and one matrix of equal values), against the oracle.
+    Bound: a cell rounds its scaled sum, its minimum's difference and C's scaling once each and
+    takes two exponentials and a logarithm of two units in the last place at most, about 8 u of
+    the largest scaled value per cell of a path."""
+    u = 2.0 ** -53
+    for C in (inputs.uniform(m, n, 3 * m + n, torch.float64, lo=-2.0, hi=3.0), torch.full((m, n), 0.25, dtype=torch.float64)):
+        D, score = wf.soft_forward(C.to(DEV), gamma)
+        wf.last_async_error()
+        ref = oracle.soft_forward(C.numpy(), gamma)
+        tol = 8 * (m + n - 1) * u * max(float(np.max(np.abs(ref))), 2 * gamma)
+        assert np.max(np.abs(D.cpu().numpy() - ref)) <= tol
+        assert float(score) == float(D[-1, -1])
