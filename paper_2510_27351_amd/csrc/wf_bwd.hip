@@ -1402,45 +1402,57 @@ __device__ __forceinline__ void walk_band(const PathArgs& a, int b) {
   if (q < 0) return;
   const int rows = b == nb - 1 ? rows_last : kBand;
   T* g0 = static_cast<T*>(a.gC) + (int64_t)b * kBand * a.ldgc;
-  const uint32_t* planes = a.sel;
   int r = rows - 1;
-  int64_t col = q;
-  int64_t run_hi = col;
-  int kcur = -1;
-  uint32_t w[6] = {0u, 0u, 0u, 0u, 0u, 0u};
-  auto flush = [&](int row, int64_t lo, int64_t hi) {
-    for (int64_t c = lo + lane; c <= hi; c += 64) g0[(int64_t)row * a.ldgc + c] = gv;
+  int64_t col = q, run_hi = q;  // the path's cells of row r from run_hi down to col so far
+  auto flush = [&]() {
+    for (int64_t c = col + lane; c <= run_hi; c += 64) g0[(int64_t)r * a.ldgc + c] = gv;
   };
-  for (;;) {
-    const int64_t s = col + r;
-    const int k = (int)(s >> 6);
-    if (k != kcur) {
-      const uint4* src = reinterpret_cast<const uint4*>(planes + sel_index(b, a.Ks, k, lane));
-      const uint4 x0 = src[0], x1 = src[1];
-      w[0] = x0.x; w[1] = x0.y; w[2] = x0.z; w[3] = x0.w; w[4] = x1.x; w[5] = x1.y;
-      kcur = k;
-    }
-    const int j = (int)(s & 63), h = j >> 5, bit = j & 31;
-    const uint32_t sw = (uint32_t)__builtin_amdgcn_readlane((int)(h ? w[1] : w[0]), r);
-    const uint32_t sn = (uint32_t)__builtin_amdgcn_readlane((int)(h ? w[3] : w[2]), r);
-    const uint32_t snw = (uint32_t)__builtin_amdgcn_readlane((int)(h ? w[5] : w[4]), r);
-    if ((sw >> bit) & 1u) {
-      if (col == 0) break;  // never selected: W of column 0 is outside the matrix
-      --col;
-      continue;
-    }
-    flush(r, col, run_hi);
-    if ((sn >> bit) & 1u) {
-      if (r == 0) break;  // into the band above
+  // A slot (row + column) only ever falls along the path, by 1 or 2, so the sub-chunks of the
+  // planes are visited in turn: the next kAhead are on their way while one is walked.  A row's
+  // run of W selections is one count of leading ones.  Cell by cell, with every sub-chunk read
+  // when it was reached, a 64 x 16384 matrix took 2.5 ms and 4096 x 4096 28 us (82 and 23 so;
+  // of the latter the chain of exits above is about 14).
+  constexpr int kAhead = 4;
+  uint4 buf[kAhead][2];
+  int k = (int)((col + r) >> 6);
+  auto load = [&](uint4 (&x)[2], int kk) {
+    const uint4* src = reinterpret_cast<const uint4*>(a.sel + sel_index(b, a.Ks, kk >= 0 ? kk : 0, lane));
+    x[0] = src[0];
+    x[1] = src[1];
+  };
+  auto row_word = [&](uint32_t lo, uint32_t hi) -> uint64_t {  // row r's 64 bits of a plane
+    return (uint32_t)__builtin_amdgcn_readlane((int)lo, r) | ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)hi, r) << 32);
+  };
+  // The path's part in the sub-chunk x holds; false when the walk is over.
+  auto walk = [&](uint4 (&x)[2]) -> bool {
+    for (;;) {
+      const int j = (int)(col + r) - 64 * k;
+      if (j < 0) break;  // into the next sub-chunk
+      const uint64_t stay = ~(row_word(x[0].x, x[0].y) << (63 - j));
+      const int run = stay == 0 ? 64 : __builtin_clzll(stay);
+      if (run > col) return false;  // never selected: W of column 0 is outside the matrix
+      col -= run;
+      if (run > j) break;  // the run goes on in the next sub-chunk
+      flush();
+      const uint64_t bit = (uint64_t)1 << (j - run);
+      if (row_word(x[0].z, x[0].w) & bit) {
+        if (r == 0) return false;  // into the band above
+      } else if (row_word(x[1].x, x[1].y) & bit) {
+        if (r == 0 || col == 0) return false;  // into the band above, or outside the matrix
+        --col;
+      } else {
+        return false;  // cell (0, 0)
+      }
       --r;
-    } else if ((snw >> bit) & 1u) {
-      if (r == 0 || col == 0) break;  // into the band above, or outside the matrix
-      --r;
-      --col;
-    } else {
-      break;  // cell (0, 0)
+      run_hi = col;
     }
-    run_hi = col;
+    load(x, k - kAhead);
+    --k;
+    return true;
+  };
+#pragma unroll
+  for (int p = 0; p < kAhead; ++p) load(buf[p], k - p);
+  while (walk(buf[0]) && walk(buf[1]) && walk(buf[2]) && walk(buf[3])) {
   }
 }
 

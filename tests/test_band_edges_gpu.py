@@ -155,3 +155,27 @@ def test_soft_forward_f64_weights(m, n, gamma):
         tol = 8 * (m + n - 1) * u * max(float(np.max(np.abs(ref))), 2 * gamma)
         assert np.max(np.abs(D.cpu().numpy() - ref)) <= tol
         assert float(score) == float(D[-1, -1])
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("m,n", [(1, 700), (2, 64), (3, 1000), (64, 3000), (65, 4097), (130, 1500), (700, 1), (200, 5)])
+def test_path_walk_long_runs(dtype, m, n):
+    """The score's gradient where the path has runs of W selections through several 64-slot
+    sub-chunks, ending on, before and after their edges: random matrices much wider than high,
+    and matrices whose path turns at given columns; bitwise equal to the oracle."""
+    prec = "f32" if dtype == torch.float32 else "f64"
+    mats = [inputs.uniform(m, n, 7 * m + n, dtype)]
+    for turn in (0, 63, 64, 65, 127, 512):  # one cheap row until 'turn', another from there on
+        if m > 1 and turn < n:
+            C = torch.full((m, n), 100.0, dtype=dtype)
+            C[0, :turn + 1] = 1.0
+            C[:, turn] = 1.0
+            C[m - 1, turn:] = 1.0
+            mats.append(C)
+    gs = torch.tensor(1.5, dtype=dtype, device=DEV)
+    for C in mats:
+        D, sel = oracle.forward(C.numpy(), prec, want_sel=True)
+        ref = torch.from_numpy(oracle.backward(sel, None, 1.5, prec))
+        got = wf.backward(C.to(DEV), g_score=gs, D=torch.from_numpy(D).to(DEV))
+        wf.last_async_error()
+        assert torch.equal(got.cpu(), ref)
