@@ -241,8 +241,8 @@ int wf_set_tile(int32_t tile);
 
 /*
  * The automatic choice: the tile G (16, 32 or 64) that wf_forward (reverse = 0; at most 32 or
- * 16 where it gives each lane two or four rows) or wf_reverse / wf_backward (reverse = 1) use
- * for an m x n instance of element type dtype,
+ * 16 where it gives each lane two or four rows) or wf_reverse / wf_backward (reverse = 1; at
+ * most 32) use for an m x n instance of element type dtype,
  * by nearest-neighbour classification (k = 1, as the paper's kNN heuristic for its
  * sub-system size in the section "Building a heuristic for the optimum sub-system size"):
  * the fastest tile of the closest shape, in (log2 m, log2 n), of a table of shapes timed on

@@ -198,14 +198,6 @@ int forced_tile() {
   return 0;
 }
 
-// Tile of the single-instance sweeps for a shape: the override, else the nearest-neighbour
-// prediction from the tiles measured on MI355X.
-int choose_tile(int dtype, int64_t m, int64_t n, bool reverse) {
-  if (const int t = forced_tile()) return t;
-  // the callers have validated dtype, m and n, so this is a tile, never an error code
-  return wf_tile_predict(dtype, m, n, reverse ? 1 : 0);
-}
-
 // Rows per lane (1, 2 or 4; a band is 64 times as many rows) of the single-instance forward
 // sweep; ld_bytes is the larger of its leading dimensions.
 //
@@ -252,8 +244,9 @@ int forward_tile(int dtype, int rows, int tile) {
   return tile < cap ? tile : cap;
 }
 
-// The same for the forward sweep with 'rows' rows per lane (the predictor's table was timed
-// with one).
+// Tile of the single-instance forward sweep with 'rows' rows per lane: the override, else the
+// nearest-neighbour prediction from the tiles measured on MI355X (with one row per lane).  The
+// callers have validated dtype, m and n, so the prediction is a tile, never an error code.
 int choose_forward_tile(int dtype, int64_t m, int64_t n, int rows) {
   if (const int t = forced_tile()) return t;
   return forward_tile(dtype, rows, wf_tile_predict(dtype, m, n, 0));
@@ -263,7 +256,15 @@ int64_t nbands(int64_t m) { return (m + kBand - 1) / kBand; }
 
 }  // namespace
 
-int pick_tile(int dtype, int64_t m, int64_t n, bool reverse) { return choose_tile(dtype, m, n, reverse); }
+// Tile of the reverse sweep: the override, else the prediction, at most 32 (its table was timed
+// with a float64 ring of two sub-chunks, where 64 won for wide matrices).  Of 16, 32 and 64, us
+// with gD: float 3000 x 2500 249, 238 and 257; 8000 x 64 414, 388 and 428; 64 x 16384 354, 338
+// and 339; double 1023 x 1300 138, 136 and 159; 3000 x 100 270, 251 and 330; 3000 x 64 207, 216
+// and 247; 64 x 16384 532, 518 and 548.
+int pick_reverse_tile(int dtype, int64_t m, int64_t n) {
+  if (const int t = forced_tile()) return t;
+  return std::min(32, (int)wf_tile_predict(dtype, m, n, 1));
+}
 
 // ---------------------------------------------------------------------------------------
 // Scratch of the allocation-free forward sweep (wf_forward_noalloc): a file-scope device
@@ -656,7 +657,7 @@ int wf_reverse(int dtype, int64_t m, int64_t n, const void* g_score, const void*
   aa.ctl = ws->ctl;
   aa.bnd = ws->bnd;
   aa.trace = (g_trace && dev == g_trace_dev && nb <= g_trace_bands) ? g_trace : nullptr;
-  hipError_t e = launch_adjoint(dtype, choose_tile(dtype, m, n, true), aa, grid, st);
+  hipError_t e = launch_adjoint(dtype, pick_reverse_tile(dtype, m, n), aa, grid, st);
   return e == hipSuccess ? WF_OK : WF_E_DEVICE;
 }
 

@@ -74,7 +74,14 @@ struct BCfg {
   static constexpr int PITCH = RING + 16 / (int)sizeof(T);
   static constexpr int FPITCH = RING + 4;
   static constexpr int MASK = RING - 1;
-  static constexpr int NSUB = RING / kSub;  // 64-slot sub-chunks in a ring
+  // Sub-chunks the loaders and the storer work in, four to a ring: with two of 64 slots in
+  // float64's the band waited at every sub-chunk for the last but one's slots to be published,
+  // stored and loaded again (3000 x 100 with gD: 407 us).
+  static constexpr int SUB = RING / 4;
+  static constexpr int NSUB = RING / SUB;
+  static constexpr int LPR = SUB / 4;            // lanes side by side that hold a row of a sub-chunk
+  static constexpr int RPV = 64 / LPR;           // rows one vector index spans across the wave
+  static constexpr int NV = kBand / 2 / RPV;     // vectors of a lane per sub-chunk and half band
 };
 
 // LDS ring of the selection recompute: 256 slots per row for 4-byte elements, 128 for 8-byte
@@ -738,7 +745,9 @@ __device__ __forceinline__ bool adj_compute(T* __restrict__ S, const uint32_t* _
   uint32_t stall = 0;
   const int which = lane & (kAdjCounters - 1);
   const bool is_sub = which == kAdjVal || which == kAdjVal1 || which == kAdjFac, is_unit = which == kAdjPolled;
-  uint32_t need = is_sub || is_unit ? 1u : 0u;
+  // sub-chunks that hold the first x slots
+  auto subs = [](int x) { return (x + C::SUB - 1) / C::SUB; };
+  uint32_t need = is_sub ? (uint32_t)subs(G) : is_unit ? 1u : 0u;
   const uint32_t per_unit = is_unit ? 1u : 0u, per_sub = is_sub ? 1u : 0u;
   auto load_ready = [&]() -> uint32_t {
     return __hip_atomic_load(&sh.ctr[which], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -767,8 +776,7 @@ __device__ __forceinline__ bool adj_compute(T* __restrict__ S, const uint32_t* _
 #pragma unroll
     for (int v = 0; v < GPS; ++v) {
       constexpr int last = GPS - 1;
-      need += per_unit;
-      if (v == last) need += per_sub;
+      need += per_unit + per_sub * (uint32_t)(subs(G * (v + 2)) - subs(G * (v + 1)));
       const uint32_t ready = load_ready();
       __builtin_amdgcn_sched_barrier(0);
       AdjGroup<T> gr[NG + 2];
@@ -820,26 +828,31 @@ __device__ __forceinline__ bool adj_compute(T* __restrict__ S, const uint32_t* _
 }
 
 // waves 1 and 6: loaders of the upstream values gD (plus gscore on the last cell; zeros when gD
-// is absent), 32 rows each, one 64-slot sub-chunk at a time from the top slot down.  The loads
+// is absent), 32 rows each, one sub-chunk at a time from the top slot down.  The loads
 // of the next PF sub-chunks are in flight in registers.
 template <typename T>
-constexpr int kAdjPF = sizeof(T) == 4 ? 3 : 2;
+constexpr int kAdjPF = sizeof(T) == 4 ? 3 : 4;
 constexpr int kAdjHalf = kBand / 2;
-constexpr int kAdjNV = kAdjHalf / 4;  // vectors of a lane per sub-chunk
 
-// Row and first slot of a lane's vector v in sub-chunk k.
-__device__ __forceinline__ int adj_row(int h, int v) { return kAdjHalf * h + 4 * v + (int)(threadIdx.x & 63) / 16; }
-__device__ __forceinline__ int adj_slot(int k) { return kSub * k + 4 * (int)(threadIdx.x & 15); }
+// Row and first slot of a lane's vector v of half h in sub-chunk k (slots [k SUB, (k+1) SUB)).
+template <typename T>
+__device__ __forceinline__ int adj_row(int h, int v) {
+  return kAdjHalf * h + BCfg<T>::RPV * v + (int)(threadIdx.x & 63) / BCfg<T>::LPR;
+}
+template <typename T>
+__device__ __forceinline__ int adj_slot(int k) {
+  return BCfg<T>::SUB * k + 4 * (int)(threadIdx.x & (BCfg<T>::LPR - 1));
+}
 
 template <typename T>
-__device__ __forceinline__ void adj_load_g(Vec4<T> (&x)[kAdjNV], __amdgpu_buffer_rsrc_t rsrc, int ldg_, int h, int k) {
+__device__ __forceinline__ void adj_load_g(Vec4<T> (&x)[BCfg<T>::NV], __amdgpu_buffer_rsrc_t rsrc, int ldg_, int h, int k) {
   // recomputed per call: hoisted out of the loop, the row offsets would stay live
   const int ldg = opaque(ldg_);
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int v = 0; v < kAdjNV; ++v) {
-    const int i = adj_row(h, v);
-    const uint32_t off = (uint32_t)(i * ldg + adj_slot(k) - i) * (uint32_t)sizeof(T);
+  for (int v = 0; v < BCfg<T>::NV; ++v) {
+    const int i = adj_row<T>(h, v);
+    const uint32_t off = (uint32_t)(i * ldg + adj_slot<T>(k) - i) * (uint32_t)sizeof(T);
     if constexpr (sizeof(T) == 4) {
       x[v] = __builtin_bit_cast(Vec4<T>, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)off, 0, 0));
     } else {
@@ -858,11 +871,12 @@ template <typename T, int G>
 __device__ __forceinline__ bool adj_wait_free(AdjShared& sh, Control* ctl, int kr, uint64_t& waited) {
   const int older = kr - BCfg<T>::NSUB;
   return older < 0 || (lds_wait_ge<false>(&sh.ctr[kAdjStored], (uint32_t)(older + 1), &sh.abort, ctl, waited) &&
-                       lds_wait_ge<false>(&sh.ctr[kAdjPub], (uint32_t)((kSub / G) * (older + 1)), &sh.abort, ctl, waited));
+                       lds_wait_ge<false>(&sh.ctr[kAdjPub], (uint32_t)((BCfg<T>::SUB * (older + 1) + G - 1) / G), &sh.abort, ctl,
+                                    waited));
 }
 
 template <typename T, int G, bool HAS_G>
-__device__ __forceinline__ bool adj_load_values(T* S, AdjShared& sh, const AdjArgs& a, int band, int Ks, int h,
+__device__ __forceinline__ bool adj_load_values(T* S, AdjShared& sh, const AdjArgs& a, int band, int Ns, int h,
                                                 uint64_t* tr) {
   using C = BCfg<T>;
   using E = typename C::E;
@@ -880,25 +894,25 @@ __device__ __forceinline__ bool adj_load_values(T* S, AdjShared& sh, const AdjAr
   const T gs = last_row >= 0 ? *static_cast<const T*>(a.gscore) : E::zero();
   const int last_slot = n - 1 + last_row;
   uint64_t waited = 0;
-  Vec4<T> buf[PF][kAdjNV];
+  Vec4<T> buf[PF][BCfg<T>::NV];
   // Loads are issued unconditionally (indices clamped to sub-chunk 0), so that the number in
   // flight is the same at every wait.
   if constexpr (HAS_G) {
 #pragma unroll
-    for (int p = 0; p < PF; ++p) adj_load_g<T>(buf[p], rsrc, ldg, h, Ks - 1 - p >= 0 ? Ks - 1 - p : 0);
+    for (int p = 0; p < PF; ++p) adj_load_g<T>(buf[p], rsrc, ldg, h, Ns - 1 - p >= 0 ? Ns - 1 - p : 0);
   }
-  for (int kr0 = 0; kr0 < Ks; kr0 += PF) {
+  for (int kr0 = 0; kr0 < Ns; kr0 += PF) {
 #pragma unroll
     for (int p = 0; p < PF; ++p) {
-      const int kr = kr0 + p, k = Ks - 1 - kr;  // the kr-th sub-chunk processed: slots [64k, 64k+64)
-      if (kr < Ks) {
+      const int kr = kr0 + p, k = Ns - 1 - kr;  // the kr-th sub-chunk processed
+      if (kr < Ns) {
         if (!adj_wait_free<T, G>(sh, a.ctl, kr, waited)) return false;
         // every column of the sub-chunk lies in the matrix (rows past it: see the resource)
-        const bool interior = k > 0 && kSub * (k + 1) <= n;
-        const bool has_last = last_row >= 0 && last_slot / kSub == k;
+        const bool interior = C::SUB * k >= kBand - 1 && C::SUB * (k + 1) <= n;
+        const bool has_last = last_row >= 0 && last_slot / C::SUB == k;
 #pragma unroll
-        for (int v = 0; v < kAdjNV; ++v) {
-          const int i = adj_row(h, v), slot = adj_slot(k);
+        for (int v = 0; v < BCfg<T>::NV; ++v) {
+          const int i = adj_row<T>(h, v), slot = adj_slot<T>(k);
           Vec4<T> x;
 #pragma unroll
           for (int e = 0; e < 4; ++e) x.v[e] = E::zero();
@@ -917,7 +931,7 @@ __device__ __forceinline__ bool adj_load_values(T* S, AdjShared& sh, const AdjAr
           }
           *reinterpret_cast<Vec4<T>*>(S + i * C::PITCH + (slot & C::MASK)) = x;
         }
-        lds_publish(&sh.ctr[h == 0 ? kAdjVal : kAdjVal1], kr + 1 < Ks ? (uint32_t)(kr + 1) : kAdjAll);
+        lds_publish(&sh.ctr[h == 0 ? kAdjVal : kAdjVal1], kr + 1 < Ns ? (uint32_t)(kr + 1) : kAdjAll);
         if constexpr (HAS_G) adj_load_g<T>(buf[p], rsrc, ldg, h, k - PF >= 0 ? k - PF : 0);
       }
     }
@@ -934,7 +948,8 @@ __device__ __forceinline__ bool adj_load_values(T* S, AdjShared& sh, const AdjAr
 // the NW word whether (r+1, s+2) selected NW -- i.e. whether that successor routes its value
 // here -- and bytes 1..3 the same for slots s+1..s+3 (the group of 4 slots); and row 0's own N
 // and NW planes, which the publisher needs.
-constexpr int kAdjPFS = 4;  // sub-chunks of bit-planes in flight
+constexpr int kAdjPFS = 4;   // 64-slot words of the bit-planes in flight
+constexpr int kAdjPubR = 4;  // of row 0's planes in LDS
 
 typedef int v4i_t __attribute__((ext_vector_type(4)));
 
@@ -968,7 +983,6 @@ __device__ __forceinline__ bool adj_load_factors(uint32_t* F, uint32_t* PubR, Ad
     for (int p = 0; p < PF; ++p) {
       const int kr = kr0 + p, k = Ks - 1 - kr;
       if (kr < Ks) {
-        if (!adj_wait_free<T, G>(sh, a.ctl, kr, waited)) return false;
         // factors, aligned to the receiving cell
         const v4i_t w0 = buf[p][0], w1 = buf[p][1];
         const uint64_t pw = (uint32_t)w0.x | ((uint64_t)(uint32_t)w0.y << 32);
@@ -983,16 +997,22 @@ __device__ __forceinline__ bool adj_load_factors(uint32_t* F, uint32_t* PubR, Ad
         carry_n = pn & 1u;
         carry_nw = pnw & 3u;
         uint32_t* frow = F + lane * C::FPITCH + ((kSub * k) & C::MASK);
+        constexpr int HALVES = kSub / C::SUB;  // sub-chunks in the 64 slots of a word, the upper first
 #pragma unroll
-        for (int g = 0; g < 16; ++g) {
-          const v4u f = {spread4(fw, g), spread4(fn, g), spread4(fnw, g), 0u};
-          *reinterpret_cast<v4u*>(frow + 4 * g) = f;
+        for (int half = HALVES - 1; half >= 0; --half) {
+          const int ns = HALVES * kr + HALVES - 1 - half;  // the ns-th sub-chunk processed
+          if (!adj_wait_free<T, G>(sh, a.ctl, ns, waited)) return false;
+#pragma unroll
+          for (int g = half * (C::SUB / 4); g < (half + 1) * (C::SUB / 4); ++g) {
+            const v4u f = {spread4(fw, g), spread4(fn, g), spread4(fnw, g), 0u};
+            *reinterpret_cast<v4u*>(frow + 4 * g) = f;
+          }
+          if (half == HALVES - 1 && lane == 0) {
+            const v4u r0 = {(uint32_t)pn_own, (uint32_t)(pn_own >> 32), (uint32_t)pnw_own, (uint32_t)(pnw_own >> 32)};
+            *reinterpret_cast<v4u*>(PubR + 4 * (k & (kAdjPubR - 1))) = r0;
+          }
+          lds_publish(&sh.ctr[kAdjFac], ns + 1 < HALVES * Ks ? (uint32_t)(ns + 1) : kAdjAll);
         }
-        if (lane == 0) {
-          const v4u r0 = {(uint32_t)pn_own, (uint32_t)(pn_own >> 32), (uint32_t)pnw_own, (uint32_t)(pnw_own >> 32)};
-          *reinterpret_cast<v4u*>(PubR + 4 * (k & (C::NSUB - 1))) = r0;
-        }
-        lds_publish(&sh.ctr[kAdjFac], kr + 1 < Ks ? (uint32_t)(kr + 1) : kAdjAll);
         load(buf[p], k - PF);
       }
     }
@@ -1075,7 +1095,7 @@ __device__ __forceinline__ bool adj_poll(T* S, AdjShared& sh, const AdjArgs& a, 
     if (lane == kSub - 1) nw_next = carry_pnw;
     carry_pnw = lane_value(vnw, kSub - cols);
     // the value ring must hold the upstream values of the units handed over
-    const uint32_t need_l = (uint32_t)((G * (u + k - 1)) / kSub + 1);
+    const uint32_t need_l = (uint32_t)((G * (u + k) + C::SUB - 1) / C::SUB);
     if (!lds_wait_ge(&sh.ctr[kAdjVal1], need_l, &sh.abort, a.ctl, waited)) return false;
     if (real && lane >= kSub - cols) {
       T* cell = S + (kBand - 1) * C::PITCH + (s & C::MASK);
@@ -1104,7 +1124,7 @@ __device__ __forceinline__ void adj_put(__amdgpu_buffer_rsrc_t r, int off, const
 }
 
 template <typename T, int G>
-__device__ __forceinline__ bool adj_store(const T* S, AdjShared& sh, const AdjArgs& a, int band, int Ks, uint64_t* tr) {
+__device__ __forceinline__ bool adj_store(const T* S, AdjShared& sh, const AdjArgs& a, int band, int Ns, uint64_t* tr) {
   using C = BCfg<T>;
   constexpr int es = sizeof(T);
   const int lane = threadIdx.x & 63;
@@ -1115,20 +1135,20 @@ __device__ __forceinline__ bool adj_store(const T* S, AdjShared& sh, const AdjAr
   const __amdgpu_buffer_rsrc_t drs =
       make_rsrc(static_cast<T*>(a.gC) + row0 * a.ldgc, (uint32_t)(((rows - 1) * (int64_t)ldo + n) * (int64_t)es));
   uint64_t waited = 0;
-  for (int kr = 0; kr < Ks; ++kr) {
-    const int k = Ks - 1 - kr;
-    if (!lds_wait_ge(&sh.ctr[kAdjPub], (uint32_t)((kSub / G) * (kr + 1)), &sh.abort, a.ctl, waited)) return false;
-    const int slot = adj_slot(k);
-    const bool interior = k > 0 && kSub * (k + 1) <= n;  // every column lies in the matrix
+  for (int kr = 0; kr < Ns; ++kr) {
+    const int k = Ns - 1 - kr;
+    if (!lds_wait_ge(&sh.ctr[kAdjPub], (uint32_t)((C::SUB * (kr + 1) + G - 1) / G), &sh.abort, a.ctl, waited)) return false;
+    const int slot = adj_slot<T>(k);
+    const bool interior = C::SUB * k >= kBand - 1 && C::SUB * (k + 1) <= n;  // every column lies in the matrix
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      Vec4<T> x[kAdjNV];
+      Vec4<T> x[BCfg<T>::NV];
 #pragma unroll
-      for (int v = 0; v < kAdjNV; ++v)
-        x[v] = *reinterpret_cast<const Vec4<T>*>(S + adj_row(h, v) * C::PITCH + (slot & C::MASK));
+      for (int v = 0; v < BCfg<T>::NV; ++v)
+        x[v] = *reinterpret_cast<const Vec4<T>*>(S + adj_row<T>(h, v) * C::PITCH + (slot & C::MASK));
 #pragma unroll
-      for (int v = 0; v < kAdjNV; ++v) {
-        const int i = adj_row(h, v), c0 = slot - i, off = (int)((uint32_t)(i * ldo + c0) * (uint32_t)es);
+      for (int v = 0; v < BCfg<T>::NV; ++v) {
+        const int i = adj_row<T>(h, v), c0 = slot - i, off = (int)((uint32_t)(i * ldo + c0) * (uint32_t)es);
         if (interior) {
           adj_put<T>(drs, off, x[v]);
           continue;
@@ -1188,7 +1208,7 @@ __device__ __forceinline__ bool adj_publish(const T* S, const uint32_t* PubR, Ad
     const int s = S0 - G * (u + k) + lane;
     if (band > 0 && !withhold && lane < cols && s < n) {
       const T A = S[s & C::MASK];  // row 0
-      const uint32_t* pr = PubR + 4 * ((s >> 6) & (C::NSUB - 1));
+      const uint32_t* pr = PubR + 4 * ((s >> 6) & (kAdjPubR - 1));
       const int h = (s >> 5) & 1, bit = s & 31;
       const T pn = ((pr[h] >> bit) & 1u) ? A : E::zero();
       const T pnw = ((pr[2 + h] >> bit) & 1u) ? A : E::zero();
@@ -1211,7 +1231,7 @@ template <typename T>
 struct AdjLds {
   Vec4<T> S4[kBand * BCfg<T>::PITCH / 4];
   uint32_t F[kBand * BCfg<T>::FPITCH];
-  uint32_t PubR[4 * BCfg<T>::NSUB];
+  uint32_t PubR[4 * kAdjPubR];
 };
 
 // One band of the instance 'a' describes, all seven roles.  The LDS counters must be zero on
@@ -1222,20 +1242,21 @@ __device__ __forceinline__ void adj_band(AdjLds<T>& L, AdjShared& sh, const AdjA
   T* S = reinterpret_cast<T*>(L.S4);
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));  // uniform branches below
   const int Ks = (int)((a.n + kBand - 1 + kSub - 1) / kSub);
+  const int Ns = Ks * (kSub / BCfg<T>::SUB);
   bool ok;
   if (wave == 0) {
     ok = adj_compute<T, G>(S, L.F, sh, a.ctl, Ks, tr);
   } else if (wave == 2) {
     ok = adj_poll<T, G>(S, sh, a, band, Ks, epoch, tr);
   } else if (wave == 3) {
-    ok = adj_store<T, G>(S, sh, a, band, Ks, tr);
+    ok = adj_store<T, G>(S, sh, a, band, Ns, tr);
   } else if (wave == 4) {
     ok = adj_publish<T, G>(S, L.PubR, sh, a, band, Ks, epoch, tr);
   } else if (wave == 5) {
     ok = adj_load_factors<T, G>(L.F, L.PubR, sh, a, band, Ks);
   } else {
-    ok = a.gD ? adj_load_values<T, G, true>(S, sh, a, band, Ks, wave == 1 ? 0 : 1, tr)
-              : adj_load_values<T, G, false>(S, sh, a, band, Ks, wave == 1 ? 0 : 1, tr);
+    ok = a.gD ? adj_load_values<T, G, true>(S, sh, a, band, Ns, wave == 1 ? 0 : 1, tr)
+              : adj_load_values<T, G, false>(S, sh, a, band, Ns, wave == 1 ? 0 : 1, tr);
   }
   if (!ok) sh.abort = 1u;
 }

@@ -191,9 +191,9 @@ struct DeviceWs {
 // Returns the workspace of device 'dev' with at least 'words' handoff words.
 int ensure_ws(int dev, size_t words, DeviceWs** out);
 int elem_size(int dtype);       // bytes per element, 0 for an invalid dtype
-// Tile of the single-instance sweeps for a shape: the override (wf_set_tile, then WF_TILE),
-// else the nearest-neighbour prediction (wf_tile_predict).  dtype, m and n must be valid.
-int pick_tile(int dtype, int64_t m, int64_t n, bool reverse);
+// Tile of the reverse sweep for a shape: the override (wf_set_tile, then WF_TILE), else the
+// nearest-neighbour prediction (wf_tile_predict), at most 32.  dtype, m and n must be valid.
+int pick_reverse_tile(int dtype, int64_t m, int64_t n);
 int words_per_elem(int dtype);  // 32-bit payload words per element in the handoff words
 
 // Largest leading dimension, in bytes: a band of up to 128 rows is addressed with 32-bit

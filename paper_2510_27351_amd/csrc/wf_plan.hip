@@ -653,7 +653,7 @@ int wf_batch_backward(wf_plan* plan, const void* C, const void* ckpt, int32_t ck
   int32_t big = 0;
   for (int32_t i = 1; i < plan->batch; ++i)
     if (plan->m[i] * plan->n[i] > plan->m[big] * plan->n[big]) big = i;
-  const int tile = pick_tile(plan->dtype, plan->m[big], plan->n[big], true);
+  const int tile = pick_reverse_tile(plan->dtype, plan->m[big], plan->n[big]);
   hipStream_t s = static_cast<hipStream_t>(stream);
   // the recompute's workgroups are small (two waves, half of a CU's LDS): two per CU
   if (launch_select_batch(plan->dtype, b, std::min(b.n_items, 2 * plan->num_cus), s) != hipSuccess)
