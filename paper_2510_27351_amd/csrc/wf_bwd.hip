@@ -95,6 +95,14 @@ struct SCfg {
   static constexpr int RING = sizeof(T) == 4 ? 256 : 128;
   static constexpr int PITCH = RING + 16 / (int)sizeof(T);
   static constexpr int MASK = RING - 1;
+  // Slots the loader stages at a time, four to a ring.  The compute wave reads two groups into
+  // the next 64 slots, so it starts 64 of them when they and the first SUB of the next are in
+  // LDS: with 64-slot steps in float64's ring of 128 no slot could be refilled meanwhile.
+  static constexpr int SUB = RING / 4;
+  static constexpr int HALVES = kSub / SUB;
+  static constexpr int LPR = SUB / 4;        // lanes side by side that hold a row
+  static constexpr int RPV = 64 / LPR;       // rows one vector index spans across the wave
+  static constexpr int NV = kBand / RPV;     // vectors of a lane
 };
 
 // Layout of the selection bit-planes in global memory: for band b, sub-chunk k (slots
@@ -106,6 +114,9 @@ __device__ __forceinline__ int64_t sel_index(int band, int Ks, int k, int lane) 
 
 // =======================================================================================
 // 1. Selection recompute: two waves (compute, loader), one 64-row band per workgroup.
+// What bounds it: about 27 ns a step in float, 38 in double (64 x 16384 in four column pieces 113
+// and 159 us; 122 and 198 before the instruction blocks and the four-piece rings below), the
+// first loads of a piece and its edges (1023 x 1300: float 22, double 26 us; 39 and 36 before).
 // =======================================================================================
 struct alignas(8) SelShared {
   uint32_t loaded;  // sub-chunks of C and of the top row in LDS
@@ -204,10 +215,79 @@ __device__ __forceinline__ void sel_bits_lab(uint32_t& pn, uint32_t& pw, double 
   L = wl ? LX : (nl ? LN : LNW);
 }
 
+// Four steps.  float: one instruction block, so that the bits' instructions stand between the
+// write of a cell and the DPP move that reads it (two wait states) and nothing waits: 8
+// instructions a step, 14 with the labels; left to the compiler every step had two or three
+// s_nop.  The s_nop covers a copy of X or LX placed right before the block.
+#define WF_SEL1(T, NW, X, C)                                             \
+  "v_mov_b32_dpp " T ", " X " wave_shr:1 row_mask:0xf bank_mask:0xf\n\t" \
+  "v_min_f32 %[m], " NW ", " T "\n\t"                                    \
+  "v_min_f32 %[v], %[m], " X "\n\t"                                      \
+  "v_add_f32 " C ", " C ", %[v]\n\t"                                     \
+  "v_cmp_lt_f32 vcc, " T ", " NW "\n\t"                                  \
+  "v_addc_co_u32 %[pn], vcc, %[pn], %[pn], vcc\n\t"                      \
+  "v_cmp_lt_f32 vcc, " X ", %[m]\n\t"                                    \
+  "v_addc_co_u32 %[pw], vcc, %[pw], %[pw], vcc\n\t"
+__device__ __forceinline__ void sel_cells4(float& X, float& NW, uint32_t& pn, uint32_t& pw, const Vec4<float>& c,
+                                           const Vec4<float>& t) {
+  float m, v;
+  float t0 = t.v[0], t1 = t.v[1], t2 = t.v[2], t3 = t.v[3], c0 = c.v[0], c1 = c.v[1], c2 = c.v[2], c3 = c.v[3];
+  asm("s_nop 1\n\t" WF_SEL1("%[t0]", "%[nw]", "%[x]", "%[c0]") WF_SEL1("%[t1]", "%[t0]", "%[c0]", "%[c1]")
+          WF_SEL1("%[t2]", "%[t1]", "%[c1]", "%[c2]") WF_SEL1("%[t3]", "%[t2]", "%[c2]", "%[c3]")
+      : [t0] "+v"(t0), [t1] "+v"(t1), [t2] "+v"(t2), [t3] "+v"(t3), [c0] "+v"(c0), [c1] "+v"(c1), [c2] "+v"(c2),
+        [c3] "+v"(c3), [pn] "+v"(pn), [pw] "+v"(pw), [m] "=&v"(m), [v] "=&v"(v)
+      : [x] "v"(X), [nw] "v"(NW)
+      : "vcc");
+  X = c3;
+  NW = t3;
+}
+#define WF_SELL1(T, L, NW, LNW, X, LX, C, LO, A, AO)                      \
+  "v_mov_b32_dpp " T ", " X " wave_shr:1 row_mask:0xf bank_mask:0xf\n\t"  \
+  "v_mov_b32_dpp " L ", " LX " wave_shr:1 row_mask:0xf bank_mask:0xf\n\t" \
+  "v_min_f32 %[m], " NW ", " T "\n\t"                                     \
+  "v_min_f32 %[v], %[m], " X "\n\t"                                       \
+  "v_add_f32 " C ", " C ", %[v]\n\t"                                      \
+  "v_cmp_lt_f32 vcc, " T ", " NW "\n\t"                                   \
+  "v_cndmask_b32 %[v], " LNW ", " L ", vcc\n\t"                           \
+  "v_addc_co_u32 %[pn], vcc, %[pn], %[pn], vcc\n\t"                       \
+  "v_cmp_lt_f32 vcc, " X ", %[m]\n\t"                                     \
+  "v_cndmask_b32 " LO ", %[v], " LX ", vcc\n\t"                           \
+  "v_addc_co_u32 %[pw], vcc, %[pw], %[pw], vcc\n\t"                       \
+  "v_mov_b32 " AO ", " LO "\n\t"                                          \
+  "v_mov_b32_dpp " AO ", " A " wave_shl:1 row_mask:0xf bank_mask:0xf\n\t"
+__device__ __forceinline__ void sel_cells4_lab(float& X, float& NW, uint32_t& pn, uint32_t& pw, const Vec4<float>& c,
+                                               const Vec4<float>& t, LabState& ls) {
+  float m, v;
+  float t0 = t.v[0], t1 = t.v[1], t2 = t.v[2], t3 = t.v[3], c0 = c.v[0], c1 = c.v[1], c2 = c.v[2], c3 = c.v[3];
+  int32_t n0 = ls.tcol, n1 = n0 + ls.inc, n2 = n1 + ls.inc, n3 = n2 + ls.inc, la, lb, acc2;
+  ls.tcol = n3 + ls.inc;
+  asm("s_nop 1\n\t" WF_SELL1("%[t0]", "%[n0]", "%[nw]", "%[lnw]", "%[x]", "%[lx]", "%[c0]", "%[la]", "%[acc]", "%[ac2]")
+          WF_SELL1("%[t1]", "%[n1]", "%[t0]", "%[n0]", "%[c0]", "%[la]", "%[c1]", "%[lb]", "%[ac2]", "%[acc]")
+              WF_SELL1("%[t2]", "%[n2]", "%[t1]", "%[n1]", "%[c1]", "%[lb]", "%[c2]", "%[la]", "%[acc]", "%[ac2]")
+                  WF_SELL1("%[t3]", "%[n3]", "%[t2]", "%[n2]", "%[c2]", "%[la]", "%[c3]", "%[lb]", "%[ac2]", "%[acc]")
+      : [t0] "+v"(t0), [t1] "+v"(t1), [t2] "+v"(t2), [t3] "+v"(t3), [c0] "+v"(c0), [c1] "+v"(c1), [c2] "+v"(c2),
+        [c3] "+v"(c3), [n0] "+v"(n0), [n1] "+v"(n1), [n2] "+v"(n2), [n3] "+v"(n3), [pn] "+v"(pn), [pw] "+v"(pw),
+        [acc] "+v"(ls.acc), [ac2] "=&v"(acc2), [la] "=&v"(la), [lb] "=&v"(lb), [m] "=&v"(m), [v] "=&v"(v)
+      : [x] "v"(X), [nw] "v"(NW), [lx] "v"(ls.LX), [lnw] "v"(ls.LNW)
+      : "vcc");
+  X = c3;
+  NW = t3;
+  ls.LX = lb;
+  ls.LNW = n3;
+}
+
+// The compute wave's wait for 'need' staged pieces of the 'all' there are.  LDS only: a global
+// load in this wave (the abort flag) would make the compiler wait for the wave's plane stores
+// as well before reusing their registers.  A launch-wide abort reaches it through the wait's
+// own time limit.
+__device__ __forceinline__ bool sel_wait(SelShared& sh, Control* ctl, int need, int all, uint64_t& waited) {
+  return lds_wait_ge<false>(&sh.loaded, (uint32_t)(need < all ? need : all), &sh.abort, ctl, waited);
+}
+
 template <typename T, bool ENTRY, bool LAB = false, bool CAP = false>
-__device__ __forceinline__ void sel_sub(const T* __restrict__ S, const T* __restrict__ Tr, const SelArgs& a, int band,
+__device__ __forceinline__ bool sel_sub(const T* __restrict__ S, const T* __restrict__ Tr, SelShared& sh, const SelArgs& a, int kl, int nk, int band,
                                         int Ks, int k, int rows, int64_t n, T& X, T& NW, T left,
-                                        SelGroup<T> (&P)[2], LabState& ls, const PathLabels& po) {
+                                        SelGroup<T> (&P)[2], LabState& ls, const PathLabels& po, uint64_t& waited) {
   using C = SCfg<T>;
   using E = typename C::E;
   typedef int v4i __attribute__((ext_vector_type(4)));
@@ -225,6 +305,11 @@ __device__ __forceinline__ void sel_sub(const T* __restrict__ S, const T* __rest
   const int cl = CAP ? lane - (kSub * k - ls.cbase) : 0;
 #pragma unroll
   for (int g = 0; g < 16; ++g) {
+    if (C::HALVES == 2 && g == 8) {
+      lds_signal(&sh.steps, (uint32_t)(kSub * kl + C::SUB));
+      if (!sel_wait(sh, a.ctl, 2 * kl + 3, 2 * nk, waited)) return false;
+      __builtin_amdgcn_sched_barrier(0);
+    }
     if (g + 2 < 16)
       sel_load_group<T>(S, Tr, base + 4 * (g + 2), lane, gr[g + 2]);
     else
@@ -232,6 +317,13 @@ __device__ __forceinline__ void sel_sub(const T* __restrict__ S, const T* __rest
     __builtin_amdgcn_sched_barrier(0);
     // per step two bits, first step in the most significant bit: W strictly smaller than
     // both others, N strictly smaller than NW
+    if constexpr (sizeof(T) == 4 && !ENTRY && !CAP) {
+      if constexpr (LAB) {
+        sel_cells4_lab(X, NW, pn, pw, gr[g].c, gr[g].t, ls);
+      } else {
+        sel_cells4(X, NW, pn, pw, gr[g].c, gr[g].t);
+      }
+    } else
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const T N = E::shr1(X, gr[g].t.v[q]);
@@ -296,9 +388,10 @@ __device__ __forceinline__ void sel_sub(const T* __restrict__ S, const T* __rest
       if (col >= 0 && col < n) po.exits[(int64_t)band * n + col] = ls.acc;
     }
   }
+  return true;
 }
 
-// The compute wave.  Sub-chunk k (64 steps, 16 groups) starts once sub-chunks k and k+1 are
+// The compute wave.  Sub-chunk k (64 steps, 16 groups) starts once it and the next SUB slots are
 // in LDS; each group's reads are issued two groups ahead of its steps, the last two groups
 // issuing the next sub-chunk's first two (left in 'P', the same registers every time).
 // The second piece of a split band starts at slot 'split' (column split - r for row r):
@@ -352,10 +445,7 @@ __device__ __forceinline__ void sel_compute(const T* __restrict__ S, const T* __
   const int nk = pc.k1 - pc.k0;
   for (int k = pc.k0; k < pc.k1; ++k) {
     const int kl = k - pc.k0;  // sub-chunks counted from the piece's first
-    // LDS-only wait: a global load in this wave (the abort flag) would make the compiler wait
-    // for the wave's plane stores as well before reusing their registers.  A launch-wide
-    // abort reaches it through the wait's own time limit.
-    if (!lds_wait_ge<false>(&sh.loaded, (uint32_t)(kl + 2 < nk ? kl + 2 : nk), &sh.abort, a.ctl, waited)) {
+    if (!sel_wait(sh, a.ctl, C::HALVES == 1 ? kl + 2 : 2 * kl + 2, C::HALVES * nk, waited)) {
       sh.abort = 1u;
       return;
     }
@@ -364,12 +454,17 @@ __device__ __forceinline__ void sel_compute(const T* __restrict__ S, const T* __
 #pragma unroll
       for (int p = 0; p < 2; ++p) sel_load_group<T>(S, Tr, base + 4 * p, lane, P[p]);
     }
+    bool ok;
     if (pc.second && k == pc.k0)
-      sel_sub<T, true, LAB>(S, Tr, a, band, Ks, k, rows, n, X, NW, left, P, ls, po);
+      ok = sel_sub<T, true, LAB>(S, Tr, sh, a, kl, nk, band, Ks, k, rows, n, X, NW, left, P, ls, po, waited);
     else if (LAB && has_cap && (int64_t)kSub * k + 63 >= ls.cbase && (int64_t)kSub * k <= (int64_t)ls.cbase + 63)
-      sel_sub<T, false, LAB, true>(S, Tr, a, band, Ks, k, rows, n, X, NW, left, P, ls, po);
+      ok = sel_sub<T, false, LAB, true>(S, Tr, sh, a, kl, nk, band, Ks, k, rows, n, X, NW, left, P, ls, po, waited);
     else
-      sel_sub<T, false, LAB>(S, Tr, a, band, Ks, k, rows, n, X, NW, left, P, ls, po);
+      ok = sel_sub<T, false, LAB>(S, Tr, sh, a, kl, nk, band, Ks, k, rows, n, X, NW, left, P, ls, po, waited);
+    if (!ok) {
+      sh.abort = 1u;
+      return;
+    }
     lds_signal(&sh.steps, (uint32_t)(kSub * (kl + 1)));
   }
   if constexpr (LAB) {
@@ -377,26 +472,27 @@ __device__ __forceinline__ void sel_compute(const T* __restrict__ S, const T* __
   }
 }
 
-// Sub-chunks of C the selection loader keeps in flight in registers (two waves per
+// Pieces of C (SUB slots) the selection loader keeps in flight in registers (two waves per
 // workgroup leave room for them).
 template <typename T>
 struct SelPF {
-  static constexpr int PF = sizeof(T) == 4 ? 3 : 1;
+  static constexpr int PF = 3;
 };
 
-// Issues the loads of sub-chunk k of C (16 lanes x 4 rows per vector, rows 0..63) and of
-// the row above the band for slots [64k, 64k+64).
+// Issues the loads of piece k of C (LPR lanes x RPV rows per vector, rows 0..63) and of the row
+// above the band for its slots [k SUB, (k+1) SUB).
 template <typename T>
-__device__ __forceinline__ void sel_load_sub(Vec4<T> (&x)[16], T& tv, __amdgpu_buffer_rsrc_t rsrc, int64_t ldc,
+__device__ __forceinline__ void sel_load_sub(Vec4<T> (&x)[SCfg<T>::NV], T& tv, __amdgpu_buffer_rsrc_t rsrc, int64_t ldc,
                                              const T* top, int64_t n, int k) {
   // Every call issues the same loads (no branch around any of them), so the compiler can
-  // count the loads in flight and wait for the oldest sub-chunk only.
+  // count the loads in flight and wait for the oldest piece only.
+  using C = SCfg<T>;
   const int lane = threadIdx.x & 63;
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    const int i = 4 * v + (lane >> 4);
-    const int64_t c0 = (int64_t)kSub * k + 4 * (lane & 15) - i;
+  for (int v = 0; v < C::NV; ++v) {
+    const int i = C::RPV * v + lane / C::LPR;
+    const int64_t c0 = (int64_t)C::SUB * k + 4 * (lane & (C::LPR - 1)) - i;
     const uint32_t off = (uint32_t)(i * ldc + c0) * (uint32_t)sizeof(T);
     if constexpr (sizeof(T) == 4) {
       x[v] = __builtin_bit_cast(Vec4<T>, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)off, 0, 0));
@@ -407,32 +503,41 @@ __device__ __forceinline__ void sel_load_sub(Vec4<T> (&x)[16], T& tv, __amdgpu_b
       x[v].v[0] = lo.y[0]; x[v].v[1] = lo.y[1]; x[v].v[2] = hi.y[0]; x[v].v[3] = hi.y[1];
     }
   }
-  const int64_t j = (int64_t)kSub * k + lane;
+  const int64_t j = (int64_t)C::SUB * k + (lane & (C::SUB - 1));
   tv = top[j < n ? j : n - 1];  // replaced by +inf in sel_store_sub where not a real column
   __builtin_amdgcn_sched_barrier(0);
 }
 
 template <typename T>
-__device__ __forceinline__ void sel_store_sub(T* S, T* Tr, const Vec4<T> (&x)[16], T tv, bool has_top, int k,
+__device__ __forceinline__ void sel_store_sub(T* S, T* Tr, const Vec4<T> (&x)[SCfg<T>::NV], T tv, bool has_top, int k,
                                               int rows, int64_t n) {
   using C = SCfg<T>;
   using E = typename C::E;
   const int lane = threadIdx.x & 63;
-  const bool interior = rows == kBand && k > 0 && (int64_t)kSub * k + kSub <= n;
+  // every column of the piece lies in the matrix; rows past it, which no other row reads and
+  // whose bits are cleared, hold the buffer's zeros
+  const bool interior = C::SUB * k >= kBand - 1 && (int64_t)C::SUB * (k + 1) <= n;
+  // One branch around all of a piece's vectors: with one around each, and 64-bit compares per
+  // element where it was taken, the first and last pieces of a band cost 8 us each.
+  if (interior) {
 #pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    const int i = 4 * v + (lane >> 4);
-    const int64_t c0 = (int64_t)kSub * k + 4 * (lane & 15) - i;
-    Vec4<T> y = x[v];
-    if (!interior) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (i >= rows || c0 + e < 0 || c0 + e >= n) y.v[e] = E::inf();
+    for (int v = 0; v < C::NV; ++v) {
+      const int i = C::RPV * v + lane / C::LPR, slot = C::SUB * k + 4 * (lane & (C::LPR - 1));
+      *reinterpret_cast<Vec4<T>*>(S + i * C::PITCH + (slot & C::MASK)) = x[v];
     }
-    *reinterpret_cast<Vec4<T>*>(S + i * C::PITCH + ((kSub * k + 4 * (lane & 15)) & C::MASK)) = y;
+  } else {
+#pragma unroll
+    for (int v = 0; v < C::NV; ++v) {
+      const int i = C::RPV * v + lane / C::LPR, slot = C::SUB * k + 4 * (lane & (C::LPR - 1));
+      const int64_t c0 = (int64_t)slot - i;
+      Vec4<T> y = x[v];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) y.v[e] = i >= rows || c0 + e < 0 || c0 + e >= n ? E::inf() : y.v[e];
+      *reinterpret_cast<Vec4<T>*>(S + i * C::PITCH + (slot & C::MASK)) = y;
+    }
   }
-  const int64_t j = (int64_t)kSub * k + lane;
-  Tr[(kSub * k + lane) & C::MASK] = (has_top && j < n) ? tv : E::inf();
+  const int j = C::SUB * k + (lane & (C::SUB - 1));
+  Tr[j & C::MASK] = (has_top && j < n) ? tv : E::inf();
 }
 
 // Zeros over the gradient's columns [64k, 64k + 64) of the band's rows (path adjoint with a
@@ -481,29 +586,30 @@ __device__ __forceinline__ void sel_loader(T* S, T* Tr, SelShared& sh, const Sel
   const bool has_top = band > 0;
   const T* top = has_top ? static_cast<const T*>(a.top) + (int64_t)(band - 1) * a.ld_top : static_cast<const T*>(a.C);
   uint64_t waited = 0;
-  Vec4<T> buf[PF][16];
+  Vec4<T> buf[PF][C::NV];
   T tv[PF];
-  const int k0 = pc.k0, k1 = pc.k1;
-  // The loads of sub-chunk k+PF are issued right after sub-chunk k is stored, unconditionally
-  // (clamped to the piece's last sub-chunk), so that PF sub-chunks are in flight at every wait.
+  const int k0 = C::HALVES * pc.k0, k1 = C::HALVES * pc.k1;  // pieces of SUB slots
+  // The loads of piece k+PF are issued right after piece k is stored, unconditionally (clamped to
+  // the last one), so that PF of them are in flight at every wait.
 #pragma unroll
   for (int p = 0; p < PF; ++p) sel_load_sub<T>(buf[p], tv[p], rsrc, ldc, top, n, k0 + p < k1 ? k0 + p : k1 - 1);
   auto store = [&](int p, int k) -> bool {
-    // sub-chunk k reuses the ring slots of sub-chunk k - RING/64 (counted from the piece's first)
-    const int older = k - k0 - C::RING / kSub;
+    // piece k reuses the ring slots of the fourth before it (counted from the first)
+    const int older = k - k0 - C::RING / C::SUB;
     if (older >= 0 &&
-        !lds_wait_ge<false>(&sh.steps, (uint32_t)(kSub * (older + 1)), &sh.abort, a.ctl, waited)) {
+        !lds_wait_ge<false>(&sh.steps, (uint32_t)(C::SUB * (older + 1)), &sh.abort, a.ctl, waited)) {
       sh.abort = 1u;
       return false;
     }
     sel_store_sub<T>(S, Tr, buf[p], tv[p], has_top, k, rows, n);
     lds_publish(&sh.loaded, (uint32_t)(k - k0 + 1));
-    // a piece's first sub-chunk is the previous piece's last: zeroed there
-    if (po.gC != nullptr && !(pc.second && k == k0)) sel_zero_sub<T>(po, band, rows, n, k);
+    // zeros by 64 columns; a column piece's first 64 are the previous one's last: zeroed there
+    if (po.gC != nullptr && k % C::HALVES == 0 && !(pc.second && k == k0))
+      sel_zero_sub<T>(po, band, rows, n, k / C::HALVES);
     return true;
   };
-  // Whole groups of PF sub-chunks carry no condition around the stores, which keeps the
-  // compiler's wait counts at PF - 1 sub-chunks in flight; the last partial group follows.
+  // Whole groups of PF pieces carry no condition around the stores, which keeps the compiler's
+  // wait counts at PF - 1 of them in flight; the last partial group follows.
   int kk = k0;
   for (; kk + PF <= k1; kk += PF) {
 #pragma unroll
@@ -907,29 +1013,28 @@ __device__ __forceinline__ bool adj_load_values(T* S, AdjShared& sh, const AdjAr
       const int kr = kr0 + p, k = Ns - 1 - kr;  // the kr-th sub-chunk processed
       if (kr < Ns) {
         if (!adj_wait_free<T, G>(sh, a.ctl, kr, waited)) return false;
-        // every column of the sub-chunk lies in the matrix (rows past it: see the resource)
-        const bool interior = C::SUB * k >= kBand - 1 && C::SUB * (k + 1) <= n;
+        // plain: every column of the sub-chunk lies in the matrix (rows past it: see the
+        // resource) and the score's cell is not in it; one branch around all the vectors
         const bool has_last = last_row >= 0 && last_slot / C::SUB == k;
+        const bool plain = HAS_G && C::SUB * k >= kBand - 1 && C::SUB * (k + 1) <= n && !has_last;
+        if (plain) {
 #pragma unroll
-        for (int v = 0; v < BCfg<T>::NV; ++v) {
-          const int i = adj_row<T>(h, v), slot = adj_slot<T>(k);
-          Vec4<T> x;
+          for (int v = 0; v < C::NV; ++v)
+            *reinterpret_cast<Vec4<T>*>(S + adj_row<T>(h, v) * C::PITCH + (adj_slot<T>(k) & C::MASK)) = buf[p][v];
+        } else {
 #pragma unroll
-          for (int e = 0; e < 4; ++e) x.v[e] = E::zero();
-          if constexpr (HAS_G) {
-            x = buf[p][v];
-            if (!interior) {
+          for (int v = 0; v < C::NV; ++v) {
+            const int i = adj_row<T>(h, v), slot = adj_slot<T>(k);
+            Vec4<T> x;
 #pragma unroll
-              for (int e = 0; e < 4; ++e)
-                if (i >= rows || slot - i + e < 0 || slot - i + e >= n) x.v[e] = E::zero();
+            for (int e = 0; e < 4; ++e) {
+              x.v[e] = E::zero();
+              if constexpr (HAS_G) x.v[e] = i >= rows || slot - i + e < 0 || slot - i + e >= n ? E::zero() : buf[p][v].v[e];
+              const T y = E::add(x.v[e], gs);
+              x.v[e] = has_last && i == last_row && last_slot == slot + e ? y : x.v[e];
             }
+            *reinterpret_cast<Vec4<T>*>(S + i * C::PITCH + (slot & C::MASK)) = x;
           }
-          if (has_last && i == last_row) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-              if (last_slot == slot + e) x.v[e] = E::add(x.v[e], gs);
-          }
-          *reinterpret_cast<Vec4<T>*>(S + i * C::PITCH + (slot & C::MASK)) = x;
         }
         lds_publish(&sh.ctr[h == 0 ? kAdjVal : kAdjVal1], kr + 1 < Ns ? (uint32_t)(kr + 1) : kAdjAll);
         if constexpr (HAS_G) adj_load_g<T>(buf[p], rsrc, ldg, h, k - PF >= 0 ? k - PF : 0);
