@@ -529,10 +529,9 @@ __device__ __forceinline__ void sel_store_sub(T* S, T* Tr, const Vec4<T> (&x)[SC
 #pragma unroll
     for (int v = 0; v < C::NV; ++v) {
       const int i = C::RPV * v + lane / C::LPR, slot = C::SUB * k + 4 * (lane & (C::LPR - 1));
-      const int64_t c0 = (int64_t)slot - i;
-      Vec4<T> y = x[v];
+      Vec4<T> y;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) y.v[e] = i >= rows || c0 + e < 0 || c0 + e >= n ? E::inf() : y.v[e];
+      for (int e = 0; e < 4; ++e) y.v[e] = i < rows && (uint32_t)(slot - i + e) < (uint32_t)n ? x[v].v[e] : E::inf();
       *reinterpret_cast<Vec4<T>*>(S + i * C::PITCH + (slot & C::MASK)) = y;
     }
   }
@@ -1029,7 +1028,7 @@ __device__ __forceinline__ bool adj_load_values(T* S, AdjShared& sh, const AdjAr
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
               x.v[e] = E::zero();
-              if constexpr (HAS_G) x.v[e] = i >= rows || slot - i + e < 0 || slot - i + e >= n ? E::zero() : buf[p][v].v[e];
+              if constexpr (HAS_G) x.v[e] = i < rows && (uint32_t)(slot - i + e) < (uint32_t)n ? buf[p][v].v[e] : E::zero();
               const T y = E::add(x.v[e], gs);
               x.v[e] = has_last && i == last_row && last_slot == slot + e ? y : x.v[e];
             }
