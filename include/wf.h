@@ -301,8 +301,9 @@ int wf_fault_inject(int32_t mode);
  * min-plus table).  D[i][j] is -gamma log of the sum over all monotone paths from (0,0) to
  * (i,j) of exp(-path cost/gamma), so the table is smooth in C and its gradient is exact
  * (no selections, no ties).  C must be finite.  WF_F32 or WF_F64; the exponentials and
- * logarithms are the device's base-2 functions, so results agree with a float64 evaluation
- * to within rounding, not bit for bit.
+ * logarithms are the device's base-2 functions in float32 and polynomials of float64 accuracy
+ * in the float64 forward, so results agree with a float64 evaluation to within rounding, not
+ * bit for bit.
  *
  * wf_soft_forward writes the full table D (m x n, ldd >= n; required, the adjoint reads it)
  * and score = D[m-1][n-1].
@@ -313,7 +314,8 @@ int wf_fault_inject(int32_t mode);
  * with w(s) = exp((D(s) - C(s) - D[i][j]) / gamma) the derivative of successor s's soft
  * minimum with respect to D[i][j].  g_score (one element) and g_D may be NULL (= 0).
  * Both are persistent band pipelines on the device workspace like wf_forward (same stream
- * ordering rules, bounded waits reported by wf_last_async_error).  gamma must be positive
+ * ordering rules, bounded waits reported by wf_last_async_error).  g_C may overlap C or D,
+ * which then pass through a copy in the workspace, and may be g_D.  gamma must be positive
  * and finite (WF_E_ARG otherwise); WF_I32 returns WF_E_UNSUPPORTED.
  */
 int wf_soft_forward(int dtype, int64_t m, int64_t n, double gamma, const void* C, int64_t ldc,

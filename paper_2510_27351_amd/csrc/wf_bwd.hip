@@ -32,7 +32,7 @@
 // skew plus the handoff (about 1.1 us).  3000 x 2500 float32 with gD: 396 us with one value
 // loader one sub-chunk ahead, address arithmetic and three counter tests per unit in the
 // compute wave and a per-element path for a last band of fewer rows (which alone took 162 us
-// against 75), 236 us so; float64 549 and 420.
+// against 75), 235 us so; float64 549 and 352.
 #include <algorithm>
 
 #include "wf_common.h"
@@ -119,7 +119,7 @@ __device__ __forceinline__ int64_t sel_index(int band, int Ks, int k, int lane) 
 // first loads of a piece and its edges (1023 x 1300: float 22, double 26 us; 39 and 36 before).
 // =======================================================================================
 struct alignas(8) SelShared {
-  uint32_t loaded;  // sub-chunks of C and of the top row in LDS
+  uint32_t loaded;  // pieces (SCfg::SUB slots) of C and of the top row in LDS
   uint32_t steps;   // steps done by the compute wave
   uint32_t item;
   uint32_t abort;
