@@ -285,14 +285,16 @@ __device__ __forceinline__ double max_raw(double a, double b) {
 
 // 2^x, x <= 0: x = n + f with |f| <= 1/2 by adding and taking away 1.5 2^52, whose sum's low
 // word is n; 2^f = 1 + f p(f), p the degree-10 polynomial through (2^f - 1) / f at Chebyshev
-// nodes (relative error of 2^f 9e-18).  Below 2^-64, and for x = -inf or NaN (inf - inf), the
-// result is 2^-64, which changes no sum with 1 that it enters.
+// nodes (relative error of 2^f 9e-18).  The scaling rounds a result below 2^-1022 as it has to
+// and makes one below 2^-1075 zero, and so for x = -inf or NaN (inf - inf), which the clamp turns
+// into -1100: a neighbour that weighs nothing adds nothing.  (log2(1 + a) is taken from a itself,
+// so a floor at 2^-64 would show: equal rows of zeros came out at -1.1e-16 gamma in 1000 columns.)
 __device__ __forceinline__ double soft_exp2(double x) {
   constexpr double kP[11] = {
       0x1.62e42fefa39efp-1, 0x1.ebfbdff82c598p-3, 0x1.c6b08d704a0c2p-5, 0x1.3b2ab6fba1ddap-7,
       0x1.5d87fe78a5276p-10, 0x1.430913096fd9fp-13, 0x1.ffcbfc670dcd4p-17, 0x1.62bfd47773353p-20,
       0x1.b524fae627834p-24, 0x1.e6063f7217bc6p-28, 0x1.e9d3fe3952179p-32};
-  x = max_raw(x, -64.0);
+  x = max_raw(x, -1100.0);
   const double t = x + 0x1.8p52;
   const double f = x - (t - 0x1.8p52);
   double p = kP[10];
