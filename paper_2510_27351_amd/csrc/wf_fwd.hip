@@ -275,8 +275,9 @@ struct Cell4<double> {
 // compare and a select, and waited a state after most inline or transcendental results.  A
 // transcendental result may be read two instructions later at the earliest: the second
 // exponential, an add and the top row's shift stand between.  Three inputs of +inf give
-// inf - inf = NaN, which the final minimum with +inf turns into +inf, and leaves every other
-// value as it is.
+// inf - inf = NaN, which the minimum with their own minimum turns into +inf; every other
+// soft minimum is not above it and stays as it is.  C is added after that: a NaN there (the
+// library asks for finite inputs) shows in its cell.
 __device__ __forceinline__ double max_raw(double a, double b) {
   double r;
   asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
@@ -363,19 +364,17 @@ __device__ __forceinline__ void soft_cells4(ComputeState<double, 1>& st, const V
   "v_log_f32 %[md], %[md]\n\t"                                            \
   "v_mov_b32_dpp %[top], %[top] wave_shl:1 row_mask:0xf bank_mask:0xf\n\t" \
   "v_sub_f32 %[md], %[mn], %[md]\n\t"                                     \
-  "v_add_f32 " D ", " C ", %[md]\n\t"                                     \
-  "v_min_f32 " D ", %[inf], " D "\n\t"
+  "v_min_f32 %[md], %[mn], %[md]\n\t"                                     \
+  "v_add_f32 " D ", " C ", %[md]\n\t"
 __device__ __forceinline__ void soft_cells4(ComputeState<float, 1>& st, const Vec4<float> (&c)[1], Vec4<float> (&d)[1]) {
   float t, mn, md, mx;
-  const float inf = Elem<float>::inf();
   asm("s_nop 0\n\t" WF_SOFT1("%[t]", "%[nw]", "%[x]", "%[d0]", "%[c0]") "s_nop 0\n\t"
           WF_SOFT1("%[nw]", "%[t]", "%[d0]", "%[d1]", "%[c1]") "s_nop 0\n\t"
               WF_SOFT1("%[t]", "%[nw]", "%[d1]", "%[d2]", "%[c2]") "s_nop 0\n\t"
                   WF_SOFT1("%[nw]", "%[t]", "%[d2]", "%[d3]", "%[c3]")
       : [top] "+v"(st.top), [nw] "+v"(st.NW), [t] "=&v"(t), [mn] "=&v"(mn), [md] "=&v"(md), [mx] "=&v"(mx),
         [d0] "=&v"(d[0].v[0]), [d1] "=&v"(d[0].v[1]), [d2] "=&v"(d[0].v[2]), [d3] "=&v"(d[0].v[3])
-      : [x] "v"(st.X[0]), [c0] "v"(c[0].v[0]), [c1] "v"(c[0].v[1]), [c2] "v"(c[0].v[2]), [c3] "v"(c[0].v[3]),
-        [inf] "v"(inf));
+      : [x] "v"(st.X[0]), [c0] "v"(c[0].v[0]), [c1] "v"(c[0].v[1]), [c2] "v"(c[0].v[2]), [c3] "v"(c[0].v[3]));
   st.X[0] = d[0].v[3];
 }
 

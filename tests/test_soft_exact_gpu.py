@@ -13,6 +13,7 @@ import pytest
 import torch
 
 import paper_2510_27351_amd as wf
+from paper_2510_27351_amd import inputs
 
 pytestmark = pytest.mark.gpu
 
@@ -54,3 +55,17 @@ def test_corridor_f64(gap, gamma, oracle_mod):
     bar = 2 * (steps + 4) * U * np.abs(ref) + steps * 2 * gamma * np.exp(1 - gap)
     assert np.all(np.abs(got - ref) <= bar), float(np.max(np.abs(got - ref) / ref))
     assert float(score) == D[-1, -1]
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("cell", [(0, 0), (0, 70), (64, 0), (37, 130), (99, 149)])
+def test_nan_in_the_input_shows_at_its_cell(cell, dtype):
+    """The library asks for finite inputs; a NaN among them is not hidden at its own cell, and
+    cells that no path through it reaches are as without it."""
+    C = inputs.uniform(100, 150, seed=5, dtype=dtype).to(DEV)
+    ref, _ = wf.soft_forward(C, 0.5)
+    C[cell] = float("nan")
+    D, _ = wf.soft_forward(C, 0.5)
+    i, j = cell
+    assert torch.isnan(D[i, j])
+    assert torch.equal(D[:i], ref[:i]) and torch.equal(D[:, :j], ref[:, :j])
