@@ -139,9 +139,14 @@ __device__ __forceinline__ double sel_min(double a, double b) {
 }
 
 // bits = 2 bits + (x < y): for 4-byte elements one compare into VCC and one add with VCC as
-// the carry in (the compiler's form takes a select, an or and a shift besides).
+// the carry in (the compiler's form takes a select, an or and a shift besides).  On gfx950 a
+// VALU instruction may read an SGPR or VCC that the VALU wrote two wait states later at the
+// earliest; the compiler does not look into these blocks, so they keep to it themselves.
 __device__ __forceinline__ void sel_bit(uint32_t& bits, float x, float y) {
-  asm("v_cmp_lt_f32 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(bits) : "v"(x), "v"(y) : "vcc");
+  asm("v_cmp_lt_f32 vcc, %1, %2\n\ts_nop 1\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc"
+      : "+v"(bits)
+      : "v"(x), "v"(y)
+      : "vcc");
 }
 __device__ __forceinline__ void sel_bit(uint32_t& bits, double x, double y) { bits = bits + bits + (uint32_t)(x < y); }
 
@@ -197,14 +202,17 @@ __device__ __forceinline__ int32_t sym_label(int piece, int r) { return -2 - ((p
 __device__ __forceinline__ void sel_bits_lab(uint32_t& pn, uint32_t& pw, float N, float NW, float X, float m,
                                              int32_t LN, int32_t LNW, int32_t LX, int32_t& L) {
   int32_t t;
-  asm("v_cmp_lt_f32 vcc, %4, %5\n\t"
-      "v_cndmask_b32 %0, %8, %7, vcc\n\t"
-      "v_addc_co_u32 %2, vcc, %2, %2, vcc\n\t"
-      "v_cmp_lt_f32 vcc, %6, %10\n\t"
-      "v_cndmask_b32 %1, %0, %9, vcc\n\t"
-      "v_addc_co_u32 %3, vcc, %3, %3, vcc"
-      : "=&v"(t), "=&v"(L), "+v"(pn), "+v"(pw)
-      : "v"(N), "v"(NW), "v"(X), "v"(LN), "v"(LNW), "v"(LX), "v"(m)
+  uint64_t w;
+  // (the two carries also stand between the write of L and a DPP move that reads it)
+  asm("v_cmp_lt_f32 vcc, %[n], %[nw]\n\t"
+      "v_cmp_lt_f32 %[w], %[x], %[m]\n\t"
+      "s_nop 0\n\t"
+      "v_cndmask_b32 %[t], %[lnw], %[ln], vcc\n\t"
+      "v_cndmask_b32 %[l], %[t], %[lx], %[w]\n\t"
+      "v_addc_co_u32 %[pn], vcc, %[pn], %[pn], vcc\n\t"
+      "v_addc_co_u32 %[pw], vcc, %[pw], %[pw], %[w]"
+      : [t] "=&v"(t), [l] "=&v"(L), [pn] "+v"(pn), [pw] "+v"(pw), [w] "=&s"(w)
+      : [n] "v"(N), [nw] "v"(NW), [x] "v"(X), [m] "v"(m), [ln] "v"(LN), [lnw] "v"(LNW), [lx] "v"(LX)
       : "vcc");
 }
 __device__ __forceinline__ void sel_bits_lab(uint32_t& pn, uint32_t& pw, double N, double NW, double X, double m,
@@ -216,26 +224,29 @@ __device__ __forceinline__ void sel_bits_lab(uint32_t& pn, uint32_t& pw, double 
 }
 
 // Four steps.  float: one instruction block, so that the bits' instructions stand between the
-// write of a cell and the DPP move that reads it (two wait states) and nothing waits: 8
-// instructions a step, 14 with the labels; left to the compiler every step had two or three
-// s_nop.  The s_nop covers a copy of X or LX placed right before the block.
+// write of a cell and the DPP move that reads it (two wait states) and the cell's between a
+// compare and the carry or select that reads it (two as well: the N bit goes through VCC, the W
+// bit through an SGPR pair): 8 instructions a step, 13 with the labels, and nothing waits; left
+// to the compiler every step had two or three s_nop.  The s_nop covers a copy of X or LX placed
+// right before the block.
 #define WF_SEL1(T, NW, X, C)                                             \
   "v_mov_b32_dpp " T ", " X " wave_shr:1 row_mask:0xf bank_mask:0xf\n\t" \
+  "v_cmp_lt_f32 vcc, " T ", " NW "\n\t"                                  \
   "v_min_f32 %[m], " NW ", " T "\n\t"                                    \
+  "v_cmp_lt_f32 %[w], " X ", %[m]\n\t"                                   \
   "v_min_f32 %[v], %[m], " X "\n\t"                                      \
   "v_add_f32 " C ", " C ", %[v]\n\t"                                     \
-  "v_cmp_lt_f32 vcc, " T ", " NW "\n\t"                                  \
   "v_addc_co_u32 %[pn], vcc, %[pn], %[pn], vcc\n\t"                      \
-  "v_cmp_lt_f32 vcc, " X ", %[m]\n\t"                                    \
-  "v_addc_co_u32 %[pw], vcc, %[pw], %[pw], vcc\n\t"
+  "v_addc_co_u32 %[pw], vcc, %[pw], %[pw], %[w]\n\t"
 __device__ __forceinline__ void sel_cells4(float& X, float& NW, uint32_t& pn, uint32_t& pw, const Vec4<float>& c,
                                            const Vec4<float>& t) {
   float m, v;
+  uint64_t w;
   float t0 = t.v[0], t1 = t.v[1], t2 = t.v[2], t3 = t.v[3], c0 = c.v[0], c1 = c.v[1], c2 = c.v[2], c3 = c.v[3];
   asm("s_nop 1\n\t" WF_SEL1("%[t0]", "%[nw]", "%[x]", "%[c0]") WF_SEL1("%[t1]", "%[t0]", "%[c0]", "%[c1]")
           WF_SEL1("%[t2]", "%[t1]", "%[c1]", "%[c2]") WF_SEL1("%[t3]", "%[t2]", "%[c2]", "%[c3]")
       : [t0] "+v"(t0), [t1] "+v"(t1), [t2] "+v"(t2), [t3] "+v"(t3), [c0] "+v"(c0), [c1] "+v"(c1), [c2] "+v"(c2),
-        [c3] "+v"(c3), [pn] "+v"(pn), [pw] "+v"(pw), [m] "=&v"(m), [v] "=&v"(v)
+        [c3] "+v"(c3), [pn] "+v"(pn), [pw] "+v"(pw), [m] "=&v"(m), [v] "=&v"(v), [w] "=&s"(w)
       : [x] "v"(X), [nw] "v"(NW)
       : "vcc");
   X = c3;
@@ -244,20 +255,21 @@ __device__ __forceinline__ void sel_cells4(float& X, float& NW, uint32_t& pn, ui
 #define WF_SELL1(T, L, NW, LNW, X, LX, C, LO, A, AO)                      \
   "v_mov_b32_dpp " T ", " X " wave_shr:1 row_mask:0xf bank_mask:0xf\n\t"  \
   "v_mov_b32_dpp " L ", " LX " wave_shr:1 row_mask:0xf bank_mask:0xf\n\t" \
+  "v_cmp_lt_f32 vcc, " T ", " NW "\n\t"                                   \
   "v_min_f32 %[m], " NW ", " T "\n\t"                                     \
+  "v_cmp_lt_f32 %[w], " X ", %[m]\n\t"                                    \
   "v_min_f32 %[v], %[m], " X "\n\t"                                       \
   "v_add_f32 " C ", " C ", %[v]\n\t"                                      \
-  "v_cmp_lt_f32 vcc, " T ", " NW "\n\t"                                   \
   "v_cndmask_b32 %[v], " LNW ", " L ", vcc\n\t"                           \
+  "v_cndmask_b32 " LO ", %[v], " LX ", %[w]\n\t"                          \
   "v_addc_co_u32 %[pn], vcc, %[pn], %[pn], vcc\n\t"                       \
-  "v_cmp_lt_f32 vcc, " X ", %[m]\n\t"                                     \
-  "v_cndmask_b32 " LO ", %[v], " LX ", vcc\n\t"                           \
-  "v_addc_co_u32 %[pw], vcc, %[pw], %[pw], vcc\n\t"                       \
+  "v_addc_co_u32 %[pw], vcc, %[pw], %[pw], %[w]\n\t"                      \
   "v_mov_b32 " AO ", " LO "\n\t"                                          \
   "v_mov_b32_dpp " AO ", " A " wave_shl:1 row_mask:0xf bank_mask:0xf\n\t"
 __device__ __forceinline__ void sel_cells4_lab(float& X, float& NW, uint32_t& pn, uint32_t& pw, const Vec4<float>& c,
                                                const Vec4<float>& t, LabState& ls) {
   float m, v;
+  uint64_t w;
   float t0 = t.v[0], t1 = t.v[1], t2 = t.v[2], t3 = t.v[3], c0 = c.v[0], c1 = c.v[1], c2 = c.v[2], c3 = c.v[3];
   int32_t n0 = ls.tcol, n1 = n0 + ls.inc, n2 = n1 + ls.inc, n3 = n2 + ls.inc, la, lb, acc2;
   ls.tcol = n3 + ls.inc;
@@ -267,7 +279,7 @@ __device__ __forceinline__ void sel_cells4_lab(float& X, float& NW, uint32_t& pn
                   WF_SELL1("%[t3]", "%[n3]", "%[t2]", "%[n2]", "%[c2]", "%[la]", "%[c3]", "%[lb]", "%[ac2]", "%[acc]")
       : [t0] "+v"(t0), [t1] "+v"(t1), [t2] "+v"(t2), [t3] "+v"(t3), [c0] "+v"(c0), [c1] "+v"(c1), [c2] "+v"(c2),
         [c3] "+v"(c3), [n0] "+v"(n0), [n1] "+v"(n1), [n2] "+v"(n2), [n3] "+v"(n3), [pn] "+v"(pn), [pw] "+v"(pw),
-        [acc] "+v"(ls.acc), [ac2] "=&v"(acc2), [la] "=&v"(la), [lb] "=&v"(lb), [m] "=&v"(m), [v] "=&v"(v)
+        [acc] "+v"(ls.acc), [ac2] "=&v"(acc2), [la] "=&v"(la), [lb] "=&v"(lb), [m] "=&v"(m), [v] "=&v"(v), [w] "=&s"(w)
       : [x] "v"(X), [nw] "v"(NW), [lx] "v"(ls.LX), [lnw] "v"(ls.LNW)
       : "vcc");
   X = c3;
