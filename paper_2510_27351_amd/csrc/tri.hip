@@ -563,12 +563,13 @@ __global__ __launch_bounds__(THREADS) void tail_kernel(TailArgs g) {
     }
     __syncthreads();
   }
-  // the deepest system; its solution replaces its right-hand side
-  if (t < 2) {
+  // the deepest system; its solution replaces its sub-diagonal
+  {
     const int n = g.n[g.L];
     T *A = arr(g.L, 0), *B = arr(g.L, 1), *C = arr(g.L, 2), *D = arr(g.L, 3);
     T prev = T(0), xnext = T(0);
-    thomas_eliminate<T>(A, B, C, D, 0, n, n, t, prev);
+    if (t < 2) thomas_eliminate<T>(A, B, C, D, 0, n, n, t, prev);
+    __syncthreads();  // lane 0 substitutes from lane 1's dp
     if (t == 0) thomas_substitute<T>(C, D, A, 0, n, n, xnext);
   }
   __syncthreads();
