@@ -795,8 +795,8 @@ __device__ __forceinline__ void unscale(Vec4<T> (&v)[NV], T gl) {
 
 // One storer per 64 LDS rows, like the loaders.
 template <typename T, int G, int R, bool SOFT>
-__device__ __forceinline__ void store_sub(const T* S, __amdgpu_buffer_rsrc_t drs, int64_t ldd, int64_t n, int h,
-                                          int s, T gl) {
+__device__ __forceinline__ void store_sub(const T* S, __amdgpu_buffer_rsrc_t drs, int64_t ldd, int rows, int64_t n,
+                                          int h, int s, T gl) {
   using C = FwdCfg<T, G, R>;
   typedef int v4i __attribute__((ext_vector_type(4)));
   auto put = [&](int off, const Vec4<T>& x) {
@@ -823,11 +823,14 @@ __device__ __forceinline__ void store_sub(const T* S, __amdgpu_buffer_rsrc_t drs
     }
     return;
   }
-  // Edge sub-chunk (first, last, or a partial band): per vector one 16-byte store if its four
-  // cells lie inside the matrix, else a store per cell that does.
+  // Edge sub-chunk (the first and the last): per vector one 16-byte store if its four cells lie
+  // inside the matrix, else a store per cell that does.  Rows past the matrix, whose stores the
+  // buffer's range check would drop, are passed over (1 x 64 in float64: 13.4 us with their
+  // stores, 10.8 without).
 #pragma unroll
   for (int k = 0; k < C::NV; ++k) {
     const SubVec<T, G, R> q(h, k, s);
+    if (q.row() >= rows) continue;
     const int64_t c0 = q.c0();
     const int off = (int)(((int64_t)q.row() * ldd + c0) * (int64_t)sizeof(T));
     if (c0 >= 0 && c0 + 4 <= n) {
@@ -874,7 +877,7 @@ __device__ __forceinline__ void store_band(const T* S, Shared& sh, const FwdArgs
       sh.abort = 1u;
       return;
     }
-    if (a.D) store_sub<T, G, R, SOFT>(S, drs, ldd, n, h, s, gl);
+    if (a.D) store_sub<T, G, R, SOFT>(S, drs, ldd, rows, n, h, s, gl);
     if (ck_cols) {
       const int l = kBand * h + lane, i = band_row<R>(l);
       if (i < rows) {
