@@ -32,7 +32,7 @@
 //
 // 3 + 2R waves per workgroup:
 //   wave 0           compute   per 4 steps and row: one 16-byte LDS read of C, 4 cells, one
-//                              16-byte LDS write of D; per G steps one read of the top row;
+//                              16-byte LDS write of D; the top row by G or by 4 steps;
 //   wave 1           publisher publishes the values of the band's last row that became final
 //                              since its previous pass (whole units of G steps, up to 64
 //                              columns) as tagged words for the band below, and the
@@ -52,6 +52,8 @@
 // SOFT option the compute wave applies the soft-min cell to values in the scaled domain
 // y = D log2(e) / gamma, the publisher hands the last row on in that domain, and the storer
 // writes D = y gamma ln 2.
+#include <type_traits>
+
 #include "wf_common.h"
 #include "wf_soft.h"
 
@@ -63,21 +65,6 @@ template <typename V>
 __device__ __forceinline__ V opaque(V x) {
   asm volatile("" : "+s"(x));
   return x;
-}
-
-// wave_shl:1 -- lane r receives lane r+1's value; lane 63 keeps its own.
-__device__ __forceinline__ uint32_t dpp_shl1_u32(uint32_t x) {
-  return (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, 0x130, 0xf, 0xf, false);
-}
-template <typename T>
-__device__ __forceinline__ T shl1(T x) {
-  if constexpr (sizeof(T) == 4) {
-    return __builtin_bit_cast(T, dpp_shl1_u32(__builtin_bit_cast(uint32_t, x)));
-  } else {
-    const uint64_t b = __builtin_bit_cast(uint64_t, x);
-    const uint64_t lo = dpp_shl1_u32((uint32_t)b), hi = dpp_shl1_u32((uint32_t)(b >> 32));
-    return __builtin_bit_cast(T, (hi << 32) | lo);
-  }
 }
 
 template <typename T, int G, int R>
@@ -141,9 +128,29 @@ template <typename T, int R>
 struct ComputeState {
   T X[R];  // previous value of each of the lane's rows (W of the next cell)
   T NW;    // previous N of the lane's first row (NW of its next cell)
-  T top;   // the row above the band, shifted down one lane per step: lane 0 holds the value
-           // at its next column
+  T top;   // without kTopVec: the row above the band, shifted down one lane per step: lane 0
+           // holds the value at its next column
 };
+
+// Whether the row above the band is read from LDS with every group, the four steps' values in
+// every lane, or with every unit, a column per lane, and shifted down a lane per step.
+template <typename T, int R>
+constexpr bool kTopVec = sizeof(T) == 8 || (R == 1 && std::is_same<T, int32_t>::value);
+
+// C of the lane's rows at four steps, and with kTopVec the row above the band there.
+template <typename T, int R>
+struct GroupRegs {
+  Vec4<T> c[R];
+  Vec4<T> t;
+};
+template <typename T, int G, int R>
+__device__ __forceinline__ void load_group(const T* __restrict__ S, const T* __restrict__ Tr, int slot, int lane,
+                                           GroupRegs<T, R>& r) {
+  using C = FwdCfg<T, G, R>;
+#pragma unroll
+  for (int k = 0; k < R; ++k) r.c[k] = *reinterpret_cast<const Vec4<T>*>(S + (k * kBand + lane) * C::PITCH + slot);
+  if constexpr (kTopVec<T, R>) r.t = *reinterpret_cast<const Vec4<T>*>(Tr + slot);
+}
 
 // Four steps, X = C + min(NW, N, W) per cell, of a lane's R adjacent rows.  N of the first
 // row is lane r-1's last row's previous value, moved by a DPP wave_shr:1 whose "old" operand
@@ -154,17 +161,17 @@ struct ComputeState {
 // VALU wrote it at the earliest, and shifting the top row and copying it into the move's
 // "old" operand are exactly those two.  Left to the compiler, the minimum (which must be
 // v_min3 itself: fminf on DPP-shifted operands costs a canonicalising instruction each)
-// drew a further wait state per step after every asm statement, and the top row came as a
-// 16-byte LDS read per group.  The s_nop covers a copy of X or 'top' that the compiler may
-// place right before the block.
+// drew a further wait state per step after every asm statement.  The s_nop covers a copy of X
+// or 'top' that the compiler may place right before the block.  (int32 with one row per lane
+// and double go another way: see below.)
 template <typename T>
 struct Cell4;
 
-#define WF_STEP1(MIN3, ADD, CLAMP, T0, NW, X, D, C)                \
-  "v_mov_b32 " T0 ", %[top]\n\t"                                   \
+#define WF_STEP1(T0, NW, X, D, C)                                         \
+  "v_mov_b32 " T0 ", %[top]\n\t"                                          \
   "v_mov_b32_dpp " T0 ", " X " wave_shr:1 row_mask:0xf bank_mask:0xf\n\t" \
-  MIN3 " " D ", " NW ", " T0 ", " X "\n\t"                         \
-  ADD " " D ", " C ", " D CLAMP "\n\t"                             \
+  "v_min3_f32 " D ", " NW ", " T0 ", " X "\n\t"                           \
+  "v_add_f32 " D ", " C ", " D "\n\t"                                     \
   "v_mov_b32_dpp %[top], %[top] wave_shl:1 row_mask:0xf bank_mask:0xf\n\t"
 #define WF_STEP2(MIN3, ADD, CLAMP, T0, NW, XA, XB, DA, DB, CA, CB) \
   "v_mov_b32 " T0 ", %[top]\n\t"                                   \
@@ -189,18 +196,9 @@ struct Cell4;
 #define WF_CELL4(T, MIN3, ADD, CLAMP)                                                                           \
   template <>                                                                                                   \
   struct Cell4<T> {                                                                                             \
-    __device__ static __forceinline__ void run(ComputeState<T, 1>& st, const Vec4<T> (&c)[1], Vec4<T> (&d)[1]) { \
-      T t;                                                                                                      \
-      asm("s_nop 0\n\t" WF_STEP1(MIN3, ADD, CLAMP, "%[t]", "%[nw]", "%[x]", "%[d0]", "%[c0]")                   \
-              WF_STEP1(MIN3, ADD, CLAMP, "%[nw]", "%[t]", "%[d0]", "%[d1]", "%[c1]")                            \
-                  WF_STEP1(MIN3, ADD, CLAMP, "%[t]", "%[nw]", "%[d1]", "%[d2]", "%[c2]")                        \
-                      WF_STEP1(MIN3, ADD, CLAMP, "%[nw]", "%[t]", "%[d2]", "%[d3]", "%[c3]")                    \
-          : [top] "+v"(st.top), [nw] "+v"(st.NW), [t] "=&v"(t), [d0] "=&v"(d[0].v[0]), [d1] "=&v"(d[0].v[1]),   \
-            [d2] "=&v"(d[0].v[2]), [d3] "=&v"(d[0].v[3])                                                        \
-          : [x] "v"(st.X[0]), [c0] "v"(c[0].v[0]), [c1] "v"(c[0].v[1]), [c2] "v"(c[0].v[2]), [c3] "v"(c[0].v[3])); \
-      st.X[0] = d[0].v[3];                                                                                      \
-    }                                                                                                           \
-    __device__ static __forceinline__ void run(ComputeState<T, 2>& st, const Vec4<T> (&c)[2], Vec4<T> (&d)[2]) { \
+    __device__ static __forceinline__ void run(ComputeState<T, 1>& st, const GroupRegs<T, 1>& r, Vec4<T> (&d)[1]); \
+    __device__ static __forceinline__ void run(ComputeState<T, 2>& st, const GroupRegs<T, 2>& r, Vec4<T> (&d)[2]) { \
+      const Vec4<T>(&c)[2] = r.c;                                                                               \
       T t;                                                                                                      \
       asm("s_nop 0\n\t" WF_STEP2(MIN3, ADD, CLAMP, "%[t]", "%[nw]", "%[xa]", "%[xb]", "%[a0]", "%[b0]", "%[c0]", "%[e0]") \
               WF_STEP2(MIN3, ADD, CLAMP, "%[nw]", "%[t]", "%[a0]", "%[b0]", "%[a1]", "%[b1]", "%[c1]", "%[e1]") \
@@ -230,14 +228,44 @@ struct Cell4;
             [ic1] "v"(c[2].v[q + 1]), [id0] "v"(c[3].v[q]), [id1] "v"(c[3].v[q + 1]));                          \
       for (int k = 0; k < 4; ++k) st.X[k] = d[k].v[q + 1];                                                      \
     }                                                                                                           \
-    __device__ static __forceinline__ void run(ComputeState<T, 4>& st, const Vec4<T> (&c)[4], Vec4<T> (&d)[4]) { \
-      two<0>(st, c, d);                                                                                         \
-      two<2>(st, c, d);                                                                                         \
+    __device__ static __forceinline__ void run(ComputeState<T, 4>& st, const GroupRegs<T, 4>& r, Vec4<T> (&d)[4]) { \
+      two<0>(st, r.c, d);                                                                                       \
+      two<2>(st, r.c, d);                                                                                         \
     }                                                                                                           \
   };
 WF_CELL4(float, "v_min3_f32", "v_add_f32", "")
 // saturating, so that +inf (INT32_MAX) stays +inf on the virtual border
 WF_CELL4(int32_t, "v_min3_i32", "v_add_i32", " clamp")
+
+// One row per lane.  float: the block.  int32 and double: the compiler's code, with the row
+// above read from LDS once per four steps (kTopVec): it needs no wait state beyond the DPP
+// move's own there and puts the LDS instructions into those, so that a step is shorter than
+// with a register to copy and to shift.  64 x 16384, scores only, us: int32 239 against 244
+// in the block, double 380 against 421 with a register; float 244 in the block, 248 in one
+// without a register, 264 in the compiler's code.
+__device__ __forceinline__ void Cell4<float>::run(ComputeState<float, 1>& st, const GroupRegs<float, 1>& r,
+                                                  Vec4<float> (&d)[1]) {
+  const Vec4<float>& c = r.c[0];
+  float t;
+  asm("s_nop 0\n\t" WF_STEP1("%[t]", "%[nw]", "%[x]", "%[d0]", "%[c0]")
+          WF_STEP1("%[nw]", "%[t]", "%[d0]", "%[d1]", "%[c1]") WF_STEP1("%[t]", "%[nw]", "%[d1]", "%[d2]", "%[c2]")
+              WF_STEP1("%[nw]", "%[t]", "%[d2]", "%[d3]", "%[c3]")
+      : [top] "+v"(st.top), [nw] "+v"(st.NW), [t] "=&v"(t), [d0] "=&v"(d[0].v[0]), [d1] "=&v"(d[0].v[1]),
+        [d2] "=&v"(d[0].v[2]), [d3] "=&v"(d[0].v[3])
+      : [x] "v"(st.X[0]), [c0] "v"(c.v[0]), [c1] "v"(c.v[1]), [c2] "v"(c.v[2]), [c3] "v"(c.v[3]));
+  st.X[0] = d[0].v[3];
+}
+__device__ __forceinline__ void Cell4<int32_t>::run(ComputeState<int32_t, 1>& st, const GroupRegs<int32_t, 1>& r,
+                                                    Vec4<int32_t> (&d)[1]) {
+  using E = Elem<int32_t>;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int32_t N = E::shr1(st.X[0], r.t.v[q]);
+    st.X[0] = E::add(r.c[0].v[q], E::min3(st.NW, N, st.X[0]));
+    st.NW = N;
+    d[0].v[q] = st.X[0];
+  }
+}
 
 __device__ __forceinline__ double min_raw(double a, double b) {
   double r;
@@ -247,18 +275,17 @@ __device__ __forceinline__ double min_raw(double a, double b) {
 template <>
 struct Cell4<double> {
   template <int R>
-  __device__ static __forceinline__ void run(ComputeState<double, R>& st, const Vec4<double> (&c)[R],
+  __device__ static __forceinline__ void run(ComputeState<double, R>& st, const GroupRegs<double, R>& r,
                                              Vec4<double> (&d)[R]) {
     using E = Elem<double>;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      double N = E::shr1(st.X[R - 1], st.top), NW = st.NW;
+      double N = E::shr1(st.X[R - 1], r.t.v[q]), NW = st.NW;
       st.NW = N;
-      st.top = shl1(st.top);
 #pragma unroll
       for (int k = 0; k < R; ++k) {
         const double W = st.X[k];
-        st.X[k] = c[k].v[q] + min_raw(min_raw(NW, W), N);
+        st.X[k] = r.c[k].v[q] + min_raw(min_raw(NW, W), N);
         NW = W;
         N = st.X[k];
         d[k].v[q] = st.X[k];
@@ -331,20 +358,19 @@ __device__ __forceinline__ double soft_log2_1p(double a) {
 // their minimum, whose own term is 1: two exponentials, of the median and the maximum, and the
 // logarithm of 1 plus their sum.  +inf neighbours give terms that vanish; three of them (the
 // padding lanes before column 0) give +inf.  A step is a serial chain of about 70 float64
-// instructions of 4.9 cycles and takes 165 ns; with the general exp2 and log2 (three and one,
+// instructions of 4.9 cycles and takes 160 ns; with the general exp2 and log2 (three and one,
 // about 175 instructions: subnormal, overflow and sign cases that cannot arise here) it took
-// 360 ns: 500 x 700 497 us then and 241 us now.  The table's error against 80-bit arithmetic is
-// the same to 1% for gamma from 0.01 to 10.
-__device__ __forceinline__ void soft_cells4(ComputeState<double, 1>& st, const Vec4<double> (&c)[1],
+// 360 ns: 500 x 700 497 us then and 238 us now.  The table's error against 80-bit arithmetic is
+// the same to 5% for gamma from 0.01 to 10 and costs from 10^-9 to 10^4 gamma.
+__device__ __forceinline__ void soft_cells4(ComputeState<double, 1>& st, const GroupRegs<double, 1>& r,
                                             Vec4<double> (&d)[1]) {
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
-    const double N = Elem<double>::shr1(st.X[0], st.top), NW = st.NW, W = st.X[0];
-    st.top = shl1(st.top);
+    const double N = Elem<double>::shr1(st.X[0], r.t.v[q]), NW = st.NW, W = st.X[0];
     const double lo = min_raw(NW, N), hi = max_raw(NW, N);
     const double mn = min_raw(lo, W), md = max_raw(lo, min_raw(hi, W)), mx = max_raw(hi, W);
     const double a = soft_exp2(mn - md) + soft_exp2(mn - mx);
-    st.X[0] = c[0].v[q] + (mn - soft_log2_1p(a));
+    st.X[0] = r.c[0].v[q] + (mn - soft_log2_1p(a));
     st.NW = N;
     d[0].v[q] = st.X[0];
   }
@@ -366,7 +392,9 @@ __device__ __forceinline__ void soft_cells4(ComputeState<double, 1>& st, const V
   "v_sub_f32 %[md], %[mn], %[md]\n\t"                                     \
   "v_min_f32 %[md], %[mn], %[md]\n\t"                                     \
   "v_add_f32 " D ", " C ", %[md]\n\t"
-__device__ __forceinline__ void soft_cells4(ComputeState<float, 1>& st, const Vec4<float> (&c)[1], Vec4<float> (&d)[1]) {
+__device__ __forceinline__ void soft_cells4(ComputeState<float, 1>& st, const GroupRegs<float, 1>& r,
+                                            Vec4<float> (&d)[1]) {
+  const Vec4<float>& c = r.c[0];
   float t, mn, md, mx;
   asm("s_nop 0\n\t" WF_SOFT1("%[t]", "%[nw]", "%[x]", "%[d0]", "%[c0]") "s_nop 0\n\t"
           WF_SOFT1("%[nw]", "%[t]", "%[d0]", "%[d1]", "%[c1]") "s_nop 0\n\t"
@@ -374,34 +402,22 @@ __device__ __forceinline__ void soft_cells4(ComputeState<float, 1>& st, const Ve
                   WF_SOFT1("%[nw]", "%[t]", "%[d2]", "%[d3]", "%[c3]")
       : [top] "+v"(st.top), [nw] "+v"(st.NW), [t] "=&v"(t), [mn] "=&v"(mn), [md] "=&v"(md), [mx] "=&v"(mx),
         [d0] "=&v"(d[0].v[0]), [d1] "=&v"(d[0].v[1]), [d2] "=&v"(d[0].v[2]), [d3] "=&v"(d[0].v[3])
-      : [x] "v"(st.X[0]), [c0] "v"(c[0].v[0]), [c1] "v"(c[0].v[1]), [c2] "v"(c[0].v[2]), [c3] "v"(c[0].v[3]));
+      : [x] "v"(st.X[0]), [c0] "v"(c.v[0]), [c1] "v"(c.v[1]), [c2] "v"(c.v[2]), [c3] "v"(c.v[3]));
   st.X[0] = d[0].v[3];
 }
 
 template <typename T, int R, bool SOFT>
-__device__ __forceinline__ void cells4(ComputeState<T, R>& st, const Vec4<T> (&c)[R], Vec4<T> (&out)[R]) {
+__device__ __forceinline__ void cells4(ComputeState<T, R>& st, const GroupRegs<T, R>& r, Vec4<T> (&out)[R]) {
   if constexpr (SOFT) {
     static_assert(R == 1, "the soft-min sweep uses one row per lane");
-    soft_cells4(st, c, out);
+    soft_cells4(st, r, out);
   } else {
-    Cell4<T>::run(st, c, out);
+    Cell4<T>::run(st, r, out);
   }
 }
 
-// C of the lane's rows at four steps.
-template <typename T, int R>
-struct GroupRegs {
-  Vec4<T> c[R];
-};
-template <typename T, int G, int R>
-__device__ __forceinline__ void load_group(const T* __restrict__ S, int slot, int lane, GroupRegs<T, R>& r) {
-  using C = FwdCfg<T, G, R>;
-#pragma unroll
-  for (int k = 0; k < R; ++k) r.c[k] = *reinterpret_cast<const Vec4<T>*>(S + (k * kBand + lane) * C::PITCH + slot);
-}
-
 // What the compute wave has read ahead of the unit it works on: the unit's first two groups
-// and its columns of the top row (lane l: column G u + l, l < G).
+// and, without kTopVec, its columns of the top row (lane l: column G u + l, l < G).
 template <typename T, int G, int R>
 struct UnitRegs {
   GroupRegs<T, R> g[2];
@@ -412,8 +428,8 @@ template <typename T, int G, int R>
 __device__ __forceinline__ void load_unit(const T* __restrict__ S, const T* __restrict__ Tr, int slot, int lane,
                                           UnitRegs<T, G, R>& r) {
 #pragma unroll
-  for (int p = 0; p < 2; ++p) load_group<T, G, R>(S, slot + 4 * p, lane, r.g[p]);
-  r.top = Tr[slot + (lane & (G - 1))];
+  for (int p = 0; p < 2; ++p) load_group<T, G, R>(S, Tr, slot + 4 * p, lane, r.g[p]);
+  if constexpr (!kTopVec<T, R>) r.top = Tr[slot + (lane & (G - 1))];
 }
 
 // The readiness of a unit's inputs: lane l's copy of counter l % 8 against what the unit
@@ -447,12 +463,12 @@ __device__ __forceinline__ bool compute_unit(T* __restrict__ S, const T* __restr
   GroupRegs<T, R> gr[NG];
   gr[0] = P.g[0];
   gr[1] = P.g[1];
-  st.top = P.top;
+  if constexpr (!kTopVec<T, R>) st.top = P.top;
   bool late = false;
 #pragma unroll
   for (int g = 0; g < NG; ++g) {
     if (g + 2 < NG) {
-      load_group<T, G, R>(S, base + 4 * (g + 2), lane, gr[g + 2]);
+      load_group<T, G, R>(S, Tr, base + 4 * (g + 2), lane, gr[g + 2]);
     } else if (g + 2 == NG) {
       late = __ballot(ready < need) != 0;
       if (trace && late) {
@@ -461,16 +477,16 @@ __device__ __forceinline__ bool compute_unit(T* __restrict__ S, const T* __restr
         stalls[1] += (b & 0x10u) != 0;
       }
       __builtin_amdgcn_sched_barrier(0);
-      load_group<T, G, R>(S, next_base, lane, P.g[0]);
-      P.top = Tr[next_base + (lane & (G - 1))];
+      load_group<T, G, R>(S, Tr, next_base, lane, P.g[0]);
+      if constexpr (!kTopVec<T, R>) P.top = Tr[next_base + (lane & (G - 1))];
     } else {
-      load_group<T, G, R>(S, next_base + 4, lane, P.g[1]);
+      load_group<T, G, R>(S, Tr, next_base + 4, lane, P.g[1]);
     }
     // keeps every group's reads two groups ahead of their use (left alone, the scheduler
     // gathers the reads of several groups into one burst just before the first of them)
     __builtin_amdgcn_sched_barrier(0);
     Vec4<T> d[R];
-    cells4<T, R, SOFT>(st, gr[g].c, d);
+    cells4<T, R, SOFT>(st, gr[g], d);
 #pragma unroll
     for (int k = 0; k < R; ++k) *reinterpret_cast<Vec4<T>*>(S + (k * kBand + lane) * C::PITCH + base + 4 * g) = d[k];
   }
