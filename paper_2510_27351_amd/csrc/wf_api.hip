@@ -202,16 +202,20 @@ int forced_tile() {
 // sweep; ld_bytes is the larger of its leading dimensions.
 //
 // A sweep takes about (bands - 1) * lag + n * step.  More rows per lane make fewer bands, each
-// with a longer lag and step; measured on MI355X (us; the lag from 16384 x 1024 and 4096 x 256,
-// the step from 256 x 16384):
+// with a longer lag and step; measured on MI355X (us, scores only; the lag from 16384 x 1024,
+// the step from 64 x 16384):
 //                     float, int32                      double
 //   rows per lane     1        2        4               1       2
-//   lag               2.9      3.9      5.1             4.5     6.3
-//   step              0.0149   0.0245   0.043           0.026   0.0455
-// so one row per lane is the fastest for m below about 0.6 n (1500 x 4001 float: 153, 162 and
-// 223 us for 1, 2 and 4), two around the square (4096^2: 282, 246, 283; 1024^2: 74, 67, 76),
-// four for m above about 2 n (16384 x 1024: 822, 552, 414).  Double, two against one: 16384 x
-// 1024 868 against 1229, 2048^2 195 against 209, 4096^2 439 against 425, hence the margin.
+//   lag               2.9      4.0      5.7             4.0     5.5
+//   step              0.0148   0.0243   0.045           0.0233  0.0439
+// so one row per lane is the fastest for m below about 0.6 n, two around the square and four
+// for m above about 2 n; with tables written (float, us for 1, 2 and 4 rows): 1500 x 4001 148,
+// 158 and 225; 1400 x 2000 112, 106 and 132; 4096^2 285, 243 and 285; 2000 x 1000 125, 96 and
+// 98; 16384 x 1024 810, 559 and 417.  Where many bands run at once their traffic adds to that
+// (16384^2: 1364, 1263 and 1648 us with tables, 1183, 1020 and 1163 without), which moves
+// the line little.  Double, one against two: 2400 x 4000 283 and 300, 1024^2 103 and 98, 2048^2
+// 207 and 191, 4096^2 400 and 413, 8192^2 1049 and 1092, 3000 x 1000 231 and 192, which the
+// constants below are fitted to.
 // A band is addressed with 32-bit byte offsets, which bounds rows * the leading dimension.
 int forward_rows(int dtype, int64_t m, int64_t n, int64_t ld_bytes) {
   struct Cost {
@@ -219,7 +223,7 @@ int forward_rows(int dtype, int64_t m, int64_t n, int64_t ld_bytes) {
     double lag, step;
   };
   static const Cost f[3] = {{1, 2.9, 0.0149}, {2, 3.9, 0.0245}, {4, 5.1, 0.043}};
-  static const Cost d[2] = {{1, 4.5, 0.026}, {2, 6.6, 0.0477}};
+  static const Cost d[2] = {{1, 4.5, 0.0239}, {2, 6.2, 0.0464}};
   const Cost* c = dtype == 1 ? d : f;
   int best = 1;
   double t_best = 0.0;

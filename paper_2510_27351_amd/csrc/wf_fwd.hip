@@ -241,7 +241,7 @@ WF_CELL4(int32_t, "v_min3_i32", "v_add_i32", " clamp")
 // above read from LDS once per four steps (kTopVec): it needs no wait state beyond the DPP
 // move's own there and puts the LDS instructions into those, so that a step is shorter than
 // with a register to copy and to shift.  64 x 16384, scores only, us: int32 239 against 244
-// in the block, double 380 against 421 with a register; float 244 in the block, 248 in one
+// in the block, double 382 against 421 with a register; float 244 in the block, 248 in one
 // without a register, 264 in the compiler's code.
 __device__ __forceinline__ void Cell4<float>::run(ComputeState<float, 1>& st, const GroupRegs<float, 1>& r,
                                                   Vec4<float> (&d)[1]) {
@@ -508,9 +508,6 @@ __device__ __forceinline__ void compute_band(T* __restrict__ S, const T* __restr
                                              int Ks, bool first_band, uint64_t* trace) {
   using E = Elem<T>;
   using C = FwdCfg<T, G, R>;
-  // The double soft-min cell is some 170 instructions: a sub-chunk's 64 unrolled would not
-  // fit the instruction cache (500 x 700: 535 us against 496).
-  constexpr int UNROLL = SOFT && sizeof(T) == 8 ? 1 : C::GPS;
   const int lane = threadIdx.x & 63;
   const bool tr = trace != nullptr;
   // what unit 0 needs, and what each next unit and each next sub-chunk add
@@ -550,7 +547,7 @@ __device__ __forceinline__ void compute_band(T* __restrict__ S, const T* __restr
     for (int s = s0; s < s1; ++s) {
       const int base = (C::SUB * s) & C::MASK;
       const int next = (C::SUB * (s + 1)) & C::MASK;
-#pragma unroll UNROLL
+#pragma unroll
       for (int v = 0; v < C::GPS; ++v) {
         need += per_unit;
         if (v + 1 == C::GPS) need += per_sub;
@@ -1017,7 +1014,8 @@ __global__ __launch_bounds__((64 * (3 + 2 * R)), 1) void fwd_kernel(FwdArgs a) {
   const uint32_t epoch = __hip_atomic_load(&ctl->epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if (threadIdx.x == 0) {
     sh.abort = 0u;
-    // (the double soft-min loop is so slow that a pass over it costs more than its fetch)
+    // (a pass over the double soft-min loop costs more than its fetch: 500 x 700 238 us without,
+    // 243 with)
     sh.warm = SOFT && sizeof(T) == 8 ? 1u : 0u;
   }
   for (;;) {
