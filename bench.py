@@ -196,7 +196,7 @@ def batch_rate(steps: int, warmup: int):
     out = {"workload": "512 instances, m and n uniform in [64, 2048] (seed 3), float32 uniform [0,1), "
                        "tables written; one persistent launch per replay of the captured graph",
            "cells": cells, "ms": ms_per, "cells_per_s": cells / (ms_per * 1e-3),
-           "effective_GBps": 3 * cells * 4 / (ms_per * 1e-3) / 1e9, "tile": plan.tile, "rows": plan.rows}
+           "effective_GBps": 3 * cells * 4 / (ms_per * 1e-3) / 1e9, "tile": plan.tile, "rows": plan.table_rows}
     plan.close()
     return out
 
@@ -481,6 +481,7 @@ def main():
                    "measured_traffic_bytes": measured_traffic(k), "bytes": what}
                for k, (t, b, ib, what) in kern.items()}
     dom = max(kernels, key=lambda k: kernels[k]["ms"])
+    tile_fwd, rows_fwd = wf.forward_config(m, n)
     out = {
         "metric": "cells/sec and effective HBM GB/s (% peak), fwd and fwd+adjoint, n=16384",
         "value": cells / (ms * 1e-3),
@@ -499,7 +500,8 @@ def main():
                                "from the checkpoint grid (wf_backward: selection recompute with the bands' "
                                "exits, then the walk of the argmin path)",
                    "m": m, "n": n, "ckpt_k": CKPT_K,
-                   "tile_forward": wf.predict_tile(m, n), "tile_reverse": wf.predict_tile(m, n, reverse=True)},
+                   "tile_forward": tile_fwd, "rows_per_lane_forward": rows_fwd,
+                   "tile_reverse": wf.predict_tile(m, n, reverse=True)},
         "fwd": {"ms": fwd_ms, "cells_per_s": cells / (fwd_ms * 1e-3),
                 "effective_GBps": eff(3 * cells * es, fwd_ms),
                 "effective_pct_peak": 100 * eff(3 * cells * es, fwd_ms) / PEAK_HBM_GBPS},

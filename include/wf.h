@@ -176,8 +176,9 @@ int wf_reverse(int dtype, int64_t m, int64_t n, const void* g_score, const void*
  *   wf_plan_destroy).  Returns WF_E_ARG for invalid sizes or overlapping offsets.
  * wf_plan_elems    number of elements the C (and D) buffer must hold, -1 for NULL.
  * wf_plan_offsets  copies the batch's element offsets into a host array of 'batch'.
- * wf_plan_config   the (tile, rows) the plan uses (with rows autotuned to 2, runs of a large
- *                  batch that write tables take one row per band instead).
+ * wf_plan_config   the (tile, rows) of the plan's runs that write scores alone.
+ * wf_plan_table_config   the (tile, rows) of its runs that write tables: the same, except that
+ *                  with rows autotuned to 2 a batch bound by its memory traffic takes 1.
  * wf_batch_forward(plan, C, D, scores, stream)
  *   C       [in]  device buffer of wf_plan_elems elements holding every instance.
  *   D       [out] same layout as C, every instance's table; NULL = scores only.
@@ -192,6 +193,7 @@ int wf_plan_create(wf_plan** plan, int dtype, int32_t batch, const int64_t* m, c
 int64_t wf_plan_elems(const wf_plan* plan);
 int wf_plan_offsets(const wf_plan* plan, int64_t* offsets);
 int wf_plan_config(const wf_plan* plan, int32_t* tile, int32_t* rows);
+int wf_plan_table_config(const wf_plan* plan, int32_t* tile, int32_t* rows);
 int wf_batch_forward(wf_plan* plan, const void* C, void* D, void* scores, void* stream);
 void wf_plan_destroy(wf_plan* plan);
 
@@ -253,6 +255,14 @@ int wf_set_tile(int32_t tile);
  * adjoint).
  */
 int32_t wf_tile_predict(int32_t dtype, int64_t m, int64_t n, int32_t reverse);
+
+/*
+ * The configuration that wf_forward and wf_forward_noalloc run an m x n instance with: the
+ * tile (the forced one, or the prediction within its bounds) and the rows per lane (1, 2 or 4;
+ * a band is 64 times as many rows).  ldc and ldd as in wf_forward (ldd = 0: no table).  No
+ * device is touched.  WF_E_ARG or WF_E_UNSUPPORTED for sizes that wf_forward refuses.
+ */
+int wf_forward_config(int dtype, int64_t m, int64_t n, int64_t ldc, int64_t ldd, int32_t* tile, int32_t* rows);
 
 /*
  * Tracing (for profiling the pipeline, off by default).  wf_trace_enable(B) allocates a

@@ -18,6 +18,7 @@ from . import _lib
 from ._lib import WfError  # noqa: F401
 
 __all__ = ["forward", "backward", "sweep", "WfFunction", "Plan", "ckpt_elems", "set_tile", "predict_tile",
+           "forward_config",
            "last_async_error", "WfError", "BAND", "soft_forward", "soft_backward", "soft_sweep", "SoftWfFunction"]
 
 BAND = 64  # rows per band of the device sweep (= wavefront size)
@@ -303,7 +304,8 @@ class Plan:
     ms, ns: instance sizes; offsets: element offsets in one packed buffer (None = packed in
     order with 256-byte aligned starts); tile / rows: 16/32/64 and 1/2, or 0 to autotune.
     forward(C) takes the packed device buffer and returns (scores, D) -- D is None unless
-    table=True or a D buffer is given."""
+    table=True or a D buffer is given.  tile, rows and table_rows hold the configuration in
+    use: rows per lane of the runs for scores alone and of those that write tables."""
 
     def __init__(self, ms, ns, dtype=torch.float32, offsets=None, tile: int = 0, rows: int = 0, device=None):
         if len(ms) != len(ns) or not len(ms):
@@ -328,6 +330,8 @@ class Plan:
         t, r = ctypes.c_int32(), ctypes.c_int32()
         _lib.check(lib.wf_plan_config(self._h, ctypes.byref(t), ctypes.byref(r)), "wf_plan_config")
         self.tile, self.rows = t.value, r.value
+        _lib.check(lib.wf_plan_table_config(self._h, None, ctypes.byref(r)), "wf_plan_table_config")
+        self.table_rows = r.value
 
     def pack(self, mats) -> torch.Tensor:
         """Packs a list of m_i x n_i tensors into one device buffer of the plan's layout."""
@@ -447,6 +451,15 @@ def predict_tile(m: int, n: int, reverse: bool = False, dtype: torch.dtype = tor
     if t not in (16, 32, 64):
         raise _lib.WfError(t, "wf_tile_predict")
     return t
+
+
+def forward_config(m: int, n: int, dtype: torch.dtype = torch.float32, table: bool = True):
+    """(tile, rows per lane) that forward() runs a contiguous m x n instance with (wf_forward_config)."""
+    t, r = ctypes.c_int32(), ctypes.c_int32()
+    rc = _lib.load().wf_forward_config(_DTYPES.get(dtype, -1), m, n, n, n if table else 0, ctypes.byref(t),
+                                       ctypes.byref(r))
+    _lib.check(rc, "wf_forward_config")
+    return t.value, r.value
 
 
 def last_async_error(device=None) -> None:

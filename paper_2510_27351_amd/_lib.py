@@ -48,6 +48,8 @@ def load():
     lib.wf_plan_offsets.restype = ctypes.c_int
     lib.wf_plan_config.argtypes = [p, ctypes.POINTER(i32), ctypes.POINTER(i32)]
     lib.wf_plan_config.restype = ctypes.c_int
+    lib.wf_plan_table_config.argtypes = [p, ctypes.POINTER(i32), ctypes.POINTER(i32)]
+    lib.wf_plan_table_config.restype = ctypes.c_int
     lib.wf_batch_forward.argtypes = [p, p, p, p, p]
     lib.wf_batch_forward.restype = ctypes.c_int
     lib.wf_plan_ckpt_elems.argtypes = [p, i32]
@@ -73,6 +75,8 @@ def load():
     lib.wf_set_tile.restype = ctypes.c_int
     lib.wf_tile_predict.argtypes = [i32, i64, i64, i32]
     lib.wf_tile_predict.restype = i32
+    lib.wf_forward_config.argtypes = [ctypes.c_int, i64, i64, i64, i64, ctypes.POINTER(i32), ctypes.POINTER(i32)]
+    lib.wf_forward_config.restype = ctypes.c_int
     lib.wf_last_async_error.argtypes = [p]
     lib.wf_last_async_error.restype = ctypes.c_int
     lib.wf_error_string.argtypes = [ctypes.c_int]

@@ -407,6 +407,20 @@ int wf_set_tile(int32_t tile) {
   return WF_OK;
 }
 
+int wf_forward_config(int dtype, int64_t m, int64_t n, int64_t ldc, int64_t ldd, int32_t* tile, int32_t* rows) {
+  const int es = elem_size(dtype);
+  if (es == 0) return WF_E_ARG;
+  if (m < 1 || n < 1 || n > (int64_t)1 << 31 || m > (int64_t)1 << 40) return WF_E_ARG;
+  if (m > INT64_MAX / n || ldc < n || (ldd != 0 && ldd < n)) return WF_E_ARG;
+  if ((m - 1) > INT64_MAX / ldc) return WF_E_ARG;
+  if (ldc > kMaxLd / es || ldd > kMaxLd / es) return WF_E_UNSUPPORTED;
+  if (nbands(m) > 0x7fffffff) return WF_E_ARG;
+  const int r = forward_rows(dtype, m, n, std::max(ldc, ldd) * es);
+  if (tile) *tile = choose_forward_tile(dtype, m, n, r);
+  if (rows) *rows = r;
+  return WF_OK;
+}
+
 int wf_forward(int dtype, int64_t m, int64_t n, const void* C, int64_t ldc, void* D, int64_t ldd,
                void* score, void* ckpt, int32_t ckpt_k, void* stream) {
   const int es = elem_size(dtype);

@@ -546,6 +546,13 @@ int wf_plan_config(const wf_plan* plan, int32_t* tile, int32_t* rows) {
   return WF_OK;
 }
 
+int wf_plan_table_config(const wf_plan* plan, int32_t* tile, int32_t* rows) {
+  if (!plan) return WF_E_ARG;
+  if (tile) *tile = plan->tile;
+  if (rows) *rows = plan->table_rows;
+  return WF_OK;
+}
+
 int64_t wf_plan_ckpt_elems(const wf_plan* plan, int32_t ckpt_k) {
   if (!plan || ckpt_k < 0 || ckpt_k > 4096) return -1;
   return ckpt_layout(*plan, ckpt_k, nullptr);
