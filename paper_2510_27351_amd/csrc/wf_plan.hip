@@ -282,6 +282,30 @@ done:
   return rc;
 }
 
+// Whether a run of the batch (4-byte elements) that writes tables is bound by its memory
+// traffic and not by its bands, with two rows per lane.  Two rows per lane are the faster shape
+// for scores alone (512 instances of 64 to 2048: 664 us against 1055; one loader's loads in
+// flight per compute unit are too few) and with tables wherever the bands' own time counts; where
+// the traffic does, one-row bands spread it more evenly.  The bands take the larger of a
+// compute unit's share of them, 3 us and 24.5 ns a step each, and of an instance's chain of
+// them, 3.9 us of lag each (forward_rows' figures); C and the tables pass at 4.3 TB/s.  Measured
+// (float, us with one row and with two; traffic over bands before): 512 of 64 to 2048, 2.0: 1168
+// and 1240; 64 of 500 to 1500, 1.6: 197 and 203; 400 of 30 to 90 x 3000 to 6000, 1.1: 281 and
+// 270; 38 of about 4000 x 800, 1.1: 538 and 468; 600 of 64 to 300, 0.9: 164 and 114; 100 of 3000
+// to 6000 x 30 to 90, 0.3: 713 and 448.
+bool tables_bound_by_memory(const wf_plan& p) {
+  constexpr double kStep = 0.0245, kBandStart = 3.0, kLag = 3.9, kBytesPerUs = 4.3e6;
+  double cells = 0.0, work = 0.0, chain = 0.0;
+  for (int32_t i = 0; i < p.batch; ++i) {
+    const double n = (double)p.n[i], bands = (double)((p.m[i] + 2 * kBand - 1) / (2 * kBand));
+    cells += (double)p.m[i] * n;
+    work += bands * (kBandStart + kStep * (n + kBand - 1));
+    chain = std::max(chain, (bands - 1) * kLag + n * kStep);
+  }
+  const double bytes = 2.0 * cells * elem_size(p.dtype);
+  return bytes / kBytesPerUs > 1.3 * std::max(work / p.num_cus, chain);
+}
+
 void free_plan(wf_plan* p) {
   if (!p) return;
   (void)hipDeviceSynchronize();
@@ -504,18 +528,7 @@ int wf_plan_create(wf_plan** out, int dtype, int32_t batch, const int64_t* m, co
     }
   }
   p->tile = want_tile;
-  // Two rows per lane are the faster shape for scores alone (512 instances of 64 to 2048:
-  // 673 us against 1070; one loader's loads in flight per compute unit are too few).  With
-  // tables to write a large batch is bound by its memory traffic, which the one-row bands
-  // spread more evenly (1333 us against 1427; 64 x 2048^2: 592 against 682), a small one by
-  // its bands' starts and ends (300 instances of 64 to 300: 98 against 75).  The line lies
-  // at six 64-row bands per compute unit.
-  int table_rows = want_rows;
-  if (rows == 0 && want_rows == 2) {
-    int64_t bands = 0;
-    for (int32_t i = 0; i < batch; ++i) bands += (m[i] + kBand - 1) / kBand;
-    if (bands >= 6 * (int64_t)p->num_cus) table_rows = 1;
-  }
+  const int table_rows = rows == 0 && want_rows == 2 && tables_bound_by_memory(*p) ? 1 : want_rows;
   rc = upload_work(*p, want_rows, table_rows, 0);
   if (rc == WF_OK && hipStreamCreateWithFlags(&p->cap, hipStreamNonBlocking) != hipSuccess) {
     p->cap = nullptr;
