@@ -807,7 +807,7 @@ __device__ __forceinline__ void unscale(Vec4<T> (&v)[NV], T gl) {
 }
 
 // One storer per 64 LDS rows, like the loaders.
-template <typename T, int G, int R, bool SOFT>
+template <typename T, int G, int R, bool SOFT, bool SKIP>
 __device__ __forceinline__ void store_sub(const T* S, __amdgpu_buffer_rsrc_t drs, int64_t ldd, int rows, int64_t n,
                                           int h, int s, T gl) {
   using C = FwdCfg<T, G, R>;
@@ -836,35 +836,37 @@ __device__ __forceinline__ void store_sub(const T* S, __amdgpu_buffer_rsrc_t drs
     }
     return;
   }
-  // Edge sub-chunk (the first and the last): per vector one 16-byte store if its four cells lie
-  // inside the matrix, else a store per cell that does.  Rows past the matrix, whose stores the
-  // buffer's range check would drop, are passed over (1 x 64 in float64: 13.4 us with their
-  // stores, 10.8 without).
+  // Edge sub-chunk (the first and the last): per vector one 16-byte store of the rows whose four
+  // cells lie inside the matrix and a store per cell of the others, the lanes that have none sent
+  // past the resource's end, where stores are dropped: no branch.  (With one around each store
+  // 4000 instances of 64 x 64 with tables took 211 us, 199 so; 100 x 100 alone 14.9 and 12.6.)
+  // SKIP: it ends after the vectors that hold the matrix's last row (1 x 64 in float64 11.3 us
+  // without, 10.2 with; 65 x 400 24.6 and 23.2).  Not in the batch kernel, where that test
+  // costs more than it saves: 4000 instances of 4 to 40 rows 163 us without, 209 with, for a
+  // reason not found.
+  constexpr uint32_t kOut = 0x80000000u;  // a band's resource is shorter
 #pragma unroll
   for (int k = 0; k < C::NV; ++k) {
+    if (SKIP && k % 4 == 0 && R * (64 / C::LPR) * k + h >= rows) break;
     const SubVec<T, G, R> q(h, k, s);
-    if (q.row() >= rows) continue;
-    const int64_t c0 = q.c0();
-    const int off = (int)(((int64_t)q.row() * ldd + c0) * (int64_t)sizeof(T));
-    if (c0 >= 0 && c0 + 4 <= n) {
-      put(off, v[k]);
-      continue;
-    }
+    const int c0 = q.c0();
+    const uint32_t off = (uint32_t)((int64_t)q.row() * ldd + c0) * (uint32_t)sizeof(T);
+    const bool whole = c0 >= 0 && c0 + 4 <= (int)n;
+    put((int)(whole ? off : kOut), v[k]);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      if (c0 + e >= 0 && c0 + e < n) {
-        if constexpr (sizeof(T) == 4) {
-          __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, v[k].v[e]), drs, off + 4 * e, 0, 0);
-        } else {
-          typedef int v2i __attribute__((ext_vector_type(2)));
-          __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(v2i, v[k].v[e]), drs, off + 8 * e, 0, 0);
-        }
+      const uint32_t o = !whole && (uint32_t)(c0 + e) < (uint32_t)n ? off + e * (uint32_t)sizeof(T) : kOut;
+      if constexpr (sizeof(T) == 4) {
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, v[k].v[e]), drs, (int)o, 0, 0);
+      } else {
+        typedef int v2i __attribute__((ext_vector_type(2)));
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(v2i, v[k].v[e]), drs, (int)o, 0, 0);
       }
     }
   }
 }
 
-template <typename T, int G, int R, bool SOFT>
+template <typename T, int G, int R, bool SOFT, bool SKIP>
 __device__ __forceinline__ void store_band(const T* S, Shared& sh, const FwdArgs& a, int band, int h, int Ks,
                                            uint64_t* tr) {
   using C = FwdCfg<T, G, R>;
@@ -890,7 +892,7 @@ __device__ __forceinline__ void store_band(const T* S, Shared& sh, const FwdArgs
       sh.abort = 1u;
       return;
     }
-    if (a.D) store_sub<T, G, R, SOFT>(S, drs, ldd, rows, n, h, s, gl);
+    if (a.D) store_sub<T, G, R, SOFT, SKIP>(S, drs, ldd, rows, n, h, s, gl);
     if (ck_cols) {
       const int l = kBand * h + lane, i = band_row<R>(l);
       if (i < rows) {
@@ -975,7 +977,7 @@ __device__ __forceinline__ void publish_band(const T* S, Shared& sh, const FwdAr
 
 // ---------------------------------------------------------------------------------------
 // One band of one instance, all five roles.  The LDS counters must be zero on entry.
-template <typename T, int G, int R, bool SOFT = false>
+template <typename T, int G, int R, bool SOFT, bool BATCH>
 __device__ __forceinline__ void run_band(T* S, T* Tr, Shared& sh, const FwdArgs& a, int band, uint32_t epoch,
                                          uint64_t* tr) {
   using C = FwdCfg<T, G, R>;
@@ -996,7 +998,7 @@ __device__ __forceinline__ void run_band(T* S, T* Tr, Shared& sh, const FwdArgs&
   } else if (wave < 3 + R) {
     loader_band<T, G, R, SOFT>(S, sh, a, band, wave - 3, Ks, tr);
   } else {
-    store_band<T, G, R, SOFT>(S, sh, a, band, wave - 3 - R, Ks, tr);
+    store_band<T, G, R, SOFT, !BATCH>(S, sh, a, band, wave - 3 - R, Ks, tr);
   }
 }
 
@@ -1032,7 +1034,7 @@ __global__ __launch_bounds__((64 * (3 + 2 * R)), 1) void fwd_kernel(FwdArgs a) {
       tr[6] = xcc;
       tr[7] = blockIdx.x;
     }
-    run_band<T, G, R, SOFT>(S, Tr, sh, a, band, epoch, tr);
+    run_band<T, G, R, SOFT, false>(S, Tr, sh, a, band, epoch, tr);
     if (tr && threadIdx.x == (3 + R) * 64) tr[3] = __builtin_amdgcn_s_memrealtime();
     __syncthreads();
   }
@@ -1081,7 +1083,7 @@ __global__ __launch_bounds__((64 * (3 + 2 * R)), 1) void fwd_batch_kernel(BatchA
     a.bnd = b.bnd + in.bnd_off;
     a.trace = nullptr;
     a.kx = a.gl = 1.0;
-    run_band<T, G, R>(S, Tr, sh, a, it.band, epoch, nullptr);
+    run_band<T, G, R, false, true>(S, Tr, sh, a, it.band, epoch, nullptr);
     __syncthreads();
   }
   finish_launch(ctl, epoch);
