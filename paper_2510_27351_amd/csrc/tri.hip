@@ -501,10 +501,17 @@ __device__ __forceinline__ int tail_at(const TailArgs& g, int l, int q) {
   return k * g.pitch[l] + (q - k * g.m[l]);
 }
 
+// BYTES = 0: LDS of the size given at launch.
+extern __shared__ __attribute__((aligned(16))) unsigned char tail_lds[];
 template <typename T, int BYTES, int THREADS>
 __global__ __launch_bounds__(THREADS) void tail_kernel(TailArgs g) {
-  __shared__ T lds0[BYTES / sizeof(T)];
-  T* lds = lds0 + kThomasAhead;
+  T* lds;
+  if constexpr (BYTES > 0) {
+    __shared__ T lds0[BYTES / sizeof(T)];
+    lds = lds0 + kThomasAhead;
+  } else {
+    lds = reinterpret_cast<T*>(tail_lds) + kThomasAhead;
+  }
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   constexpr int WAVES = THREADS / 64;
   const int64_t sys = blockIdx.x;
@@ -666,10 +673,15 @@ hipError_t launch_thomas(int dtype, int32_t batch, int64_t n, const void* a, con
   return hipGetLastError();
 }
 
-// LDS of the deep levels' workgroup: 144 KiB, one workgroup per compute unit, or 36 KiB and
-// four where there are more systems than compute units.
+// LDS of the deep levels' workgroup: 144 KiB and 512 threads, one workgroup per compute unit; or,
+// where there are more systems than compute units, what the levels take, at most 36 KiB, and
+// four waves, or one for every 5 KiB from eight systems per compute unit on, where workgroups of
+// four would wait for one another.  100000 systems of 20 rows took 739 us (float32) and 728
+// (float64) with 36 KiB and four waves for each, 594 and 741 with the stages in launches of their
+// own, 211 and 302 so; 1000 of 100 rows 12.6 and 12.9 with four waves, 16.2 and 15.7 with one.
 constexpr int kTailBig = 144 * 1024, kTailSmall = 36 * 1024;
-constexpr int kTailBatch = 256;  // systems beyond which the small one is used
+constexpr int kTailBatch = 256;  // the chip's compute units
+constexpr int kTailWave = 5 * 1024;
 
 int tail_bytes(int32_t batch) { return batch > kTailBatch ? kTailSmall : kTailBig; }
 
@@ -681,19 +693,25 @@ int64_t tail_need(int es, const int64_t* n, const int32_t* m, int32_t R, int l0)
 }
 
 template <typename T>
-void launch_tail_t(int32_t batch, const TailArgs& g, hipStream_t s) {
-  if (batch > kTailBatch) {
-    hipLaunchKernelGGL((tail_kernel<T, kTailSmall, 256>), dim3((unsigned)batch), dim3(256), 0, s, g);
+void launch_tail_t(int32_t batch, const TailArgs& g, unsigned bytes, hipStream_t s) {
+  const dim3 grid((unsigned)batch);
+  if (batch <= kTailBatch) {
+    hipLaunchKernelGGL((tail_kernel<T, kTailBig, 512>), grid, dim3(512), 0, s, g);
+  } else if (bytes <= kTailWave && batch > 8 * kTailBatch) {
+    hipLaunchKernelGGL((tail_kernel<T, 0, 64>), grid, dim3(64), bytes, s, g);
+  } else if (bytes <= 2 * kTailWave && batch > 8 * kTailBatch) {
+    hipLaunchKernelGGL((tail_kernel<T, 0, 128>), grid, dim3(128), bytes, s, g);
   } else {
-    hipLaunchKernelGGL((tail_kernel<T, kTailBig, 512>), dim3((unsigned)batch), dim3(512), 0, s, g);
+    hipLaunchKernelGGL((tail_kernel<T, 0, 256>), grid, dim3(256), bytes, s, g);
   }
 }
 
-hipError_t launch_tail(int dtype, int32_t batch, const TailArgs& g, hipStream_t s) {
+// 'bytes': LDS of the levels in g (tail_need).
+hipError_t launch_tail(int dtype, int32_t batch, const TailArgs& g, unsigned bytes, hipStream_t s) {
   if (dtype == WF_F64) {
-    launch_tail_t<double>(batch, g, s);
+    launch_tail_t<double>(batch, g, bytes, s);
   } else {
-    launch_tail_t<float>(batch, g, s);
+    launch_tail_t<float>(batch, g, bytes, s);
   }
   return hipGetLastError();
 }
@@ -1014,7 +1032,8 @@ int tri_solve(const tri_plan* p, const void* a, const void* b, const void* c, co
       g.at[j] = at;
       at += 4 * g.size[j];
     }
-    if (launch_tail(dt, p->batch, g, s) != hipSuccess) return WF_E_DEVICE;
+    const int64_t bytes = tail_need(elem_bytes(dt), p->n, p->m, p->R, top);
+    if (launch_tail(dt, p->batch, g, (unsigned)bytes, s) != hipSuccess) return WF_E_DEVICE;
   } else {
     // Stage 2: the deepest interface system, directly
     void* const* L = p->lv[p->R + 1];

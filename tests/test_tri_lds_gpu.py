@@ -88,3 +88,18 @@ def test_bitwise_at_the_limit(dtype, batch, case):
     want = [tridiag.c_partition_solve(*(v.numpy() for v in base[k]), ms, PREC[dtype]) for k in range(kinds)]
     for i, k in enumerate(order):
         assert np.array_equal(x[i], want[k]), (i, k)
+
+
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+@pytest.mark.parametrize("batch,N,ms", [
+    (2048, 20, [4]), (2049, 2, [2]), (2049, 20, [4]), (2049, 100, [16]), (2049, 131, [16]), (2500, 170, [9]),
+    (2500, 260, [16]), (2500, 300, [16]), (2500, 420, [16, 4]), (2500, 560, [8, 6]), (2500, 1000, [16])])
+def test_many_systems_bitwise(batch, N, ms, dtype):
+    """One, two and four waves per system, on both sides of eight systems per compute unit."""
+    base = [tuple(v.to(dtype) for v in inputs.tridiagonal_dd(N, 5 * N + k)) for k in range(3)]
+    args = [torch.stack([base[k % 3][q] for k in range(batch)]).to(DEV) for q in range(4)]
+    plan = tri.Plan(batch, N, dtype, m=ms[0], R=len(ms) - 1, ms=ms[1:])
+    x = plan.solve(*args).cpu()
+    for k in range(3):
+        want = torch.from_numpy(tridiag.c_partition_solve(*(v.numpy() for v in base[k]), ms, PREC[dtype]))
+        assert torch.equal(x[k::3], want.expand_as(x[k::3])), k
