@@ -526,8 +526,9 @@ __device__ __forceinline__ void sel_store_sub(T* S, T* Tr, const Vec4<T> (&x)[SC
   using C = SCfg<T>;
   using E = typename C::E;
   const int lane = threadIdx.x & 63;
-  // every column of the piece lies in the matrix; rows past it, which no other row reads and
-  // whose bits are cleared, hold the buffer's zeros
+  // every column of the piece lies in the matrix; rows past it, which no row of it reads and
+  // whose bits are cleared, hold the buffer's zeros, in an edge piece whatever was there (1000
+  // instances of 20 x 20, float: 66 us with +inf in all of them, 57 so)
   const bool interior = C::SUB * k >= kBand - 1 && (int64_t)C::SUB * (k + 1) <= n;
   // One branch around all of a piece's vectors: with one around each, and 64-bit compares per
   // element where it was taken, the first and last pieces of a band cost 8 us each.
@@ -540,6 +541,7 @@ __device__ __forceinline__ void sel_store_sub(T* S, T* Tr, const Vec4<T> (&x)[SC
   } else {
 #pragma unroll
     for (int v = 0; v < C::NV; ++v) {
+      if (C::RPV * v % 16 == 0 && C::RPV * v >= rows) break;
       const int i = C::RPV * v + lane / C::LPR, slot = C::SUB * k + 4 * (lane & (C::LPR - 1));
       Vec4<T> y;
 #pragma unroll
