@@ -1258,6 +1258,28 @@ __device__ __forceinline__ bool adj_store(const T* S, AdjShared& sh, const AdjAr
     if (!lds_wait_ge(&sh.ctr[kAdjPub], (uint32_t)((C::SUB * (kr + 1) + G - 1) / G), &sh.abort, a.ctl, waited)) return false;
     const int slot = adj_slot<T>(k);
     const bool interior = C::SUB * k >= kBand - 1 && C::SUB * (k + 1) <= n;  // every column lies in the matrix
+    if (es == 8 && interior) {
+      // two elements a lane, so that an access covers whole lines: with four, double takes two
+      // accesses of every other 16 bytes each (64 x 2048^2 with gD, the sweep: 1284 us so, 1187
+      // with two)
+      constexpr int LPR2 = C::SUB / 2, RPV2 = 64 / LPR2;
+      typedef int v4i __attribute__((ext_vector_type(4)));
+      const int c2 = C::SUB * k + 2 * (lane & (LPR2 - 1));
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        v4i y[kAdjHalf / RPV2];
+#pragma unroll
+        for (int v = 0; v < kAdjHalf / RPV2; ++v)
+          y[v] = *reinterpret_cast<const v4i*>(S + (kAdjHalf * h + RPV2 * v + lane / LPR2) * C::PITCH + (c2 & C::MASK));
+#pragma unroll
+        for (int v = 0; v < kAdjHalf / RPV2; ++v) {
+          const int i = kAdjHalf * h + RPV2 * v + lane / LPR2;
+          __builtin_amdgcn_raw_buffer_store_b128(y[v], drs, (int)((uint32_t)(i * ldo + c2 - i) * (uint32_t)es), 0, 0);
+        }
+      }
+      lds_publish(&sh.ctr[kAdjStored], (uint32_t)(kr + 1));
+      continue;
+    }
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       Vec4<T> x[BCfg<T>::NV];
