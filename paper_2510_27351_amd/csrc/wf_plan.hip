@@ -167,7 +167,10 @@ hipError_t launch_plan(const wf_plan& p, const void* C, void* D, void* scores, v
 // ---------------------------------------------------------------------------------------
 // Autotuner cache: the best (tile, rows) per (device kind, dtype, shape list), kept for the
 // process and, when WF_TUNE_CACHE names a file, in that file (one "key tile rows" line per
-// entry, appended when a new entry is measured).
+// entry, appended when a new entry is measured).  Keys begin with the version of the batch
+// kernels and of what the tuner times: entries measured with others are not taken (those of
+// keys without one were timed with tables, on bands of rows 64 apart).
+constexpr int kTuneVersion = 2;
 std::mutex g_tune_mu;
 std::map<std::string, std::pair<int, int>> g_tune;
 bool g_tune_file_read = false;
@@ -186,7 +189,8 @@ std::string tune_key(const wf_plan& p) {
     mix((uint64_t)p.n[i]);
   }
   char buf[96];
-  std::snprintf(buf, sizeof(buf), "cu%d-dt%d-b%d-%016llx", p.num_cus, p.dtype, (int)p.batch, (unsigned long long)h);
+  std::snprintf(buf, sizeof(buf), "v%d-cu%d-dt%d-b%d-%016llx", kTuneVersion, p.num_cus, p.dtype, (int)p.batch,
+                (unsigned long long)h);
   return buf;
 }
 
