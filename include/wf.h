@@ -269,10 +269,10 @@ int wf_forward_config(int dtype, int64_t m, int64_t n, int64_t ldc, int64_t ldd,
  * device buffer of B records on the current device; later forward calls and reverse sweeps
  * of wf_backward on that device whose band count is <= B fill record b for band b (a later
  * call overwrites earlier records).  wf_trace_enable(0) frees it.  wf_trace_fetch synchronizes the device and
- * copies up to max_bands records (8 uint64 each: claim time, first sub-chunk ready,
- * compute done, store done -- 100 MHz ticks --, sub-chunks the compute wave found not yet
- * loaded, sub-chunks whose top row had not yet arrived, XCC id, workgroup id) into 'host';
- * it returns the number of records copied, or minus an error code.
+ * copies up to max_bands records of 24 uint64 each into 'host' (claim time, first sub-chunk
+ * ready, compute done, store done -- 100 MHz ticks --, units for which the compute wave found C
+ * not yet loaded, units whose top row had not yet arrived, XCC id, workgroup id, and 16 further
+ * words of the profiler's own); it returns the number of records copied, or minus an error code.
  */
 int wf_trace_enable(int64_t max_bands);
 int64_t wf_trace_fetch(uint64_t* host, int64_t max_bands);
