@@ -753,7 +753,8 @@ namespace {
 // Table I), the fastest sub-system size m and recursion depth R of the device solver on one
 // MI355X, in float64 and in float32, timed by python -m paper_2510_27351_amd.tri_sweep
 // (m in {4, 8, 16, 20, 32, 40, 64, 128}, R in 0..4; best of 3 rounds of 10 solves).  A copy
-// is in tests/golden/mi355x_tri_table.txt.
+// is in tests/golden/mi355x_tri_table.txt.  Timed with two launches per level and the direct
+// solve in one lane: with the deep levels in one launch other plans may be the faster.
 struct SizeObs {
   int64_t N;
   int32_t m64, R64, m32, R32;

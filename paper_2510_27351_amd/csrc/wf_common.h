@@ -12,9 +12,7 @@ namespace wf {
 
 // ---------------------------------------------------------------------------------------
 // Element traits.  'W' is the number of 32-bit payload words per element in the tagged
-// handoff words; RING is the per-row length (in elements) of the LDS ring of a band and
-// PITCH its row pitch, chosen so that the byte pitch is 16 mod 256: a 16-byte read by each
-// lane of a different row then hits distinct LDS banks.
+// handoff words.
 // ---------------------------------------------------------------------------------------
 template <typename T>
 struct Elem;
@@ -32,8 +30,6 @@ __device__ __forceinline__ uint32_t dpp_shr1z_u32(uint32_t src) {
 template <>
 struct Elem<float> {
   static constexpr int W = 1;
-  static constexpr int RING = 512;
-  static constexpr int PITCH = RING + 4;
   __device__ static __forceinline__ float inf() { return __builtin_inff(); }
   __device__ static __forceinline__ float zero() { return 0.0f; }
   __device__ static __forceinline__ float shr1(float src, float old) {
@@ -43,17 +39,6 @@ struct Elem<float> {
   __device__ static __forceinline__ float shr1z(float src) {
     return __builtin_bit_cast(float, dpp_shr1z_u32(__builtin_bit_cast(uint32_t, src)));
   }
-  __device__ static __forceinline__ float min3(float a, float b, float c) {
-    return __builtin_fminf(__builtin_fminf(a, b), c);
-  }
-  // v_min3 on operands the compiler cannot prove canonical (DPP-shifted ones): fminf would
-  // quieten each with an extra instruction first.  Inputs hold no NaN.
-  __device__ static __forceinline__ float min3v(float a, float b, float c) {
-    float r;
-    asm("v_min3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-    return r;
-  }
-  __device__ static __forceinline__ float min2(float a, float b) { return __builtin_fminf(a, b); }
   __device__ static __forceinline__ float add(float c, float v) { return c + v; }
   __device__ static __forceinline__ uint32_t word(float x, int) { return __builtin_bit_cast(uint32_t, x); }
   __device__ static __forceinline__ float from_words(const uint32_t* w) { return __builtin_bit_cast(float, w[0]); }
@@ -62,8 +47,6 @@ struct Elem<float> {
 template <>
 struct Elem<int32_t> {
   static constexpr int W = 1;
-  static constexpr int RING = 512;
-  static constexpr int PITCH = RING + 4;
   __device__ static __forceinline__ int32_t inf() { return 0x7fffffff; }
   __device__ static __forceinline__ int32_t zero() { return 0; }
   __device__ static __forceinline__ int32_t shr1(int32_t src, int32_t old) {
@@ -74,8 +57,6 @@ struct Elem<int32_t> {
     int32_t x = a < b ? a : b;
     return x < c ? x : c;
   }
-  __device__ static __forceinline__ int32_t min2(int32_t a, int32_t b) { return a < b ? a : b; }
-  __device__ static __forceinline__ int32_t min3v(int32_t a, int32_t b, int32_t c) { return min3(a, b, c); }
   // Saturating, so that +inf (INT32_MAX) stays +inf on the virtual border; real cells
   // never saturate under the documented bound on |C|.
   __device__ static __forceinline__ int32_t add(int32_t c, int32_t v) { return __builtin_elementwise_add_sat(c, v); }
@@ -86,8 +67,6 @@ struct Elem<int32_t> {
 template <>
 struct Elem<double> {
   static constexpr int W = 2;
-  static constexpr int RING = 256;
-  static constexpr int PITCH = RING + 2;
   __device__ static __forceinline__ double inf() { return __builtin_inf(); }
   __device__ static __forceinline__ double zero() { return 0.0; }
   __device__ static __forceinline__ double shr1(double src, double old) {
@@ -101,11 +80,6 @@ struct Elem<double> {
     const uint32_t lo = dpp_shr1z_u32((uint32_t)s), hi = dpp_shr1z_u32((uint32_t)(s >> 32));
     return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
   }
-  __device__ static __forceinline__ double min3(double a, double b, double c) {
-    return __builtin_fmin(__builtin_fmin(a, b), c);
-  }
-  __device__ static __forceinline__ double min2(double a, double b) { return __builtin_fmin(a, b); }
-  __device__ static __forceinline__ double min3v(double a, double b, double c) { return min3(a, b, c); }
   __device__ static __forceinline__ double add(double c, double v) { return c + v; }
   __device__ static __forceinline__ uint32_t word(double x, int k) {
     uint64_t b = __builtin_bit_cast(uint64_t, x);
@@ -139,7 +113,7 @@ struct alignas(16) Vec4 {
 // ---------------------------------------------------------------------------------------
 // Synchronisation helpers.
 //
-// Inside a workgroup the four waves hand sub-chunks to each other through LDS counters: a
+// Inside a workgroup the waves hand sub-chunks to each other through LDS counters: a
 // producer writes its data to LDS, waits for those writes (lgkmcnt) and then stores the
 // counter; a consumer spins on the counter.  Nothing here waits on global-memory counters,
 // so the loader's prefetches stay in flight.

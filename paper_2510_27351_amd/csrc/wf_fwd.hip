@@ -571,7 +571,7 @@ __device__ __forceinline__ void compute_band(T* __restrict__ S, const T* __restr
 }
 
 // ---------------------------------------------------------------------------------------
-// wave 1: global -> LDS loader.
+// waves 3 .. 2+R: global -> LDS loaders.
 //
 // One loader per 64 LDS rows (loader h: rows 64h .. 64h+63).  Vector k of a lane covers LDS
 // row l = 64h + (64/LPR) k + lane/LPR and slots [SUB s + 4j, SUB s + 4j + 4) of sub-chunk s,
@@ -795,7 +795,7 @@ __device__ __forceinline__ void top_band(T* Tr, Shared& sh, const FwdArgs& a, in
 }
 
 // ---------------------------------------------------------------------------------------
-// wave 3: storer.  SOFT: the ring holds scaled values; D = y * gl (gl = gamma ln 2).
+// waves 3+R ..: storers.  SOFT: the ring holds scaled values; D = y * gl (gl = gamma ln 2).
 template <typename T, int NV, bool SOFT>
 __device__ __forceinline__ void unscale(Vec4<T> (&v)[NV], T gl) {
   if constexpr (SOFT) {
@@ -918,7 +918,7 @@ __device__ __forceinline__ void store_band(const T* S, Shared& sh, const FwdArgs
 }
 
 // ---------------------------------------------------------------------------------------
-// wave 4: publisher of the band's last row (and of the checkpoint rows)
+// wave 1: publisher of the band's last row (and of the checkpoint rows)
 template <typename T, int G, int R>
 __device__ __forceinline__ void publish_band(const T* S, Shared& sh, const FwdArgs& a, int band, int Us,
                                              uint32_t epoch, uint64_t* tr) {

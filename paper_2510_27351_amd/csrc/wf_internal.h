@@ -50,8 +50,8 @@ struct FwdArgs {
 // Per-band trace record, written when tracing is enabled (times in ticks of the 100 MHz
 // real-time counter):
 //   0 claim time        1 first sub-chunk ready   2 compute done     3 store done
-//   4 sub-chunks the compute wave found not yet loaded
-//   5 sub-chunks whose top row had not yet arrived
+//   4 units for which the compute wave found C not yet loaded
+//   5 units whose top row had not yet arrived
 //   6 XCC id            7 workgroup id
 //   8..11 ticks spent waiting by the compute, loader, top and storer waves
 //   12 loader done      13 top done               18 ticks the publisher waited
@@ -166,7 +166,7 @@ struct BwdBatchArgs {
 
 // Host-side launchers (defined in wf_fwd.hip).  'tile' is 16, 32 or 64.
 hipError_t launch_forward(int dtype, int tile, const FwdArgs& a, int grid, hipStream_t s);
-// Batch sweep; 'rows' = 64-row sub-bands per band: 1, or 2 for the 4-byte types.
+// Batch sweep; 'rows' = rows per lane (a band is 64 times as many): 1, or 2 for the 4-byte types.
 hipError_t launch_forward_batch(int dtype, int tile, int rows, const BatchArgs& b, int grid, hipStream_t s);
 // Adjoint launchers (defined in wf_bwd.hip), float (dtype 0) and double (dtype 1) only.
 hipError_t launch_select(int dtype, const SelArgs& a, int grid, hipStream_t s);
@@ -197,7 +197,7 @@ int pick_reverse_tile(int dtype, int64_t m, int64_t n);
 int words_per_elem(int dtype);  // 32-bit payload words per element in the handoff words
 
 // Largest leading dimension, in bytes: a band of up to 128 rows is addressed with 32-bit
-// byte offsets.
+// byte offsets.  (The forward's bands of 256 rows have a bound of their own, forward_rows.)
 constexpr int64_t kMaxLd = ((int64_t)1 << 31) / 128 - 16;
 
 }  // namespace wf
