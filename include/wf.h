@@ -324,8 +324,9 @@ int wf_fault_inject(int32_t mode);
  * with w(s) = exp((D(s) - C(s) - D[i][j]) / gamma) the derivative of successor s's soft
  * minimum with respect to D[i][j].  g_score (one element) and g_D may be NULL (= 0).
  * Both are persistent band pipelines on the device workspace like wf_forward (same stream
- * ordering rules, bounded waits reported by wf_last_async_error).  g_C may overlap C or D,
- * which then pass through a copy in the workspace, and may be g_D.  gamma must be positive
+ * ordering rules, bounded waits reported by wf_last_async_error).  g_C may share elements with
+ * C or D, which then pass through a copy in the workspace (sized, like the rest of it, by a call
+ * outside stream capture), and may be g_D.  gamma must be positive
  * and finite (WF_E_ARG otherwise); WF_I32 returns WF_E_UNSUPPORTED.
  */
 int wf_soft_forward(int dtype, int64_t m, int64_t n, double gamma, const void* C, int64_t ldc,

@@ -818,7 +818,13 @@ int wf_soft_backward(int dtype, int64_t m, int64_t n, double gamma, const void* 
   auto bytes_of = [&](int64_t ld) { return (size_t)((m - 1) * ld + n) * es; };
   auto overlaps = [&](const void* p, int64_t ld) {
     const uintptr_t a0 = reinterpret_cast<uintptr_t>(p), b0 = reinterpret_cast<uintptr_t>(g_C);
-    return a0 < b0 + bytes_of(ldgc) && b0 < a0 + bytes_of(ld);
+    if (a0 >= b0 + bytes_of(ldgc) || b0 >= a0 + bytes_of(ld)) return false;
+    if (ld != ldgc) return true;
+    // of one stride: the columns of p begin 'from' bytes after those of g_C, and share none with
+    // them if they begin behind them and end before the next row's
+    const uintptr_t stride = (uintptr_t)ld * es, width = (uintptr_t)n * es;
+    const uintptr_t from = a0 >= b0 ? (a0 - b0) % stride : (stride - (b0 - a0) % stride) % stride;
+    return from < width || from + width > stride;
   };
   const void** in[2] = {&C, &D};
   int64_t* ld[2] = {&ldc, &ldd};
