@@ -261,10 +261,10 @@ int64_t nbands(int64_t m) { return (m + kBand - 1) / kBand; }
 }  // namespace
 
 // Tile of the reverse sweep: the override, else the prediction, at most 32 (its table was timed
-// with a float64 ring of two sub-chunks, where 64 won for wide matrices).  Of 16, 32 and 64, us
-// with gD: float 3000 x 2500 249, 238 and 257; 8000 x 64 414, 388 and 428; 64 x 16384 354, 338
-// and 339; double 1023 x 1300 138, 136 and 159; 3000 x 100 270, 251 and 330; 3000 x 64 207, 216
-// and 247; 64 x 16384 532, 518 and 548.
+// with a float64 ring of two sub-chunks, where 64 won for wide matrices).  Of 16, 32 and 64, us of
+// the sweep with gD: float 3000 x 2500 243, 234 and 258; 8000 x 64 412, 379 and 431; 64 x 16384
+// 351, 338 and 339; double 1023 x 1300 131, 134 and 153; 3000 x 100 246, 240 and 311; 3000 x 64
+// 206, 214 and 239; 64 x 16384 545, 528 and 547.
 int pick_reverse_tile(int dtype, int64_t m, int64_t n) {
   if (const int t = forced_tile()) return t;
   return std::min(32, (int)wf_tile_predict(dtype, m, n, 1));

@@ -32,7 +32,7 @@
 // skew plus the handoff (about 1.1 us).  3000 x 2500 float32 with gD: 396 us with one value
 // loader one sub-chunk ahead, address arithmetic and three counter tests per unit in the
 // compute wave and a per-element path for a last band of fewer rows (which alone took 162 us
-// against 75), 235 us so; float64 549 and 352.
+// against 75), 235 us so; float64 549 and 336.
 #include <algorithm>
 
 #include "wf_common.h"
@@ -116,7 +116,7 @@ __device__ __forceinline__ int64_t sel_index(int band, int Ks, int k, int lane) 
 // 1. Selection recompute: two waves (compute, loader), one 64-row band per workgroup.
 // What bounds it: about 27 ns a step in float, 38 in double (64 x 16384 in four column pieces 113
 // and 159 us; 122 and 198 before the instruction blocks and the four-piece rings below), the
-// first loads of a piece and its edges (1023 x 1300: float 22, double 26 us; 39 and 36 before).
+// first loads of a piece and its edges (1023 x 1300: float 21, double 25 us; 39 and 36 before).
 // =======================================================================================
 struct alignas(8) SelShared {
   uint32_t loaded;  // pieces (SCfg::SUB slots) of C and of the top row in LDS
