@@ -358,9 +358,9 @@ __device__ __forceinline__ double soft_log2_1p(double a) {
 // their minimum, whose own term is 1: two exponentials, of the median and the maximum, and the
 // logarithm of 1 plus their sum.  +inf neighbours give terms that vanish; three of them (the
 // padding lanes before column 0) give +inf.  A step is a serial chain of about 70 float64
-// instructions of 4.9 cycles and takes 160 ns; with the general exp2 and log2 (three and one,
+// instructions of 4.9 cycles and takes 156 ns; with the general exp2 and log2 (three and one,
 // about 175 instructions: subnormal, overflow and sign cases that cannot arise here) it took
-// 360 ns: 500 x 700 497 us then and 238 us now.  The table's error against 80-bit arithmetic is
+// 360 ns: 500 x 700 497 us then and 234 us now.  The table's error against 80-bit arithmetic is
 // the same to 5% for gamma from 0.01 to 10 and costs from 10^-9 to 10^4 gamma.
 __device__ __forceinline__ void soft_cells4(ComputeState<double, 1>& st, const GroupRegs<double, 1>& r,
                                             Vec4<double> (&d)[1]) {
@@ -1017,7 +1017,7 @@ __global__ __launch_bounds__((64 * (3 + 2 * R)), 1) void fwd_kernel(FwdArgs a) {
   const uint32_t epoch = __hip_atomic_load(&ctl->epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if (threadIdx.x == 0) {
     sh.abort = 0u;
-    // (a pass over the double soft-min loop costs more than its fetch: 500 x 700 238 us without,
+    // (a pass over the double soft-min loop costs more than its fetch: 500 x 700 234 us without,
     // 243 with)
     sh.warm = SOFT && sizeof(T) == 8 ? 1u : 0u;
   }
